@@ -6,8 +6,9 @@
  * The paper repairs a kernel by alternating Solve (a weighted partial MaxSAT
  * query over barrier variables) and Verify (a GPUVerify run) in Alg. 1.  This
  * library computes the concrete counterpart on a finite kernel model: Verify
- * enumerates every thread of every block, so it decides races and barrier
- * divergence exactly for the model; Solve is an exact minimum-weight search.
+ * covers every thread of every block (by their affine addresses in closed
+ * form, or access by access), so it decides races and barrier divergence
+ * exactly for the model; Solve is an exact minimum-weight search.
  *
  * Kernel model (the instrumented program P of Section 2.3):
  *   - `blocks` x `threads` threads; thread (bid, tid);
@@ -149,7 +150,8 @@ typedef struct {
   double ms_sort_kernels;        /* sum of the radix-pass kernel durations */
   double ms_j0;                  /* first partners with no barrier enabled
                                     (once per kernel) */
-  uint64_t records;              /* access records generated (both views) */
+  uint64_t records;              /* access records generated (both views); 0
+                                    where closed forms decide every conflict */
   uint64_t accesses;             /* (point, block, thread) accesses */
   uint64_t records_scanned;      /* records read by conflict scans */
   uint32_t sort_passes, sort_launches, rounds, conf_launches;
@@ -399,11 +401,18 @@ uint32_t rp_sort_key_bits(const rp_kernel* const* ks, uint32_t n);
  *                            generation order) writes long runs and gains
  *                            from more resident workgroups; one whose digit
  *                            changes fast writes short runs and gains from
- *                            longer tiles, so their best tiles differ. */
+ *                            longer tiles, so their best tiles differ;
+ *   RP_TUNE_RACE_ROUTE       how conflicts are decided: 0 = in closed form,
+ *                            pair of points by pair of points, for the
+ *                            arrays where that is bounded by less work than
+ *                            sorting their access records, and from the
+ *                            records for the others (default), 1 = from the
+ *                            records always.  Results and workspace sizes
+ *                            are the same. */
 enum { RP_TUNE_SORT_DIGIT_BITS = 0, RP_TUNE_SCATTER_SHAPE = 1, RP_TUNE_TIMING = 2,
        RP_TUNE_SCATTER_WGS = 3, RP_TUNE_SOLVER_NODES = 4, RP_TUNE_SCAN_PIPELINE = 5,
        RP_TUNE_DIGIT_ORDER = 6, RP_TUNE_LOW_DIGIT_BITS = 7, RP_TUNE_SCAN_FIELDS = 8,
-       RP_TUNE_PASS_SHAPES = 9 };
+       RP_TUNE_PASS_SHAPES = 9, RP_TUNE_RACE_ROUTE = 10 };
 int rp_set_tuning(int knob, int value);
 
 /* For callers that cannot allocate device memory (code under stream

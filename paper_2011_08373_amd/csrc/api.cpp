@@ -141,7 +141,7 @@ rp_status rp_check(const rp_kernel* k, uint64_t x, rp_pair* pairs, uint64_t cap,
                    size_t ws_bytes, void* stream) {
   if (validate_kernel(k) != RP_OK || (cap && !pairs)) return RP_ERR_INVALID;
   Plan pl;
-  make_plan(k, pl);
+  make_plan(k, pl, false);
   JobInput ji;
   ji.plan = &pl;
   ji.x = x;
@@ -400,6 +400,9 @@ int rp_set_tuning(int knob, int value) {
     case RP_TUNE_LOW_DIGIT_BITS:
       if (value != 0 && (value < 6 || value > 9)) return -1;
       return low_digit_bits(value, true);
+    case RP_TUNE_RACE_ROUTE:
+      if (value < 0 || value > 1) return -1;
+      return race_route(value, true);
     case RP_TUNE_SCAN_FIELDS:
       if (value < 0 || value > 1) return -1;
       return j0_fields_variant(value, true);

@@ -56,8 +56,10 @@ constexpr int MAX_SORT_PASSES = 8;
 
 // flags of DPoint::flags.  PF_TCONST: the word does not depend on the thread
 // (a = 0 mod words); PF_BCONST: it does not depend on the block (b = 0 mod
-// words).
-constexpr uint8_t PF_WRITE = 1, PF_GLOBAL = 2, PF_POW2 = 4, PF_TCONST = 8, PF_BCONST = 16;
+// words).  PF_CLOSED: the conflicts of the point's array are decided in
+// closed form (closed.h) and it has no records.
+constexpr uint8_t PF_WRITE = 1, PF_GLOBAL = 2, PF_POW2 = 4, PF_TCONST = 8, PF_BCONST = 16,
+                  PF_CLOSED = 32;
 
 struct DPoint {          // 40 B, one per program point
   int32_t a, b, c;

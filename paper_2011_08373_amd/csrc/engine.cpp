@@ -28,7 +28,7 @@ struct Layout {
   size_t o_recA = 0, o_recB = 0, o_dig = 0, o_cnt = 0, o_tot = 0, o_off = 0, o_err = 0;
   std::vector<size_t> o_ivl, o_minj, o_j0, o_phi, o_scratch, o_traj, o_bitmap, o_pairs, o_ptotal;
   std::vector<uint32_t> phi_cap, scratch_cap;
-  uint64_t n_rec = 0;
+  uint64_t n_rec = 0;             // records of the logs
   uint32_t rb = 8, passes = 0;   // widest digit of the passes (table sizes), passes
   std::vector<DigitPass> digits;  // the passes' digits in execution order
   uint32_t n_chunks = 0;          // sort chunks = generation items (built on the device)
@@ -54,11 +54,18 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
   L.passes = (uint32_t)L.digits.size();
   L.rb = 6;
   for (const DigitPass& dp : L.digits) L.rb = std::max(L.rb, dp.bits);
-  uint64_t rec = 0;
+  // sizes as for a log of every access (size_rec records, size_chunks chunks,
+  // ...), whatever part of the accesses is decided without records
+  uint64_t rec = 0, size_rec = 0;
+  size_t size_segs = 0;
+  uint32_t size_chunks = 0, size_cblk = 0;
   for (size_t j = 0; j < N; j++) {
     const Plan& p = *jobs[j].plan;
     for (int v = 0; v < 2; v++) {
-      const uint64_t n = v == 0 ? p.n_intra : p.n_inter;
+      const uint64_t all = v == 0 ? p.n_intra : p.n_inter;
+      size_rec += all;
+      size_segs += all != 0;
+      const uint64_t n = v == 0 ? p.log_intra() : p.log_inter();
       if (n == 0) continue;
       SortSeg s{};
       s.beg = rec;
@@ -78,7 +85,7 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
   // written by the column scans: fewer, longer chunks keep those tables
   // small on billion-record logs)
   const uint64_t tile = sort_tile_size();
-  uint64_t chunk = std::max<uint64_t>(2 * tile, (rec + 16383) / 16384);
+  uint64_t chunk = std::max<uint64_t>(2 * tile, (size_rec + 16383) / 16384);
   chunk = (chunk + tile - 1) / tile * tile;
   L.chunk_len = chunk;
   for (size_t s = 0; s < L.ssegs.size(); s++) {
@@ -91,6 +98,13 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
     L.n_cblk += nb;
     L.max_cblk = std::max(L.max_cblk, nb);
   }
+  for (size_t j = 0; j < N; j++)
+    for (int v = 0; v < 2; v++) {
+      const uint64_t all = v == 0 ? jobs[j].plan->n_intra : jobs[j].plan->n_inter;
+      const uint32_t nc = (uint32_t)((all + chunk - 1) / chunk);
+      size_chunks += nc;
+      size_cblk += (nc + COL_BLOCK_CHUNKS - 1) / COL_BLOCK_CHUNKS;
+    }
   const uint32_t R = 1u << L.rb;
   // ---- meta region (uploaded)
   size_t off = 0;
@@ -99,8 +113,8 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
   // words: 0 error, 8 running-job count, 9 conflict-tile counter, 10 scatter
   // chunk ticket; uploaded as zeros
   L.o_err = off; off = up(off + 64);
-  L.o_ssegs = off; off = up(off + L.ssegs.size() * sizeof(SortSeg));
-  L.o_csegs = off; off = up(off + L.ssegs.size() * sizeof(ConfSeg));
+  L.o_ssegs = off; off = up(off + size_segs * sizeof(SortSeg));
+  L.o_csegs = off; off = up(off + size_segs * sizeof(ConfSeg));
   L.o_pts.resize(N); L.o_bany.resize(N); L.o_bgrid.resize(N); L.o_w.resize(N);
   L.o_wbits.resize(N);
   L.o_cpre.resize(N); L.o_gpre.resize(N); L.o_phi0j.resize(N);
@@ -117,10 +131,10 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
   }
   L.meta = off;
   // ---- device-only region
-  L.o_items = off; off = up(off + (size_t)L.n_chunks * sizeof(GenItem));
-  L.o_chunks = off; off = up(off + (size_t)L.n_chunks * sizeof(SortChunk));
-  L.o_recA = off; off = up(off + L.n_rec * sizeof(uint64_t));
-  L.o_recB = off; off = up(off + L.n_rec * sizeof(uint64_t));   // sort ping-pong, then run log
+  L.o_items = off; off = up(off + (size_t)size_chunks * sizeof(GenItem));
+  L.o_chunks = off; off = up(off + (size_t)size_chunks * sizeof(SortChunk));
+  L.o_recA = off; off = up(off + size_rec * sizeof(uint64_t));
+  L.o_recB = off; off = up(off + size_rec * sizeof(uint64_t));   // sort ping-pong, then run log
   // each record's digit of the next pass, written by a scatter beside its
   // output and counted by the next pass (read as whole 16-byte vectors)
   if (L.passes > 1) {
@@ -128,12 +142,12 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
     for (uint32_t p = 1; p < L.passes; p++)    // more than 8 bits
       if (L.digits[p].bits > 8) wide = 2;
     L.o_dig = off;
-    off = up(off + L.n_rec * wide + 16);
+    off = up(off + size_rec * wide + 16);
   }
-  L.o_cnt = off; off = up(off + (size_t)L.n_chunks * R * sizeof(uint32_t));
-  L.o_tot = off; off = up(off + L.ssegs.size() * (size_t)R * sizeof(uint64_t));
-  L.o_part = off; off = up(off + (size_t)L.n_cblk * R * sizeof(uint64_t));
-  L.o_off = off; off = up(off + (size_t)L.n_chunks * R * sizeof(uint64_t));
+  L.o_cnt = off; off = up(off + (size_t)size_chunks * R * sizeof(uint32_t));
+  L.o_tot = off; off = up(off + size_segs * (size_t)R * sizeof(uint64_t));
+  L.o_part = off; off = up(off + (size_t)size_cblk * R * sizeof(uint64_t));
+  L.o_off = off; off = up(off + (size_t)size_chunks * R * sizeof(uint64_t));
   L.o_ivl.resize(N); L.o_minj.resize(N); L.o_j0.resize(N); L.o_phi.resize(N); L.o_scratch.resize(N);
   L.o_traj.resize(N); L.o_bitmap.resize(N); L.o_pairs.resize(N); L.o_ptotal.resize(N);
   L.phi_cap.resize(N); L.scratch_cap.resize(N);
@@ -315,8 +329,8 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
     J.div_if_enabled = p.div_if_enabled;
     J.pad_array = p.pad_array;
     J.log[0] = J.log[1] = nullptr;
-    J.nlog[0] = p.n_intra;
-    J.nlog[1] = p.n_inter;
+    J.nlog[0] = p.log_intra();
+    J.nlog[1] = p.log_inter();
     J.ivl = (uint32_t*)(d + L.o_ivl[j]);
     J.minj = (uint32_t*)(d + L.o_minj[j]);
     J.j0 = (uint32_t*)(d + L.o_j0[j]);
@@ -409,20 +423,28 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   // (a job without access records keeps the cleared table: no partner)
   if (o.op != OP_CHECK && o.op != OP_SOLVE) {
     uint32_t maxP = 1;
-    bool lo32 = true;
+    bool lo32 = true, any_closed = false, closed_small = true;
     for (const JobInput& j : jobs) {
+      any_closed = any_closed || j.plan->any_closed;
+      closed_small = closed_small && j.plan->closed_small;
       maxP = std::max(maxP, j.plan->P);
       lo32 = lo32 && j.plan->tbits < 32 && j.plan->bbits < 32 &&
              j.plan->tbits + j.plan->bbits + j.plan->pbits <= 32;
     }
-    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_ZERO, s));
+    // the scan of the logs fills every row of every job; the closed form
+    // then sets the rows of its own points (or, with no log, every row)
     if (!L.ssegs.empty()) {
+      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_ZERO, s));
       HIPCHK(launch_conf_tiles(djobs, dcs, (int)L.ssegs.size(), derr + 9, s));
       tm.mark(T_SUMPRE);
       HIPCHK(launch_j0(djobs, dcs, (int)L.ssegs.size(), maxP, lo32, derr + 9, s));
       tm.mark(T_SUMMARY);
+      HIPCHK(launch_save_j0(djobs, (uint32_t)N, s));
     }
-    HIPCHK(launch_save_j0(djobs, (uint32_t)N, s));
+    if (L.ssegs.empty() || any_closed) {
+      HIPCHK(launch_first_closed(djobs, (uint32_t)N, maxP, closed_small, s));
+      if (L.ssegs.empty()) tm.mark(T_SUMPRE);
+    }
   }
   return RP_OK;
 }
@@ -532,9 +554,9 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   bool ended = false, have_results = false;
   // the run logs are scanned once: by the all-pairs scan of a check, else
   // by the first-partner scan of the preparation
-  const uint64_t scanned = o.op == OP_SOLVE ? 0 : L.n_rec;
+  const uint64_t scanned = o.op == OP_SOLVE ? 0 : L.n_rec;    // (0: all in closed form)
   uint32_t rounds_run = 0;
-  const uint32_t conf_launches = o.op == OP_SOLVE ? 0 : 1;
+  const uint32_t conf_launches = o.op == OP_SOLVE || L.ssegs.empty() ? 0 : 1;
   if (o.op == OP_CHECK) {
     HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, s));
     HIPCHK(launch_conf_tiles(djobs, dcs, nseg, dtiles, s));

@@ -54,6 +54,11 @@ hipError_t launch_conf(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t 
 // (thread, block and point bits together at most 32, in every job)
 hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t max_points,
                      bool lo32, const uint32_t* tiles, hipStream_t s);
+// First partners of the PF_CLOSED points, into j0 (every row of a job that has
+// no records).  small: every closed array of every job fits the 32-bit form
+// of closed.h.
+hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
+                               hipStream_t s);
 hipError_t launch_pairs(const Job* job, rp_pair* out, uint64_t* total, hipStream_t s);
 hipError_t launch_clause(const Job* jobs, uint32_t njobs, int learn, hipStream_t s);
 hipError_t launch_solve(const Job* jobs, uint32_t njobs, hipStream_t s);

@@ -4,9 +4,11 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstring>
 #include <vector>
 
+#include "closed.h"
 #include "common.h"
 #include "launch.h"
 #include "plan.h"
@@ -27,6 +29,14 @@ static int g_digit_order = 1;         // RP_TUNE_DIGIT_ORDER
 int digit_order(int v, bool set) {
   const int old = g_digit_order;
   if (set) g_digit_order = v;
+  return old;
+}
+
+static int g_race_route = 0;          // RP_TUNE_RACE_ROUTE
+
+int race_route(int v, bool set) {
+  const int old = g_race_route;
+  if (set) g_race_route = v;
   return old;
 }
 
@@ -261,7 +271,121 @@ void compact_words(const rp_kernel* k, Plan& pl) {
   pl.key_bits = pl.abits + pl.nbits;
 }
 
-void make_plan(const rp_kernel* k, Plan& pl) {
+// Which arrays are decided in closed form.  The closed form tests pairs of
+// points of one array, each over the values of an arithmetic progression that
+// fall into an interval (closed_scan); the log sorts every access.  For an
+// array with n points, pairs <= n(n+1)/2, and the tests of a pair are bounded
+// by how often the progression can enter the interval and how long it can
+// stay there: trips = (terms * |step| / W + 1) * (width / |step| + 2), at most
+// one per term.  Measured on pairs that never conflict: a test 14 ps with the
+// chip full (512 kernels of 64 points, 64 blocks) and 0.2 to 0.4 us one after
+// another in one lane (64 points, 4,096 blocks); a record of the log costs 16
+// ps (31.9 ms for the 2.0G records of the stress kernel) and the log's
+// launches alone about 0.1 ms.  So the closed form is taken where its bound
+// is no larger than the log's own work (RECORDS_FREE tests cost no more than
+// the launches), and where the tests of one lane in sequence end before the
+// log would.
+namespace {
+constexpr double RECORDS_FREE = 4.0e6, SERIAL_FREE = 512, SERIAL_RECORDS = 16384;
+
+double scan_trips(double n, double step, double w, double W) {
+  step = step < 0 ? -step : step;
+  if (step == 0 || n <= 1) return 1;
+  return std::min(n, (n * step / W + 1) * (w / step + 2));
+}
+
+struct ClosedArray {
+  static constexpr int MAXC = 8;         // distinct (b, block condition) of its points
+  struct Blocks { int32_t b, S; uint32_t bm, br, Z; } c[MAXC];
+  int nc = 0;
+  bool many = false;                     // more than MAXC of them
+  uint64_t n = 0, records = 0;
+  int64_t span = 0, bspan = 0;           // largest |A| * (X - 1) and |S| * (Z - 1)
+};
+}  // namespace
+
+void mark_closed(const rp_kernel* k, Plan& pl) {
+  static thread_local std::vector<ClosedArray> as;
+  static thread_local std::vector<uint8_t> take;
+  as.assign(k->n_arrays, ClosedArray{});
+  take.assign(k->n_arrays, 0);
+  const uint32_t B = pl.B;
+  for (uint32_t i = 0; i < pl.P; i++) {
+    const DPoint& d = pl.pts[i];
+    if (d.kind != RP_ACCESS) continue;
+    ClosedArray& a = as[d.array];
+    a.n++;
+    if (d.cnt == 0 || d.br >= B) continue;
+    a.records += (pl.cnt_pre[i + 1] - pl.cnt_pre[i]) * B + (pl.gcnt_pre[i + 1] - pl.gcnt_pre[i]);
+    const Access s = make_access(d.a, d.b, d.c, d.words, d.m, d.r, d.cnt, d.bm, d.br, B);
+    a.span = std::max<int64_t>(a.span, abs_of<int64_t>(s.A) * (int64_t)(s.X - 1));
+    a.bspan = std::max<int64_t>(a.bspan, abs_of<int64_t>(s.S) * (int64_t)(s.Z - 1));
+    int q = 0;
+    while (q < a.nc && !(a.c[q].b == s.b && a.c[q].bm == s.bm && a.c[q].br == s.br)) q++;
+    if (q < a.nc) continue;
+    if (a.nc == ClosedArray::MAXC) a.many = true;
+    else a.c[a.nc++] = {s.b, s.S, s.bm, s.br, s.Z};
+  }
+  for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
+    const ClosedArray& a = as[arr];
+    if (a.n == 0 || a.span >= MAX_SPAN || a.bspan >= MAX_SPAN) continue;
+    const uint32_t words = k->arrays[arr].words;
+    const double W = words, w = 2.0 * (double)a.span, wraps = 1 + std::floor(w / W);
+    const double bw = 2.0 * (double)a.bspan;
+    const bool cross = k->arrays[arr].space == RP_GLOBAL && B > 1;
+    double t0 = 1, t1 = cross ? 1 : 0;   // tests of a pair: same block, different blocks
+    if (a.many) {                        // whatever the steps are
+      t0 = B;
+      if (cross) t1 = std::min(bw + 1, (double)B * B);
+    }
+    for (int u = 0; u < a.nc && !a.many; u++) {
+      for (int v = 0; v <= u; v++) {
+        const auto &p = a.c[u], &q = a.c[v];
+        const double lcm = p.bm == q.bm ? p.bm : (double)p.bm * q.bm / gcd_of<uint32_t>(p.bm, q.bm);
+        if (lcm < B) {
+          const int64_t db = step_mod((int64_t)p.b - q.b, words);
+          t0 = std::max(t0, scan_trips(std::floor(B / lcm) + 1,
+                                       step_mod(db * (int64_t)lcm, words), w, W));
+        }
+        if (cross) {
+          const double sp = std::abs((double)p.S), sq = std::abs((double)q.S);
+          const double g = gcd_of<int64_t>((int64_t)sp, (int64_t)sq);
+          const double n = g > 0 ? (sp * (p.Z - 1.0) + sq * (q.Z - 1.0)) / g + 1 : 1;
+          if (n <= (double)p.Z * q.Z) t1 = std::max(t1, scan_trips(n, g, w, W));
+          else t1 = std::max(t1, p.Z <= q.Z ? p.Z * scan_trips(q.Z, q.S, w, W)
+                                            : q.Z * scan_trips(p.Z, p.S, w, W));
+        }
+      }
+    }
+    const double n = (double)a.n, rec = (double)a.records;
+    const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
+    const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
+    if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) continue;
+    take[arr] = 1;
+    pl.any_closed = true;
+    if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE || pl.T > SMALL_SIZE ||
+        B > SMALL_SIZE)
+      pl.closed_small = false;
+  }
+  if (!pl.any_closed) return;
+  uint64_t in = 0, ex = 0, in0 = 0, ex0 = 0;   // (in0, ex0: the full prefixes)
+  for (uint32_t i = 0; i < pl.P; i++) {
+    const uint64_t in1 = pl.cnt_pre[i + 1], ex1 = pl.gcnt_pre[i + 1];
+    DPoint& d = pl.pts[i];
+    if (d.kind == RP_ACCESS && take[d.array]) {
+      d.flags |= PF_CLOSED;
+    } else {
+      in += in1 - in0;
+      ex += ex1 - ex0;
+    }
+    in0 = in1;
+    ex0 = ex1;
+    pl.cnt_pre[i + 1] = in;
+    pl.gcnt_pre[i + 1] = ex;
+  }
+}
+
+void make_plan(const rp_kernel* k, Plan& pl, bool closed) {
   pl.P = k->n_points;
   pl.S = k->n_slots;
   pl.B = k->blocks;
@@ -363,6 +487,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
   }
   pl.n_intra = pl.cnt_pre[pl.P] * pl.B;
   pl.n_inter = pl.gcnt_pre[pl.P];
+  if (closed && g_race_route == 0) mark_closed(k, pl);
 }
 
 // Automatic digit width: the fewest passes of at most 10 bits, each as

@@ -13,15 +13,25 @@ struct Plan {
   std::vector<uint64_t> wbits;      // bit i: point i writes
   std::vector<uint64_t> bits_any, bits_grid;
   std::vector<uint32_t> weights;
+  // (records are generated for the points outside PF_CLOSED arrays only)
   std::vector<uint64_t> cnt_pre;    // prefix of same-block records per block over points
   std::vector<uint64_t> gcnt_pre;   // prefix of cross-block records over points
   uint64_t div_if_enabled = 0, grid_slots = 0, pre_slots = 0;
   uint32_t pad_array = 0;           // array id of padding records (block conditions)
+  // records of a log of every access: workspace sizes follow these whether
+  // or not the records are generated
   uint64_t n_intra = 0, n_inter = 0, accesses = 0;
+  bool any_closed = false;          // some array is decided in closed form
+  bool closed_small = true;         // every such array in 32-bit arithmetic
+  uint64_t log_intra() const { return cnt_pre.empty() ? 0 : cnt_pre[P] * B; }
+  uint64_t log_inter() const { return gcnt_pre.empty() ? 0 : gcnt_pre[P]; }
 };
 
 int validate_kernel(const rp_kernel* k);
-void make_plan(const rp_kernel* k, Plan& pl);
+// closed: arrays may be decided in closed form (first partners), else every
+// access gets its records (the all-pairs scan).
+void make_plan(const rp_kernel* k, Plan& pl, bool closed = true);
+void mark_closed(const rp_kernel* k, Plan& pl);
 void compact_words(const rp_kernel* k, Plan& pl);
 int pick_digit_bits(uint32_t key_bits);
 // One radix pass: it sorts by key bits [lo, lo + bits) above the key shift.
@@ -42,6 +52,9 @@ int timing_level(int v, bool set);
 // Order of the radix passes' digits (RP_TUNE_DIGIT_ORDER: 0 lowest first,
 // 1 highest first); returns the old setting.
 int digit_order(int v, bool set);
+// First partners in closed form where the plan's rule takes it, or from the
+// records always (RP_TUNE_RACE_ROUTE 0, 1); returns the old setting.
+int race_route(int v, bool set);
 // Node budget of the exact solver's branch and bound (RP_TUNE_SOLVER_NODES,
 // as log2); returns the old log2.
 int solver_nodes_log2(int v, bool set);

@@ -139,6 +139,7 @@ TUNE_DIGIT_ORDER = 6
 TUNE_LOW_DIGIT_BITS = 7
 TUNE_SCAN_FIELDS = 8
 TUNE_PASS_SHAPES = 9
+TUNE_RACE_ROUTE = 10
 PASS_SHAPES_DEFAULT = 0x0FFFFFFF     # every radix pass on TUNE_SCATTER_SHAPE's tile
 
 

@@ -1,0 +1,128 @@
+"""First partners in closed form against the oracle and against the access
+records, on the GPU: edges of the sizes and strides the closed form takes,
+kernels whose arrays go both ways, and the repository's full-size parity with
+every conflict decided from the records (RP_TUNE_RACE_ROUTE 1)."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2011_08373_amd import synth
+import bruteforce as BF
+import test_gpu_full_size as full
+import test_gpu_parity as parity
+from test_gpu_parity import L, _first_from_pairs, same_repair  # noqa: F401  (L is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture()
+def records(L):  # noqa: F811
+    old = L.set_tuning(L.TUNE_RACE_ROUTE, 1)
+    yield
+    L.set_tuning(L.TUNE_RACE_ROUTE, old)
+
+
+def _random_kernel(rng, B, T, words, strides, P=70, glob=True, conds=True):
+    pts = []
+    for i in range(P):
+        if rng.random() < 0.15:
+            pts.append(dict(kind=2))
+            continue
+        pts.append(dict(kind=0, is_write=int(rng.random() < 0.4), array=int(rng.integers(0, 2)),
+                        guard=int(rng.integers(0, 5)), a=int(rng.choice(strides[0])),
+                        b=int(rng.choice(strides[1])), c=int(rng.integers(-9, 10))))
+    guards = [(1, 0), (1, 0), (2, 1), (3, 2), (T + 1, T)]       # the last runs on no thread
+    bg = [(1, 0), (2, 1), (3, 0), (1, 0), (1, 0)] if conds else None
+    return synth.make_kernel(B, T, [(words, 1 if glob else 0), (words + 1, 1)], guards, pts, [],
+                             block_guards=bg)
+
+
+SHAPES = [
+    # blocks, threads, words, thread strides, block strides
+    (1, 1, 1, (0, 1), (0, 1)),
+    (1, 64, 128, (1, 2, -1), (0,)),                    # 64, 65: one chunk of lanes and one more
+    (3, 65, 64, (0, 1, -2, 64), (0, 65)),              # every address wraps
+    (7, 33, 4096, (1, 3, -5), (33, 99)),
+    (64, 31, 2039, (1, -1, 7), (0, 31, 62)),           # an odd array size
+    (5, 40, 0xFFFFFFF0, (1, -1, 2**31 - 1, -2**31), (0, 40, -2**31)),   # 64-bit arithmetic
+    (300, 20, 1 << 14, (1, 2), tuple(range(1, 40, 3))),  # more block strides than the rule lists
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[str(s[:3]) for s in SHAPES])
+def test_first_partners_edges(L, shape):  # noqa: F811
+    B, T, words, sa, sb = shape
+    for seed in range(3):
+        rng = np.random.default_rng(1000 * seed + T)
+        km = _random_kernel(rng, B, T, words, (sa, sb), glob=seed != 1, conds=seed != 2)
+        st, got, div = L.first_partners(km, 0)
+        o = O.check(km, 0)
+        assert st == 0 and div == o[2]
+        assert (got.astype(np.uint64) == _first_from_pairs(o[1], km.n_points)).all(), seed
+
+
+def _both_ways_kernel(seed):
+    # the first array has more distinct block strides than the rule bounds, on
+    # many blocks: its accesses get records; the second is closed
+    rng = np.random.default_rng(seed)
+    pts = []
+    for i in range(36):
+        if i % 3 == 2:
+            pts.append(dict(kind=1, slot=i // 3))
+        elif i % 3 == 0:
+            pts.append(dict(kind=0, is_write=int(rng.random() < 0.5), array=0, a=1,
+                            b=int(8 + 5 * i), c=int(rng.integers(-2, 3))))
+        else:
+            pts.append(dict(kind=0, is_write=int(rng.random() < 0.5), array=1,
+                            a=int(rng.choice([1, -1, 2])), b=8, c=int(rng.integers(-2, 3))))
+    slots = [(int(rng.integers(0, 2)), 0, int(rng.integers(1, 4))) for _ in range(12)]
+    return synth.make_kernel(1500, 8, [(1 << 20, 1), (1 << 15, 1)], [(1, 0)], pts, slots)
+
+
+def test_both_ways_in_one_kernel(L):  # noqa: F811
+    for seed in range(3):
+        km = _both_ways_kernel(seed)
+        st, got, div = L.first_partners(km, 0)
+        n = L.last_stats()["records"]
+        assert n == 2 * 12 * km.blocks * km.threads          # both views of one array only
+        assert (got.astype(np.uint64) == _first_from_pairs(O.check(km, 0)[1], km.n_points)).all()
+        assert same_repair(L.repair(km), O.repair(km)), seed
+    kms = [_both_ways_kernel(7), BF.tiny_kernel(np.random.default_rng(3)), _both_ways_kernel(8)]
+    st, res = L.repair_batch(kms)
+    assert st == 0
+    for km, r in zip(kms, res):
+        o = O.repair(km)
+        assert all(r[k] == o[k] for k in ("status", "assign", "weight", "rounds", "n_clauses"))
+
+
+def test_routes_agree_on_the_large_kernels(L):  # noqa: F811
+    for name, mode in (("plain-large", "literal"), ("plain-large", "planted")):
+        km = synth.generate(name, mode=mode)
+        a = L.first_partners(km, 0)
+        assert L.last_stats()["records"] == 0                         # no record was generated
+        old = L.set_tuning(L.TUNE_RACE_ROUTE, 1)
+        try:
+            b = L.first_partners(km, 0)
+            assert L.last_stats()["records"] > 0
+        finally:
+            L.set_tuning(L.TUNE_RACE_ROUTE, old)
+        assert a[0] == b[0] == 0 and (a[1] == b[1]).all()
+
+
+# the suites of the sort and of the first-partner scan, on the records
+def test_records_scan_variants(L, records):  # noqa: F811
+    for name in ("literal", "planted"):
+        parity.test_scan_variants_full_size(L, "plain_large_" + name, name)
+    parity.test_ragged_tiles(L)
+    parity.test_edge_empty_and_degenerate(L)
+    parity.test_block_conditions(L)
+
+
+def test_records_sort_knobs(L, records):  # noqa: F811
+    parity.test_pass_shapes_full_size(L)
+
+
+def test_records_batched(L, records):  # noqa: F811
+    full.test_batched_full_size(L, full._expected("batched"), "planted")
+    parity.test_batch_many_kernels(L)
+    parity.test_server_continuous_batching(L)
