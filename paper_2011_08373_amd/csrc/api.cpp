@@ -141,7 +141,7 @@ rp_status rp_check(const rp_kernel* k, uint64_t x, rp_pair* pairs, uint64_t cap,
                    size_t ws_bytes, void* stream) {
   if (validate_kernel(k) != RP_OK || (cap && !pairs)) return RP_ERR_INVALID;
   Plan pl;
-  make_plan(k, pl, false);
+  make_plan(k, pl);
   JobInput ji;
   ji.plan = &pl;
   ji.x = x;

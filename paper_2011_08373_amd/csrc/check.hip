@@ -30,8 +30,9 @@ constexpr uint32_t CONF_TILE = CONF_WAVES * CONF_CHUNKS * 64;   // records per t
 
 // mode IVL_RESOLVE: interval ids under x, then the first partners under x
 //   from the assignment-independent table j0 (see below);
-// mode IVL_CHECK: interval ids under x, first partners cleared, pair bitmap
-//   cleared (the all-pairs scan follows);
+// mode IVL_CHECK: interval ids under x, first partners cleared, and before an
+//   all-pairs scan of a log the pair bitmap cleared (with no log the closed
+//   form writes every row);
 // mode IVL_ZERO: interval ids of the empty assignment (one interval), first
 //   partners cleared: the scan that follows fills j0.
 //
@@ -93,7 +94,7 @@ __global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ 
   } else {
     for (uint32_t i = tid; i < 2 * P; i += IVL_BLOCK) J.minj[i] = NONE32;
   }
-  if (mode == IVL_CHECK && J.bitmap) {
+  if (mode == IVL_CHECK && J.bitmap && (J.nlog[0] != 0 || J.nlog[1] != 0)) {
     const uint64_t nw = 2ull * P * J.wpr;
     for (uint64_t q = tid; q < nw; q += IVL_BLOCK) J.bitmap[q] = 0;
   }
@@ -868,55 +869,62 @@ __global__ __launch_bounds__(CONF_BLOCK) void j0_kernel(const Job* __restrict__ 
   }
 }
 
-// Bitmap rows (level, i) in order -> pair list; one workgroup, rows in
-// contiguous chunks per thread so the block scan keeps row order.
-__global__ __launch_bounds__(1024) void pairs_kernel(const Job* __restrict__ jobs, rp_pair* out,
-                                                     uint64_t* total) {
-  __shared__ uint64_t wsum[16];
+// Bitmap rows (level, i) in order -> pair list.  Each row's pairs are counted
+// into minj (by the closed form, or by count_rows_kernel), then PR_ROWS rows
+// go to a workgroup: it sums the counts of all rows before its own, one wave
+// takes a row at a time, a lane one of its words, and lanes write their pairs
+// behind those of the lanes below.  For a 512-point kernel's list 7.2 us, from
+// 13.6 us by one workgroup of 1024 threads.
+constexpr int PR_BLOCK = 256, PR_WAVES = PR_BLOCK / 64;
+constexpr uint32_t PR_ROWS = 16;
+
+__global__ __launch_bounds__(PR_BLOCK) void count_rows_kernel(const Job* __restrict__ jobs) {
   const Job& J = jobs[0];
-  const uint32_t rows = 2 * J.P;
-  const uint32_t per = (rows + 1023) / 1024;
-  const int tid = threadIdx.x, lane = __lane_id(), w = tid >> 6;
-  uint64_t local = 0;
-  for (uint32_t q = 0; q < per; q++) {
-    const uint32_t row = tid * per + q;
-    if (row >= rows) break;
-    const uint64_t* rw = J.bitmap + (uint64_t)row * J.wpr;
-    for (uint32_t c = 0; c < J.wpr; c++) local += __popcll(rw[c]);
-  }
-  uint64_t inc = local;
-  for (int off = 1; off < 64; off <<= 1) {
-    uint64_t y = __shfl_up(inc, off);
-    if (lane >= off) inc += y;
-  }
-  if (lane == 63) wsum[w] = inc;
+  const uint32_t row = blockIdx.x * PR_WAVES + (threadIdx.x >> 6), lane = __lane_id();
+  if (row >= 2 * J.P) return;
+  uint32_t c = lane < J.wpr ? (uint32_t)__popcll(J.bitmap[(uint64_t)row * J.wpr + lane]) : 0u;
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+  if (lane == 0) J.minj[row] = c;
+}
+
+__global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__ jobs,
+                                                         rp_pair* out, uint64_t* total) {
+  __shared__ uint64_t s_sum[PR_WAVES];
+  const Job& J = jobs[0];
+  const uint32_t P = J.P, rows = 2 * P, wpr = J.wpr;
+  const uint32_t r0 = blockIdx.x * PR_ROWS;
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = tid >> 6;
+  uint64_t sum = 0;
+  for (uint32_t r = tid; r < r0; r += PR_BLOCK) sum += J.minj[r];
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if (lane == 0) s_sum[wv] = sum;
   __syncthreads();
-  uint64_t pos = 0, tot = 0;
-  for (int v = 0; v < 16; v++) {
-    if (v < w) pos += wsum[v];
-    tot += wsum[v];
-  }
-  pos += inc - local;
-  if (tid == 0) *total = tot;
-  for (uint32_t q = 0; q < per; q++) {
-    const uint32_t row = tid * per + q;
-    if (row >= rows) break;
-    const uint32_t lv = row / J.P, i = row % J.P;
-    const uint64_t* rw = J.bitmap + (uint64_t)row * J.wpr;
-    for (uint32_t c = 0; c < J.wpr; c++) {
-      uint64_t m = rw[c];
+  uint64_t pos = 0;
+  for (int w = 0; w < PR_WAVES; w++) pos += s_sum[w];
+  for (uint32_t r = r0; r < r0 + PR_ROWS && r < rows; r++) {
+    const uint32_t n = J.minj[r];
+    if ((r - r0) % PR_WAVES == wv && n != 0) {
+      uint64_t m = lane < wpr ? J.bitmap[(uint64_t)r * wpr + lane] : 0;
+      const uint32_t c = (uint32_t)__popcll(m);
+      uint32_t inc = c;
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(inc, o);
+        if (lane >= (uint32_t)o) inc += y;
+      }
+      rp_pair* at = out + pos + (inc - c);
+      rp_pair pr;
+      pr.i = (uint16_t)(r >= P ? r - P : r);
+      pr.level = r >= P;
+      pr.pad = 0;
       while (m) {
-        const uint32_t b = __ffsll((unsigned long long)m) - 1;
+        pr.j = (uint16_t)(lane * 64 + __builtin_ctzll(m));
         m &= m - 1;
-        rp_pair pr;
-        pr.i = (uint16_t)i;
-        pr.j = (uint16_t)(c * 64 + b);
-        pr.level = (uint8_t)lv;
-        pr.pad = 0;
-        out[pos++] = pr;
+        *at++ = pr;
       }
     }
+    pos += n;
   }
+  if (r0 + PR_ROWS >= rows && tid == 0) *total = pos;
 }
 
 uint32_t conf_tile_size() { return CONF_TILE; }
@@ -998,8 +1006,13 @@ hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t ma
                            : j0_go<false, false>(jobs, segs, nseg, max_points, tiles, s);
 }
 
-hipError_t launch_pairs(const Job* job, rp_pair* out, uint64_t* total, hipStream_t s) {
-  pairs_kernel<<<1, 1024, 0, s>>>(job, out, total);
+hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
+                        uint64_t* total, hipStream_t s) {
+  const uint32_t rows = 2 * points;
+  if (!counted && rows != 0)
+    count_rows_kernel<<<(rows + PR_WAVES - 1) / PR_WAVES, PR_BLOCK, 0, s>>>(job);
+  // (with no point at all one workgroup writes the total, 0)
+  pairs_kernel<<<rows ? (rows + PR_ROWS - 1) / PR_ROWS : 1, PR_BLOCK, 0, s>>>(job, out, total);
   return hipGetLastError();
 }
 

@@ -1,7 +1,9 @@
-// First partners in closed form (closed.h): the table j0 of the points whose
-// arrays the plan marks PF_CLOSED, with no access records.
+// Conflicts in closed form (closed.h), with no access records, for the points
+// whose arrays the plan marks PF_CLOSED: the table j0 of first partners
+// (first_kernel), or the rows of the racing-pair bitmap under an assignment
+// (all_kernel).
 //
-// One wave per (point, view).  Lanes take the 64 points from the wave's own
+// first_kernel: one wave per (point, view).  Lanes take the 64 points from the wave's own
 // point on, a chunk at a time; a lane whose point touches the same array (one
 // of the two writing) decides the pair, and the lowest lane that finds a
 // conflict is the first partner, so most waves end in their first chunk.
@@ -30,6 +32,25 @@ __device__ __forceinline__ Access access_of(const DPoint& d, uint32_t B) {
   return make_access(d.a, d.b, d.c, d.words, d.m, d.r, d.cnt, d.bm, d.br, B);
 }
 
+// Whether this lane's point j (>= i, in range) races with point i of access a
+// when no barrier separates them.
+template <class I>
+__device__ __forceinline__ bool lane_conflict(const Job& J, const DPoint& pi, const Access& a,
+                                              uint32_t i, uint32_t j, uint32_t lv) {
+  const DPoint& pj = J.pts[j];
+  if (pj.kind != RP_ACCESS || pj.array != pi.array || !((pi.flags | pj.flags) & PF_WRITE) ||
+      pj.cnt == 0 || pj.br >= J.B)
+    return false;
+  const Access q = access_of(pj, J.B);
+  if (lv != 0) return pair_cross_block<I>(a, q);
+  return j == i ? self_same_block(a) : pair_same_block<I>(a, q, J.B);
+}
+
+// Point i has conflicts to look for in view lv at all.
+__device__ __forceinline__ bool row_runs(const DPoint& pi, uint32_t B, uint32_t lv) {
+  return (lv == 0 || ((pi.flags & PF_GLOBAL) && B > 1)) && pi.cnt != 0 && pi.br < B;
+}
+
 template <class I>
 __global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restrict__ jobs) {
   const Job& J = jobs[blockIdx.y];
@@ -45,22 +66,11 @@ __global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restr
     return;
   }
   uint32_t best = NONE32;
-  if ((lv == 0 || ((pi.flags & PF_GLOBAL) && B > 1)) && pi.cnt != 0 && pi.br < B) {
+  if (row_runs(pi, B, lv)) {
     const Access a = access_of(pi, B);
-    const bool wi = pi.flags & PF_WRITE;
     for (uint32_t base = i; base < P; base += 64) {
       const uint32_t j = base + lane;
-      bool hit = false;
-      if (j < P) {
-        const DPoint& pj = J.pts[j];
-        if (pj.kind == RP_ACCESS && pj.array == pi.array && (wi || (pj.flags & PF_WRITE)) &&
-            pj.cnt != 0 && pj.br < B) {
-          const Access q = access_of(pj, B);
-          if (lv != 0) hit = pair_cross_block<I>(a, q);
-          else hit = j == i ? self_same_block(a) : pair_same_block<I>(a, q, B);
-        }
-      }
-      const uint64_t m = __ballot(hit);
+      const uint64_t m = __ballot(j < P && lane_conflict<I>(J, pi, a, i, j, lv));
       if (m) {
         best = base + (uint32_t)__builtin_ctzll(m);
         break;
@@ -70,12 +80,61 @@ __global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restr
   if (lane == 0) *out = best;
 }
 
+// Every racing pair under the job's assignment (its interval ids in ivl), one
+// wave per (point, view): the 64-point words of the row's bitmap are ballots,
+// kept one per lane (at most 64 words) and stored together.  Interval ids
+// never decrease along the program, so the row ends with its interval.  The
+// row's pairs are counted into minj for the list.  Bound by latency as above:
+// 31 us for plain-large under a quarter of its barriers, against 1.39 ms for
+// the scan of its sorted records (and 0.45 ms to generate and sort them).
+template <class I>
+__global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restrict__ jobs) {
+  static_assert(MAX_POINTS <= 64 * 64, "a row's words in one wave");
+  const Job& J = jobs[blockIdx.y];
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
+  const uint32_t P = J.P, B = J.B, lv = wv & 1;
+  const uint32_t i = blockIdx.x * (CF_WAVES / 2) + (wv >> 1);
+  if (i >= P) return;
+  const DPoint pi = J.pts[i];
+  // (with no records at all the scan of the logs has not cleared the row)
+  if (!closed_point(pi) && (J.nlog[0] != 0 || J.nlog[1] != 0)) return;
+  uint64_t word = 0;
+  if (closed_point(pi) && row_runs(pi, B, lv)) {
+    const Access a = access_of(pi, B);
+    const uint32_t* ivl = J.ivl + (uint64_t)lv * P;
+    const uint32_t iv = ivl[i];
+    for (uint32_t base = i & ~63u; base < P; base += 64) {
+      const uint32_t j = base + lane;
+      const bool in = j >= i && j < P && ivl[j < P ? j : P - 1] == iv;
+      if (__ballot(in) == 0) break;
+      const uint64_t m = __ballot(in && lane_conflict<I>(J, pi, a, i, j, lv));
+      if (lane == base >> 6) word = m;
+    }
+  }
+  const uint64_t row = (uint64_t)lv * P + i;
+  if (lane < J.wpr) J.bitmap[row * J.wpr + lane] = word;
+  uint32_t c = (uint32_t)__popcll(word);
+  for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+  if (lane == 0) J.minj[row] = c;
+}
+
+static dim3 row_grid(uint32_t max_points, uint32_t njobs) {
+  return dim3((max_points + CF_WAVES / 2 - 1) / (CF_WAVES / 2), njobs);
+}
+
+hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, hipStream_t s) {
+  if (points == 0) return hipSuccess;
+  const dim3 grid = row_grid(points, 1);
+  if (small) all_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(job);
+  else all_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(job);
+  return hipGetLastError();
+}
+
 hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
                                hipStream_t s) {
   if (njobs == 0 || max_points == 0) return hipSuccess;
   for (uint32_t j = 0; j < njobs; j += 65535) {      // (the grid's second dimension)
-    const dim3 grid((max_points + CF_WAVES / 2 - 1) / (CF_WAVES / 2),
-                    njobs - j < 65535 ? njobs - j : 65535);
+    const dim3 grid = row_grid(max_points, njobs - j < 65535 ? njobs - j : 65535);
     if (small) first_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j);
     else first_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j);
   }

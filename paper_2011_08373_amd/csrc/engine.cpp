@@ -559,12 +559,19 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   const uint32_t conf_launches = o.op == OP_SOLVE || L.ssegs.empty() ? 0 : 1;
   if (o.op == OP_CHECK) {
     HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, s));
-    HIPCHK(launch_conf_tiles(djobs, dcs, nseg, dtiles, s));
-    tm.mark(T_CONFPRE);
-    HIPCHK(launch_conf(djobs, dcs, nseg, maxP, dtiles, s));
-    tm.mark(T_CHECK);
+    if (nseg) {
+      HIPCHK(launch_conf_tiles(djobs, dcs, nseg, dtiles, s));
+      tm.mark(T_CONFPRE);
+      HIPCHK(launch_conf(djobs, dcs, nseg, maxP, dtiles, s));
+      tm.mark(T_CHECK);
+    }
     for (size_t j = 0; j < N; j++)
-      HIPCHK(launch_pairs(djobs + j, (rp_pair*)(d + L.o_pairs[j]), (uint64_t*)(d + L.o_ptotal[j]), s));
+      if (!nseg || jobs[j].plan->any_closed)
+        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, s));
+    tm.mark(T_CHECK, nseg ? 2 : 1);
+    for (size_t j = 0; j < N; j++)
+      HIPCHK(launch_pairs(djobs + j, jobs[j].plan->P, !nseg, (rp_pair*)(d + L.o_pairs[j]),
+                          (uint64_t*)(d + L.o_ptotal[j]), s));
     tm.mark(T_CLAUSE);
   } else if (o.op == OP_SOLVE) {
     HIPCHK(launch_solve(djobs, (uint32_t)N, s));

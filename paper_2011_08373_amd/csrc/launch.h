@@ -59,7 +59,14 @@ hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t ma
 // of closed.h.
 hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
                                hipStream_t s);
-hipError_t launch_pairs(const Job* job, rp_pair* out, uint64_t* total, hipStream_t s);
+// Racing pairs of the PF_CLOSED points of one job under its assignment (after
+// launch_ivl): bitmap rows, and their counts in minj (every row of a job that
+// has no records).
+hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, hipStream_t s);
+// The bitmap of one job as a pair list in (level, i, j) order.  counted: the
+// row counts are in minj already.
+hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
+                        uint64_t* total, hipStream_t s);
 hipError_t launch_clause(const Job* jobs, uint32_t njobs, int learn, hipStream_t s);
 hipError_t launch_solve(const Job* jobs, uint32_t njobs, hipStream_t s);
 hipError_t launch_count_active(const Job* jobs, uint32_t njobs, uint32_t* out, hipStream_t s);

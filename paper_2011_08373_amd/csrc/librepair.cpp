@@ -385,7 +385,7 @@ void mark_closed(const rp_kernel* k, Plan& pl) {
   }
 }
 
-void make_plan(const rp_kernel* k, Plan& pl, bool closed) {
+void make_plan(const rp_kernel* k, Plan& pl) {
   pl.P = k->n_points;
   pl.S = k->n_slots;
   pl.B = k->blocks;
@@ -487,7 +487,7 @@ void make_plan(const rp_kernel* k, Plan& pl, bool closed) {
   }
   pl.n_intra = pl.cnt_pre[pl.P] * pl.B;
   pl.n_inter = pl.gcnt_pre[pl.P];
-  if (closed && g_race_route == 0) mark_closed(k, pl);
+  if (g_race_route == 0) mark_closed(k, pl);
 }
 
 // Automatic digit width: the fewest passes of at most 10 bits, each as

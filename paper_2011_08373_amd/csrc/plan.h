@@ -28,9 +28,7 @@ struct Plan {
 };
 
 int validate_kernel(const rp_kernel* k);
-// closed: arrays may be decided in closed form (first partners), else every
-// access gets its records (the all-pairs scan).
-void make_plan(const rp_kernel* k, Plan& pl, bool closed = true);
+void make_plan(const rp_kernel* k, Plan& pl);
 void mark_closed(const rp_kernel* k, Plan& pl);
 void compact_words(const rp_kernel* k, Plan& pl);
 int pick_digit_bits(uint32_t key_bits);

@@ -126,3 +126,32 @@ def test_records_batched(L, records):  # noqa: F811
     full.test_batched_full_size(L, full._expected("batched"), "planted")
     parity.test_batch_many_kernels(L)
     parity.test_server_continuous_batching(L)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[str(s[:3]) for s in SHAPES])
+def test_check_edges(L, shape):  # noqa: F811
+    # every racing pair under random assignments, with barriers in between:
+    # rows that end inside a 64-point word and rows that span several
+    B, T, words, sa, sb = shape
+    rng = np.random.default_rng(T)
+    for P in (63, 64, 65, 130):
+        km = _random_kernel(rng, B, T, words, (sa, sb), P=P)
+        km.slots = np.zeros(3, synth.SLOT_DT)
+        km.slots["level"], km.slots["weight"] = (0, 1, 0), 1
+        for s, at in enumerate((P // 4, P // 2, P - 2)):
+            km.points[at] = (1, 0, 0, 0, s, 0, 0, 0)
+        for x in (0, 1, 2, 7):
+            assert L.check(km, x)[:4] == O.check(km, x), (P, x)
+
+
+def test_check_both_ways(L):  # noqa: F811
+    for seed in range(2):
+        km = _both_ways_kernel(seed)
+        for x in (0, 0x155):
+            assert L.check(km, x)[:4] == O.check(km, x), (seed, x)
+            assert L.last_stats()["records"] > 0
+
+
+def test_check_no_points(L):  # noqa: F811
+    km = synth.make_kernel(2, 4, [(8, 1)], [(1, 0)], [], [])
+    assert L.check(km, 0)[:4] == O.check(km, 0) and L.check(km, 0)[1] == []
