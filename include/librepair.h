@@ -211,9 +211,8 @@ rp_status rp_repair(const rp_kernel* k, const rp_repair_opts* opts,
                     void* ws, size_t ws_bytes, void* stream);
 
 /* Batched Alg. 1 over n kernels of any sizes: one launch per phase covers
- * every kernel (records, sort, run logs), each round is one captured hipGraph
- * (when `stream` is not NULL) over every kernel still running, and the host
- * reads one 32-bit count per round.  outs[j] gets kernel j's result exactly
+ * every kernel, and one launch runs every kernel's rounds to its verdict on
+ * the device.  outs[j] gets kernel j's result exactly
  * as rp_repair would give it, status included: a kernel that fails
  * validation gets RP_ERR_INVALID, one whose constraint set or a table of its
  * own overflows on the device RP_ERR_CAPACITY, one whose exact search spends
@@ -349,7 +348,9 @@ uint32_t rp_sort_key_bits(const rp_kernel* const* ks, uint32_t n);
  *                            (upload, generation, each radix pass and its
  *                            scatter, the first-partner scan, the all-pairs
  *                            scan) and the total (default), 2 = every phase
- *                            (rounds split into check / clause / solve).
+ *                            (rounds split into check / clause / solve by
+ *                            the device's clock; in a batch, those of the
+ *                            job that spent most).
  *                            Each event recorded on the stream costs a few
  *                            microseconds of device idle time;
  *   RP_TUNE_SCATTER_WGS      resident workgroups per compute unit of the
@@ -424,8 +425,7 @@ int rp_set_tuning(int knob, int value);
  * (rp_workspace_bytes(k, RP_OP_REPAIR)) exceeds it is rejected with
  * RP_ERR_WORKSPACE before any device work.  The call makes no device or
  * page-locked allocation (descriptors and results go through ordinary host
- * memory, rounds are launched without a graph, no timing events; host
- * planning uses the heap) and synchronises `stream` before it returns.
+ * memory, no timing events; host planning uses the heap) and synchronises `stream` before it returns.
  * Every call on one GPU shares that GPU's array: calls that overlap on one
  * GPU (from several host threads or streams) race and must be serialised by
  * the caller.  rp_last_stats is not updated. */

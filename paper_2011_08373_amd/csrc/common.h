@@ -79,13 +79,15 @@ struct JobState {        // device-resident per-job state; the host reads it
   uint32_t n_phi;        // clauses in phi (reduced)
   uint32_t state;        // 0 running, 1 safe, 2 unsat, 3 error
   uint32_t rounds;       // Verify calls made
-  uint32_t races;        // (point, level) rows with a race at the last Verify
+  uint32_t t_clause;     // ticks of the device clock in GenerateClause (timing level 2)
   uint32_t err;          // device-side error code (0 = none)
   uint32_t max_rounds;   // 0 = unlimited
-  uint64_t traj_pad;
+  uint32_t n_full;       // clauses of the job's table of all race clauses
+  uint32_t t_check;      // ticks in Verify
   uint32_t phase;        // PH_*: which Solve the next call makes
-  uint32_t pad3;
+  uint32_t t_solve;      // ticks in Solve
 };
+static_assert(sizeof(JobState) == 64, "read back by size");
 constexpr uint32_t ST_RUN = 0, ST_SAFE = 1, ST_UNSAT = 2, ST_ERROR = 3, ST_ROUNDS = 4;
 // Solve phases.  PH_EXACT: the exact optimum.  PH_GREEDY (mhs strategy,
 // until the first SAFE): the greedy hitting set of the positive clauses, the

@@ -1,6 +1,6 @@
 // Execution engine: lays out one or many jobs in a device workspace and runs
-// record generation, the radix sort and the per-round Verify / GenerateClause /
-// Solve kernels of Alg. 1 on a stream.
+// first partners (in closed form, or record generation, radix sort and scan)
+// and the rounds of Alg. 1 on a stream.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -226,10 +226,8 @@ struct Timer {
 };
 
 // phase tags for the stats
-// T_ROUND opens a repair round: the time since the previous mark (the
-// host's per-round readback) is counted in ms_total only.
-enum { T_START = 0, T_UPLOAD, T_GEN, T_SORTPASS, T_SORT, T_RUNS, T_SUMPRE, T_SUMMARY, T_ROUND,
-       T_CONFPRE, T_CHECK, T_CLAUSE, T_SOLVE, T_END };
+enum { T_START = 0, T_UPLOAD, T_GEN, T_SORTPASS, T_SORT, T_RUNS, T_SUMPRE, T_SUMMARY, T_CONFPRE,
+       T_CHECK, T_CLAUSE, T_SOLVE, T_END };
 
 }  // namespace
 
@@ -480,18 +478,16 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   // left as they are by the solver
   bool any_units = false;
   for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
-  if (any_units) HIPCHK(launch_solve((const Job*)(d + L.o_jobs), (uint32_t)jobs.size(), s));
+  HIPCHK(launch_rounds((const Job*)(d + L.o_jobs), (uint32_t)jobs.size(),
+                       RD_BUILD | (any_units ? RD_SOLVE : 0), 0, s));
   out.resize(jobs.size());
   for (size_t j = 0; j < jobs.size(); j++)
     std::memcpy(&out[j].job, staging.data() + L.o_jobs + j * sizeof(Job), sizeof(Job));
   return RP_OK;
 }
 
-int engine_round(const Job* djobs, uint32_t njobs, uint32_t* dactive, hipStream_t s) {
-  HIPCHK(launch_ivl(djobs, njobs, IVL_RESOLVE, s));
-  HIPCHK(launch_clause(djobs, njobs, 1, s));
-  HIPCHK(launch_solve(djobs, njobs, s));
-  HIPCHK(launch_count_active(djobs, njobs, dactive, s));
+int engine_round(const Job* djobs, uint32_t njobs, hipStream_t s) {
+  HIPCHK(launch_rounds(djobs, njobs, RD_LOOP, 1, s));
   return RP_OK;
 }
 
@@ -530,7 +526,7 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   std::vector<JobState> hst(N);
   // job states, the error word and the start of each job's trajectory (the
   // usual few rounds) are read back into page-locked memory in one go
-  const uint32_t traj_head = std::min<uint32_t>(o.traj_cap, 16);
+  const uint32_t traj_head = std::min<uint32_t>(o.traj_cap, 64);
   const size_t rb_bytes = N * sizeof(JobState) + 64 + N * traj_head * sizeof(uint64_t);
   uint8_t* rb;
   if (o.no_alloc) {
@@ -551,11 +547,9 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
                          hipMemcpyDeviceToHost, s);
     return e;
   };
-  bool ended = false, have_results = false;
   // the run logs are scanned once: by the all-pairs scan of a check, else
   // by the first-partner scan of the preparation
   const uint64_t scanned = o.op == OP_SOLVE ? 0 : L.n_rec;    // (0: all in closed form)
-  uint32_t rounds_run = 0;
   const uint32_t conf_launches = o.op == OP_SOLVE || L.ssegs.empty() ? 0 : 1;
   if (o.op == OP_CHECK) {
     HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, s));
@@ -574,94 +568,26 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
                           (uint64_t*)(d + L.o_ptotal[j]), s));
     tm.mark(T_CLAUSE);
   } else if (o.op == OP_SOLVE) {
-    HIPCHK(launch_solve(djobs, (uint32_t)N, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_SOLVE, 0, s));
     tm.mark(T_SOLVE);
   } else if (o.op == OP_FIRST) {
     HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s));
     tm.mark(T_CHECK);
   } else if (o.op == OP_CLAUSES) {
-    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s));
-    tm.mark(T_CHECK);
-    HIPCHK(launch_clause(djobs, (uint32_t)N, 1, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_BUILD | RD_LEARN, 0, s));
     tm.mark(T_CLAUSE);
   } else {
-    uint32_t* dactive = (uint32_t*)(d + L.o_err) + 8;
     // the first Solve of Alg. 1: with no option units phi is empty and its
     // answer is x = 0 (weight 0), which the job states already hold
     bool any_units = false;
     for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
-    if (any_units) HIPCHK(launch_solve(djobs, (uint32_t)N, s));
-    tm.mark(T_SOLVE, 2);
-    auto round = [&]() -> hipError_t {
-      hipError_t e;
-      if ((e = launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s)) != hipSuccess) return e;
-      if ((e = launch_clause(djobs, (uint32_t)N, 1, s)) != hipSuccess) return e;
-      if ((e = launch_solve(djobs, (uint32_t)N, s)) != hipSuccess) return e;
-      return launch_count_active(djobs, (uint32_t)N, dactive, s);
-    };
-    // the first round is launched directly; if jobs remain, the round is
-    // captured once in a graph and replayed until every job has a verdict.
-    // A small batch reads every verdict together with the round's count of
-    // running jobs (it sits in the error word), so the round that ends the
-    // loop needs no further wait; a large one reads the count alone.
-    const bool with_results = N <= 64;
-    hipGraphExec_t gexec = nullptr;
-    hipGraph_t graph = nullptr;
-    bool tried_graph = false;
-    uint32_t n_active = 1;
-    int rc_loop = RP_OK;
-    while (n_active) {
-      if (rounds_run == 1 && !tried_graph && o.use_graph && s != nullptr) {
-        tried_graph = true;
-        if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-          const hipError_t e = round();
-          const hipError_t ec = hipStreamEndCapture(s, &graph);
-          if (e != hipSuccess || ec != hipSuccess ||
-              hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0) != hipSuccess) {
-            if (graph) (void)hipGraphDestroy(graph);
-            graph = nullptr;
-            gexec = nullptr;
-            (void)hipGetLastError();
-          }
-        }
-      }
-      tm.mark(T_ROUND, 2);
-      if (gexec) {
-        if (hipGraphLaunch(gexec, s) != hipSuccess) { rc_loop = RP_ERR_DEVICE; break; }
-        tm.mark(T_CHECK, 2);
-      } else {
-        HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s));
-        tm.mark(T_CHECK, 2);
-        HIPCHK(launch_clause(djobs, (uint32_t)N, 1, s));
-        tm.mark(T_CLAUSE, 2);
-        HIPCHK(launch_solve(djobs, (uint32_t)N, s));
-        tm.mark(T_SOLVE, 2);
-        HIPCHK(launch_count_active(djobs, (uint32_t)N, dactive, s));
-      }
-      tm.mark(T_END);           // the last one recorded ends the final round
-      const hipError_t e = with_results
-                               ? enqueue_results()
-                               : hipMemcpyAsync(herr + 8, dactive, sizeof(uint32_t),
-                                                hipMemcpyDeviceToHost, s);
-      if (e != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
-        rc_loop = RP_ERR_DEVICE;
-        break;
-      }
-      n_active = herr[8];
-      rounds_run++;
-      if (rounds_run > 100000) { rc_loop = RP_ERR_DEVICE; break; }
-    }
-    if (gexec) (void)hipGraphExecDestroy(gexec);
-    if (graph) (void)hipGraphDestroy(graph);
-    if (rc_loop != RP_OK) return rc_loop;
-    ended = true;
-    have_results = with_results;
+    HIPCHK(launch_rounds(djobs, (uint32_t)N,
+                         RD_BUILD | RD_LOOP | (any_units ? RD_SOLVE : 0) |
+                             (tm.level >= 2 ? RD_TIMED : 0), 0, s));
   }
-  if (!ended) tm.mark(T_END);
-  if (!have_results) {
-    HIPCHK(enqueue_results());
-    HIPCHK(hipStreamSynchronize(s));
-  }
+  tm.mark(T_END);
+  HIPCHK(enqueue_results());
+  HIPCHK(hipStreamSynchronize(s));
   std::memcpy(hst.data(), pst, N * sizeof(JobState));
   if (herr[0]) return RP_ERR_DEVICE;
   res.assign(N, JobResult{});
@@ -744,7 +670,23 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     for (const JobInput& j : jobs) stats->accesses += j.plan->accesses;
     stats->records_scanned = scanned;
     stats->sort_passes = L.passes;
-    stats->rounds = rounds_run;
+    // (the rounds run on the device: their phases are counted there, and in
+    // a batch the job that spent most in a phase stands for it)
+    uint32_t tc = 0, tl = 0, ts = 0;
+    for (const JobState& st : hst) {
+      if (o.op == OP_REPAIR) stats->rounds = std::max(stats->rounds, st.rounds);
+      tc = std::max(tc, st.t_check);
+      tl = std::max(tl, st.t_clause);
+      ts = std::max(ts, st.t_solve);
+    }
+    if (tm.level >= 2 && o.op == OP_REPAIR) {
+      int khz = 0;
+      if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, tm.dev) == hipSuccess && khz) {
+        stats->ms_check += (double)tc / khz;
+        stats->ms_clause += (double)tl / khz;
+        stats->ms_solve += (double)ts / khz;
+      }
+    }
     stats->conf_launches = conf_launches;
   }
   return RP_OK;

@@ -67,8 +67,12 @@ hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, hipStr
 // row counts are in minj already.
 hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
                         uint64_t* total, hipStream_t s);
-hipError_t launch_clause(const Job* jobs, uint32_t njobs, int learn, hipStream_t s);
-hipError_t launch_solve(const Job* jobs, uint32_t njobs, hipStream_t s);
-hipError_t launch_count_active(const Job* jobs, uint32_t njobs, uint32_t* out, hipStream_t s);
+// The rounds of Alg. 1 on every running job.  RD_BUILD: the job's clause tables
+// from j0 first; RD_SOLVE: one Solve first; RD_LOOP: rounds, at most limit of
+// them (0: until a verdict); RD_LEARN: Verify and GenerateClause under the
+// job's assignment only; RD_TIMED: the phases' clock ticks into the job state.
+constexpr int RD_BUILD = 1, RD_SOLVE = 2, RD_LOOP = 4, RD_LEARN = 8, RD_TIMED = 16;
+hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int flags, uint32_t limit,
+                         hipStream_t s);
 
 }  // namespace rp

@@ -13,9 +13,8 @@
 // there.  Calls that overlap on one device race on the array.
 //
 // The call makes no device or page-locked allocation: the descriptor upload
-// and the result readback go through ordinary host memory, every round is
-// launched directly (no graph is instantiated) and no timing events are
-// recorded.  Host-side planning still uses the heap.
+// and the result readback go through ordinary host memory and no timing
+// events are recorded.  Host-side planning still uses the heap.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -79,7 +78,6 @@ rp_status rp_repair_noalloc(const rp_kernel* k, const rp_repair_opts* opts, rp_r
   EngineOpts o;
   o.op = OP_REPAIR;
   o.traj_cap = traj_cap;
-  o.use_graph = false;
   o.no_alloc = true;
   std::vector<JobInput> v{ji};
   // too large for the fixed array: rejected before any device work

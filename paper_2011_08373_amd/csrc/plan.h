@@ -88,7 +88,6 @@ struct EngineOpts {
   uint64_t pair_cap = 0;            // check: caller's capacity
   uint32_t traj_cap = 0;
   bool want_pairs = true;
-  bool use_graph = true;            // capture each round in a hipGraph (non-null stream)
   bool no_alloc = false;            // stage through ordinary host memory, record no
                                     // timing events (no device or page-locked allocation)
 };
@@ -111,10 +110,9 @@ size_t engine_group_bytes(const std::vector<JobInput>& jobs);
 int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t bytes,
                          hipStream_t s, std::vector<PreparedJob>& out,
                          std::vector<uint8_t>& staging);
-// Enqueues one round (Verify, GenerateClause, Solve, active count) over the
-// device table of njobs prepared jobs; *dactive receives the number of jobs
-// still running after it.
-int engine_round(const Job* djobs, uint32_t njobs, uint32_t* dactive, hipStream_t s);
+// Enqueues one round (Verify, GenerateClause, Solve) over the device table of
+// njobs prepared jobs.
+int engine_round(const Job* djobs, uint32_t njobs, hipStream_t s);
 
 // Runs the op over all jobs; returns RP_OK or an error status.
 int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws, size_t ws_bytes,

@@ -128,7 +128,6 @@ struct Server {
   // fixed tables at the start of the arena
   Job* d_jobs = nullptr;
   JobState* d_states = nullptr;
-  uint32_t* d_active = nullptr;
   size_t tables = 0;
   Arena alloc;
   std::deque<std::unique_ptr<SJob>> pending;
@@ -185,7 +184,7 @@ rp_status rp_server_create(void* arena, size_t arena_bytes, const rp_repair_opts
   size_t o = 0;
   sv->d_jobs = (Job*)(sv->arena + o); o += sup(max_resident * sizeof(Job));
   sv->d_states = (JobState*)(sv->arena + o); o += sup(max_resident * sizeof(JobState));
-  sv->d_active = (uint32_t*)(sv->arena + o); o += SALIGN;
+  o += SALIGN;
   sv->tables = o;
   sv->alloc.init(o, arena_bytes - o);
   *out = sv;
@@ -265,7 +264,7 @@ rp_status rp_server_step(void* srv, uint32_t* n_resident, uint32_t* n_pending) {
     if (hipMemcpyAsync(sv->d_jobs, sv->h_jobs.data(), n * sizeof(Job), hipMemcpyHostToDevice, s) !=
         hipSuccess)
       return RP_ERR_DEVICE;
-    const int rc = engine_round(sv->d_jobs, n, sv->d_active, s);
+    const int rc = engine_round(sv->d_jobs, n, s);
     if (rc != RP_OK) return (rp_status)rc;
     gather_states_kernel<<<(n + 255) / 256, 256, 0, s>>>(sv->d_jobs, n, sv->d_states);
     sv->h_states.resize(n);

@@ -9,7 +9,7 @@
 // hitting set of greedy_solve instead, and the round after it the exact
 // query (phase PH_FINAL) that confirms or replaces the greedy answer.
 //
-// One workgroup per job:
+// One workgroup of SV_BLOCK threads (the round loop's) per job:
 //   1. unit propagation: positive units force a slot on, negative units
 //      force it off, a clause with no literal left proves UNSAT; a slot that
 //      is in no positive literal of an open clause is set off (it can only
@@ -32,14 +32,14 @@
 //      far (a shared word) as well as its own best key.  The optimum is
 //      unique, so the smallest of the waves' best keys is the answer whatever
 //      order the waves run in.
+#pragma once
 #include "common.h"
-#include "launch.h"
 
 namespace rp {
 
 constexpr int SV_BLOCK = 256;
 constexpr int SV_WAVES = SV_BLOCK / 64;
-constexpr uint32_t SV_LDS_CLAUSES = 3072;
+constexpr uint32_t SV_CLAUSES = 1536;     // clauses of a component; open clauses kept in LDS
 constexpr int ENUM_MAX = 20;
 
 struct Key { uint64_t hi, lo; };
@@ -107,6 +107,22 @@ constexpr int SPLIT_DEPTH = 3;           // depth whose nodes are dealt out to t
 
 constexpr uint32_t GREEDY_MAX = 16384;   // clauses the greedy step handles (bitset in LDS)
 
+// LDS of the solver.
+struct SolveLds {
+  rp_clause cl[SV_CLAUSES];                // open clauses (restricted)
+  uint64_t lp[SV_CLAUSES], ln[SV_CLAUSES], la[SV_CLAUSES];  // per component: local pos / neg / aux
+  uint64_t kh[64], kl[64];                 // local slot key parts
+  uint64_t lowh[64], lowl[64];             // key of each low pattern
+  uint32_t order[64], gslot[64];
+  uint64_t smA[SV_WAVES], smB[SV_WAVES];
+  uint64_t inch[SV_WAVES], incl[SV_WAVES];
+  DfsFrame stack[SV_WAVES][65];
+  unsigned long long bound;                // smallest weight part found by any wave
+  uint32_t cnt, overflow, best;
+  uint32_t c64[64], pick[64];
+  uint32_t hit[GREEDY_MAX / 32];
+};
+
 // The mhs strategy's Solve (Section 2.4): the greedy minimal hitting set of
 // the positive clauses of phi -- repeatedly the slot hitting the most clauses
 // not yet hit per unit of weight (exact integer comparison, ties to the lower
@@ -114,8 +130,9 @@ constexpr uint32_t GREEDY_MAX = 16384;   // clauses the greedy step handles (bit
 // dropped, last pick first.  Returns false (the caller solves exactly) when
 // phi has an empty clause, is too long, or the set breaks a clause of phi.
 __device__ bool greedy_solve(const Job& J, JobState* st, uint32_t n, const rp_clause* C,
-                             uint32_t* s_hit, uint32_t* s_c64, uint32_t* s_pick,
-                             uint32_t* s_best, uint64_t* sm) {
+                             SolveLds& s) {
+  uint32_t *s_hit = s.hit, *s_c64 = s.c64, *s_pick = s.pick, *s_best = &s.best;
+  uint64_t* sm = s.smA;
   const int tid = threadIdx.x;
   const uint32_t S = J.S;
   if (n > GREEDY_MAX) return false;
@@ -190,34 +207,17 @@ __device__ bool greedy_solve(const Job& J, JobState* st, uint32_t n, const rp_cl
   return true;
 }
 
-__global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__ jobs) {
-  __shared__ rp_clause s_cl[SV_LDS_CLAUSES];    // open clauses (restricted), 48 KiB
-  __shared__ uint64_t s_lp[SV_LDS_CLAUSES / 2];  // per component: local pos / neg / aux
-  __shared__ uint64_t s_ln[SV_LDS_CLAUSES / 2];
-  __shared__ uint64_t s_la[SV_LDS_CLAUSES / 2];
-  __shared__ uint64_t s_kh[64], s_kl[64];        // local slot key parts
-  __shared__ uint64_t s_lowh[64], s_lowl[64];    // key of each low pattern
-  __shared__ uint32_t s_order[64];
-  __shared__ uint32_t s_gslot[64];
-  __shared__ uint64_t smA[SV_WAVES], smB[SV_WAVES];
-  __shared__ uint32_t s_cnt;
-  __shared__ DfsFrame s_stack[SV_WAVES][65];
-  __shared__ unsigned long long s_bound;         // smallest weight part found by any wave
-  __shared__ uint32_t s_overflow;
-  __shared__ uint64_t s_inch[SV_WAVES], s_incl[SV_WAVES];
-  __shared__ uint32_t s_hit[GREEDY_MAX / 32];
-  __shared__ uint32_t s_c64[64], s_pick[64], s_best;
-
-  const Job& J = jobs[blockIdx.x];
-  JobState* st = J.st;
-  if (st->state != ST_RUN) return;
+// Solve over phi = C[0..n) for the job state *st (in LDS; thread 0 writes it):
+// x and weight, or a final state.  Every thread of the workgroup calls it.
+__device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint32_t n,
+                           SolveLds& L) {
+  uint64_t *smA = L.smA, *smB = L.smB;
   const int tid = threadIdx.x, lane = __lane_id(), wv = tid >> 6;
   const uint32_t S = J.S;
   const uint64_t all = S >= 64 ? ~0ull : ((1ull << S) - 1);
-  const uint32_t n = st->n_phi;
-  const rp_clause* C = J.phi;
   const uint32_t phase = st->phase;
-  if (phase == PH_GREEDY && greedy_solve(J, st, n, C, s_hit, s_c64, s_pick, &s_best, smA)) return;
+  __syncthreads();          // (every thread has the phase before thread 0 may change it)
+  if (phase == PH_GREEDY && greedy_solve(J, st, n, C, L)) return;
 
   // ---- 1. propagation
   uint64_t on = 0, off = 0;
@@ -250,21 +250,20 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
   const uint64_t freeS = all & ~on & ~off;
 
   // ---- open clauses restricted to the free slots
-  if (tid == 0) s_cnt = 0;
+  if (tid == 0) L.cnt = 0;
   __syncthreads();
-  rp_clause* U = s_cl;
-  const bool lds = n <= SV_LDS_CLAUSES;
-  if (!lds) U = J.scratch;   // scratch holds >= n clauses
+  // (the first phi_cap clauses of scratch hold at least n)
+  rp_clause* U = n <= SV_CLAUSES ? L.cl : J.scratch;
   for (uint32_t q = tid; q < n; q += SV_BLOCK) {
     const rp_clause c = C[q];
     if ((c.pos & on) || (c.neg & off)) continue;
     rp_clause r;
     r.pos = c.pos & freeS;
     r.neg = c.neg & freeS;
-    U[atomicAdd(&s_cnt, 1u)] = r;
+    U[atomicAdd(&L.cnt, 1u)] = r;
   }
   __syncthreads();
-  const uint32_t nu = s_cnt;
+  const uint32_t nu = L.cnt;
 
   uint64_t result = on;
   uint64_t left = freeS;
@@ -290,30 +289,30 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
       while (m) {
         const uint32_t s = __ffsll((unsigned long long)m) - 1;
         m &= m - 1;
-        s_gslot[b] = s;
-        s_kh[b] = (uint64_t)J.weights[s] * 128u + 1u;
-        s_kl[b] = 1ull << s;
+        L.gslot[b] = s;
+        L.kh[b] = (uint64_t)J.weights[s] * 128u + 1u;
+        L.kl[b] = 1ull << s;
         b++;
       }
-      s_cnt = 0;
+      L.cnt = 0;
     }
     __syncthreads();
-    // component clauses in local numbering (s_lp/s_ln), aux = lower bound
-    const uint32_t cap_local = SV_LDS_CLAUSES / 2;
+    // component clauses in local numbering (L.lp/L.ln), aux = lower bound
+    const uint32_t cap_local = SV_CLAUSES;
     for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
       const rp_clause c = U[q];
       if (!((c.pos | c.neg) & comp)) continue;
       uint64_t lp = 0, ln = 0, lb = ~0ull;
       for (int b = 0; b < k; b++) {
-        const uint64_t g = 1ull << s_gslot[b];
-        if (c.pos & g) { lp |= 1ull << b; lb = s_kh[b] < lb ? s_kh[b] : lb; }
+        const uint64_t g = 1ull << L.gslot[b];
+        if (c.pos & g) { lp |= 1ull << b; lb = L.kh[b] < lb ? L.kh[b] : lb; }
         if (c.neg & g) ln |= 1ull << b;
       }
-      const uint32_t slot = atomicAdd(&s_cnt, 1u);
-      if (slot < cap_local) { s_lp[slot] = lp; s_ln[slot] = ln; s_la[slot] = lp ? lb : 0; }
+      const uint32_t slot = atomicAdd(&L.cnt, 1u);
+      if (slot < cap_local) { L.lp[slot] = lp; L.ln[slot] = ln; L.la[slot] = lp ? lb : 0; }
     }
     __syncthreads();
-    const uint32_t nc = s_cnt;
+    const uint32_t nc = L.cnt;
     if (nc > cap_local) {
       if (tid == 0) { st->err = ERR_SCRATCH; st->state = ST_ERROR; }
       return;
@@ -325,19 +324,19 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
       if (tid < 64) {
         uint64_t h = 0, l = 0;
         for (int b = 0; b < low; b++)
-          if ((tid >> b) & 1) { h += s_kh[b]; l |= s_kl[b]; }
-        s_lowh[tid] = h;
-        s_lowl[tid] = l;
+          if ((tid >> b) & 1) { h += L.kh[b]; l |= L.kl[b]; }
+        L.lowh[tid] = h;
+        L.lowl[tid] = l;
       }
       __syncthreads();
       if (tid < 64) {   // rank of pattern tid by key
         uint32_t rk = 0;
-        const Key me = {s_lowh[tid], s_lowl[tid]};
+        const Key me = {L.lowh[tid], L.lowl[tid]};
         for (int o = 0; o < 64; o++) {
-          const Key ot = {s_lowh[o], s_lowl[o]};
+          const Key ot = {L.lowh[o], L.lowl[o]};
           if (key_lt(ot, me) || (ot.hi == me.hi && ot.lo == me.lo && o < tid)) rk++;
         }
-        s_order[rk] = tid;
+        L.order[rk] = tid;
       }
       __syncthreads();
       const uint64_t valid = low == 6 ? ~0ull : ((1ull << (1u << low)) - 1);
@@ -347,7 +346,7 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
         uint64_t feas = valid;
         const uint64_t hbits = (uint64_t)H << low;
         for (uint32_t q = 0; q < nc && feas; q++) {
-          const uint64_t lp = s_lp[q], ln = s_ln[q];
+          const uint64_t lp = L.lp[q], ln = L.ln[q];
           uint64_t sp, sn;
           if (lp & hbits) sp = ~0ull;
           else {
@@ -369,13 +368,13 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
         while (m) {
           const int b = __ffsll((unsigned long long)m) - 1;
           m &= m - 1;
-          kh.hi += s_kh[b];
-          kh.lo |= s_kl[b];
+          kh.hi += L.kh[b];
+          kh.lo |= L.kl[b];
         }
         for (int o = 0; o < 64; o++) {
-          const uint32_t pt = s_order[o];
+          const uint32_t pt = L.order[o];
           if ((feas >> pt) & 1) {
-            const Key cand = {kh.hi + s_lowh[pt], kh.lo | s_lowl[pt]};
+            const Key cand = {kh.hi + L.lowh[pt], kh.lo | L.lowl[pt]};
             if (key_lt(cand, best)) best = cand;
             break;
           }
@@ -385,12 +384,12 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
     } else {
       // ---- 4. depth-first branch and bound by every wave
       if (tid == 0) {
-        s_bound = ~0ull;
-        s_overflow = 0;
+        L.bound = ~0ull;
+        L.overflow = 0;
       }
       __syncthreads();
       {
-        DfsFrame* stk = s_stack[wv];
+        DfsFrame* stk = L.stack[wv];
         Key inc = {~0ull, ~0ull};
         bool found = false;
         uint64_t nodes = 0;
@@ -411,7 +410,7 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
             // bound pruning there, so the numbering agrees); below it a node
             // no better than a known weight is skipped
             const uint64_t bound = depth >= SPLIT_DEPTH
-                                       ? (uint64_t)__hip_atomic_load(&s_bound, __ATOMIC_RELAXED,
+                                       ? (uint64_t)__hip_atomic_load(&L.bound, __ATOMIC_RELAXED,
                                                                      __HIP_MEMORY_SCOPE_WORKGROUP)
                                        : ~0ull;
             if (mine) nodes++;
@@ -421,13 +420,13 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
             if (!skip) {
               uint64_t dead = 0, pick = ~0ull, lbmax = 0;
               for (uint32_t q = lane; q < nc; q += 64) {
-                const uint64_t lp = s_lp[q], ln = s_ln[q];
+                const uint64_t lp = L.lp[q], ln = L.ln[q];
                 if ((lp & ones) || (ln & ~ones)) continue;   // satisfied with undecided = 0
                 const uint64_t fr = lp & ~zeros;
                 if (fr == 0) { dead = 1; continue; }
                 const uint64_t cand = ((uint64_t)__popcll(fr) << 32) | q;
                 pick = cand < pick ? cand : pick;
-                lbmax = s_la[q] > lbmax ? s_la[q] : lbmax;
+                lbmax = L.la[q] > lbmax ? L.la[q] : lbmax;
               }
               dead = wave_or(dead);
               pick = wave_min_u64(pick);
@@ -439,7 +438,7 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
                     inc = key;
                     found = true;
                     if (lane == 0)
-                      __hip_atomic_fetch_min(&s_bound, (unsigned long long)key.hi,
+                      __hip_atomic_fetch_min(&L.bound, (unsigned long long)key.hi,
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                   }
                 } else if (depth < SPLIT_DEPTH ||
@@ -449,7 +448,7 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
                   // read follows its own write
                   DfsFrame f;
                   f.ones = ones; f.zeros = zeros; f.khi = key.hi; f.klo = key.lo;
-                  f.todo = s_lp[q] & ~zeros; f.tried = 0;
+                  f.todo = L.lp[q] & ~zeros; f.tried = 0;
                   stk[depth] = f;
                   __builtin_amdgcn_wave_barrier();
                   depth++;
@@ -470,25 +469,25 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
           __builtin_amdgcn_wave_barrier();
           ones = f.ones | sbit;
           zeros = f.zeros | f.tried;
-          key.hi = f.khi + s_kh[b];
-          key.lo = f.klo | s_kl[b];
+          key.hi = f.khi + L.kh[b];
+          key.lo = f.klo | L.kl[b];
           eval_pending = true;
         }
         if (lane == 0) {
-          if (overflow) atomicOr(&s_overflow, 1u);
-          s_inch[wv] = found ? inc.hi : ~0ull;
-          s_incl[wv] = found ? inc.lo : ~0ull;
+          if (overflow) atomicOr(&L.overflow, 1u);
+          L.inch[wv] = found ? inc.hi : ~0ull;
+          L.incl[wv] = found ? inc.lo : ~0ull;
         }
       }
       __syncthreads();
-      if (s_overflow) {
+      if (L.overflow) {
         if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
         return;
       }
-      best.hi = s_inch[0];
-      best.lo = s_incl[0];
+      best.hi = L.inch[0];
+      best.lo = L.incl[0];
       for (int q = 1; q < SV_WAVES; q++) {
-        const Key o = {s_inch[q], s_incl[q]};
+        const Key o = {L.inch[q], L.incl[q]};
         if (key_lt(o, best)) best = o;
       }
       __syncthreads();
@@ -517,12 +516,6 @@ __global__ __launch_bounds__(SV_BLOCK) void solve_kernel(const Job* __restrict__
     st->weight = W;
     if (st->max_rounds && st->rounds >= st->max_rounds) st->state = ST_ROUNDS;
   }
-}
-
-hipError_t launch_solve(const Job* jobs, uint32_t njobs, hipStream_t s) {
-  if (njobs == 0) return hipSuccess;
-  solve_kernel<<<njobs, SV_BLOCK, 0, s>>>(jobs);
-  return hipGetLastError();
 }
 
 }  // namespace rp
