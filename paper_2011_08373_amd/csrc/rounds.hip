@@ -270,17 +270,18 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   __shared__ RoundLds L;
   __shared__ JobState s_st;
   __shared__ uint64_t sm[RD_WAVES];
-  __shared__ uint32_t s_row, s_n;
+  __shared__ uint32_t s_row, s_n, s_w[64];
   const Job& J = jobs[blockIdx.x];
   const uint32_t tid = threadIdx.x, lane = __lane_id(), P = J.P;
   JobState* st = &s_st;
   if (J.st->state != ST_RUN) return;
   if (tid < sizeof(JobState) / 4) ((uint32_t*)st)[tid] = ((const uint32_t*)J.st)[tid];
+  if (tid < 64) s_w[tid] = tid < J.S ? J.weights[tid] : 0;
   __syncthreads();
   const bool one = J.policy == 1 && !(flags & RD_LEARN);
   if (flags & RD_BUILD) build_tables(J, st, J.policy == 1, L.b, sm);
   if (flags & RD_SOLVE) {
-    solve_body(J, st, J.phi, st->n_phi, L.s);
+    solve_body(J, st, J.phi, st->n_phi, s_w, L.s);
     __syncthreads();
   }
   const uint64_t* F = full_of(J);
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
     lap(st->t_clause);
     if (flags & RD_LEARN) break;
     if (solve) {
-      solve_body(J, st, J.phi, n, L.s);
+      solve_body(J, st, J.phi, n, s_w, L.s);
       __syncthreads();
     }
     lap(st->t_solve);

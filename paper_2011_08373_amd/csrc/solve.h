@@ -10,17 +10,25 @@
 // query (phase PH_FINAL) that confirms or replaces the greedy answer.
 //
 // One workgroup of SV_BLOCK threads (the round loop's) per job:
-//   1. unit propagation: positive units force a slot on, negative units
+//   1. reduction to a fixpoint: positive units force a slot on, negative units
 //      force it off, a clause with no literal left proves UNSAT; a slot that
 //      is in no positive literal of an open clause is set off (it can only
-//      add weight);
-//   2. the open clauses split into components over the free slots (the key
-//      is additive, so components are solved independently);
-//   3. a component of k <= 20 slots is enumerated bit-sliced: a 64-bit word
+//      add weight); and a slot s is set off when another slot t with a smaller
+//      key is in every open clause that s is in (and in no negative literal):
+//      an assignment with s would be improved by t in its place, so the
+//      optimum has no s.  Subsumed open clauses are dropped in between;
+//   2. if what is left is all positive and every clause is a contiguous run of
+//      the slots left (a race's clause is the run of barriers between two
+//      points), the optimum is a shortest path over the slots
+//      (interval_optimum), one step per slot;
+//   3. else the open clauses split into components over the free slots (the
+//      key is additive, so components are solved independently): again a
+//      path where one is made of runs;
+//   4. a component of k <= 20 slots is enumerated bit-sliced: a 64-bit word
 //      holds the six lowest slots' 64 assignments, every clause is evaluated
 //      on whole words with AND/OR, and each word's cheapest feasible pattern
 //      is found through the patterns pre-sorted by key;
-//   4. a wider component is searched depth-first by all waves of the
+//   5. a wider component is searched depth-first by all waves of the
 //      workgroup: branch on the free positive literals of the open clause
 //      with the fewest of them, prune on key and on a per-clause lower bound;
 //      clause tests are spread over the 64 lanes and combined with
@@ -32,6 +40,14 @@
 //      far (a shared word) as well as its own best key.  The optimum is
 //      unique, so the smallest of the waves' best keys is the answer whatever
 //      order the waves run in.
+// phi is staged in LDS (up to SV_CLAUSES clauses; more are read from memory
+// until few enough are open).  Bound: latency, a chain of workgroup-wide
+// reductions of one barrier each.  Measured: 300 runs over 56 slots of weights
+// 1 to 10, 87 us by reduction and path, 1 to 90 ms (two or three seconds at 64
+// slots) by the search alone; the 35 greedy rounds of plain-large one trace
+// at a time, 0.85 ms from 2.5 ms with LDS counters per slot and one thread
+// comparing them; the Solves of 512 instrumented programs 0.12 ms from 0.47
+// ms by enumeration alone.
 #pragma once
 #include "common.h"
 
@@ -39,16 +55,33 @@ namespace rp {
 
 constexpr int SV_BLOCK = 256;
 constexpr int SV_WAVES = SV_BLOCK / 64;
-constexpr uint32_t SV_CLAUSES = 1536;     // clauses of a component; open clauses kept in LDS
+constexpr uint32_t SV_CLAUSES = 1536;     // clauses of a component; clauses kept in LDS
 constexpr int ENUM_MAX = 20;
 
 struct Key { uint64_t hi, lo; };
 __device__ __forceinline__ bool key_lt(Key a, Key b) { return a.hi != b.hi ? a.hi < b.hi : a.lo < b.lo; }
 
-template <typename T>
-__device__ __forceinline__ T wave_or(T v) {
-  for (int off = 32; off > 0; off >>= 1) v |= __shfl_xor(v, off);
-  return v;
+__device__ __forceinline__ uint32_t sv_uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t sv_uni64(uint64_t v) {
+  return ((uint64_t)sv_uni((uint32_t)(v >> 32)) << 32) | sv_uni((uint32_t)v);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, uint32_t l) {   // v of lane l, uniform
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+}
+
+// OR over the wave (DPP row shifts and broadcasts; the result is uniform).
+__device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
+  v |= __builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr 1, 2, 4, 8
+  v |= __builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+  v |= __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+  v |= __builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+  v |= __builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xF, 0xF, false);   // row_bcast 15, 31
+  v |= __builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xF, 0xF, false);
+  return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ uint64_t wave_or(uint64_t v) {
+  return ((uint64_t)wave_or32((uint32_t)(v >> 32)) << 32) | wave_or32((uint32_t)v);
 }
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
   for (int off = 32; off > 0; off >>= 1) {
@@ -63,17 +96,6 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
     v = o > v ? o : v;
   }
   return v;
-}
-
-__device__ __forceinline__ uint64_t block_or(uint64_t v, uint64_t* sm) {
-  v = wave_or(v);
-  const int w = threadIdx.x >> 6;
-  if (__lane_id() == 0) sm[w] = v;
-  __syncthreads();
-  uint64_t r = 0;
-  for (int q = 0; q < SV_WAVES; q++) r |= sm[q];
-  __syncthreads();
-  return r;
 }
 
 __device__ __forceinline__ Key block_min_key(Key k, uint64_t* smh, uint64_t* sml) {
@@ -105,23 +127,54 @@ __device__ __forceinline__ uint64_t pat(int b) {
 struct DfsFrame { uint64_t ones, zeros, khi, klo, todo, tried; };
 constexpr int SPLIT_DEPTH = 3;           // depth whose nodes are dealt out to the waves
 
-constexpr uint32_t GREEDY_MAX = 16384;   // clauses the greedy step handles (bitset in LDS)
+constexpr uint32_t GREEDY_MAX = 16384;   // clauses the greedy step handles
 
 // LDS of the solver.
 struct SolveLds {
-  rp_clause cl[SV_CLAUSES];                // open clauses (restricted)
-  uint64_t lp[SV_CLAUSES], ln[SV_CLAUSES], la[SV_CLAUSES];  // per component: local pos / neg / aux
+  rp_clause cl[SV_CLAUSES];                // phi, then the open clauses (restricted)
+  union {
+    rp_clause u[SV_CLAUSES];               // open clauses on their way through the reduction
+    struct {                               // per component: local pos / neg
+      uint64_t lp[SV_CLAUSES], ln[SV_CLAUSES];
+    };
+  };
+  uint64_t la[SV_CLAUSES];                 // aux per component clause
   uint64_t kh[64], kl[64];                 // local slot key parts
   uint64_t lowh[64], lowl[64];             // key of each low pattern
   uint32_t order[64], gslot[64];
+  int32_t first[64], last[64];             // per last (first) slot: the largest first (last) slot
   uint64_t smA[SV_WAVES], smB[SV_WAVES];
   uint64_t inch[SV_WAVES], incl[SV_WAVES];
-  DfsFrame stack[SV_WAVES][65];
+  uint64_t red[2][SV_WAVES][5];            // reductions, two in turn (one barrier each)
+  union {
+    uint64_t dom[2][SV_WAVES][64];         // of the reduction, of the greedy set, of the search
+    uint32_t c64[2][SV_WAVES][64];
+    DfsFrame stack[SV_WAVES][65];
+  };
   unsigned long long bound;                // smallest weight part found by any wave
-  uint32_t cnt, overflow, best;
-  uint32_t c64[64], pick[64];
-  uint32_t hit[GREEDY_MAX / 32];
+  uint32_t cnt, overflow;
 };
+
+// OR of K values over the workgroup.  turn alternates between calls, so that a
+// call's values are read by everyone before the call after next writes there.
+template <int K>
+__device__ __forceinline__ void block_or(uint64_t (&v)[K], SolveLds& L, uint32_t& turn) {
+  const uint32_t w = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < K; k++) v[k] = wave_or(v[k]);
+  if (__lane_id() == 0) {
+#pragma unroll
+    for (int k = 0; k < K; k++) L.red[turn][w][k] = v[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < K; k++) {
+    uint64_t r = 0;
+    for (int q = 0; q < SV_WAVES; q++) r |= L.red[turn][q][k];
+    v[k] = sv_uni64(r);
+  }
+  turn ^= 1;
+}
 
 // The mhs strategy's Solve (Section 2.4): the greedy minimal hitting set of
 // the positive clauses of phi -- repeatedly the slot hitting the most clauses
@@ -129,77 +182,86 @@ struct SolveLds {
 // slot), then every pick whose removal leaves all positive clauses hit is
 // dropped, last pick first.  Returns false (the caller solves exactly) when
 // phi has an empty clause, is too long, or the set breaks a clause of phi.
-__device__ bool greedy_solve(const Job& J, JobState* st, uint32_t n, const rp_clause* C,
-                             SolveLds& s) {
-  uint32_t *s_hit = s.hit, *s_c64 = s.c64, *s_pick = s.pick, *s_best = &s.best;
-  uint64_t* sm = s.smA;
-  const int tid = threadIdx.x;
-  const uint32_t S = J.S;
+// A lane is a slot: the waves share the clauses of a count (LDS: each clause
+// read once by all lanes; from memory a clause per lane, counted with LDS
+// adds), and every wave finds the best slot alike (a float quotient narrows
+// the lanes down, integer products decide), so a pick costs one barrier.
+template <bool LDS, class G>
+__device__ bool greedy_solve(const Job& J, const uint32_t* s_w, JobState* st, uint32_t n, G get,
+                             SolveLds& L, uint32_t& turn) {
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = sv_uni(tid >> 6);
   if (n > GREEDY_MAX) return false;
-  const uint32_t nw = (n + 31) / 32;
-  for (uint32_t q = tid; q < nw; q += SV_BLOCK) s_hit[q] = 0;
-  __syncthreads();
-  uint64_t bad = 0;
+  uint64_t bad[1] = {0};
   for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-    const rp_clause c = C[q];
-    if (c.pos == 0 && c.neg == 0) bad = 1;
-    if (!(c.pos && !c.neg)) atomicOr(&s_hit[q >> 5], 1u << (q & 31));   // not positive: ignored
+    const rp_clause c = get(q);
+    if (c.pos == 0 && c.neg == 0) bad[0] = 1;
   }
-  if (block_or(bad, sm)) return false;
+  block_or(bad, L, turn);
+  if (bad[0]) return false;
+  const uint32_t w = lane < J.S ? s_w[lane] : 1;
   uint64_t x = 0;
-  uint32_t np = 0;
-  for (uint32_t it = 0; it < 64; it++) {
-    if (tid < 64) s_c64[tid] = 0;
-    __syncthreads();
-    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-      if ((s_hit[q >> 5] >> (q & 31)) & 1) continue;
-      uint64_t p = C[q].pos;
-      while (p) {
-        const uint32_t b = __ffsll((unsigned long long)p) - 1;
-        p &= p - 1;
-        atomicAdd(&s_c64[b], 1u);
+  uint32_t np = 0, mine = 0;               // picks; lane q keeps the q-th
+  while (np < 64) {
+    uint32_t c = 0;
+    if constexpr (LDS) {
+      for (uint32_t q = wv; q < n; q += SV_WAVES) {
+        const rp_clause t = get(q);
+        const uint64_t pos = sv_uni64(t.pos), neg = sv_uni64(t.neg);
+        if (neg == 0 && (pos & x) == 0) c += (uint32_t)(pos >> lane) & 1u;
+      }
+      L.c64[turn][wv][lane] = c;
+    } else {
+      L.c64[turn][wv][lane] = 0;
+      for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+        const rp_clause t = get(q);
+        if (t.neg != 0 || (t.pos & x) != 0) continue;
+        for (uint64_t p = t.pos; p; p &= p - 1) atomicAdd(&L.c64[turn][wv][__builtin_ctzll(p)], 1u);
       }
     }
     __syncthreads();
-    if (tid == 0) {
-      int best = -1;
-      for (uint32_t b = 0; b < S; b++) {
-        if (!s_c64[b]) continue;
-        if (best < 0 || (uint64_t)s_c64[b] * J.weights[best] > (uint64_t)s_c64[best] * J.weights[b])
-          best = (int)b;
+    c = 0;
+    for (int q = 0; q < SV_WAVES; q++) c += L.c64[turn][q][lane];
+    turn ^= 1;
+    if (__ballot(c != 0) == 0) break;
+    const float f = (float)c / (float)w;
+    float top = f;
+    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    uint64_t cand = __ballot(c != 0 && f >= top * 0.9999f);
+    uint32_t best = (uint32_t)__builtin_ctzll(cand);
+    auto of = [](uint32_t v, uint32_t l) { return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    uint64_t bc = of(c, best), bw = of(w, best);
+    for (cand &= cand - 1; cand; cand &= cand - 1) {
+      const uint32_t b = (uint32_t)__builtin_ctzll(cand);
+      const uint64_t cb = of(c, b), wb = of(w, b);
+      if (cb * bw > bc * wb) {
+        best = b;
+        bc = cb;
+        bw = wb;
       }
-      *s_best = best < 0 ? NONE32 : (uint32_t)best;
-      if (best >= 0) s_pick[np] = (uint32_t)best;
     }
-    __syncthreads();
-    const uint32_t b = *s_best;
-    if (b == NONE32) break;
-    x |= 1ull << b;
+    x |= 1ull << best;
+    if (lane == np) mine = best;
     np++;
-    for (uint32_t q = tid; q < n; q += SV_BLOCK)
-      if (!((s_hit[q >> 5] >> (q & 31)) & 1) && ((C[q].pos >> b) & 1))
-        atomicOr(&s_hit[q >> 5], 1u << (q & 31));
-    __syncthreads();
   }
-  for (int k = (int)np - 1; k >= 0; k--) {
-    const uint64_t y = x & ~(1ull << s_pick[k]);
-    uint64_t miss = 0;
-    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-      const rp_clause c = C[q];
-      if (c.pos && !c.neg && !(c.pos & y)) miss = 1;
+  // every wave tests every clause, alike
+  for (uint32_t k = np; k-- > 0;) {
+    const uint64_t y = x & ~(1ull << __builtin_amdgcn_readlane(mine, k));
+    bool miss = false;
+    for (uint32_t q = lane; q < n && !miss; q += 64) {
+      const rp_clause c = get(q);
+      miss = c.pos && !c.neg && !(c.pos & y);
     }
-    if (!block_or(miss, sm)) x = y;
+    if (__ballot(miss) == 0) x = y;
   }
-  uint64_t viol = 0;
-  for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-    const rp_clause c = C[q];
-    if (!((c.pos & x) || (c.neg & ~x))) viol = 1;
+  bool viol = false;
+  for (uint32_t q = lane; q < n && !viol; q += 64) {
+    const rp_clause c = get(q);
+    viol = !((c.pos & x) || (c.neg & ~x));
   }
-  if (block_or(viol, sm)) return false;
+  if (__ballot(viol)) return false;
   if (tid == 0) {
     uint64_t W = 0;
-    for (uint32_t b = 0; b < S; b++)
-      if ((x >> b) & 1) W += J.weights[b];
+    for (uint64_t m = x; m; m &= m - 1) W += s_w[__builtin_ctzll(m)];
     st->x = x;
     st->weight = W;
     if (st->max_rounds && st->rounds >= st->max_rounds) st->state = ST_ROUNDS;
@@ -207,98 +269,273 @@ __device__ bool greedy_solve(const Job& J, JobState* st, uint32_t n, const rp_cl
   return true;
 }
 
+// Reduction of the n clauses get(q): on and off grow to the fixpoint, by units
+// and, with DOM (clauses in LDS), by slots another one makes needless.
+// Returns false when the clauses cannot be satisfied.
+template <bool DOM, class G>
+__device__ bool propagate(G get, uint32_t n, uint64_t all, const uint32_t* s_w, uint64_t& on,
+                          uint64_t& off, SolveLds& L, uint32_t& turn) {
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = sv_uni(tid >> 6);
+  for (;;) {
+    uint64_t v[5] = {0, 0, 0, 0, 0};       // new units on, off, positive, negative literals, empty
+    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+      const rp_clause c = get(q);
+      if ((c.pos & on) || (c.neg & off)) continue;
+      const uint64_t p = c.pos & ~off, m = c.neg & ~on;
+      if (p == 0 && m == 0) v[4] = 1;
+      else if (p == 0 && (m & (m - 1)) == 0) v[1] |= m;
+      else if (m == 0 && (p & (p - 1)) == 0) v[0] |= p;
+      v[2] |= p;
+      v[3] |= m;
+    }
+    block_or(v, L, turn);
+    const uint64_t non = v[0], noff = v[1], core = v[2];
+    if (v[4] || (non & (off | noff)) || (noff & (on | non))) return false;
+    const uint64_t nz = all & ~on & ~off & ~non & ~noff & ~core;
+    on |= non;
+    off |= noff | nz;
+    if (non | noff | nz) continue;
+    if (!DOM || core == 0) return true;
+    // slots in every open clause of the lane's slot
+    uint64_t d = ~0ull;
+    for (uint32_t q = wv; q < n; q += SV_WAVES) {
+      const rp_clause c = get(q);
+      const uint64_t pos = sv_uni64(c.pos), neg = sv_uni64(c.neg);
+      if ((pos & on) || (neg & off)) continue;
+      if ((pos >> lane) & 1) d &= pos;
+    }
+    L.dom[turn][wv][lane] = d;
+    __syncthreads();
+    for (int q = 0; q < SV_WAVES; q++) d &= L.dom[turn][q][lane];
+    turn ^= 1;
+    bool worse = false;
+    if ((core >> lane) & 1) {
+      const uint32_t w = s_w[lane];
+      for (uint64_t t = d & core & ~v[3] & ~(1ull << lane); t && !worse; t &= t - 1) {
+        const uint32_t b = (uint32_t)__builtin_ctzll(t);
+        worse = s_w[b] < w || (s_w[b] == w && b < lane);
+      }
+    }
+    const uint64_t drop = __ballot(worse);
+    if (drop == 0) return true;
+    off |= drop;
+  }
+}
+
+// The optimum over the slots of M when every clause is positive and a
+// contiguous run of them; first[h]: the largest first slot of the clauses
+// whose last slot is h (-1: none), last[l]: the largest last slot of those
+// whose first is l.  Slots are taken in ascending order: a chosen slot s may
+// follow a chosen slot p exactly when no clause lies wholly between them,
+// that is when p >= the largest first slot of the clauses that end before s.
+// Every wave computes the same; lane p keeps the best key of a choice that
+// ends with p.  A run of linked slots longer than ENUM_MAX and than the node
+// budget counts as a search that spends it (returns false).
+__device__ bool interval_optimum(uint64_t M, const uint32_t* s_w, uint64_t budget,
+                                 const SolveLds& L, uint64_t& answer) {
+  const uint32_t lane = __lane_id();
+  const uint32_t w = (M >> lane) & 1 ? s_w[lane] : 0;
+  const int32_t fl = L.first[lane], ll = L.last[lane];
+  uint64_t bh = ~0ull, bl = 0;             // this lane's best key
+  int32_t need = -1, reach = -1;           // largest first slot that ended; last slot reached
+  uint32_t run = 0;
+  for (uint64_t m = M; m; m &= m - 1) {
+    const uint32_t s = (uint32_t)__builtin_ctzll(m);
+    run = reach >= (int32_t)s ? run + 1 : 1;
+    if (run > (uint32_t)ENUM_MAX && run > budget) return false;
+    Key k = {0, 0};                        // nothing before s has to be hit
+    if (need >= 0) {
+      const bool in = lane < s && (int32_t)lane >= need && ((M >> lane) & 1);
+      const uint64_t h = wave_min_u64(in ? bh : ~0ull);
+      uint64_t tie = __ballot(in && bh == h);
+      k.hi = h;
+      k.lo = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
+      for (tie &= tie - 1; tie; tie &= tie - 1) {
+        const uint64_t o = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
+        k.lo = o < k.lo ? o : k.lo;
+      }
+    }
+    if (lane == s) {
+      bh = k.hi + (uint64_t)w * 128u + 1u;
+      bl = k.lo | 1ull << s;
+    }
+    const int32_t f = __builtin_amdgcn_readlane(fl, s), l = __builtin_amdgcn_readlane(ll, s);
+    need = f > need ? f : need;
+    reach = l > reach ? l : reach;
+  }
+  const bool in = (int32_t)lane >= need && ((M >> lane) & 1);
+  const uint64_t h = wave_min_u64(in ? bh : ~0ull);
+  uint64_t tie = __ballot(in && bh == h);
+  answer = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
+  for (tie &= tie - 1; tie; tie &= tie - 1) {
+    const uint64_t o = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
+    answer = o < answer ? o : answer;
+  }
+  return true;
+}
+
+// Whether the clauses U[0..n) inside the slots M are all positive contiguous
+// runs of M; then first and last are filled for interval_optimum.
+__device__ bool intervals_of(const rp_clause* U, uint32_t n, uint64_t M, SolveLds& L,
+                             uint32_t& turn) {
+  const uint32_t tid = threadIdx.x;
+  if (tid < 64) L.first[tid] = L.last[tid] = -1;
+  __syncthreads();
+  uint64_t other[1] = {0};
+  for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+    const rp_clause c = U[q];
+    if (!((c.pos | c.neg) & M)) continue;
+    if (c.pos == 0 || c.neg != 0) {
+      other[0] = 1;
+      continue;
+    }
+    const uint32_t lo = (uint32_t)__builtin_ctzll(c.pos), hi = 63u - (uint32_t)__builtin_clzll(c.pos);
+    const uint64_t span = (~0ull >> (63 - hi)) & (~0ull << lo);
+    if ((M & span) != c.pos) other[0] = 1;
+    atomicMax(&L.first[hi], (int32_t)lo);
+    atomicMax(&L.last[lo], (int32_t)hi);
+  }
+  block_or(other, L, turn);
+  return other[0] == 0;
+}
+
 // Solve over phi = C[0..n) for the job state *st (in LDS; thread 0 writes it):
-// x and weight, or a final state.  Every thread of the workgroup calls it.
+// x and weight, or a final state.  s_w: the slots' weights (LDS).  Every
+// thread of the workgroup calls it.
 __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint32_t n,
-                           SolveLds& L) {
+                           const uint32_t* s_w, SolveLds& L) {
   uint64_t *smA = L.smA, *smB = L.smB;
   const int tid = threadIdx.x, lane = __lane_id(), wv = tid >> 6;
   const uint32_t S = J.S;
   const uint64_t all = S >= 64 ? ~0ull : ((1ull << S) - 1);
   const uint32_t phase = st->phase;
-  __syncthreads();          // (every thread has the phase before thread 0 may change it)
-  if (phase == PH_GREEDY && greedy_solve(J, st, n, C, L)) return;
+  uint32_t turn = 0;
+  const bool lds = n <= SV_CLAUSES;
+  if (lds)
+    for (uint32_t q = tid; q < n; q += SV_BLOCK) L.cl[q] = C[q];
+  __syncthreads();          // (and every thread has the phase before thread 0 may change it)
+  auto in_lds = [&](uint32_t q) { return L.cl[q]; };
+  auto in_memory = [&](uint32_t q) { return C[q]; };
+  if (phase == PH_GREEDY && (lds ? greedy_solve<true>(J, s_w, st, n, in_lds, L, turn)
+                                 : greedy_solve<false>(J, s_w, st, n, in_memory, L, turn)))
+    return;
 
-  // ---- 1. propagation
+  // ---- 1. reduction
   uint64_t on = 0, off = 0;
-  bool unsat = false;
-  for (int iter = 0; iter < 200; iter++) {
-    uint64_t non = 0, noff = 0, core = 0, bad = 0;
+  bool sat = lds ? propagate<false>(in_lds, n, all, s_w, on, off, L, turn)
+                 : propagate<false>(in_memory, n, all, s_w, on, off, L, turn);
+  rp_clause* U = L.cl;
+  uint32_t nu = n;
+  if (sat && !lds) {
+    // the open clauses alone, restricted, into LDS if they fit, else into the
+    // first phi_cap clauses of scratch (which hold at least n)
+    uint64_t open = 0;
+    if (tid == 0) L.cnt = 0;
+    __syncthreads();
+    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+      const rp_clause c = C[q];
+      if (!(c.pos & on) && !(c.neg & off)) open++;
+    }
+    if (open) atomicAdd(&L.cnt, (uint32_t)open);
+    __syncthreads();
+    if (L.cnt > SV_CLAUSES) U = J.scratch;
+    __syncthreads();
+    if (tid == 0) L.cnt = 0;
+    __syncthreads();
     for (uint32_t q = tid; q < n; q += SV_BLOCK) {
       const rp_clause c = C[q];
       if ((c.pos & on) || (c.neg & off)) continue;
-      const uint64_t p = c.pos & ~off, m = c.neg & ~on;
-      if (p == 0 && m == 0) bad = 1;
-      else if (p == 0 && __popcll(m) == 1) noff |= m;
-      else if (m == 0 && __popcll(p) == 1) non |= p;
-      core |= p;
+      U[atomicAdd(&L.cnt, 1u)] = rp_clause{c.pos & ~off, c.neg & ~on};
     }
-    non = block_or(non, smA);
-    noff = block_or(noff, smA);
-    core = block_or(core, smA);
-    bad = block_or(bad, smA);
-    if (bad || (non & (off | noff)) || (noff & (on | non))) { unsat = true; break; }
-    const uint64_t nz = all & ~on & ~off & ~non & ~noff & ~core;
-    if ((non | noff | nz) == 0) break;
-    on |= non;
-    off |= noff | nz;
+    __syncthreads();
+    nu = L.cnt;
   }
-  if (unsat) {
+  if (U == L.cl) {
+    // restrict, drop the satisfied and the subsumed, reduce again until that
+    // changes nothing
+    while (sat && nu) {
+      for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
+        const rp_clause c = L.cl[q];
+        L.cl[q] = (c.pos & on) || (c.neg & off) ? rp_clause{~0ull, ~0ull}     // (a tautology)
+                                                : rp_clause{c.pos & ~off, c.neg & ~on};
+      }
+      if (tid == 0) L.cnt = 0;
+      __syncthreads();
+      for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
+        const rp_clause c = L.cl[q];
+        bool dead = (c.pos & c.neg) != 0;
+        for (uint32_t r = 0; r < nu && !dead; r++) {
+          const rp_clause d = L.cl[r];
+          dead = (d.pos & ~c.pos) == 0 && (d.neg & ~c.neg) == 0 &&
+                 (d.pos != c.pos || d.neg != c.neg || r < q);
+        }
+        if (!dead) L.u[atomicAdd(&L.cnt, 1u)] = c;
+      }
+      __syncthreads();
+      nu = L.cnt;
+      const uint64_t fixed = on | off;
+      sat = propagate<true>([&](uint32_t q) { return L.u[q]; }, nu, all, s_w, on, off, L, turn);
+      __syncthreads();
+      for (uint32_t q = tid; q < nu; q += SV_BLOCK) L.cl[q] = L.u[q];
+      __syncthreads();
+      if (fixed == (on | off)) break;
+    }
+  }
+  if (!sat) {
     if (tid == 0) st->state = ST_UNSAT;
     return;
   }
-  const uint64_t freeS = all & ~on & ~off;
-
-  // ---- open clauses restricted to the free slots
-  if (tid == 0) L.cnt = 0;
-  __syncthreads();
-  // (the first phi_cap clauses of scratch hold at least n)
-  rp_clause* U = n <= SV_CLAUSES ? L.cl : J.scratch;
-  for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-    const rp_clause c = C[q];
-    if ((c.pos & on) || (c.neg & off)) continue;
-    rp_clause r;
-    r.pos = c.pos & freeS;
-    r.neg = c.neg & freeS;
-    U[atomicAdd(&L.cnt, 1u)] = r;
-  }
-  __syncthreads();
-  const uint32_t nu = L.cnt;
-
   uint64_t result = on;
-  uint64_t left = freeS;
+  uint64_t left = all & ~on & ~off;
+  // ---- 2. one path over all that is left
+  const bool paths = U == L.cl;            // (a component over more clauses is refused below)
+  if (left && paths && intervals_of(U, nu, left, L, turn)) {
+    uint64_t x;
+    if (!interval_optimum(left, s_w, J.node_limit, L, x)) {
+      if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
+      return;
+    }
+    result |= x;
+    left = 0;
+  }
   while (left) {
-    // ---- 2. component of the lowest free slot
+    // ---- 3. component of the lowest free slot
     uint64_t comp = left & (~left + 1);
     for (;;) {
-      uint64_t add = 0;
+      uint64_t add[1] = {0};
       for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
         const uint64_t l = U[q].pos | U[q].neg;
-        if ((l & comp) && (l & ~comp)) add |= l;
+        if ((l & comp) && (l & ~comp)) add[0] |= l;
       }
-      add = block_or(add, smA);
-      if (add == 0 || (add & ~comp) == 0) break;
-      comp |= add;
+      block_or(add, L, turn);
+      if ((add[0] & ~comp) == 0) break;
+      comp |= add[0];
     }
     left &= ~comp;
     const int k = __popcll(comp);
-    // local slot numbering
-    if (tid == 0) {
-      uint64_t m = comp;
-      int b = 0;
-      while (m) {
-        const uint32_t s = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1;
-        L.gslot[b] = s;
-        L.kh[b] = (uint64_t)J.weights[s] * 128u + 1u;
-        L.kl[b] = 1ull << s;
-        b++;
+    if (paths && intervals_of(U, nu, comp, L, turn)) {
+      uint64_t x;
+      if (!interval_optimum(comp, s_w, J.node_limit, L, x)) {
+        if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
+        return;
       }
-      L.cnt = 0;
+      result |= x;
+      continue;
     }
+    // local slot numbering
+    if (tid < 64 && ((comp >> lane) & 1)) {
+      const uint32_t b = (uint32_t)__popcll(comp & lanemask_lt());
+      L.gslot[b] = lane;
+      L.kh[b] = (uint64_t)s_w[lane] * 128u + 1u;
+      L.kl[b] = 1ull << lane;
+    }
+    if (tid == 0) L.cnt = 0;
     __syncthreads();
-    // component clauses in local numbering (L.lp/L.ln), aux = lower bound
-    const uint32_t cap_local = SV_CLAUSES;
+    // component clauses in local numbering (lp / ln); aux = the low slots'
+    // pattern of a clause to enumerate, the lower bound of one to search
+    const bool enumerate = k <= ENUM_MAX;
+    const int low = k < 6 ? k : 6;
+    const uint64_t lowmask = (1ull << low) - 1;
     for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
       const rp_clause c = U[q];
       if (!((c.pos | c.neg) & comp)) continue;
@@ -308,19 +545,24 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
         if (c.pos & g) { lp |= 1ull << b; lb = L.kh[b] < lb ? L.kh[b] : lb; }
         if (c.neg & g) ln |= 1ull << b;
       }
+      if (enumerate) {
+        lb = 0;
+        for (uint64_t m = lp & lowmask; m; m &= m - 1) lb |= pat(__builtin_ctzll(m));
+      } else if (lp == 0) {
+        lb = 0;
+      }
       const uint32_t slot = atomicAdd(&L.cnt, 1u);
-      if (slot < cap_local) { L.lp[slot] = lp; L.ln[slot] = ln; L.la[slot] = lp ? lb : 0; }
+      if (slot < SV_CLAUSES) { L.lp[slot] = lp; L.ln[slot] = ln; L.la[slot] = lb; }
     }
     __syncthreads();
     const uint32_t nc = L.cnt;
-    if (nc > cap_local) {
+    if (nc > SV_CLAUSES) {
       if (tid == 0) { st->err = ERR_SCRATCH; st->state = ST_ERROR; }
       return;
     }
     Key best = {~0ull, ~0ull};
-    if (k <= ENUM_MAX) {
-      // ---- 3. bit-sliced enumeration
-      const int low = k < 6 ? k : 6;
+    if (enumerate) {
+      // ---- 4. bit-sliced enumeration
       if (tid < 64) {
         uint64_t h = 0, l = 0;
         for (int b = 0; b < low; b++)
@@ -341,26 +583,18 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
       __syncthreads();
       const uint64_t valid = low == 6 ? ~0ull : ((1ull << (1u << low)) - 1);
       const uint32_t nwords = 1u << (k - low);
-      const uint64_t lowmask = (1ull << low) - 1;
       for (uint32_t H = tid; H < nwords; H += SV_BLOCK) {
         uint64_t feas = valid;
         const uint64_t hbits = (uint64_t)H << low;
         for (uint32_t q = 0; q < nc && feas; q++) {
-          const uint64_t lp = L.lp[q], ln = L.ln[q];
-          uint64_t sp, sn;
-          if (lp & hbits) sp = ~0ull;
-          else {
-            sp = 0;
-            uint64_t m = lp & lowmask;
-            while (m) { const int b = __ffsll((unsigned long long)m) - 1; m &= m - 1; sp |= pat(b); }
+          if (L.lp[q] & hbits) continue;
+          uint64_t s = L.la[q];
+          const uint64_t ln = L.ln[q];
+          if (ln) {
+            if (ln & ~hbits & ~lowmask) continue;
+            for (uint64_t m = ln & lowmask; m; m &= m - 1) s |= ~pat(__builtin_ctzll(m));
           }
-          if (ln & ~hbits & ~lowmask) sn = ~0ull;
-          else {
-            sn = 0;
-            uint64_t m = ln & lowmask;
-            while (m) { const int b = __ffsll((unsigned long long)m) - 1; m &= m - 1; sn |= ~pat(b); }
-          }
-          feas &= sp | sn;
+          feas &= s;
         }
         if (!feas) continue;
         Key kh = {0, 0};
@@ -382,7 +616,7 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
       }
       best = block_min_key(best, smA, smB);
     } else {
-      // ---- 4. depth-first branch and bound by every wave
+      // ---- 5. depth-first branch and bound by every wave
       if (tid == 0) {
         L.bound = ~0ull;
         L.overflow = 0;
@@ -501,8 +735,7 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
   }
   if (tid == 0) {
     uint64_t W = 0;
-    for (uint32_t s = 0; s < S; s++)
-      if ((result >> s) & 1) W += J.weights[s];
+    for (uint64_t m = result; m; m &= m - 1) W += s_w[__builtin_ctzll(m)];
     if (phase == PH_FINAL) {
       // the exact query after the greedy answer was verified SAFE
       st->phase = PH_EXACT;
