@@ -142,8 +142,14 @@ typedef struct {
   uint64_t removed;   /* pre-existing barriers left disabled */
 } rp_repair_out;
 
-/* Timings of the last call made on this thread (hipEvent milliseconds on the
- * call's stream) and the work it did. */
+/* Timings of the last call made on this thread (milliseconds) and the work it
+ * did.  Calls that generate records are timed by hipEvents on their stream.
+ * In a call whose conflicts are all decided in closed form the kernels leave
+ * stamps of the device's clock instead (RP_TUNE_TIMING 1): ms_gen and ms_sort
+ * are then the time in which its first wave has its own access and has picked
+ * the accesses of that array out of the first 64 points, ms_j0 (ms_check of
+ * rp_check) the rest of the pair tests, ms_total the time from the first
+ * kernel's start to the last one's end, and ms_upload 0. */
 typedef struct {
   double ms_gen, ms_sort, ms_check, ms_clause, ms_solve, ms_total;
   double ms_sort_pass_max;       /* longest single sort pass */
@@ -352,7 +358,8 @@ uint32_t rp_sort_key_bits(const rp_kernel* const* ks, uint32_t n);
  *                            the device's clock; in a batch, those of the
  *                            job that spent most).
  *                            Each event recorded on the stream costs a few
- *                            microseconds of device idle time;
+ *                            microseconds of device idle time; with no
+ *                            records, level 1 records none;
  *   RP_TUNE_SCATTER_WGS      resident workgroups per compute unit of the
  *                            persistent radix scatter: 0 = what the
  *                            occupancy query reports (default), else 1..8;

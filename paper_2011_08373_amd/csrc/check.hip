@@ -44,9 +44,11 @@ constexpr uint32_t CONF_TILE = CONF_WAVES * CONF_CHUNKS * 64;   // records per t
 // first partner of i under any x is j0[i] (its first partner when no barrier
 // is enabled) if no enabled barrier lies strictly between i and j0[i], and
 // none otherwise.
-__global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ jobs, int mode) {
+__global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ jobs, int mode,
+                                                        uint64_t* stamps) {
   __shared__ uint64_t wsum[IVL_BLOCK / 64];
   __shared__ uint32_t s_iv[2][MAX_POINTS];
+  stamp_if(stamps, mode == IVL_CHECK ? STAMP_BEGIN : STAMP_FIRST);
   const Job& J = jobs[blockIdx.x];
   JobState* st = J.st;
   if (st->state != ST_RUN) return;
@@ -99,6 +101,7 @@ __global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ 
     for (uint64_t q = tid; q < nw; q += IVL_BLOCK) J.bitmap[q] = 0;
   }
   if (tid == 0 && mode != IVL_ZERO) st->divergent = x & J.div_if_enabled;
+  if (mode == IVL_RESOLVE) stamp_end(stamps);
 }
 
 // j0 := the first partners just computed under the empty assignment.
@@ -888,8 +891,10 @@ __global__ __launch_bounds__(PR_BLOCK) void count_rows_kernel(const Job* __restr
 }
 
 __global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__ jobs,
-                                                         rp_pair* out, uint64_t* total) {
+                                                         rp_pair* out, uint64_t* total,
+                                                         uint64_t* stamps) {
   __shared__ uint64_t s_sum[PR_WAVES];
+  stamp_if(stamps, STAMP_FIRST);
   const Job& J = jobs[0];
   const uint32_t P = J.P, rows = 2 * P, wpr = J.wpr;
   const uint32_t r0 = blockIdx.x * PR_ROWS;
@@ -925,13 +930,14 @@ __global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__
     pos += n;
   }
   if (r0 + PR_ROWS >= rows && tid == 0) *total = pos;
+  stamp_end(stamps);
 }
 
 uint32_t conf_tile_size() { return CONF_TILE; }
 
-hipError_t launch_ivl(const Job* jobs, uint32_t njobs, int mode, hipStream_t s) {
+hipError_t launch_ivl(const Job* jobs, uint32_t njobs, int mode, uint64_t* stamps, hipStream_t s) {
   if (njobs == 0) return hipSuccess;
-  ivl_kernel<<<njobs, IVL_BLOCK, 0, s>>>(jobs, mode);
+  ivl_kernel<<<njobs, IVL_BLOCK, 0, s>>>(jobs, mode, stamps);
   return hipGetLastError();
 }
 
@@ -1007,12 +1013,13 @@ hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t ma
 }
 
 hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
-                        uint64_t* total, hipStream_t s) {
+                        uint64_t* total, uint64_t* stamps, hipStream_t s) {
   const uint32_t rows = 2 * points;
   if (!counted && rows != 0)
     count_rows_kernel<<<(rows + PR_WAVES - 1) / PR_WAVES, PR_BLOCK, 0, s>>>(job);
   // (with no point at all one workgroup writes the total, 0)
-  pairs_kernel<<<rows ? (rows + PR_ROWS - 1) / PR_ROWS : 1, PR_BLOCK, 0, s>>>(job, out, total);
+  pairs_kernel<<<rows ? (rows + PR_ROWS - 1) / PR_ROWS : 1, PR_BLOCK, 0, s>>>(job, out, total,
+                                                                            stamps);
   return hipGetLastError();
 }
 

@@ -51,14 +51,31 @@ __device__ __forceinline__ bool row_runs(const DPoint& pi, uint32_t B, uint32_t 
   return (lv == 0 || ((pi.flags & PF_GLOBAL) && B > 1)) && pi.cnt != 0 && pi.br < B;
 }
 
+// Stamps of the first wave: when it has its own point, and when it has picked
+// the points of that point's array out of the first 64 (the closed form's
+// counterparts of generating the records and of grouping them by location).
+__device__ __forceinline__ void stamp_gather(uint64_t* stamps, const Job& J, const DPoint& pi) {
+  if (!stamps || blockIdx.x != 0 || blockIdx.y != 0 || threadIdx.x >= 64) return;
+  const uint32_t l = threadIdx.x;
+  asm volatile("" ::"v"((uint32_t)pi.array));      // (waits for the value)
+  stamp_if(stamps, STAMP_GEN);
+  const bool same = l < J.P && J.pts[l].kind == RP_ACCESS && J.pts[l].array == pi.array;
+  const uint64_t m = __ballot(same);
+  asm volatile("" ::"s"(m));
+  stamp_if(stamps, STAMP_SORT);
+}
+
 template <class I>
-__global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restrict__ jobs) {
+__global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restrict__ jobs,
+                                                              uint64_t* stamps) {
+  stamp_if(stamps, STAMP_BEGIN);
   const Job& J = jobs[blockIdx.y];
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
   const uint32_t P = J.P, B = J.B, lv = wv & 1;
   const uint32_t i = blockIdx.x * (CF_WAVES / 2) + (wv >> 1);
   if (i >= P) return;
   const DPoint pi = J.pts[i];
+  stamp_gather(stamps, J, pi);
   uint32_t* out = J.j0 + (uint64_t)lv * P + i;
   if (!closed_point(pi)) {
     // with no records at all the scan of the logs has not cleared the row
@@ -88,7 +105,8 @@ __global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restr
 // 31 us for plain-large under a quarter of its barriers, against 1.39 ms for
 // the scan of its sorted records (and 0.45 ms to generate and sort them).
 template <class I>
-__global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restrict__ jobs) {
+__global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restrict__ jobs,
+                                                            uint64_t* stamps) {
   static_assert(MAX_POINTS <= 64 * 64, "a row's words in one wave");
   const Job& J = jobs[blockIdx.y];
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
@@ -96,6 +114,7 @@ __global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restric
   const uint32_t i = blockIdx.x * (CF_WAVES / 2) + (wv >> 1);
   if (i >= P) return;
   const DPoint pi = J.pts[i];
+  stamp_gather(stamps, J, pi);
   // (with no records at all the scan of the logs has not cleared the row)
   if (!closed_point(pi) && (J.nlog[0] != 0 || J.nlog[1] != 0)) return;
   uint64_t word = 0;
@@ -122,21 +141,23 @@ static dim3 row_grid(uint32_t max_points, uint32_t njobs) {
   return dim3((max_points + CF_WAVES / 2 - 1) / (CF_WAVES / 2), njobs);
 }
 
-hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, hipStream_t s) {
+hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, uint64_t* stamps,
+                             hipStream_t s) {
   if (points == 0) return hipSuccess;
   const dim3 grid = row_grid(points, 1);
-  if (small) all_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(job);
-  else all_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(job);
+  if (small) all_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(job, stamps);
+  else all_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(job, stamps);
   return hipGetLastError();
 }
 
 hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
-                               hipStream_t s) {
+                               uint64_t* stamps, hipStream_t s) {
   if (njobs == 0 || max_points == 0) return hipSuccess;
   for (uint32_t j = 0; j < njobs; j += 65535) {      // (the grid's second dimension)
     const dim3 grid = row_grid(max_points, njobs - j < 65535 ? njobs - j : 65535);
-    if (small) first_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j);
-    else first_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j);
+    uint64_t* const st = j == 0 ? stamps : nullptr;
+    if (small) first_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, st);
+    else first_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, st);
   }
   return hipGetLastError();
 }

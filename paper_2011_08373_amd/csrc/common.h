@@ -130,6 +130,20 @@ struct Job {
   uint64_t node_limit;        // nodes the exact solver's branch and bound may visit
 };
 
+// Device-clock stamps of a call that has no log (timing level 1), as 64-bit
+// words of the call's zeroed word block (0: nothing stamped); STAMP_END is the
+// largest of its writers.  Stamps cost a store each, where an event recorded
+// between two kernels costs about 5 us of device idle time.
+constexpr int STAMP_BEGIN = 1, STAMP_GEN = 2, STAMP_SORT = 3, STAMP_FIRST = 6, STAMP_END = 7;
+// (one workgroup stamps, by its first thread)
+__device__ __forceinline__ void stamp_if(uint64_t* stamps, int which) {
+  if (stamps && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0) stamps[which] = wall_clock64();
+}
+__device__ __forceinline__ void stamp_end(uint64_t* stamps) {
+  if (stamps && threadIdx.x == 0)
+    atomicMax((unsigned long long*)&stamps[STAMP_END], (unsigned long long)wall_clock64());
+}
+
 // sort segment: one log of one job in the record buffer
 struct SortSeg {
   uint64_t beg, end;     // record range

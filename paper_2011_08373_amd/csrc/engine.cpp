@@ -244,8 +244,9 @@ size_t engine_workspace(const std::vector<JobInput>& jobs, const EngineOpts& o) 
 
 // Page-locked host staging for the descriptor upload, one per host thread,
 // grown on demand and kept for the life of the thread (never freed: a
-// thread-exit free could run after the runtime is gone).  An event marks the
-// last upload out of it; the next call waits for that event before writing.
+// thread-exit free could run after the runtime is gone).  A call waits for
+// its stream before it returns; one that fails before that leaves an event
+// behind its upload, which the next call waits for before writing.
 struct PinnedStage {
   uint8_t* p = nullptr;
   size_t cap = 0;
@@ -303,7 +304,7 @@ namespace {
 // table for the jobs laid out by L in the device buffer d (all enqueued on
 // s, no sync).
 int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const Layout& L,
-                 uint8_t* d, uint8_t* hbuf, hipStream_t s, Timer& tm) {
+                 uint8_t* d, uint8_t* hbuf, uint64_t* stamps, hipStream_t s, Timer& tm) {
   const size_t N = jobs.size();
   // the job and state tables and the error words come first and are the
   // only ones not written in full below
@@ -432,7 +433,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
     // the scan of the logs fills every row of every job; the closed form
     // then sets the rows of its own points (or, with no log, every row)
     if (!L.ssegs.empty()) {
-      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_ZERO, s));
+      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_ZERO, nullptr, s));
       HIPCHK(launch_conf_tiles(djobs, dcs, (int)L.ssegs.size(), derr + 9, s));
       tm.mark(T_SUMPRE);
       HIPCHK(launch_j0(djobs, dcs, (int)L.ssegs.size(), maxP, lo32, derr + 9, s));
@@ -440,7 +441,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
       HIPCHK(launch_save_j0(djobs, (uint32_t)N, s));
     }
     if (L.ssegs.empty() || any_closed) {
-      HIPCHK(launch_first_closed(djobs, (uint32_t)N, maxP, closed_small, s));
+      HIPCHK(launch_first_closed(djobs, (uint32_t)N, maxP, closed_small, stamps, s));
       if (L.ssegs.empty()) tm.mark(T_SUMPRE);
     }
   }
@@ -471,7 +472,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   uint8_t* d = (uint8_t*)region;
   Timer tm(s, 0);
   staging.resize(L.meta);
-  const int rc = prepare_jobs(jobs, o, L, d, staging.data(), s, tm);
+  const int rc = prepare_jobs(jobs, o, L, d, staging.data(), nullptr, s, tm);
   if (rc != RP_OK) return rc;
   // the first Solve of the jobs with option units (an empty phi is
   // answered by the initial x = 0): over the whole group, the others are
@@ -479,7 +480,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   bool any_units = false;
   for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
   HIPCHK(launch_rounds((const Job*)(d + L.o_jobs), (uint32_t)jobs.size(),
-                       RD_BUILD | (any_units ? RD_SOLVE : 0), 0, s));
+                       RD_BUILD | (any_units ? RD_SOLVE : 0), 0, nullptr, s));
   out.resize(jobs.size());
   for (size_t j = 0; j < jobs.size(); j++)
     std::memcpy(&out[j].job, staging.data() + L.o_jobs + j * sizeof(Job), sizeof(Job));
@@ -487,7 +488,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
 }
 
 int engine_round(const Job* djobs, uint32_t njobs, hipStream_t s) {
-  HIPCHK(launch_rounds(djobs, njobs, RD_LOOP, 1, s));
+  HIPCHK(launch_rounds(djobs, njobs, RD_LOOP, 1, nullptr, s));
   return RP_OK;
 }
 
@@ -499,19 +500,33 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   if (!ws && L.total) return RP_ERR_WORKSPACE;
   const size_t N = jobs.size();
   uint8_t* d = (uint8_t*)ws;
-  Timer tm(s, o.no_alloc ? 0 : timing_level(0, false));
+  // a call with no log is timed at level 1 by clock stamps its kernels leave,
+  // other calls (and every phase at level 2) by events
+  const int level = o.no_alloc ? 0 : timing_level(0, false);
+  uint64_t* const stamps =
+      level == 1 && L.ssegs.empty() ? (uint64_t*)((uint8_t*)ws + L.o_err) : nullptr;
+  Timer tm(s, stamps ? 0 : level);
   // host staging: page-locked and kept per thread, or (no_alloc) ordinary
   // memory, which the upload has read before hipMemcpyAsync returns
   static thread_local std::vector<uint8_t> plain_stage, plain_rb;
+  // a call that ends without having waited for its stream leaves an event
+  // behind its uploads
+  struct Upload {
+    hipStream_t s;
+    bool from_pinned = false, waited = false;
+    ~Upload() {
+      if (from_pinned && !waited) t_stage.in_flight(s);
+    }
+  } upload{s};
   if (o.no_alloc) {
     plain_stage.resize(L.meta);
-    const int rc = prepare_jobs(jobs, o, L, d, plain_stage.data(), s, tm);
+    const int rc = prepare_jobs(jobs, o, L, d, plain_stage.data(), nullptr, s, tm);
     if (rc != RP_OK) return rc;
   } else {
     uint8_t* h = t_stage.get(L.meta);
     if (!h) return RP_ERR_DEVICE;
-    const int rc = prepare_jobs(jobs, o, L, d, h, s, tm);
-    t_stage.in_flight(s);
+    upload.from_pinned = true;
+    const int rc = prepare_jobs(jobs, o, L, d, h, stamps, s, tm);
     if (rc != RP_OK) return rc;
   }
   const Job* djobs = (const Job*)(d + L.o_jobs);
@@ -552,7 +567,7 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   const uint64_t scanned = o.op == OP_SOLVE ? 0 : L.n_rec;    // (0: all in closed form)
   const uint32_t conf_launches = o.op == OP_SOLVE || L.ssegs.empty() ? 0 : 1;
   if (o.op == OP_CHECK) {
-    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, s));
+    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, stamps, s));
     if (nseg) {
       HIPCHK(launch_conf_tiles(djobs, dcs, nseg, dtiles, s));
       tm.mark(T_CONFPRE);
@@ -561,20 +576,20 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     }
     for (size_t j = 0; j < N; j++)
       if (!nseg || jobs[j].plan->any_closed)
-        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, s));
+        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, stamps, s));
     tm.mark(T_CHECK, nseg ? 2 : 1);
     for (size_t j = 0; j < N; j++)
       HIPCHK(launch_pairs(djobs + j, jobs[j].plan->P, !nseg, (rp_pair*)(d + L.o_pairs[j]),
-                          (uint64_t*)(d + L.o_ptotal[j]), s));
+                          (uint64_t*)(d + L.o_ptotal[j]), stamps, s));
     tm.mark(T_CLAUSE);
   } else if (o.op == OP_SOLVE) {
-    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_SOLVE, 0, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_SOLVE, 0, stamps, s));
     tm.mark(T_SOLVE);
   } else if (o.op == OP_FIRST) {
-    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s));
+    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, stamps, s));
     tm.mark(T_CHECK);
   } else if (o.op == OP_CLAUSES) {
-    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_BUILD | RD_LEARN, 0, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_BUILD | RD_LEARN, 0, stamps, s));
     tm.mark(T_CLAUSE);
   } else {
     // the first Solve of Alg. 1: with no option units phi is empty and its
@@ -583,11 +598,12 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
     HIPCHK(launch_rounds(djobs, (uint32_t)N,
                          RD_BUILD | RD_LOOP | (any_units ? RD_SOLVE : 0) |
-                             (tm.level >= 2 ? RD_TIMED : 0), 0, s));
+                             (tm.level >= 2 ? RD_TIMED : 0), 0, stamps, s));
   }
   tm.mark(T_END);
   HIPCHK(enqueue_results());
   HIPCHK(hipStreamSynchronize(s));
+  upload.waited = true;
   std::memcpy(hst.data(), pst, N * sizeof(JobState));
   if (herr[0]) return RP_ERR_DEVICE;
   res.assign(N, JobResult{});
@@ -663,6 +679,30 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
         default: break;
       }
     }
+    int khz = 0;
+    if ((stamps || tm.level >= 2) &&
+        (hipGetDevice(&tm.dev) != hipSuccess ||
+         hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, tm.dev) != hipSuccess))
+      khz = 0;
+    if (stamps && khz) {
+      const uint64_t* t = (const uint64_t*)herr;
+      auto ms = [&](int from, int to) {
+        return t[from] && t[to] > t[from] ? (double)(t[to] - t[from]) / khz : 0.0;
+      };
+      stats->ms_total = ms(STAMP_BEGIN, STAMP_END);
+      stats->ms_gen = ms(STAMP_BEGIN, STAMP_GEN);
+      stats->ms_sort = ms(STAMP_GEN, STAMP_SORT);
+      const double rest = ms(STAMP_SORT, STAMP_FIRST), last = ms(STAMP_FIRST, STAMP_END);
+      if (o.op == OP_CHECK) {
+        stats->ms_check = rest;
+        stats->ms_clause = last;
+      } else {
+        stats->ms_j0 = rest;
+        if (o.op == OP_FIRST) stats->ms_check = last;
+        if (o.op == OP_CLAUSES) stats->ms_clause = last;
+        if (o.op == OP_SOLVE) stats->ms_solve = stats->ms_total;
+      }
+    }
     float tot = 0;
     if (tm.ev.size() >= 2 && hipEventElapsedTime(&tot, tm.ev.front(), tm.ev.back()) == hipSuccess)
       stats->ms_total = tot;
@@ -679,13 +719,10 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
       tl = std::max(tl, st.t_clause);
       ts = std::max(ts, st.t_solve);
     }
-    if (tm.level >= 2 && o.op == OP_REPAIR) {
-      int khz = 0;
-      if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, tm.dev) == hipSuccess && khz) {
-        stats->ms_check += (double)tc / khz;
-        stats->ms_clause += (double)tl / khz;
-        stats->ms_solve += (double)ts / khz;
-      }
+    if (tm.level >= 2 && o.op == OP_REPAIR && khz) {
+      stats->ms_check += (double)tc / khz;
+      stats->ms_clause += (double)tl / khz;
+      stats->ms_solve += (double)ts / khz;
     }
     stats->conf_launches = conf_launches;
   }
