@@ -148,6 +148,7 @@ rp_status rp_check(const rp_kernel* k, uint64_t x, rp_pair* pairs, uint64_t cap,
   EngineOpts o;
   o.op = OP_CHECK;
   o.pair_cap = cap;
+  o.pair_out = pairs;
   std::vector<JobInput> v{ji};
   std::vector<JobResult> res;
   rp_stats st;
@@ -157,7 +158,6 @@ rp_status rp_check(const rp_kernel* k, uint64_t x, rp_pair* pairs, uint64_t cap,
   if (res[0].st.state == ST_ERROR) return (rp_status)job_error_status(res[0].st);
   if (n_pairs) *n_pairs = res[0].n_pairs;
   if (res[0].n_pairs > cap) return RP_ERR_CAPACITY;
-  if (res[0].n_pairs) std::memcpy(pairs, res[0].pairs.data(), res[0].n_pairs * sizeof(rp_pair));
   if (divergent) *divergent = res[0].st.divergent;
   if (n_records) *n_records = pl.accesses;
   return RP_OK;

@@ -30,9 +30,8 @@ constexpr uint32_t CONF_TILE = CONF_WAVES * CONF_CHUNKS * 64;   // records per t
 
 // mode IVL_RESOLVE: interval ids under x, then the first partners under x
 //   from the assignment-independent table j0 (see below);
-// mode IVL_CHECK: interval ids under x, first partners cleared, and before an
-//   all-pairs scan of a log the pair bitmap cleared (with no log the closed
-//   form writes every row);
+// mode IVL_CHECK: interval ids under x, first partners cleared, pair bitmap
+//   cleared (the all-pairs scan of the logs follows);
 // mode IVL_ZERO: interval ids of the empty assignment (one interval), first
 //   partners cleared: the scan that follows fills j0.
 //
@@ -44,11 +43,9 @@ constexpr uint32_t CONF_TILE = CONF_WAVES * CONF_CHUNKS * 64;   // records per t
 // first partner of i under any x is j0[i] (its first partner when no barrier
 // is enabled) if no enabled barrier lies strictly between i and j0[i], and
 // none otherwise.
-__global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ jobs, int mode,
-                                                        uint64_t* stamps) {
+__global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ jobs, int mode) {
   __shared__ uint64_t wsum[IVL_BLOCK / 64];
   __shared__ uint32_t s_iv[2][MAX_POINTS];
-  stamp_if(stamps, mode == IVL_CHECK ? STAMP_BEGIN : STAMP_FIRST);
   const Job& J = jobs[blockIdx.x];
   JobState* st = J.st;
   if (st->state != ST_RUN) return;
@@ -96,12 +93,11 @@ __global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ 
   } else {
     for (uint32_t i = tid; i < 2 * P; i += IVL_BLOCK) J.minj[i] = NONE32;
   }
-  if (mode == IVL_CHECK && J.bitmap && (J.nlog[0] != 0 || J.nlog[1] != 0)) {
+  if (mode == IVL_CHECK && J.bitmap) {
     const uint64_t nw = 2ull * P * J.wpr;
     for (uint64_t q = tid; q < nw; q += IVL_BLOCK) J.bitmap[q] = 0;
   }
   if (tid == 0 && mode != IVL_ZERO) st->divergent = x & J.div_if_enabled;
-  if (mode == IVL_RESOLVE) stamp_end(stamps);
 }
 
 // j0 := the first partners just computed under the empty assignment.
@@ -892,9 +888,9 @@ __global__ __launch_bounds__(PR_BLOCK) void count_rows_kernel(const Job* __restr
 
 __global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__ jobs,
                                                          rp_pair* out, uint64_t* total,
-                                                         uint64_t* stamps) {
+                                                         CallBlock call) {
   __shared__ uint64_t s_sum[PR_WAVES];
-  stamp_if(stamps, STAMP_FIRST);
+  stamp_if(call.stamps, STAMP_FIRST);
   const Job& J = jobs[0];
   const uint32_t P = J.P, rows = 2 * P, wpr = J.wpr;
   const uint32_t r0 = blockIdx.x * PR_ROWS;
@@ -916,7 +912,8 @@ __global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__
         const uint32_t y = __shfl_up(inc, o);
         if (lane >= (uint32_t)o) inc += y;
       }
-      rp_pair* at = out + pos + (inc - c);
+      uint64_t at = pos + (inc - c);
+      rp_pair* const head = call.page ? (rp_pair*)call.page->tail() : nullptr;
       rp_pair pr;
       pr.i = (uint16_t)(r >= P ? r - P : r);
       pr.level = r >= P;
@@ -924,20 +921,25 @@ __global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__
       while (m) {
         pr.j = (uint16_t)(lane * 64 + __builtin_ctzll(m));
         m &= m - 1;
-        *at++ = pr;
+        out[at] = pr;
+        if (head && at < PAGE_PAIRS) head[at] = pr;
+        at++;
       }
     }
     pos += n;
   }
-  if (r0 + PR_ROWS >= rows && tid == 0) *total = pos;
-  stamp_end(stamps);
+  if (r0 + PR_ROWS >= rows && tid == 0) {
+    *total = pos;
+    if (call.page) call.page->total = pos;
+  }
+  finish_call(call, J.st);
 }
 
 uint32_t conf_tile_size() { return CONF_TILE; }
 
-hipError_t launch_ivl(const Job* jobs, uint32_t njobs, int mode, uint64_t* stamps, hipStream_t s) {
+hipError_t launch_ivl(const Job* jobs, uint32_t njobs, int mode, hipStream_t s) {
   if (njobs == 0) return hipSuccess;
-  ivl_kernel<<<njobs, IVL_BLOCK, 0, s>>>(jobs, mode, stamps);
+  ivl_kernel<<<njobs, IVL_BLOCK, 0, s>>>(jobs, mode);
   return hipGetLastError();
 }
 
@@ -1013,13 +1015,13 @@ hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t ma
 }
 
 hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
-                        uint64_t* total, uint64_t* stamps, hipStream_t s) {
+                        uint64_t* total, const CallBlock& call, hipStream_t s) {
   const uint32_t rows = 2 * points;
   if (!counted && rows != 0)
     count_rows_kernel<<<(rows + PR_WAVES - 1) / PR_WAVES, PR_BLOCK, 0, s>>>(job);
   // (with no point at all one workgroup writes the total, 0)
   pairs_kernel<<<rows ? (rows + PR_ROWS - 1) / PR_ROWS : 1, PR_BLOCK, 0, s>>>(job, out, total,
-                                                                            stamps);
+                                                                            call);
   return hipGetLastError();
 }
 

@@ -65,48 +65,65 @@ __device__ __forceinline__ void stamp_gather(uint64_t* stamps, const Job& J, con
   stamp_if(stamps, STAMP_SORT);
 }
 
-template <class I>
+// The first point at or after base, among the chunk's 64, with an enabled
+// barrier of the view (64: none): no pair reaches past it.
+__device__ __forceinline__ uint32_t chunk_limit(const Job& J, uint32_t lv, uint64_t x, uint32_t i,
+                                                uint32_t j) {
+  const uint64_t* bits = lv ? J.bits_grid : J.bits_any;
+  const uint64_t m = __ballot(j > i && j < J.P && (bits[j] & x) != 0);
+  return m ? (uint32_t)__builtin_ctzll(m) : 64u;
+}
+
+// X = false: the table j0, with no barrier enabled.  X = true: first partners
+// under the job's assignment, into minj (and the page), of a job that has no
+// records at all.
+template <class I, bool X>
 __global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restrict__ jobs,
-                                                              uint64_t* stamps) {
-  stamp_if(stamps, STAMP_BEGIN);
+                                                              CallBlock call) {
+  stamp_if(call.stamps, STAMP_BEGIN);
   const Job& J = jobs[blockIdx.y];
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
   const uint32_t P = J.P, B = J.B, lv = wv & 1;
   const uint32_t i = blockIdx.x * (CF_WAVES / 2) + (wv >> 1);
-  if (i >= P) return;
-  const DPoint pi = J.pts[i];
-  stamp_gather(stamps, J, pi);
-  uint32_t* out = J.j0 + (uint64_t)lv * P + i;
-  if (!closed_point(pi)) {
-    // with no records at all the scan of the logs has not cleared the row
-    if (lane == 0 && J.nlog[0] == 0 && J.nlog[1] == 0) *out = NONE32;
-    return;
-  }
-  uint32_t best = NONE32;
-  if (row_runs(pi, B, lv)) {
-    const Access a = access_of(pi, B);
-    for (uint32_t base = i; base < P; base += 64) {
-      const uint32_t j = base + lane;
-      const uint64_t m = __ballot(j < P && lane_conflict<I>(J, pi, a, i, j, lv));
-      if (m) {
-        best = base + (uint32_t)__builtin_ctzll(m);
-        break;
+  if (i < P) {
+    const DPoint pi = J.pts[i];
+    stamp_gather(call.stamps, J, pi);
+    uint32_t best = NONE32;
+    if (closed_point(pi) && row_runs(pi, B, lv)) {
+      const Access a = access_of(pi, B);
+      const uint64_t x = X ? J.st->x : 0;
+      for (uint32_t base = i; base < P; base += 64) {
+        const uint32_t j = base + lane;
+        const uint32_t end = X ? chunk_limit(J, lv, x, i, j) : 64u;
+        const uint64_t m = __ballot(j < P && lane < end && lane_conflict<I>(J, pi, a, i, j, lv));
+        if (m) best = base + (uint32_t)__builtin_ctzll(m);
+        if (m || end < 64) break;
+      }
+    }
+    const uint32_t row = lv * P + i;
+    if (lane == 0) {
+      if constexpr (X) {
+        J.minj[row] = best;
+        if (call.page) ((uint32_t*)call.page->tail())[row] = best;
+      } else if (closed_point(pi) || (J.nlog[0] == 0 && J.nlog[1] == 0)) {
+        // (with a log its scan has set the rows of the other points)
+        J.j0[row] = best;
       }
     }
   }
-  if (lane == 0) *out = best;
+  if constexpr (X) finish_call(call, J.st);
 }
 
-// Every racing pair under the job's assignment (its interval ids in ivl), one
-// wave per (point, view): the 64-point words of the row's bitmap are ballots,
-// kept one per lane (at most 64 words) and stored together.  Interval ids
-// never decrease along the program, so the row ends with its interval.  The
-// row's pairs are counted into minj for the list.  Bound by latency as above:
-// 31 us for plain-large under a quarter of its barriers, against 1.39 ms for
+// Every racing pair under the job's assignment, one wave per (point, view):
+// the 64-point words of the row's bitmap are ballots, kept one per lane (at
+// most 64 words) and stored together.  A row ends at the first enabled barrier
+// after its point.  The row's pairs are counted into minj for the list.  Bound
+// by latency as above: 31 us for plain-large under a quarter of its barriers, against 1.39 ms for
 // the scan of its sorted records (and 0.45 ms to generate and sort them).
 template <class I>
 __global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restrict__ jobs,
-                                                            uint64_t* stamps) {
+                                                            CallBlock call) {
+  stamp_if(call.stamps, STAMP_BEGIN);
   static_assert(MAX_POINTS <= 64 * 64, "a row's words in one wave");
   const Job& J = jobs[blockIdx.y];
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
@@ -114,20 +131,20 @@ __global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restric
   const uint32_t i = blockIdx.x * (CF_WAVES / 2) + (wv >> 1);
   if (i >= P) return;
   const DPoint pi = J.pts[i];
-  stamp_gather(stamps, J, pi);
+  stamp_gather(call.stamps, J, pi);
   // (with no records at all the scan of the logs has not cleared the row)
   if (!closed_point(pi) && (J.nlog[0] != 0 || J.nlog[1] != 0)) return;
   uint64_t word = 0;
   if (closed_point(pi) && row_runs(pi, B, lv)) {
     const Access a = access_of(pi, B);
-    const uint32_t* ivl = J.ivl + (uint64_t)lv * P;
-    const uint32_t iv = ivl[i];
+    const uint64_t x = J.st->x;
     for (uint32_t base = i & ~63u; base < P; base += 64) {
       const uint32_t j = base + lane;
-      const bool in = j >= i && j < P && ivl[j < P ? j : P - 1] == iv;
-      if (__ballot(in) == 0) break;
-      const uint64_t m = __ballot(in && lane_conflict<I>(J, pi, a, i, j, lv));
+      const uint32_t end = chunk_limit(J, lv, x, i, j);
+      const uint64_t m = __ballot(j >= i && j < P && lane < end &&
+                                  lane_conflict<I>(J, pi, a, i, j, lv));
       if (lane == base >> 6) word = m;
+      if (end < 64) break;
     }
   }
   const uint64_t row = (uint64_t)lv * P + i;
@@ -141,25 +158,36 @@ static dim3 row_grid(uint32_t max_points, uint32_t njobs) {
   return dim3((max_points + CF_WAVES / 2 - 1) / (CF_WAVES / 2), njobs);
 }
 
-hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, uint64_t* stamps,
+hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, const CallBlock& call,
                              hipStream_t s) {
   if (points == 0) return hipSuccess;
   const dim3 grid = row_grid(points, 1);
-  if (small) all_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(job, stamps);
-  else all_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(job, stamps);
+  if (small) all_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(job, call);
+  else all_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(job, call);
+  return hipGetLastError();
+}
+
+template <bool X>
+static hipError_t first_go(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
+                           const CallBlock& call, hipStream_t s) {
+  for (uint32_t j = 0; j < njobs; j += 65535) {      // (the grid's second dimension)
+    const dim3 grid = row_grid(max_points, njobs - j < 65535 ? njobs - j : 65535);
+    const CallBlock c = j == 0 ? call : CallBlock{};
+    if (small) first_kernel<int32_t, X><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, c);
+    else first_kernel<int64_t, X><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, c);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
-                               uint64_t* stamps, hipStream_t s) {
+                               const CallBlock& call, hipStream_t s) {
   if (njobs == 0 || max_points == 0) return hipSuccess;
-  for (uint32_t j = 0; j < njobs; j += 65535) {      // (the grid's second dimension)
-    const dim3 grid = row_grid(max_points, njobs - j < 65535 ? njobs - j : 65535);
-    uint64_t* const st = j == 0 ? stamps : nullptr;
-    if (small) first_kernel<int32_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, st);
-    else first_kernel<int64_t><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, st);
-  }
-  return hipGetLastError();
+  return first_go<false>(jobs, njobs, max_points, small, call, s);
+}
+
+hipError_t launch_first_under(const Job* job, uint32_t points, bool small, const CallBlock& call,
+                              hipStream_t s) {
+  return first_go<true>(job, 1, points ? points : 1, small, call, s);
 }
 
 }  // namespace rp

@@ -144,6 +144,39 @@ __device__ __forceinline__ void stamp_end(uint64_t* stamps) {
     atomicMax((unsigned long long*)&stamps[STAMP_END], (unsigned long long)wall_clock64());
 }
 
+// What the host reads of a call over one job whose conflicts are all in
+// closed form, in page-locked host memory: the last kernel of the call writes
+// it (finish_call, or the rounds' only workgroup), so nothing is copied back.
+constexpr uint32_t PAGE_TRAJ = 64, PAGE_PAIRS = 2048;
+struct ResultPage {
+  JobState st;
+  uint32_t words[16];        // the call's word block
+  uint64_t total;            // racing pairs
+  uint64_t pad[15];
+  uint64_t traj[PAGE_TRAJ];  // the first verified assignments
+  // then first partners [2][P] (u32), clauses [n_phi], or the first
+  // PAGE_PAIRS pairs of the list
+  __device__ __host__ uint8_t* tail() { return (uint8_t*)(this + 1); }
+};
+struct CallBlock {
+  uint64_t* stamps;          // NULL: no stamps
+  uint32_t* words;           // the call's word block (word 11: workgroups that have finished)
+  ResultPage* page;          // NULL: results are copied back
+};
+// Ends a workgroup of a call's last kernel: the end stamp, and by the
+// workgroup that ends last the job state and the word block into the page.
+__device__ __forceinline__ void finish_call(const CallBlock& c, const JobState* st) {
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  stamp_end(c.stamps);
+  if (!c.page) return;
+  __threadfence();
+  if (atomicAdd(&c.words[11], 1u) != gridDim.x * gridDim.y - 1) return;
+  c.page->st = *st;
+  for (int q = 0; q < 16; q++)
+    c.page->words[q] = __hip_atomic_load(&c.words[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // sort segment: one log of one job in the record buffer
 struct SortSeg {
   uint64_t beg, end;     // record range

@@ -304,7 +304,7 @@ namespace {
 // table for the jobs laid out by L in the device buffer d (all enqueued on
 // s, no sync).
 int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const Layout& L,
-                 uint8_t* d, uint8_t* hbuf, uint64_t* stamps, hipStream_t s, Timer& tm) {
+                 uint8_t* d, uint8_t* hbuf, const CallBlock& call, hipStream_t s, Timer& tm) {
   const size_t N = jobs.size();
   // the job and state tables and the error words come first and are the
   // only ones not written in full below
@@ -420,7 +420,9 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   // ---- first partners with no barrier enabled (once per job): every
   // later Verify call resolves its first partners from them
   // (a job without access records keeps the cleared table: no partner)
-  if (o.op != OP_CHECK && o.op != OP_SOLVE) {
+  // (with no log at all a check or a first-partner call goes to its pairs
+  // directly, under its assignment)
+  if (o.op != OP_CHECK && o.op != OP_SOLVE && !(o.op == OP_FIRST && L.ssegs.empty())) {
     uint32_t maxP = 1;
     bool lo32 = true, any_closed = false, closed_small = true;
     for (const JobInput& j : jobs) {
@@ -433,7 +435,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
     // the scan of the logs fills every row of every job; the closed form
     // then sets the rows of its own points (or, with no log, every row)
     if (!L.ssegs.empty()) {
-      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_ZERO, nullptr, s));
+      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_ZERO, s));
       HIPCHK(launch_conf_tiles(djobs, dcs, (int)L.ssegs.size(), derr + 9, s));
       tm.mark(T_SUMPRE);
       HIPCHK(launch_j0(djobs, dcs, (int)L.ssegs.size(), maxP, lo32, derr + 9, s));
@@ -441,7 +443,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
       HIPCHK(launch_save_j0(djobs, (uint32_t)N, s));
     }
     if (L.ssegs.empty() || any_closed) {
-      HIPCHK(launch_first_closed(djobs, (uint32_t)N, maxP, closed_small, stamps, s));
+      HIPCHK(launch_first_closed(djobs, (uint32_t)N, maxP, closed_small, call, s));
       if (L.ssegs.empty()) tm.mark(T_SUMPRE);
     }
   }
@@ -472,7 +474,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   uint8_t* d = (uint8_t*)region;
   Timer tm(s, 0);
   staging.resize(L.meta);
-  const int rc = prepare_jobs(jobs, o, L, d, staging.data(), nullptr, s, tm);
+  const int rc = prepare_jobs(jobs, o, L, d, staging.data(), CallBlock{}, s, tm);
   if (rc != RP_OK) return rc;
   // the first Solve of the jobs with option units (an empty phi is
   // answered by the initial x = 0): over the whole group, the others are
@@ -480,7 +482,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   bool any_units = false;
   for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
   HIPCHK(launch_rounds((const Job*)(d + L.o_jobs), (uint32_t)jobs.size(),
-                       RD_BUILD | (any_units ? RD_SOLVE : 0), 0, nullptr, s));
+                       RD_BUILD | (any_units ? RD_SOLVE : 0), 0, CallBlock{}, s));
   out.resize(jobs.size());
   for (size_t j = 0; j < jobs.size(); j++)
     std::memcpy(&out[j].job, staging.data() + L.o_jobs + j * sizeof(Job), sizeof(Job));
@@ -488,7 +490,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
 }
 
 int engine_round(const Job* djobs, uint32_t njobs, hipStream_t s) {
-  HIPCHK(launch_rounds(djobs, njobs, RD_LOOP, 1, nullptr, s));
+  HIPCHK(launch_rounds(djobs, njobs, RD_LOOP, 1, CallBlock{}, s));
   return RP_OK;
 }
 
@@ -506,9 +508,32 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   uint64_t* const stamps =
       level == 1 && L.ssegs.empty() ? (uint64_t*)((uint8_t*)ws + L.o_err) : nullptr;
   Timer tm(s, stamps ? 0 : level);
+  // results: a call over one job with no log gets them in a page-locked page
+  // that its last kernel writes; others copy the job states and the word
+  // block behind them (and the start of each trajectory) into page-locked, or
+  // (no_alloc) ordinary, memory
+  const size_t words_at = L.o_err - L.o_states;
+  const bool paged = !o.no_alloc && N == 1 && L.ssegs.empty();
+  const uint32_t traj_head = std::min<uint32_t>(o.traj_cap, PAGE_TRAJ);
+  size_t rb_bytes = words_at + 64 + N * traj_head * sizeof(uint64_t);
+  if (paged)
+    rb_bytes = sizeof(ResultPage) +
+               std::max<size_t>({2 * (size_t)jobs[0].plan->P * sizeof(uint32_t),
+                                 o.op == OP_CLAUSES ? L.phi_cap[0] * sizeof(rp_clause) : 0,
+                                 PAGE_PAIRS * sizeof(rp_pair)});
   // host staging: page-locked and kept per thread, or (no_alloc) ordinary
   // memory, which the upload has read before hipMemcpyAsync returns
   static thread_local std::vector<uint8_t> plain_stage, plain_rb;
+  uint8_t* rb;
+  if (o.no_alloc) {
+    plain_rb.resize(rb_bytes);
+    rb = plain_rb.data();
+  } else {
+    rb = (uint8_t*)t_stage.readback(rb_bytes);
+  }
+  if (!rb) return RP_ERR_DEVICE;
+  ResultPage* const page = paged ? (ResultPage*)rb : nullptr;
+  const CallBlock call{stamps, (uint32_t*)(d + L.o_err), page};
   // a call that ends without having waited for its stream leaves an event
   // behind its uploads
   struct Upload {
@@ -520,13 +545,13 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   } upload{s};
   if (o.no_alloc) {
     plain_stage.resize(L.meta);
-    const int rc = prepare_jobs(jobs, o, L, d, plain_stage.data(), nullptr, s, tm);
+    const int rc = prepare_jobs(jobs, o, L, d, plain_stage.data(), CallBlock{}, s, tm);
     if (rc != RP_OK) return rc;
   } else {
     uint8_t* h = t_stage.get(L.meta);
     if (!h) return RP_ERR_DEVICE;
     upload.from_pinned = true;
-    const int rc = prepare_jobs(jobs, o, L, d, h, stamps, s, tm);
+    const int rc = prepare_jobs(jobs, o, L, d, h, call, s, tm);
     if (rc != RP_OK) return rc;
   }
   const Job* djobs = (const Job*)(d + L.o_jobs);
@@ -538,25 +563,12 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   uint32_t* dtiles = derr + 9;     // conf tiles of the all-pairs scan
   uint32_t maxP = 1;
   for (const JobInput& j : jobs) maxP = std::max(maxP, j.plan->P);
-  std::vector<JobState> hst(N);
-  // job states, the error word and the start of each job's trajectory (the
-  // usual few rounds) are read back into page-locked memory in one go
-  const uint32_t traj_head = std::min<uint32_t>(o.traj_cap, 64);
-  const size_t rb_bytes = N * sizeof(JobState) + 64 + N * traj_head * sizeof(uint64_t);
-  uint8_t* rb;
-  if (o.no_alloc) {
-    plain_rb.resize(rb_bytes);
-    rb = plain_rb.data();
-  } else {
-    rb = (uint8_t*)t_stage.readback(rb_bytes);
-  }
-  if (!rb) return RP_ERR_DEVICE;
-  JobState* pst = (JobState*)rb;
-  uint32_t* herr = (uint32_t*)(rb + N * sizeof(JobState));
-  uint64_t* ptraj = (uint64_t*)(rb + N * sizeof(JobState) + 64);
+  const JobState* hst = page ? &page->st : (const JobState*)rb;
+  const uint32_t* herr = page ? page->words : (const uint32_t*)(rb + words_at);
+  uint64_t* ptraj = page ? page->traj : (uint64_t*)(rb + words_at + 64);
   auto enqueue_results = [&]() -> hipError_t {
-    hipError_t e = hipMemcpyAsync(pst, d + L.o_states, N * sizeof(JobState), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(herr, derr, 64, hipMemcpyDeviceToHost, s);
+    if (page) return hipSuccess;
+    hipError_t e = hipMemcpyAsync(rb, d + L.o_states, words_at + 64, hipMemcpyDeviceToHost, s);
     for (size_t j = 0; j < N && traj_head && e == hipSuccess; j++)
       e = hipMemcpyAsync(ptraj + j * traj_head, d + L.o_traj[j], traj_head * sizeof(uint64_t),
                          hipMemcpyDeviceToHost, s);
@@ -567,8 +579,8 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   const uint64_t scanned = o.op == OP_SOLVE ? 0 : L.n_rec;    // (0: all in closed form)
   const uint32_t conf_launches = o.op == OP_SOLVE || L.ssegs.empty() ? 0 : 1;
   if (o.op == OP_CHECK) {
-    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, stamps, s));
     if (nseg) {
+      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_CHECK, s));
       HIPCHK(launch_conf_tiles(djobs, dcs, nseg, dtiles, s));
       tm.mark(T_CONFPRE);
       HIPCHK(launch_conf(djobs, dcs, nseg, maxP, dtiles, s));
@@ -576,20 +588,25 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     }
     for (size_t j = 0; j < N; j++)
       if (!nseg || jobs[j].plan->any_closed)
-        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, stamps, s));
+        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, call, s));
     tm.mark(T_CHECK, nseg ? 2 : 1);
     for (size_t j = 0; j < N; j++)
       HIPCHK(launch_pairs(djobs + j, jobs[j].plan->P, !nseg, (rp_pair*)(d + L.o_pairs[j]),
-                          (uint64_t*)(d + L.o_ptotal[j]), stamps, s));
+                          (uint64_t*)(d + L.o_ptotal[j]), call, s));
     tm.mark(T_CLAUSE);
   } else if (o.op == OP_SOLVE) {
-    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_SOLVE, 0, stamps, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_SOLVE, 0, call, s));
     tm.mark(T_SOLVE);
   } else if (o.op == OP_FIRST) {
-    HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, stamps, s));
+    if (nseg) {
+      HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s));
+    } else {
+      for (size_t j = 0; j < N; j++)
+        HIPCHK(launch_first_under(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, call, s));
+    }
     tm.mark(T_CHECK);
   } else if (o.op == OP_CLAUSES) {
-    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_BUILD | RD_LEARN, 0, stamps, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_BUILD | RD_LEARN, 0, call, s));
     tm.mark(T_CLAUSE);
   } else {
     // the first Solve of Alg. 1: with no option units phi is empty and its
@@ -598,41 +615,62 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
     HIPCHK(launch_rounds(djobs, (uint32_t)N,
                          RD_BUILD | RD_LOOP | (any_units ? RD_SOLVE : 0) |
-                             (tm.level >= 2 ? RD_TIMED : 0), 0, stamps, s));
+                             (tm.level >= 2 ? RD_TIMED : 0), 0, call, s));
   }
   tm.mark(T_END);
   HIPCHK(enqueue_results());
   HIPCHK(hipStreamSynchronize(s));
   upload.waited = true;
-  std::memcpy(hst.data(), pst, N * sizeof(JobState));
   if (herr[0]) return RP_ERR_DEVICE;
   res.assign(N, JobResult{});
+  bool copies = false;             // copies enqueued after the wait
+  auto fetch = [&](void* to, const void* from, size_t n) -> hipError_t {
+    if (n == 0) return hipSuccess;
+    copies = true;
+    return hipMemcpyAsync(to, from, n, hipMemcpyDeviceToHost, s);
+  };
   for (size_t j = 0; j < N; j++) {
     res[j].st = hst[j];
     // a job that failed on the device keeps its own error state; the other
     // jobs of the call are unaffected and read out as usual
     if (hst[j].state == ST_ERROR) continue;
     if (o.op == OP_FIRST) {
-      res[j].first.resize(2 * (size_t)jobs[j].plan->P);
-      if (!res[j].first.empty())
-        HIPCHK(hipMemcpyAsync(res[j].first.data(), d + L.o_minj[j],
-                              res[j].first.size() * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+      const size_t n = 2 * (size_t)jobs[j].plan->P;
+      if (page) {
+        const uint32_t* f = (const uint32_t*)page->tail();
+        res[j].first.assign(f, f + n);
+        // (no kernel has resolved the divergent slots)
+        res[j].st.divergent = jobs[j].x & jobs[j].plan->div_if_enabled;
+      } else {
+        res[j].first.resize(n);
+        HIPCHK(fetch(res[j].first.data(), d + L.o_minj[j], n * sizeof(uint32_t)));
+        if (!nseg) res[j].st.divergent = jobs[j].x & jobs[j].plan->div_if_enabled;
+      }
     }
     if (o.op == OP_CLAUSES) {
-      res[j].phi.resize(hst[j].n_phi);
-      if (hst[j].n_phi)
-        HIPCHK(hipMemcpyAsync(res[j].phi.data(), d + L.o_phi[j], hst[j].n_phi * sizeof(rp_clause),
-                              hipMemcpyDeviceToHost, s));
+      if (page) {
+        const rp_clause* c = (const rp_clause*)page->tail();
+        res[j].phi.assign(c, c + hst[j].n_phi);
+      } else {
+        res[j].phi.resize(hst[j].n_phi);
+        HIPCHK(fetch(res[j].phi.data(), d + L.o_phi[j], hst[j].n_phi * sizeof(rp_clause)));
+      }
     }
     if (o.op == OP_CHECK) {
       uint64_t tot = 0;
-      HIPCHK(hipMemcpyAsync(&tot, d + L.o_ptotal[j], sizeof(tot), hipMemcpyDeviceToHost, s));
-      HIPCHK(hipStreamSynchronize(s));
+      if (page) {
+        tot = page->total;
+      } else {
+        HIPCHK(hipMemcpyAsync(&tot, d + L.o_ptotal[j], sizeof(tot), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+      }
+      if (!nseg) res[j].st.divergent = jobs[j].x & jobs[j].plan->div_if_enabled;
       res[j].n_pairs = tot;
-      if (o.want_pairs && tot <= o.pair_cap && tot) {
-        res[j].pairs.resize(tot);
-        HIPCHK(hipMemcpyAsync(res[j].pairs.data(), d + L.o_pairs[j], tot * sizeof(rp_pair),
-                              hipMemcpyDeviceToHost, s));
+      if (o.pair_out && tot <= o.pair_cap && tot) {
+        if (page && tot <= PAGE_PAIRS)
+          std::memcpy(o.pair_out, page->tail(), tot * sizeof(rp_pair));
+        else
+          HIPCHK(fetch(o.pair_out, d + L.o_pairs[j], tot * sizeof(rp_pair)));
       }
     }
     if (o.traj_cap) {
@@ -641,11 +679,10 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
       if (nt <= traj_head)
         std::memcpy(res[j].traj.data(), ptraj + j * traj_head, nt * sizeof(uint64_t));
       else
-        HIPCHK(hipMemcpyAsync(res[j].traj.data(), d + L.o_traj[j], nt * sizeof(uint64_t),
-                              hipMemcpyDeviceToHost, s));
+        HIPCHK(fetch(res[j].traj.data(), d + L.o_traj[j], nt * sizeof(uint64_t)));
     }
   }
-  HIPCHK(hipStreamSynchronize(s));
+  if (copies) HIPCHK(hipStreamSynchronize(s));
   if (stats) {
     std::memset(stats, 0, sizeof(*stats));
     for (size_t q = 1; q < tm.ev.size(); q++) {
@@ -713,7 +750,8 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     // (the rounds run on the device: their phases are counted there, and in
     // a batch the job that spent most in a phase stands for it)
     uint32_t tc = 0, tl = 0, ts = 0;
-    for (const JobState& st : hst) {
+    for (size_t j = 0; j < N; j++) {
+      const JobState& st = hst[j];
       if (o.op == OP_REPAIR) stats->rounds = std::max(stats->rounds, st.rounds);
       tc = std::max(tc, st.t_check);
       tl = std::max(tl, st.t_clause);

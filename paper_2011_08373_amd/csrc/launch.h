@@ -40,9 +40,7 @@ hipError_t launch_sort_scatter(int rb, int pass, const uint64_t* in, uint64_t* o
 constexpr int SCATTER_SHAPE_MAX = 9;
 constexpr int PASS_SHAPES_DEFAULT = 0x0FFFFFFF;
 constexpr int IVL_RESOLVE = 0, IVL_CHECK = 1, IVL_ZERO = 2;
-// (stamps: the call's clock stamps or NULL, here and below; a launch stamps
-// what its comment in common.h and its place in the call give it)
-hipError_t launch_ivl(const Job* jobs, uint32_t njobs, int mode, uint64_t* stamps, hipStream_t s);
+hipError_t launch_ivl(const Job* jobs, uint32_t njobs, int mode, hipStream_t s);
 hipError_t launch_save_j0(const Job* jobs, uint32_t njobs, hipStream_t s);
 // Lays out the round's tiles over the logs of running jobs: ctile_beg of
 // each segment, the total in *tiles.
@@ -60,22 +58,26 @@ hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t ma
 // no records).  small: every closed array of every job fits the 32-bit form
 // of closed.h.
 hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
-                               uint64_t* stamps, hipStream_t s);
-// Racing pairs of the PF_CLOSED points of one job under its assignment (after
-// launch_ivl): bitmap rows, and their counts in minj (every row of a job that
+                               const CallBlock& call, hipStream_t s);
+// First partners under its assignment of one job that has no records, into
+// minj; the last kernel of its call.
+hipError_t launch_first_under(const Job* job, uint32_t points, bool small, const CallBlock& call,
+                              hipStream_t s);
+// Racing pairs of the PF_CLOSED points of one job under its assignment: bitmap
+// rows, and their counts in minj (every row of a job that
 // has no records).
-hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, uint64_t* stamps,
+hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, const CallBlock& call,
                              hipStream_t s);
 // The bitmap of one job as a pair list in (level, i, j) order.  counted: the
 // row counts are in minj already.
 hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
-                        uint64_t* total, uint64_t* stamps, hipStream_t s);
+                        uint64_t* total, const CallBlock& call, hipStream_t s);
 // The rounds of Alg. 1 on every running job.  RD_BUILD: the job's clause tables
 // from j0 first; RD_SOLVE: one Solve first; RD_LOOP: rounds, at most limit of
 // them (0: until a verdict); RD_LEARN: Verify and GenerateClause under the
 // job's assignment only; RD_TIMED: the phases' clock ticks into the job state.
 constexpr int RD_BUILD = 1, RD_SOLVE = 2, RD_LOOP = 4, RD_LEARN = 8, RD_TIMED = 16;
 hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int flags, uint32_t limit,
-                         uint64_t* stamps, hipStream_t s);
+                         const CallBlock& call, hipStream_t s);
 
 }  // namespace rp

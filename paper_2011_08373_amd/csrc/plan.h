@@ -77,7 +77,6 @@ struct JobInput {
 struct JobResult {
   JobState st;
   std::vector<rp_clause> phi;       // clauses mode: reduced learned clauses
-  std::vector<rp_pair> pairs;       // check mode
   std::vector<uint32_t> first;      // first-partner mode: [2][P]
   uint64_t n_pairs = 0;
   std::vector<uint64_t> traj;
@@ -87,7 +86,7 @@ struct EngineOpts {
   Op op = OP_REPAIR;
   uint64_t pair_cap = 0;            // check: caller's capacity
   uint32_t traj_cap = 0;
-  bool want_pairs = true;
+  rp_pair* pair_out = nullptr;      // check of one job: the caller's list (at most pair_cap)
   bool no_alloc = false;            // stage through ordinary host memory, record no
                                     // timing events (no device or page-locked allocation)
 };

@@ -266,12 +266,12 @@ __device__ uint32_t learn_one(const Job& J, rp_clause c, uint32_t n, uint32_t* s
 // units); RD_LEARN generates the clauses under the job's assignment and stops.
 // limit: rounds to run (0: until a verdict).
 __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict__ jobs, int flags,
-                                                          uint32_t limit, uint64_t* stamps) {
+                                                          uint32_t limit, CallBlock call) {
   __shared__ RoundLds L;
   __shared__ JobState s_st;
   __shared__ uint64_t sm[RD_WAVES];
   __shared__ uint32_t s_row, s_n, s_w[64];
-  stamp_if(stamps, flags & RD_BUILD ? STAMP_FIRST : STAMP_BEGIN);
+  stamp_if(call.stamps, flags & RD_BUILD ? STAMP_FIRST : STAMP_BEGIN);
   const Job& J = jobs[blockIdx.x];
   const uint32_t tid = threadIdx.x, P = J.P;
   JobState* st = &s_st;
@@ -362,13 +362,22 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   }
   __syncthreads();
   if (tid < sizeof(JobState) / 4) ((uint32_t*)J.st)[tid] = ((const uint32_t*)st)[tid];
-  stamp_end(stamps);
+  if (call.page) {
+    // (a call over one job)
+    const uint32_t nt = J.traj ? (st->rounds < J.traj_cap ? st->rounds : J.traj_cap) : 0;
+    for (uint32_t q = tid; q < nt && q < PAGE_TRAJ; q += RD_BLOCK) call.page->traj[q] = J.traj[q];
+    if (flags & RD_LEARN) {
+      const uint32_t n = st->n_phi < J.phi_cap ? st->n_phi : J.phi_cap;
+      for (uint32_t q = tid; q < n; q += RD_BLOCK) ((rp_clause*)call.page->tail())[q] = J.phi[q];
+    }
+  }
+  finish_call(call, st);
 }
 
 hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int flags, uint32_t limit,
-                         uint64_t* stamps, hipStream_t s) {
+                         const CallBlock& call, hipStream_t s) {
   if (njobs == 0) return hipSuccess;
-  rounds_kernel<<<njobs, RD_BLOCK, 0, s>>>(jobs, flags, limit, stamps);
+  rounds_kernel<<<njobs, RD_BLOCK, 0, s>>>(jobs, flags, limit, call);
   return hipGetLastError();
 }
 
