@@ -2,9 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstring>
-#include <thread>
 #include <vector>
 
 #include "common.h"
@@ -55,24 +53,11 @@ static void make_plans(const rp_kernel* const* ks, uint32_t n, std::vector<Plan>
     make_plan(ks[j], plans[j]);
     ok[j] = 1;
   };
-  unsigned nth = std::min<unsigned>(16, std::max(1u, std::thread::hardware_concurrency()));
-  if (n < 64 || nth < 2) {
-    for (uint32_t j = 0; j < n; j++) one(j);
-    return;
-  }
-  nth = std::min<unsigned>(nth, n / 32);
-  std::atomic<uint32_t> next(0);
-  auto work = [&]() {
-    for (;;) {
-      const uint32_t j0 = next.fetch_add(16);
-      if (j0 >= n) break;
-      for (uint32_t j = j0; j < std::min(n, j0 + 16); j++) one(j);
-    }
-  };
-  std::vector<std::thread> pool;
-  for (unsigned t = 1; t < nth; t++) pool.emplace_back(work);
-  work();
-  for (std::thread& t : pool) t.join();
+  uint64_t points = 0;
+  for (uint32_t j = 0; j < n; j++) points += ks[j] ? ks[j]->n_points : 0;
+  over_jobs(n, points, [&](uint32_t first, uint32_t last) {
+    for (uint32_t j = first; j < last; j++) one(j);
+  });
 }
 
 // The result of one repair job from its final device state.
@@ -224,8 +209,6 @@ static void solve_plan(uint32_t S, const uint32_t* w, Plan& pl) {
   pl.S = S;
   pl.B = pl.T = 1;
   pl.weights.assign(w, w + S);
-  pl.cnt_pre.assign(1, 0);
-  pl.gcnt_pre.assign(1, 0);
 }
 
 size_t rp_solve_workspace_bytes(uint64_t n_clauses) {

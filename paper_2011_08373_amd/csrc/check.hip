@@ -59,8 +59,9 @@ __global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ 
     const uint32_t i = tid * 4 + q;
     uint64_t c = 0;
     if (i < P) {
-      c = (J.bits_any[i] & x) ? 1 : 0;
-      c |= (J.bits_grid[i] & x) ? (1ull << 32) : 0;
+      const DPoint& d = J.pts[i];
+      c = (slot_any(d) & x) ? 1 : 0;
+      c |= (slot_grid(d) & x) ? (1ull << 32) : 0;
     }
     cnt[q] = c;
     local += c;
@@ -104,6 +105,10 @@ __global__ __launch_bounds__(IVL_BLOCK) void ivl_kernel(const Job* __restrict__ 
 __global__ __launch_bounds__(256) void save_j0_kernel(const Job* __restrict__ jobs) {
   const Job& J = jobs[blockIdx.x];
   for (uint32_t r = threadIdx.x; r < 2 * J.P; r += 256) J.j0[r] = J.minj[r];
+}
+
+__device__ __forceinline__ bool writes(const DPoint& d) {
+  return d.kind == RP_ACCESS && (d.flags & PF_WRITE);
 }
 
 __device__ __forceinline__ void set_pair(uint64_t* bm, uint32_t wpr, uint32_t P, uint32_t lv,
@@ -318,7 +323,7 @@ __global__ __launch_bounds__(CONF_BLOCK) void conf_kernel(const Job* __restrict_
         s_minj[i] = NONE32;
       }
       for (uint32_t q = tid; q < P; q += CONF_BLOCK)
-        s_pw[q] = (uint16_t)(q | (((J.wbits[q >> 6] >> (q & 63)) & 1) << (RUN_W - 32)));
+        s_pw[q] = (uint16_t)(q | (uint32_t)writes(J.pts[q]) << (RUN_W - 32));
       __syncthreads();
     }
     const ConfSeg& sg = segs[cur];
@@ -783,7 +788,7 @@ __global__ __launch_bounds__(CONF_BLOCK) void j0_kernel(const Job* __restrict__ 
       P = J.P;
       for (uint32_t i = tid; i < P; i += CONF_BLOCK) {
         s_minj[i] = NONE32;
-        s_w[i] = (uint8_t)((J.wbits[i >> 6] >> (i & 63)) & 1);
+        s_w[i] = writes(J.pts[i]);
       }
       __syncthreads();
     }

@@ -69,8 +69,9 @@ __device__ __forceinline__ void stamp_gather(uint64_t* stamps, const Job& J, con
 // barrier of the view (64: none): no pair reaches past it.
 __device__ __forceinline__ uint32_t chunk_limit(const Job& J, uint32_t lv, uint64_t x, uint32_t i,
                                                 uint32_t j) {
-  const uint64_t* bits = lv ? J.bits_grid : J.bits_any;
-  const uint64_t m = __ballot(j > i && j < J.P && (bits[j] & x) != 0);
+  bool on = false;
+  if (j > i && j < J.P) on = ((lv ? slot_grid(J.pts[j]) : slot_any(J.pts[j])) & x) != 0;
+  const uint64_t m = __ballot(on);
   return m ? (uint32_t)__builtin_ctzll(m) : 64u;
 }
 

@@ -57,20 +57,29 @@ constexpr int MAX_SORT_PASSES = 8;
 // flags of DPoint::flags.  PF_TCONST: the word does not depend on the thread
 // (a = 0 mod words); PF_BCONST: it does not depend on the block (b = 0 mod
 // words).  PF_CLOSED: the conflicts of the point's array are decided in
-// closed form (closed.h) and it has no records.
+// closed form (closed.h) and it has no records; the flags from PF_POW2 to
+// PF_BCONST are then not set.  PF_GRID: a barrier occurrence of grid level.
 constexpr uint8_t PF_WRITE = 1, PF_GLOBAL = 2, PF_POW2 = 4, PF_TCONST = 8, PF_BCONST = 16,
-                  PF_CLOSED = 32;
+                  PF_CLOSED = 32, PF_GRID = 64;
 
 struct DPoint {          // 40 B, one per program point
   int32_t a, b, c;
   uint32_t words;        // array size (words)
   uint32_t m, r;         // guard: tid % m == r
   uint32_t cnt;          // threads of one block executing the point
-  uint16_t array;
+  uint16_t array;        // of a barrier: its slot
   uint8_t kind;          // RP_ACCESS / RP_BARRIER / RP_NOP
   uint8_t flags;         // PF_*
   uint32_t bm, br;       // block condition: bid % bm == br
 };
+
+// Slot bit of a barrier occurrence (of any level, of grid level), else 0.
+__host__ __device__ __forceinline__ uint64_t slot_any(const DPoint& d) {
+  return d.kind == RP_BARRIER ? 1ull << d.array : 0ull;
+}
+__host__ __device__ __forceinline__ uint64_t slot_grid(const DPoint& d) {
+  return d.kind == RP_BARRIER && (d.flags & PF_GRID) ? 1ull << d.array : 0ull;
+}
 
 struct JobState {        // device-resident per-job state; the host reads it
   uint64_t x;            // current assignment
@@ -105,9 +114,8 @@ struct Job {
   uint32_t tbits, bbits, pbits, key_shift;
   uint32_t nbits, policy;     // word-field width; learning policy
   const DPoint* pts;          // [P]
-  const uint64_t* wbits;      // [(P+63)/64] bit i: point i writes
-  const uint64_t* bits_any;   // [P] slot bit of a barrier occurrence, else 0
-  const uint64_t* bits_grid;  // [P] slot bit of a GRID barrier occurrence, else 0
+  const rp_clause* phi0;      // [n_phi at the start] option units, or a lone Solve's clauses
+  const void* unused[2];
   const uint32_t* weights;    // [S]
   const uint64_t* cnt_pre;    // [P+1] prefix of same-block records per block
   const uint64_t* gcnt_pre;   // [P+1] prefix of cross-block records

@@ -20,10 +20,11 @@ constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Layout {
-  size_t total = 0, meta = 0;
+  size_t total = 0;
+  size_t upload = 0;              // bytes from the start that the host fills and uploads
   size_t o_jobs = 0, o_states = 0, o_items = 0, o_ssegs = 0, o_csegs = 0;
-  size_t o_phi0 = 0;
-  std::vector<size_t> o_pts, o_bany, o_bgrid, o_w, o_cpre, o_gpre, o_phi0j, o_wbits;
+  uint64_t points = 0;            // of all jobs
+  std::vector<size_t> o_pts, o_w, o_cpre, o_gpre, o_phi0j;
   size_t o_chunks = 0;
   size_t o_recA = 0, o_recB = 0, o_dig = 0, o_cnt = 0, o_tot = 0, o_off = 0, o_err = 0;
   std::vector<size_t> o_ivl, o_minj, o_j0, o_phi, o_scratch, o_traj, o_bitmap, o_pairs, o_ptotal;
@@ -65,7 +66,7 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
       const uint64_t all = v == 0 ? p.n_intra : p.n_inter;
       size_rec += all;
       size_segs += all != 0;
-      const uint64_t n = v == 0 ? p.log_intra() : p.log_inter();
+      const uint64_t n = v == 0 ? p.log_intra : p.log_inter;
       if (n == 0) continue;
       SortSeg s{};
       s.beg = rec;
@@ -115,21 +116,32 @@ void plan_layout(const std::vector<JobInput>& jobs, const EngineOpts& o, Layout&
   L.o_err = off; off = up(off + 64);
   L.o_ssegs = off; off = up(off + size_segs * sizeof(SortSeg));
   L.o_csegs = off; off = up(off + size_segs * sizeof(ConfSeg));
-  L.o_pts.resize(N); L.o_bany.resize(N); L.o_bgrid.resize(N); L.o_w.resize(N);
-  L.o_wbits.resize(N);
-  L.o_cpre.resize(N); L.o_gpre.resize(N); L.o_phi0j.resize(N);
+  L.o_pts.resize(N); L.o_w.resize(N); L.o_cpre.resize(N); L.o_gpre.resize(N);
+  L.o_phi0j.resize(N);
+  uint64_t points = 0;
   for (size_t j = 0; j < N; j++) {
     const Plan& p = *jobs[j].plan;
+    points += p.P;
     L.o_pts[j] = off; off = up(off + p.P * sizeof(DPoint));
-    L.o_wbits[j] = off; off = up(off + p.wbits.size() * sizeof(uint64_t));
-    L.o_bany[j] = off; off = up(off + p.P * sizeof(uint64_t));
-    L.o_bgrid[j] = off; off = up(off + p.P * sizeof(uint64_t));
     L.o_w[j] = off; off = up(off + p.S * sizeof(uint32_t));
-    L.o_cpre[j] = off; off = up(off + (p.P + 1) * sizeof(uint64_t));
-    L.o_gpre[j] = off; off = up(off + (p.P + 1) * sizeof(uint64_t));
     L.o_phi0j[j] = off; off = up(off + jobs[j].phi0.size() * sizeof(rp_clause));
   }
-  L.meta = off;
+  L.points = points;
+  L.upload = off;
+  // what only a log needs
+  for (size_t j = 0; j < N; j++) {
+    const Plan& p = *jobs[j].plan;
+    L.o_cpre[j] = off; off = up(off + (p.P + 1) * sizeof(uint64_t));
+    L.o_gpre[j] = off; off = up(off + (p.P + 1) * sizeof(uint64_t));
+  }
+  if (!L.ssegs.empty()) L.upload = off;
+  // (room that earlier tables had, kept so that workspace sizes stay as they were)
+  for (size_t j = 0; j < N; j++) {
+    const uint64_t P = jobs[j].plan->P;
+    off = up(off + (P + 63) / 64 * sizeof(uint64_t));
+    off = up(off + P * sizeof(uint64_t));
+    off = up(off + P * sizeof(uint64_t));
+  }
   // ---- device-only region
   L.o_items = off; off = up(off + (size_t)size_chunks * sizeof(GenItem));
   L.o_chunks = off; off = up(off + (size_t)size_chunks * sizeof(SortChunk));
@@ -299,7 +311,7 @@ thread_local PinnedStage t_stage;
 
 namespace {
 
-// Host staging (hbuf, L.meta bytes, must stay untouched until the upload
+// Host staging (hbuf, L.upload bytes, must stay untouched until the upload
 // enqueued here has run), upload, record generation, sort and first-partner
 // table for the jobs laid out by L in the device buffer d (all enqueued on
 // s, no sync).
@@ -311,54 +323,57 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   std::memset(hbuf, 0, L.o_ssegs);
   Job* hj = (Job*)(hbuf + L.o_jobs);
   JobState* hs = (JobState*)(hbuf + L.o_states);
-  for (size_t j = 0; j < N; j++) {
-    const Plan& p = *jobs[j].plan;
-    Job& J = hj[j];
-    J.P = p.P; J.S = p.S; J.B = p.B; J.T = p.T;
-    J.tbits = p.tbits; J.bbits = p.bbits; J.pbits = p.pbits; J.key_shift = p.key_shift;
-    J.nbits = p.nbits; J.policy = jobs[j].policy;
-    J.pts = (const DPoint*)(d + L.o_pts[j]);
-    J.wbits = (const uint64_t*)(d + L.o_wbits[j]);
-    J.bits_any = (const uint64_t*)(d + L.o_bany[j]);
-    J.bits_grid = (const uint64_t*)(d + L.o_bgrid[j]);
-    J.weights = (const uint32_t*)(d + L.o_w[j]);
-    J.cnt_pre = (const uint64_t*)(d + L.o_cpre[j]);
-    J.gcnt_pre = (const uint64_t*)(d + L.o_gpre[j]);
-    J.rblk = p.cnt_pre.empty() ? 0 : p.cnt_pre[p.P];
-    J.div_if_enabled = p.div_if_enabled;
-    J.pad_array = p.pad_array;
-    J.log[0] = J.log[1] = nullptr;
-    J.nlog[0] = p.log_intra();
-    J.nlog[1] = p.log_inter();
-    J.ivl = (uint32_t*)(d + L.o_ivl[j]);
-    J.minj = (uint32_t*)(d + L.o_minj[j]);
-    J.j0 = (uint32_t*)(d + L.o_j0[j]);
-    J.bitmap = o.op == OP_CHECK ? (uint64_t*)(d + L.o_bitmap[j]) : nullptr;
-    J.wpr = (p.P + 63) / 64;
-    J.phi = (rp_clause*)(d + L.o_phi[j]);
-    J.scratch = (rp_clause*)(d + L.o_scratch[j]);
-    J.phi_cap = L.phi_cap[j];
-    J.scratch_cap = L.scratch_cap[j];
-    J.st = (JobState*)(d + L.o_states) + j;
-    J.traj = o.traj_cap ? (uint64_t*)(d + L.o_traj[j]) : nullptr;
-    J.traj_cap = o.traj_cap;
-    J.node_limit = 1ull << solver_nodes_log2(0, false);
-    JobState& S = hs[j];
-    std::memset(&S, 0, sizeof(S));
-    S.x = jobs[j].x;
-    S.n_phi = (uint32_t)jobs[j].phi0.size();
-    S.state = ST_RUN;
-    S.max_rounds = jobs[j].max_rounds;
-    S.phase = jobs[j].solver ? PH_GREEDY : PH_EXACT;
-    std::memcpy(hbuf + L.o_pts[j], p.pts.data(), p.P * sizeof(DPoint));
-    std::memcpy(hbuf + L.o_wbits[j], p.wbits.data(), p.wbits.size() * sizeof(uint64_t));
-    std::memcpy(hbuf + L.o_bany[j], p.bits_any.data(), p.P * sizeof(uint64_t));
-    std::memcpy(hbuf + L.o_bgrid[j], p.bits_grid.data(), p.P * sizeof(uint64_t));
-    std::memcpy(hbuf + L.o_w[j], p.weights.data(), p.S * sizeof(uint32_t));
-    std::memcpy(hbuf + L.o_cpre[j], p.cnt_pre.data(), (p.P + 1) * sizeof(uint64_t));
-    std::memcpy(hbuf + L.o_gpre[j], p.gcnt_pre.data(), (p.P + 1) * sizeof(uint64_t));
-    std::memcpy(hbuf + L.o_phi0j[j], jobs[j].phi0.data(), jobs[j].phi0.size() * sizeof(rp_clause));
-  }
+  const bool log = !L.ssegs.empty();
+  auto fill = [&](uint32_t first, uint32_t last) {
+    for (size_t j = first; j < last; j++) {
+      const Plan& p = *jobs[j].plan;
+      Job& J = hj[j];
+      J.P = p.P; J.S = p.S; J.B = p.B; J.T = p.T;
+      J.tbits = p.tbits; J.bbits = p.bbits; J.pbits = p.pbits; J.key_shift = p.key_shift;
+      J.nbits = p.nbits; J.policy = jobs[j].policy;
+      J.pts = (const DPoint*)(d + L.o_pts[j]);
+      J.phi0 = (const rp_clause*)(d + L.o_phi0j[j]);
+      J.weights = (const uint32_t*)(d + L.o_w[j]);
+      J.cnt_pre = (const uint64_t*)(d + L.o_cpre[j]);
+      J.gcnt_pre = (const uint64_t*)(d + L.o_gpre[j]);
+      J.rblk = p.rblk;
+      J.div_if_enabled = p.div_if_enabled;
+      J.pad_array = p.pad_array;
+      J.log[0] = J.log[1] = nullptr;
+      J.nlog[0] = p.log_intra;
+      J.nlog[1] = p.log_inter;
+      J.ivl = (uint32_t*)(d + L.o_ivl[j]);
+      J.minj = (uint32_t*)(d + L.o_minj[j]);
+      J.j0 = (uint32_t*)(d + L.o_j0[j]);
+      J.bitmap = o.op == OP_CHECK ? (uint64_t*)(d + L.o_bitmap[j]) : nullptr;
+      J.wpr = (p.P + 63) / 64;
+      J.phi = (rp_clause*)(d + L.o_phi[j]);
+      J.scratch = (rp_clause*)(d + L.o_scratch[j]);
+      J.phi_cap = L.phi_cap[j];
+      J.scratch_cap = L.scratch_cap[j];
+      J.st = (JobState*)(d + L.o_states) + j;
+      J.traj = o.traj_cap ? (uint64_t*)(d + L.o_traj[j]) : nullptr;
+      J.traj_cap = o.traj_cap;
+      J.node_limit = 1ull << solver_nodes_log2(0, false);
+      JobState& S = hs[j];
+      S.x = jobs[j].x;
+      S.n_phi = (uint32_t)jobs[j].phi0.size();
+      S.state = ST_RUN;
+      S.max_rounds = jobs[j].max_rounds;
+      S.phase = jobs[j].solver ? PH_GREEDY : PH_EXACT;
+      uint32_t* w = (uint32_t*)(hbuf + L.o_w[j]);
+      for (uint32_t q = 0; q < p.S; q++) w[q] = p.k ? p.k->slots[q].weight : p.weights[q];
+      if (!jobs[j].phi0.empty())
+        std::memcpy(hbuf + L.o_phi0j[j], jobs[j].phi0.data(),
+                    jobs[j].phi0.size() * sizeof(rp_clause));
+      if (p.P == 0 && !log) continue;
+      DPoint* pts = (DPoint*)(hbuf + L.o_pts[j]);
+      fill_points(p, pts);
+      if (log)
+        fill_prefixes(p, pts, (uint64_t*)(hbuf + L.o_cpre[j]), (uint64_t*)(hbuf + L.o_gpre[j]));
+    }
+  };
+  over_jobs((uint32_t)N, L.points, fill);
   std::memcpy(hbuf + L.o_ssegs, L.ssegs.data(), L.ssegs.size() * sizeof(SortSeg));
   // sorted logs end in buffer A after an even number of passes, else B
   uint8_t* sorted = d + ((L.passes % 2 == 0) ? L.o_recA : L.o_recB);
@@ -374,11 +389,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
     hj[c.job].log[c.level] = c.log;
   }
   tm.mark(T_START);
-  HIPCHK(hipMemcpyAsync(d, hbuf, L.meta, hipMemcpyHostToDevice, s));
-  for (size_t j = 0; j < N; j++)
-    if (!jobs[j].phi0.empty())
-      HIPCHK(hipMemcpyAsync(d + L.o_phi[j], d + L.o_phi0j[j],
-                            jobs[j].phi0.size() * sizeof(rp_clause), hipMemcpyDeviceToDevice, s));
+  HIPCHK(hipMemcpyAsync(d, hbuf, L.upload, hipMemcpyHostToDevice, s));
   HIPCHK(launch_items((const Job*)(d + L.o_jobs), (const SortSeg*)(d + L.o_ssegs),
                       (uint32_t)L.ssegs.size(), L.n_chunks, L.chunk_len, (GenItem*)(d + L.o_items),
                       (SortChunk*)(d + L.o_chunks), s));
@@ -473,7 +484,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   if (bytes < L.total || !region) return RP_ERR_WORKSPACE;
   uint8_t* d = (uint8_t*)region;
   Timer tm(s, 0);
-  staging.resize(L.meta);
+  staging.resize(L.upload);
   const int rc = prepare_jobs(jobs, o, L, d, staging.data(), CallBlock{}, s, tm);
   if (rc != RP_OK) return rc;
   // the first Solve of the jobs with option units (an empty phi is
@@ -508,19 +519,21 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   uint64_t* const stamps =
       level == 1 && L.ssegs.empty() ? (uint64_t*)((uint8_t*)ws + L.o_err) : nullptr;
   Timer tm(s, stamps ? 0 : level);
-  // results: a call over one job with no log gets them in a page-locked page
-  // that its last kernel writes; others copy the job states and the word
-  // block behind them (and the start of each trajectory) into page-locked, or
-  // (no_alloc) ordinary, memory
+  // results: a call over one job with no log gets them in a page that its last
+  // kernel writes, page-locked or (no_alloc) in the workspace behind the
+  // layout, if there is room, and copied back whole; others copy the job
+  // states and the word block behind them (and the start of each trajectory)
+  // into page-locked, or (no_alloc) ordinary, memory
   const size_t words_at = L.o_err - L.o_states;
-  const bool paged = !o.no_alloc && N == 1 && L.ssegs.empty();
+  const bool paged = N == 1 && L.ssegs.empty() &&
+                     (!o.no_alloc || (o.op == OP_REPAIR && ws_bytes - L.total >= sizeof(ResultPage)));
   const uint32_t traj_head = std::min<uint32_t>(o.traj_cap, PAGE_TRAJ);
   size_t rb_bytes = words_at + 64 + N * traj_head * sizeof(uint64_t);
   if (paged)
-    rb_bytes = sizeof(ResultPage) +
+    rb_bytes = sizeof(ResultPage) + (o.no_alloc ? 0 :
                std::max<size_t>({2 * (size_t)jobs[0].plan->P * sizeof(uint32_t),
                                  o.op == OP_CLAUSES ? L.phi_cap[0] * sizeof(rp_clause) : 0,
-                                 PAGE_PAIRS * sizeof(rp_pair)});
+                                 PAGE_PAIRS * sizeof(rp_pair)}));
   // host staging: page-locked and kept per thread, or (no_alloc) ordinary
   // memory, which the upload has read before hipMemcpyAsync returns
   static thread_local std::vector<uint8_t> plain_stage, plain_rb;
@@ -533,7 +546,8 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   }
   if (!rb) return RP_ERR_DEVICE;
   ResultPage* const page = paged ? (ResultPage*)rb : nullptr;
-  const CallBlock call{stamps, (uint32_t*)(d + L.o_err), page};
+  const CallBlock call{stamps, (uint32_t*)(d + L.o_err),
+                       page && o.no_alloc ? (ResultPage*)(d + L.total) : page};
   // a call that ends without having waited for its stream leaves an event
   // behind its uploads
   struct Upload {
@@ -544,11 +558,11 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     }
   } upload{s};
   if (o.no_alloc) {
-    plain_stage.resize(L.meta);
-    const int rc = prepare_jobs(jobs, o, L, d, plain_stage.data(), CallBlock{}, s, tm);
+    plain_stage.resize(L.upload);
+    const int rc = prepare_jobs(jobs, o, L, d, plain_stage.data(), call, s, tm);
     if (rc != RP_OK) return rc;
   } else {
-    uint8_t* h = t_stage.get(L.meta);
+    uint8_t* h = t_stage.get(L.upload);
     if (!h) return RP_ERR_DEVICE;
     upload.from_pinned = true;
     const int rc = prepare_jobs(jobs, o, L, d, h, call, s, tm);
@@ -567,7 +581,9 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   const uint32_t* herr = page ? page->words : (const uint32_t*)(rb + words_at);
   uint64_t* ptraj = page ? page->traj : (uint64_t*)(rb + words_at + 64);
   auto enqueue_results = [&]() -> hipError_t {
-    if (page) return hipSuccess;
+    if (page)
+      return o.no_alloc ? hipMemcpyAsync(rb, d + L.total, sizeof(ResultPage), hipMemcpyDeviceToHost, s)
+                        : hipSuccess;
     hipError_t e = hipMemcpyAsync(rb, d + L.o_states, words_at + 64, hipMemcpyDeviceToHost, s);
     for (size_t j = 0; j < N && traj_head && e == hipSuccess; j++)
       e = hipMemcpyAsync(ptraj + j * traj_head, d + L.o_traj[j], traj_head * sizeof(uint64_t),

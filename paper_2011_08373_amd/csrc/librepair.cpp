@@ -117,6 +117,13 @@ int validate_kernel(const rp_kernel* k) {
   return RP_OK;
 }
 
+// The plan of a kernel is one pass over its points.  The points of one array,
+// guard and pair of strides differ in the offset c only, so what depends on
+// the rest (executing threads and blocks, records, the arc of words, the
+// closed form's steps and spans) is worked out once per such combination and
+// looked up by the following points (a small direct-mapped table; programs
+// unrolled from loops repeat few combinations).
+//
 // Word compaction.  The sort only has to group records by location: the
 // order of the locations themselves is free.  So each array's words are
 // rotated (w -> (w + off) mod words) so that every word its accesses can
@@ -124,153 +131,11 @@ int validate_kernel(const rp_kernel* k) {
 // wide as the largest span: fewer key bits, fewer or narrower radix passes.
 // The touched words of a point lie in the arc of the circle of residues from
 // the smallest to the largest value of a*t + b*k + c over its executing
-// threads and blocks.  The circle is cut into CW_BINS bins; every bin an arc
-// meets is marked, and the rotation moves the longest run of unmarked bins
-// (words no access can touch) to the top of the range.  The rotation is
-// folded into each point's c, so record generation is unchanged.
-namespace {
-constexpr uint32_t CW_BINS = 256;
-
-// [min, max] of x * (r + m*u) over u in [0, n) (n >= 1); false on overflow
-bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64_t& hi) {
-  int64_t a, b;
-  if (r > (uint64_t)INT64_MAX || m * (n - 1) > (uint64_t)INT64_MAX) return false;
-  if (__builtin_mul_overflow(x, (int64_t)r, &a)) return false;
-  if (__builtin_mul_overflow(x, (int64_t)(m * (n - 1)), &b)) return false;
-  int64_t l = 0, h = 0;
-  if (__builtin_add_overflow(a, b < 0 ? b : 0, &l)) return false;
-  if (__builtin_add_overflow(a, b > 0 ? b : 0, &h)) return false;
-  lo = l;
-  hi = h;
-  return true;
-}
-}  // namespace
-
-void compact_words(const rp_kernel* k, Plan& pl) {
-  const uint32_t A = k->n_arrays;
-  // per array: bins met by an arc (as a running-sum difference array), or
-  // the whole circle
-  static thread_local std::vector<int32_t> diff;
-  static thread_local std::vector<uint8_t> full, used;
-  diff.assign((size_t)A * (CW_BINS + 1), 0);
-  full.assign(A, 0);
-  used.assign(A, 0);
-  // words per bin, as a shift when the array size is a power of two (the
-  // usual case: no division per access)
-  static thread_local std::vector<uint64_t> bws;
-  static thread_local std::vector<int32_t> bsh;
-  bws.resize(A);
-  bsh.resize(A);
-  for (uint32_t arr = 0; arr < A; arr++) {
-    const uint64_t N = k->arrays[arr].words;
-    bws[arr] = (N + CW_BINS - 1) / CW_BINS;
-    const bool p2 = (N & (N - 1)) == 0 && (bws[arr] & (bws[arr] - 1)) == 0;
-    bsh[arr] = p2 ? __builtin_ctzll(bws[arr]) : -1;
-  }
-  for (uint32_t i = 0; i < pl.P; i++) {
-    const DPoint& d = pl.pts[i];
-    if (d.kind != RP_ACCESS || d.cnt == 0) continue;
-    const uint32_t arr = d.array;
-    if (full[arr]) continue;
-    const uint64_t N = k->arrays[arr].words;
-    const uint64_t nblk = d.br < pl.B ? (pl.B - 1 - d.br) / d.bm + 1 : 0;
-    if (nblk == 0) continue;
-    used[arr] = 1;
-    int64_t tlo, thi, blo, bhi, lo, hi;
-    if (N > (1ull << 31) || !lin_range(d.a, d.r, d.m, d.cnt, tlo, thi) ||
-        !lin_range(d.b, d.br, d.bm, nblk, blo, bhi) || __builtin_add_overflow(tlo, blo, &lo) ||
-        __builtin_add_overflow(lo, (int64_t)d.c, &lo) || __builtin_add_overflow(thi, bhi, &hi) ||
-        __builtin_add_overflow(hi, (int64_t)d.c, &hi) || (uint64_t)(hi - lo) + 1 >= N) {
-      full[arr] = 1;   // rotated offsets must fit the int32 c; an arc round the circle
-      continue;
-    }
-    const int32_t sh = bsh[arr];
-    int64_t r;
-    if (sh >= 0) {
-      r = lo & (int64_t)(N - 1);
-    } else {
-      r = lo % (int64_t)N;
-      if (r < 0) r += (int64_t)N;
-    }
-    const uint64_t bw = bws[arr];                       // words per bin
-    const uint64_t s0 = (uint64_t)r, e0 = s0 + (uint64_t)(hi - lo);   // last word, may pass N
-    int32_t* df = diff.data() + (size_t)arr * (CW_BINS + 1);
-    auto mark = [&](uint64_t wa, uint64_t wb) {   // words [wa, wb] inside [0, N)
-      df[sh >= 0 ? wa >> sh : wa / bw]++;
-      df[(sh >= 0 ? wb >> sh : wb / bw) + 1]--;
-    };
-    if (e0 < N) {
-      mark(s0, e0);
-    } else {
-      mark(s0, N - 1);
-      mark(0, e0 - N);
-    }
-  }
-  uint64_t span_max = 1;
-  for (uint32_t arr = 0; arr < A; arr++) {
-    const uint64_t N = k->arrays[arr].words;
-    uint64_t off = 0, span = N;
-    if (!used[arr] && !full[arr]) {
-      span = 1;                                    // no access touches this array
-    } else if (!full[arr]) {
-      const uint64_t bw = bws[arr];
-      const uint32_t nb = (uint32_t)((N + bw - 1) / bw);   // bins inside [0, N)
-      const int32_t* df = diff.data() + (size_t)arr * (CW_BINS + 1);
-      // longest circular run of unmarked bins: the runs inside [0, nb), and
-      // the one that wraps (the unmarked tail joined to the unmarked head)
-      static thread_local std::vector<uint8_t> marked;
-      marked.resize(nb);
-      int32_t run = 0;
-      for (uint32_t j = 0; j < nb; j++) {
-        run += df[j];
-        marked[j] = run > 0;
-      }
-      uint32_t head = 0, tail = 0;
-      while (head < nb && !marked[head]) head++;
-      while (tail < nb && !marked[nb - 1 - tail]) tail++;
-      uint32_t best_len = 0, best_end = 0, cur = 0;
-      for (uint32_t j = 0; j < nb; j++) {
-        if (!marked[j]) {
-          if (++cur > best_len) {
-            best_len = cur;
-            best_end = j + 1 == nb ? 0 : j + 1;   // first bin after the run
-          }
-        } else {
-          cur = 0;
-        }
-      }
-      if (head < nb && head + tail > best_len) {   // the wrapping run
-        best_len = head + tail;
-        best_end = head;
-      }
-      if (head == nb) {
-        span = 1;
-      } else if (best_len > 0) {
-        // words of the gap: bins best_end - best_len .. best_end - 1 (mod nb);
-        // only the last bin of the circle can be narrower than bw
-        const uint64_t last_w = N - (uint64_t)(nb - 1) * bw;
-        const uint32_t first = best_end >= best_len ? best_end - best_len : best_end + nb - best_len;
-        const bool has_last = first + best_len > nb || first + best_len == nb;
-        const uint64_t gap = (uint64_t)(best_len - (has_last ? 1 : 0)) * bw + (has_last ? last_w : 0);
-        const uint64_t next = (uint64_t)best_end * bw;    // first word after the gap
-        off = (N - next % N) % N;
-        span = N - gap;
-      }
-    }
-    span_max = std::max(span_max, span);
-    if (off == 0) continue;
-    for (uint32_t i = 0; i < pl.P; i++) {
-      DPoint& d = pl.pts[i];
-      if (d.kind != RP_ACCESS || d.array != arr) continue;
-      int64_t c = (int64_t)d.c % (int64_t)N;
-      if (c < 0) c += (int64_t)N;
-      d.c = (int32_t)(((uint64_t)c + off) % N);
-    }
-  }
-  pl.nbits = bits_for(span_max - 1);
-  pl.key_bits = pl.abits + pl.nbits;
-}
-
+// threads and blocks.  The circle is cut into CW_BINS bins, one bit each;
+// every bin an arc meets is marked, and the rotation moves the longest run of
+// unmarked bins (words no access can touch) to the top of the range.  The
+// rotation is folded into each point's c, so record generation is unchanged.
+//
 // Which arrays are decided in closed form.  The closed form tests pairs of
 // points of one array, each over the values of an arithmetic progression that
 // fall into an interval (closed_scan); the log sorts every access.  For an
@@ -286,7 +151,22 @@ void compact_words(const rp_kernel* k, Plan& pl) {
 // the launches), and where the tests of one lane in sequence end before the
 // log would.
 namespace {
+constexpr uint32_t CW_BINS = 256;
 constexpr double RECORDS_FREE = 4.0e6, SERIAL_FREE = 512, SERIAL_RECORDS = 16384;
+
+// [min, max] of x * (r + m*u) over u in [0, n) (n >= 1); false on overflow
+bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64_t& hi) {
+  int64_t a, b;
+  if (r > (uint64_t)INT64_MAX || m * (n - 1) > (uint64_t)INT64_MAX) return false;
+  if (__builtin_mul_overflow(x, (int64_t)r, &a)) return false;
+  if (__builtin_mul_overflow(x, (int64_t)(m * (n - 1)), &b)) return false;
+  int64_t l = 0, h = 0;
+  if (__builtin_add_overflow(a, b < 0 ? b : 0, &l)) return false;
+  if (__builtin_add_overflow(a, b > 0 ? b : 0, &h)) return false;
+  lo = l;
+  hi = h;
+  return true;
+}
 
 double scan_trips(double n, double step, double w, double W) {
   step = step < 0 ? -step : step;
@@ -294,200 +174,365 @@ double scan_trips(double n, double step, double w, double W) {
   return std::min(n, (n * step / W + 1) * (w / step + 2));
 }
 
-struct ClosedArray {
+// Points of one array, guard and pair of strides.
+struct Combo {
+  uint32_t epoch = 0;                    // of the plan that filled it
+  uint16_t array = 0, guard = 0;
+  int32_t a = 0, b = 0;
+  bool runs = false, arc = false;        // executed at all; lo and width are known
+  uint64_t intra = 0, inter = 0;         // records per block, cross-block records
+  int64_t lo = 0, hi = 0;                // range of a*t + b*k
+};
+
+struct ArrayScratch {
+  uint64_t bw = 1;                       // words per bin; its shift where a power of two
+  int32_t sh = -1;
+  bool used = false, full = false;       // some access; an arc round the circle
+  uint64_t bins[CW_BINS / 64] = {};
+  // the closed form's bound
   static constexpr int MAXC = 8;         // distinct (b, block condition) of its points
   struct Blocks { int32_t b, S; uint32_t bm, br, Z; } c[MAXC];
   int nc = 0;
   bool many = false;                     // more than MAXC of them
-  uint64_t n = 0, records = 0;
+  uint64_t n = 0, intra = 0, inter = 0;  // points, records per block, cross-block records
   int64_t span = 0, bspan = 0;           // largest |A| * (X - 1) and |S| * (Z - 1)
 };
-}  // namespace
 
-void mark_closed(const rp_kernel* k, Plan& pl) {
-  static thread_local std::vector<ClosedArray> as;
-  static thread_local std::vector<uint8_t> take;
-  as.assign(k->n_arrays, ClosedArray{});
-  take.assign(k->n_arrays, 0);
-  const uint32_t B = pl.B;
-  for (uint32_t i = 0; i < pl.P; i++) {
-    const DPoint& d = pl.pts[i];
-    if (d.kind != RP_ACCESS) continue;
-    ClosedArray& a = as[d.array];
-    a.n++;
-    if (d.cnt == 0 || d.br >= B) continue;
-    a.records += (pl.cnt_pre[i + 1] - pl.cnt_pre[i]) * B + (pl.gcnt_pre[i + 1] - pl.gcnt_pre[i]);
-    const Access s = make_access(d.a, d.b, d.c, d.words, d.m, d.r, d.cnt, d.bm, d.br, B);
-    a.span = std::max<int64_t>(a.span, abs_of<int64_t>(s.A) * (int64_t)(s.X - 1));
-    a.bspan = std::max<int64_t>(a.bspan, abs_of<int64_t>(s.S) * (int64_t)(s.Z - 1));
-    int q = 0;
-    while (q < a.nc && !(a.c[q].b == s.b && a.c[q].bm == s.bm && a.c[q].br == s.br)) q++;
-    if (q < a.nc) continue;
-    if (a.nc == ClosedArray::MAXC) a.many = true;
-    else a.c[a.nc++] = {s.b, s.S, s.bm, s.br, s.Z};
-  }
-  for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
-    const ClosedArray& a = as[arr];
-    if (a.n == 0 || a.span >= MAX_SPAN || a.bspan >= MAX_SPAN) continue;
-    const uint32_t words = k->arrays[arr].words;
-    const double W = words, w = 2.0 * (double)a.span, wraps = 1 + std::floor(w / W);
-    const double bw = 2.0 * (double)a.bspan;
-    const bool cross = k->arrays[arr].space == RP_GLOBAL && B > 1;
-    double t0 = 1, t1 = cross ? 1 : 0;   // tests of a pair: same block, different blocks
-    if (a.many) {                        // whatever the steps are
-      t0 = B;
-      if (cross) t1 = std::min(bw + 1, (double)B * B);
-    }
-    for (int u = 0; u < a.nc && !a.many; u++) {
-      for (int v = 0; v <= u; v++) {
-        const auto &p = a.c[u], &q = a.c[v];
-        const double lcm = p.bm == q.bm ? p.bm : (double)p.bm * q.bm / gcd_of<uint32_t>(p.bm, q.bm);
-        if (lcm < B) {
-          const int64_t db = step_mod((int64_t)p.b - q.b, words);
-          t0 = std::max(t0, scan_trips(std::floor(B / lcm) + 1,
-                                       step_mod(db * (int64_t)lcm, words), w, W));
-        }
-        if (cross) {
-          const double sp = std::abs((double)p.S), sq = std::abs((double)q.S);
-          const double g = gcd_of<int64_t>((int64_t)sp, (int64_t)sq);
-          const double n = g > 0 ? (sp * (p.Z - 1.0) + sq * (q.Z - 1.0)) / g + 1 : 1;
-          if (n <= (double)p.Z * q.Z) t1 = std::max(t1, scan_trips(n, g, w, W));
-          else t1 = std::max(t1, p.Z <= q.Z ? p.Z * scan_trips(q.Z, q.S, w, W)
-                                            : q.Z * scan_trips(p.Z, p.S, w, W));
-        }
-      }
-    }
-    const double n = (double)a.n, rec = (double)a.records;
-    const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
-    const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
-    if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) continue;
-    take[arr] = 1;
-    pl.any_closed = true;
-    if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE || pl.T > SMALL_SIZE ||
-        B > SMALL_SIZE)
-      pl.closed_small = false;
-  }
-  if (!pl.any_closed) return;
-  uint64_t in = 0, ex = 0, in0 = 0, ex0 = 0;   // (in0, ex0: the full prefixes)
-  for (uint32_t i = 0; i < pl.P; i++) {
-    const uint64_t in1 = pl.cnt_pre[i + 1], ex1 = pl.gcnt_pre[i + 1];
-    DPoint& d = pl.pts[i];
-    if (d.kind == RP_ACCESS && take[d.array]) {
-      d.flags |= PF_CLOSED;
-    } else {
-      in += in1 - in0;
-      ex += ex1 - ex0;
-    }
-    in0 = in1;
-    ex0 = ex1;
-    pl.cnt_pre[i + 1] = in;
-    pl.gcnt_pre[i + 1] = ex;
+struct PlanScratch {
+  uint32_t epoch = 0;
+  Combo combos[256];
+  std::vector<ArrayScratch> arrays;
+};
+thread_local PlanScratch t_scratch;
+
+void mark_bins(ArrayScratch& a, uint64_t wa, uint64_t wb) {   // words [wa, wb] inside [0, N)
+  uint32_t j = (uint32_t)(a.sh >= 0 ? wa >> a.sh : wa / a.bw);
+  const uint32_t e = (uint32_t)(a.sh >= 0 ? wb >> a.sh : wb / a.bw);
+  for (; j <= e; j = (j | 63) + 1) {
+    uint64_t m = ~0ull << (j & 63);
+    if ((j | 63) > e) m &= ~0ull >> (63 - (e & 63));
+    a.bins[j >> 6] |= m;
   }
 }
 
+// The first bin at or after j that is marked (or not), nb if there is none.
+uint32_t next_bin(const ArrayScratch& a, uint32_t j, uint32_t nb, bool marked) {
+  while (j < nb) {
+    const uint64_t w = (marked ? a.bins[j >> 6] : ~a.bins[j >> 6]) >> (j & 63);
+    if (w) return std::min<uint32_t>(nb, j + (uint32_t)__builtin_ctzll(w));
+    j = (j | 63) + 1;
+  }
+  return nb;
+}
+
+// Rotation and span of an array of N words whose marked bins are known.
+void rotation_of(const ArrayScratch& a, uint64_t N, uint64_t& off, uint64_t& span) {
+  off = 0;
+  span = N;
+  if (a.full) return;
+  if (!a.used) {
+    span = 1;                                        // no access touches this array
+    return;
+  }
+  const uint64_t bw = a.bw;
+  const uint32_t nb = (uint32_t)((N + bw - 1) / bw);     // bins inside [0, N)
+  // longest circular run of unmarked bins: the runs inside [0, nb), and the
+  // one that wraps (the unmarked tail joined to the unmarked head)
+  const uint32_t head = next_bin(a, 0, nb, true);
+  if (head == nb) {
+    span = 1;
+    return;
+  }
+  uint32_t best_len = 0, best_end = 0, tail = 0;
+  for (uint32_t j = 0; j < nb;) {
+    const uint32_t z = next_bin(a, j, nb, false);
+    const uint32_t o = next_bin(a, z, nb, true);
+    if (o - z > best_len) {
+      best_len = o - z;
+      best_end = o == nb ? 0 : o;                    // first bin after the run
+    }
+    if (o == nb) tail = o - z;
+    j = o;
+  }
+  if (head + tail > best_len) {                      // the wrapping run
+    best_len = head + tail;
+    best_end = head;
+  }
+  if (best_len == 0) return;
+  // words of the gap: bins best_end - best_len .. best_end - 1 (mod nb);
+  // only the last bin of the circle can be narrower than bw
+  const uint64_t last_w = N - (uint64_t)(nb - 1) * bw;
+  const uint32_t first = best_end >= best_len ? best_end - best_len : best_end + nb - best_len;
+  const bool has_last = first + best_len > nb || first + best_len == nb;
+  const uint64_t gap = (uint64_t)(best_len - (has_last ? 1 : 0)) * bw + (has_last ? last_w : 0);
+  const uint64_t next = (uint64_t)best_end * bw;     // first word after the gap
+  off = (N - next % N) % N;
+  span = N - gap;
+}
+
+// Whether the closed form's bound takes the array (see above).
+bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B) {
+  if (a.n == 0 || a.span >= MAX_SPAN || a.bspan >= MAX_SPAN) return false;
+  const double W = words, w = 2.0 * (double)a.span, wraps = 1 + std::floor(w / W);
+  const double bw = 2.0 * (double)a.bspan;
+  const bool cross = global && B > 1;
+  double t0 = 1, t1 = cross ? 1 : 0;   // tests of a pair: same block, different blocks
+  if (a.many) {                        // whatever the steps are
+    t0 = B;
+    if (cross) t1 = std::min(bw + 1, (double)B * B);
+  }
+  for (int u = 0; u < a.nc && !a.many; u++) {
+    for (int v = 0; v <= u; v++) {
+      const auto &p = a.c[u], &q = a.c[v];
+      const double lcm = p.bm == q.bm ? p.bm : (double)p.bm * q.bm / gcd_of<uint32_t>(p.bm, q.bm);
+      if (lcm < B) {
+        const int64_t db = step_mod((int64_t)p.b - q.b, words);
+        t0 = std::max(t0, scan_trips(std::floor(B / lcm) + 1,
+                                     step_mod(db * (int64_t)lcm, words), w, W));
+      }
+      if (cross) {
+        const double sp = std::abs((double)p.S), sq = std::abs((double)q.S);
+        const double g = gcd_of<int64_t>((int64_t)sp, (int64_t)sq);
+        const double n = g > 0 ? (sp * (p.Z - 1.0) + sq * (q.Z - 1.0)) / g + 1 : 1;
+        if (n <= (double)p.Z * q.Z) t1 = std::max(t1, scan_trips(n, g, w, W));
+        else t1 = std::max(t1, p.Z <= q.Z ? p.Z * scan_trips(q.Z, q.S, w, W)
+                                          : q.Z * scan_trips(p.Z, p.S, w, W));
+      }
+    }
+  }
+  const double n = (double)a.n, rec = (double)a.intra * B + (double)a.inter;
+  const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
+  const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
+  return work <= RECORDS_FREE + rec && serial <= SERIAL_FREE + rec / SERIAL_RECORDS;
+}
+
+bool divides(uint32_t words, int32_t a) {                // a = 0 mod words
+  return (words & (words - 1)) == 0 ? ((int64_t)a & ((int64_t)words - 1)) == 0
+                                    : (int64_t)a % (int64_t)words == 0;
+}
+
+// Records of an access point (the reductions are listed in common.h): per
+// block of the same-block log, and in the cross-block log.
+void records_of(uint32_t cnt, uint64_t nblk, bool tconst, bool bconst, bool cross,
+                uint64_t& intra, uint64_t& inter) {
+  intra = tconst ? std::min<uint64_t>(cnt, 2) : cnt;
+  inter = 0;
+  if (cross)
+    inter = (tconst ? std::min<uint64_t>(cnt, 1) : cnt) *
+            (bconst ? std::min<uint64_t>(nblk, 2) : nblk);
+}
+
+}  // namespace
+
 void make_plan(const rp_kernel* k, Plan& pl) {
+  pl.k = k;
   pl.P = k->n_points;
   pl.S = k->n_slots;
   pl.B = k->blocks;
   pl.T = k->threads;
-  uint64_t maxw = 1;
-  for (uint32_t a = 0; a < k->n_arrays; a++) maxw = std::max<uint64_t>(maxw, k->arrays[a].words);
   bool bguard = false;
-  if (k->block_guards)
-    for (uint32_t g = 0; g < k->n_guards; g++) bguard |= k->block_guards[g].m > 1;
+  pl.guards.resize(k->n_guards);
+  for (uint32_t g = 0; g < k->n_guards; g++) {
+    // threads t < T with t % m == r, blocks likewise
+    const rp_guard& t = k->guards[g];
+    PlanGuard& o = pl.guards[g];
+    o.cnt = t.r < pl.T ? (pl.T - 1 - t.r) / t.m + 1 : 0;
+    o.bm = 1;
+    o.br = 0;
+    o.nblk = pl.B;
+    if (k->block_guards) {
+      o.bm = k->block_guards[g].m;
+      o.br = k->block_guards[g].r;
+      bguard |= o.bm > 1;
+      o.nblk = o.br < pl.B ? (pl.B - 1 - o.br) / o.bm + 1 : 0;
+    }
+  }
   // padding records of the same-block log (blocks that do not execute a
   // point) use array id n_arrays
   pl.pad_array = bguard ? k->n_arrays : 0;
   pl.abits = bits_for(k->n_arrays ? k->n_arrays - 1 + bguard : 0);
-  pl.nbits = bits_for(maxw - 1);
   pl.bbits = bits_for(pl.B - 1);
   pl.pbits = bits_for(pl.P ? pl.P - 1 : 0);
   pl.tbits = bits_for(pl.T - 1);
   pl.key_shift = pl.tbits + pl.bbits + pl.pbits;
-  pl.key_bits = pl.abits + pl.nbits;
-  pl.pts.assign(pl.P, DPoint{});
-  pl.wbits.assign((pl.P + 63) / 64, 0);
-  pl.bits_any.assign(pl.P, 0);
-  pl.bits_grid.assign(pl.P, 0);
-  pl.cnt_pre.assign(pl.P + 1, 0);
-  pl.gcnt_pre.assign(pl.P + 1, 0);
   pl.div_if_enabled = 0;
   pl.accesses = 0;
+  PlanScratch& sc = t_scratch;
+  if (++sc.epoch == 0) {                     // (wrapped: forget every combination)
+    for (Combo& c : sc.combos) c.epoch = 0;
+    sc.epoch = 1;
+  }
+  sc.arrays.assign(k->n_arrays, ArrayScratch{});
+  for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
+    // words per bin, as a shift when it is a power of two (the usual case: no
+    // division per access)
+    const uint64_t N = k->arrays[arr].words;
+    ArrayScratch& a = sc.arrays[arr];
+    a.bw = (N + CW_BINS - 1) / CW_BINS;
+    if ((N & (N - 1)) == 0 && (a.bw & (a.bw - 1)) == 0) a.sh = __builtin_ctzll(a.bw);
+  }
   for (uint32_t i = 0; i < pl.P; i++) {
     const rp_point& p = k->points[i];
-    DPoint& d = pl.pts[i];
-    d.kind = p.kind;
-    d.flags = 0;
-    d.cnt = 0;
-    d.bm = 1;
-    d.br = 0;
-    uint64_t nblk = pl.B;           // blocks executing the point
-    if (p.kind != RP_NOP) {
-      const rp_guard& g = k->guards[p.guard];
-      d.m = g.m;
-      d.r = g.r;
-      // threads t < T with t % m == r
-      d.cnt = g.r < pl.T ? (pl.T - 1 - g.r) / g.m + 1 : 0;
-      if (k->block_guards) {
-        d.bm = k->block_guards[p.guard].m;
-        d.br = k->block_guards[p.guard].r;
-        nblk = d.br < pl.B ? (pl.B - 1 - d.br) / d.bm + 1 : 0;
-      }
-    }
-    if (p.kind == RP_ACCESS) {
-      const rp_array& a = k->arrays[p.array];
-      d.a = p.a; d.b = p.b; d.c = p.c;
-      d.words = a.words;
-      d.array = p.array;
-      if (p.is_write) {
-        d.flags |= PF_WRITE;
-        pl.wbits[i >> 6] |= 1ull << (i & 63);
-      }
-      if (a.space == RP_GLOBAL) d.flags |= PF_GLOBAL;
-      if ((a.words & (a.words - 1)) == 0) d.flags |= PF_POW2;
-      // a, b multiples of the array size (a mask test for power-of-two sizes)
-      const int64_t nw = (int64_t)a.words;
-      const bool p2 = (a.words & (a.words - 1)) == 0;
-      if (p2 ? (((int64_t)p.a & (nw - 1)) == 0) : ((int64_t)p.a % nw == 0)) d.flags |= PF_TCONST;
-      if (p2 ? (((int64_t)p.b & (nw - 1)) == 0) : ((int64_t)p.b % nw == 0)) d.flags |= PF_BCONST;
-      pl.accesses += (uint64_t)d.cnt * nblk;
-    }
+    if (p.kind == RP_NOP) continue;
+    const PlanGuard& g = pl.guards[p.guard];
     if (p.kind == RP_BARRIER) {
-      pl.bits_any[i] = 1ull << p.slot;
-      if (k->slots[p.slot].level == RP_GRID) pl.bits_grid[i] = 1ull << p.slot;
       // a block barrier must be reached by all threads of each block that
       // reaches it, a grid barrier by all threads of the grid
-      const uint64_t reach = (uint64_t)d.cnt * nblk;
+      const uint64_t reach = (uint64_t)g.cnt * g.nblk;
       const bool div = k->slots[p.slot].level == RP_GRID
                            ? reach > 0 && reach < (uint64_t)pl.B * pl.T
-                           : nblk > 0 && d.cnt > 0 && d.cnt < pl.T;
+                           : g.nblk > 0 && g.cnt > 0 && g.cnt < pl.T;
       if (div) pl.div_if_enabled |= 1ull << p.slot;
+      continue;
     }
-    // records emitted per point (the reductions are listed in common.h)
-    uint64_t intra = 0, inter = 0;
-    if (p.kind == RP_ACCESS) {
-      const bool tc = d.flags & PF_TCONST;
-      intra = tc ? std::min<uint64_t>(d.cnt, 2) : d.cnt;
-      if ((d.flags & PF_GLOBAL) && pl.B > 1) {
-        const uint64_t per_block = tc ? std::min<uint64_t>(d.cnt, 1) : d.cnt;
-        const uint64_t blocks = (d.flags & PF_BCONST) ? std::min<uint64_t>(nblk, 2) : nblk;
-        inter = per_block * blocks;
+    const rp_array& ar = k->arrays[p.array];
+    ArrayScratch& a = sc.arrays[p.array];
+    Combo& c = sc.combos[((uint32_t)p.array * 31u + (uint32_t)p.guard * 7u + (uint32_t)p.a * 5u +
+                          (uint32_t)p.b) & 255u];
+    if (!(c.epoch == sc.epoch && c.array == p.array && c.guard == p.guard && c.a == p.a &&
+          c.b == p.b)) {
+      c.epoch = sc.epoch;
+      c.array = p.array;
+      c.guard = p.guard;
+      c.a = p.a;
+      c.b = p.b;
+      records_of(g.cnt, g.nblk, divides(ar.words, p.a), divides(ar.words, p.b),
+                 ar.space == RP_GLOBAL && pl.B > 1, c.intra, c.inter);
+      c.runs = g.cnt != 0 && g.nblk != 0;
+      c.arc = false;
+      if (c.runs) {
+        const rp_guard& t = k->guards[p.guard];
+        int64_t tlo, thi, blo, bhi;
+        c.arc = ar.words <= (1ull << 31) && lin_range(p.a, t.r, t.m, g.cnt, tlo, thi) &&
+                lin_range(p.b, g.br, g.bm, g.nblk, blo, bhi) &&
+                !__builtin_add_overflow(tlo, blo, &c.lo) && !__builtin_add_overflow(thi, bhi, &c.hi);
+        const Access s = make_access(p.a, p.b, 0, ar.words, t.m, t.r, g.cnt, g.bm, g.br, pl.B);
+        a.span = std::max<int64_t>(a.span, abs_of<int64_t>(s.A) * (int64_t)(s.X - 1));
+        a.bspan = std::max<int64_t>(a.bspan, abs_of<int64_t>(s.S) * (int64_t)(s.Z - 1));
+        int q = 0;
+        while (q < a.nc && !(a.c[q].b == s.b && a.c[q].bm == s.bm && a.c[q].br == s.br)) q++;
+        if (q == a.nc) {
+          if (a.nc == ArrayScratch::MAXC) a.many = true;
+          else a.c[a.nc++] = {s.b, s.S, s.bm, s.br, s.Z};
+        }
       }
     }
-    pl.cnt_pre[i + 1] = pl.cnt_pre[i] + intra;
-    pl.gcnt_pre[i + 1] = pl.gcnt_pre[i] + inter;
+    pl.accesses += (uint64_t)g.cnt * g.nblk;
+    a.n++;
+    a.intra += c.intra;
+    a.inter += c.inter;
+    if (!c.runs || a.full) continue;
+    a.used = true;
+    // the arc of the point's words (rotated offsets must fit the int32 c)
+    int64_t lo, hi;
+    const uint64_t N = ar.words;
+    if (!c.arc || __builtin_add_overflow(c.lo, (int64_t)p.c, &lo) ||
+        __builtin_add_overflow(c.hi, (int64_t)p.c, &hi) || (uint64_t)(hi - lo) + 1 >= N) {
+      a.full = true;
+      continue;
+    }
+    const uint64_t s0 = word_mod(lo, (uint32_t)N), e0 = s0 + (uint64_t)(hi - lo);   // may pass N
+    if (e0 < N) {
+      mark_bins(a, s0, e0);
+    } else {
+      mark_bins(a, s0, N - 1);
+      mark_bins(a, 0, e0 - N);
+    }
   }
-  compact_words(k, pl);
-  pl.weights.assign(pl.S, 0);
+  uint64_t span_max = 1, intra = 0, inter = 0, log_intra = 0, log_inter = 0;
+  pl.arrays.resize(k->n_arrays);
+  pl.any_closed = false;
+  pl.closed_small = true;
+  for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
+    const ArrayScratch& a = sc.arrays[arr];
+    const uint32_t words = k->arrays[arr].words;
+    PlanArray& o = pl.arrays[arr];
+    uint64_t off, span;
+    rotation_of(a, words, off, span);
+    span_max = std::max(span_max, span);
+    o.off = (uint32_t)off;
+    o.closed = g_race_route == 0 && takes_closed(a, words, k->arrays[arr].space == RP_GLOBAL, pl.B);
+    intra += a.intra;
+    inter += a.inter;
+    if (o.closed) {
+      pl.any_closed = true;
+      if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE ||
+          pl.T > SMALL_SIZE || pl.B > SMALL_SIZE)
+        pl.closed_small = false;
+    } else {
+      log_intra += a.intra;
+      log_inter += a.inter;
+    }
+  }
+  pl.nbits = bits_for(span_max - 1);
+  pl.key_bits = pl.abits + pl.nbits;
+  pl.rblk = log_intra;
+  pl.n_intra = intra * pl.B;
+  pl.n_inter = inter;
+  pl.log_intra = log_intra * pl.B;
+  pl.log_inter = log_inter;
   pl.grid_slots = pl.pre_slots = 0;
   for (uint32_t s = 0; s < pl.S; s++) {
-    pl.weights[s] = k->slots[s].weight;
     if (k->slots[s].level == RP_GRID) pl.grid_slots |= 1ull << s;
     if (k->slots[s].preexisting) pl.pre_slots |= 1ull << s;
   }
-  pl.n_intra = pl.cnt_pre[pl.P] * pl.B;
-  pl.n_inter = pl.gcnt_pre[pl.P];
-  if (g_race_route == 0) mark_closed(k, pl);
+}
+
+void fill_points(const Plan& pl, DPoint* pts) {
+  const rp_kernel* k = pl.k;
+  for (uint32_t i = 0; i < pl.P; i++) {
+    const rp_point& p = k->points[i];
+    DPoint d{};
+    d.kind = p.kind;
+    d.bm = 1;
+    if (p.kind == RP_BARRIER) {
+      d.array = p.slot;
+      if (k->slots[p.slot].level == RP_GRID) d.flags = PF_GRID;
+    } else if (p.kind == RP_ACCESS) {
+      const PlanGuard& g = pl.guards[p.guard];
+      const PlanArray& pa = pl.arrays[p.array];
+      const rp_array& a = k->arrays[p.array];
+      d.a = p.a;
+      d.b = p.b;
+      d.c = p.c;
+      d.words = a.words;
+      d.m = k->guards[p.guard].m;
+      d.r = k->guards[p.guard].r;
+      d.cnt = g.cnt;
+      d.bm = g.bm;
+      d.br = g.br;
+      d.array = p.array;
+      uint8_t f = (p.is_write ? PF_WRITE : 0) | (a.space == RP_GLOBAL ? PF_GLOBAL : 0);
+      if (pa.closed) {
+        f |= PF_CLOSED;
+      } else {
+        if ((a.words & (a.words - 1)) == 0) f |= PF_POW2;
+        if (divides(a.words, p.a)) f |= PF_TCONST;
+        if (divides(a.words, p.b)) f |= PF_BCONST;
+        if (pa.off != 0)
+          d.c = (int32_t)(((uint64_t)word_mod(p.c, a.words) + pa.off) % a.words);
+      }
+      d.flags = f;
+    }
+    pts[i] = d;
+  }
+}
+
+void fill_prefixes(const Plan& pl, const DPoint* pts, uint64_t* cnt_pre, uint64_t* gcnt_pre) {
+  uint64_t in = 0, ex = 0;
+  for (uint32_t i = 0; i < pl.P; i++) {
+    cnt_pre[i] = in;
+    gcnt_pre[i] = ex;
+    const DPoint& d = pts[i];
+    if (d.kind != RP_ACCESS || (d.flags & PF_CLOSED)) continue;
+    uint64_t a, b;
+    records_of(d.cnt, pl.guards[pl.k->points[i].guard].nblk, d.flags & PF_TCONST,
+               d.flags & PF_BCONST, (d.flags & PF_GLOBAL) && pl.B > 1, a, b);
+    in += a;
+    ex += b;
+  }
+  cnt_pre[pl.P] = in;
+  gcnt_pre[pl.P] = ex;
 }
 
 // Automatic digit width: the fewest passes of at most 10 bits, each as

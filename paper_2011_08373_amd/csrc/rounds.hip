@@ -84,14 +84,14 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
   uint64_t cnt = 0;
   for (uint32_t q = 0; q < per; q++) {
     const uint32_t i = tid * per + q;
-    if (i < P) cnt += (J.bits_any[i] ? 1ull : 0ull) + (J.bits_grid[i] ? 1ull << 32 : 0ull);
+    if (i < P) cnt += (slot_any(J.pts[i]) ? 1ull : 0ull) + (slot_grid(J.pts[i]) ? 1ull << 32 : 0ull);
   }
   uint64_t nocc;
   uint64_t at = block_excl_scan(cnt, sm, &nocc);
   for (uint32_t q = 0; q < per; q++) {
     const uint32_t i = tid * per + q;
     if (i >= P) break;
-    const uint64_t a = J.bits_any[i], g = J.bits_grid[i];
+    const uint64_t a = slot_any(J.pts[i]), g = slot_grid(J.pts[i]);
     const uint32_t ta = (uint32_t)at, tg = (uint32_t)(at >> 32);
     L.next[0][i] = (uint16_t)ta;
     L.next[1][i] = (uint16_t)tg;
@@ -280,9 +280,12 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   if (tid < 64) s_w[tid] = tid < J.S ? J.weights[tid] : 0;
   __syncthreads();
   const bool one = J.policy == 1 && !(flags & RD_LEARN);
+  // (a lone Solve reads its clauses where they are)
+  if (flags & RD_BUILD)
+    for (uint32_t q = tid; q < st->n_phi; q += RD_BLOCK) J.phi[q] = J.phi0[q];
   if (flags & RD_BUILD) build_tables(J, st, J.policy == 1, L.b, sm);
   if (flags & RD_SOLVE) {
-    solve_body(J, st, J.phi, st->n_phi, s_w, L.s);
+    solve_body(J, st, flags & RD_BUILD ? J.phi : J.phi0, st->n_phi, s_w, L.s);
     __syncthreads();
   }
   const uint64_t* F = full_of(J);
