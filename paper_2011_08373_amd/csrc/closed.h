@@ -47,8 +47,16 @@ RP_HD uint32_t word_mod(int64_t v, uint32_t W) {
   if ((W & (W - 1)) == 0) return (uint32_t)(uint64_t)v & (W - 1);
   if (v >= 0 && v < (int64_t)W) return (uint32_t)v;
   if (v < 0 && v >= -(int64_t)W) return (uint32_t)(v + (int64_t)W);
-  const int64_t r = v % (int64_t)W;
-  return (uint32_t)(r < 0 ? r + (int64_t)W : r);
+  // the quotient in double precision, twice: the first leaves a few thousand W
+  // at most (|v| < 2^63 and the quotient is right to 52 bits), the second one
+  // W too many or too few.  (A 64-bit integer division is 100 instructions
+  // and a dozen registers on the device, at every place that reduces.)
+  const double inv = 1.0 / (double)W;
+  int64_t r = (int64_t)((uint64_t)v - (uint64_t)(int64_t)((double)v * inv) * (uint64_t)W);
+  r -= (int64_t)((double)r * inv) * (int64_t)W;
+  if (r < 0) r += (int64_t)W;
+  if (r >= (int64_t)W) r -= (int64_t)W;
+  return (uint32_t)r;
 }
 RP_HD int32_t step_mod(int64_t v, uint32_t W) {
   const uint32_t r = word_mod(v, W);
@@ -77,6 +85,13 @@ RP_HD Access make_access(int32_t a, int32_t b, int32_t c, uint32_t W, uint32_t m
 
 template <class I>
 RP_HD I abs_of(I v) { return v < 0 ? -v : v; }
+
+template <class I>
+struct Unsigned;
+template <>
+struct Unsigned<int32_t> { using type = uint32_t; };
+template <>
+struct Unsigned<int64_t> { using type = uint64_t; };
 
 template <class I>
 RP_HD I gcd_of(I x, I y) {     // x, y >= 0
@@ -218,31 +233,33 @@ struct PairEq {
 // Some z in [0, n) with ok(z) and a solution for D = D0 + beta*z mod W, where
 // v0 = (D0 - lo) mod W.  Values of D outside the interval are stepped over.
 template <class I, class F>
-RP_HD bool closed_scan(const PairEq<I>& q, uint32_t W, uint32_t v0, int32_t beta, uint64_t n,
+RP_HD bool closed_scan(const PairEq<I>& q, uint32_t W, uint32_t v0, int32_t beta, uint64_t terms,
                        F ok) {
-  const int64_t w = (int64_t)q.w, Wl = (int64_t)W;
-  int64_t v = v0;
-  uint64_t z = 0;
+  using U = typename Unsigned<I>::type;
+  const I w = q.w, Wl = (I)W;
+  const U n = (U)terms;
+  I v = (I)v0;
+  U z = 0;
   if (beta == 0 && v > w) return false;
   while (z < n) {
     if (v <= w) {
       if (ok(z))
-        for (int64_t e = v; e <= w; e += Wl)
-          if (q.hit(q.lo + (I)e)) return true;
+        for (I e = v; e <= w; e += Wl)
+          if (q.hit(q.lo + e)) return true;
       z++;
-      v += beta;
+      v += (I)beta;
       if (v >= Wl) v -= Wl;
       if (v < 0) v += Wl;
     } else if (beta > 0) {
       // to the first value past the top of the range
       const uint32_t s = (uint32_t)(Wl - v - 1) / (uint32_t)beta + 1;
       z += s;
-      v += (int64_t)s * beta - Wl;
+      v = (I)((U)v + (U)s * (U)beta - (U)Wl);       // in [0, beta)
     } else {
       const uint32_t d = (uint32_t)(-(int64_t)beta);
       const uint32_t s = (uint32_t)(v - w - 1) / d + 1;
       z += s;
-      v -= (int64_t)s * d;
+      v = (I)((U)v - (U)s * (U)d);                  // in (w - d, w]
       if (v < 0) v += Wl;
     }
   }
@@ -299,7 +316,7 @@ RP_HD bool pair_same_block(const Access& p, const Access& q, uint32_t B) {
   int32_t dw = 0, beta = 0;
   if (db != 0) {
     const int32_t d = step_mod(db, W);
-    dw = step_mod((int64_t)d * (int64_t)k, W);
+    if (k != 0) dw = step_mod((int64_t)d * (int64_t)k, W);
     if (n > 1) beta = step_mod((int64_t)d * (int64_t)step, W);
   }
   const uint32_t v0 =
@@ -312,8 +329,8 @@ RP_HD bool pair_same_block(const Access& p, const Access& q, uint32_t B) {
 // difference is itself such an equation, S_q*z - S_p*y = u over the executing
 // blocks with different block ids: u runs over the multiples of its gcd, or,
 // where those are more than the pairs of blocks, the pairs are taken one by
-// one (a few blocks with unrelated strides).
-template <class I>
+// one (a few blocks with unrelated strides; FEW_TERMS: never so).
+template <class I, bool FEW_TERMS = false>
 RP_HD bool pair_cross_block(const Access& p, const Access& q) {
   const uint32_t W = p.W;
   const PairEq<I> eq(threads_of(p), threads_of(q), false);
@@ -323,7 +340,7 @@ RP_HD bool pair_cross_block(const Access& p, const Access& q) {
                      (q.br ? (int64_t)step_mod((int64_t)q.b * (int64_t)q.br, W) : 0) -
                      (p.br ? (int64_t)step_mod((int64_t)p.b * (int64_t)p.br, W) : 0);
   const uint64_t n = bl.g == 0 ? 1 : (uint64_t)(bl.w / bl.g) + 1;
-  if (n <= (uint64_t)p.Z * q.Z)
+  if (FEW_TERMS || n <= (uint64_t)p.Z * q.Z)
     return closed_scan(eq, W, word_mod(d0 + (int64_t)bl.lo - (int64_t)eq.lo, W),
                        bl.g == 0 ? 0 : step_mod((int64_t)bl.g, W), n,
                        [&](uint64_t u) { return bl.hit(bl.lo + bl.g * (I)u); });

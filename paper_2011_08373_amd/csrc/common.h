@@ -62,8 +62,13 @@ constexpr int MAX_SORT_PASSES = 8;
 constexpr uint8_t PF_WRITE = 1, PF_GLOBAL = 2, PF_POW2 = 4, PF_TCONST = 8, PF_BCONST = 16,
                   PF_CLOSED = 32, PF_GRID = 64;
 
+// Forms of the closed-form kernels, from the narrowest: 32-bit arithmetic with
+// no block conditions and few terms over the blocks, 32-bit, any.
+constexpr int FORM_PLAIN = 0, FORM_SMALL = 1, FORM_WIDE = 2;
+
 struct DPoint {          // 40 B, one per program point
-  int32_t a, b, c;
+  int32_t a, b, c;       // of a PF_CLOSED point reduced: step per executing thread, step
+                         // per block, word of the first executing thread
   uint32_t words;        // array size (words)
   uint32_t m, r;         // guard: tid % m == r
   uint32_t cnt;          // threads of one block executing the point
@@ -91,7 +96,8 @@ struct JobState {        // device-resident per-job state; the host reads it
   uint32_t t_clause;     // ticks of the device clock in GenerateClause (timing level 2)
   uint32_t err;          // device-side error code (0 = none)
   uint32_t max_rounds;   // 0 = unlimited
-  uint32_t n_full;       // clauses of the job's table of all race clauses
+  uint32_t n_full;       // clauses of the job's table of all race clauses, and << 16 its
+                         // racing rows (both at most 2 * MAX_POINTS)
   uint32_t t_check;      // ticks in Verify
   uint32_t phase;        // PH_*: which Solve the next call makes
   uint32_t t_solve;      // ticks in Solve

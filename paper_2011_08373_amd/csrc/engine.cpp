@@ -435,10 +435,11 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   // directly, under its assignment)
   if (o.op != OP_CHECK && o.op != OP_SOLVE && !(o.op == OP_FIRST && L.ssegs.empty())) {
     uint32_t maxP = 1;
-    bool lo32 = true, any_closed = false, closed_small = true;
+    bool lo32 = true, any_closed = false;
+    int form = FORM_PLAIN;
     for (const JobInput& j : jobs) {
       any_closed = any_closed || j.plan->any_closed;
-      closed_small = closed_small && j.plan->closed_small;
+      form = std::max(form, j.plan->closed_form);
       maxP = std::max(maxP, j.plan->P);
       lo32 = lo32 && j.plan->tbits < 32 && j.plan->bbits < 32 &&
              j.plan->tbits + j.plan->bbits + j.plan->pbits <= 32;
@@ -453,8 +454,12 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
       tm.mark(T_SUMMARY);
       HIPCHK(launch_save_j0(djobs, (uint32_t)N, s));
     }
-    if (L.ssegs.empty() || any_closed) {
-      HIPCHK(launch_first_closed(djobs, (uint32_t)N, maxP, closed_small, call, s));
+    // (the rounds kernel does the jobs of few points itself)
+    uint32_t large = 0;                // jobs up to the last one it is for
+    for (size_t j = 0; j < N; j++)
+      if (jobs[j].plan->P > PACKED_POINTS || !L.ssegs.empty()) large = (uint32_t)j + 1;
+    if (large && (L.ssegs.empty() || any_closed)) {
+      HIPCHK(launch_first_closed(djobs, large, maxP, form, call, s));
       if (L.ssegs.empty()) tm.mark(T_SUMPRE);
     }
   }
@@ -492,7 +497,13 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
   // left as they are by the solver
   bool any_units = false;
   for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
-  HIPCHK(launch_rounds((const Job*)(d + L.o_jobs), (uint32_t)jobs.size(),
+  uint32_t maxP = 0;
+  int form = FORM_PLAIN;
+  for (const JobInput& j : jobs) {
+    maxP = std::max(maxP, j.plan->P);
+    form = std::max(form, j.plan->closed_form);
+  }
+  HIPCHK(launch_rounds((const Job*)(d + L.o_jobs), (uint32_t)jobs.size(), form,
                        RD_BUILD | (any_units ? RD_SOLVE : 0), 0, CallBlock{}, s));
   out.resize(jobs.size());
   for (size_t j = 0; j < jobs.size(); j++)
@@ -501,7 +512,7 @@ int engine_prepare_group(const std::vector<JobInput>& jobs, void* region, size_t
 }
 
 int engine_round(const Job* djobs, uint32_t njobs, hipStream_t s) {
-  HIPCHK(launch_rounds(djobs, njobs, RD_LOOP, 1, CallBlock{}, s));
+  HIPCHK(launch_rounds(djobs, njobs, FORM_SMALL, RD_LOOP, 1, CallBlock{}, s));
   return RP_OK;
 }
 
@@ -576,7 +587,12 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   const int nseg = (int)L.ssegs.size();
   uint32_t* dtiles = derr + 9;     // conf tiles of the all-pairs scan
   uint32_t maxP = 1;
-  for (const JobInput& j : jobs) maxP = std::max(maxP, j.plan->P);
+  int form = FORM_PLAIN;
+  for (const JobInput& j : jobs) {
+    maxP = std::max(maxP, j.plan->P);
+    form = std::max(form, j.plan->closed_form);
+  }
+  const int build = RD_BUILD | (nseg == 0 && maxP <= PACKED_POINTS ? RD_FIRST : 0);
   const JobState* hst = page ? &page->st : (const JobState*)rb;
   const uint32_t* herr = page ? page->words : (const uint32_t*)(rb + words_at);
   uint64_t* ptraj = page ? page->traj : (uint64_t*)(rb + words_at + 64);
@@ -604,33 +620,33 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
     }
     for (size_t j = 0; j < N; j++)
       if (!nseg || jobs[j].plan->any_closed)
-        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, call, s));
+        HIPCHK(launch_all_closed(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_form, call, s));
     tm.mark(T_CHECK, nseg ? 2 : 1);
     for (size_t j = 0; j < N; j++)
       HIPCHK(launch_pairs(djobs + j, jobs[j].plan->P, !nseg, (rp_pair*)(d + L.o_pairs[j]),
                           (uint64_t*)(d + L.o_ptotal[j]), call, s));
     tm.mark(T_CLAUSE);
   } else if (o.op == OP_SOLVE) {
-    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_SOLVE, 0, call, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, form, RD_SOLVE, 0, call, s));
     tm.mark(T_SOLVE);
   } else if (o.op == OP_FIRST) {
     if (nseg) {
       HIPCHK(launch_ivl(djobs, (uint32_t)N, IVL_RESOLVE, s));
     } else {
       for (size_t j = 0; j < N; j++)
-        HIPCHK(launch_first_under(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_small, call, s));
+        HIPCHK(launch_first_under(djobs + j, jobs[j].plan->P, jobs[j].plan->closed_form, call, s));
     }
     tm.mark(T_CHECK);
   } else if (o.op == OP_CLAUSES) {
-    HIPCHK(launch_rounds(djobs, (uint32_t)N, RD_BUILD | RD_LEARN, 0, call, s));
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, form, build | RD_LEARN, 0, call, s));
     tm.mark(T_CLAUSE);
   } else {
     // the first Solve of Alg. 1: with no option units phi is empty and its
     // answer is x = 0 (weight 0), which the job states already hold
     bool any_units = false;
     for (const JobInput& j : jobs) any_units |= !j.phi0.empty();
-    HIPCHK(launch_rounds(djobs, (uint32_t)N,
-                         RD_BUILD | RD_LOOP | (any_units ? RD_SOLVE : 0) |
+    HIPCHK(launch_rounds(djobs, (uint32_t)N, form,
+                         build | RD_LOOP | (any_units ? RD_SOLVE : 0) |
                              (tm.level >= 2 ? RD_TIMED : 0), 0, call, s));
   }
   tm.mark(T_END);

@@ -55,29 +55,34 @@ hipError_t launch_conf(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t 
 hipError_t launch_j0(const Job* jobs, const ConfSeg* segs, int nseg, uint32_t max_points,
                      bool lo32, const uint32_t* tiles, hipStream_t s);
 // First partners of the PF_CLOSED points, into j0 (every row of a job that has
-// no records).  small: every closed array of every job fits the 32-bit form
-// of closed.h.
-hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, bool small,
+// no records).  form: the narrowest one that every closed array of every job
+// fits (FORM_*).
+hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, int form,
                                const CallBlock& call, hipStream_t s);
 // First partners under its assignment of one job that has no records, into
 // minj; the last kernel of its call.
-hipError_t launch_first_under(const Job* job, uint32_t points, bool small, const CallBlock& call,
+hipError_t launch_first_under(const Job* job, uint32_t points, int form, const CallBlock& call,
                               hipStream_t s);
 // Racing pairs of the PF_CLOSED points of one job under its assignment: bitmap
 // rows, and their counts in minj (every row of a job that
 // has no records).
-hipError_t launch_all_closed(const Job* job, uint32_t points, bool small, const CallBlock& call,
+hipError_t launch_all_closed(const Job* job, uint32_t points, int form, const CallBlock& call,
                              hipStream_t s);
 // The bitmap of one job as a pair list in (level, i, j) order.  counted: the
 // row counts are in minj already.
 hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
                         uint64_t* total, const CallBlock& call, hipStream_t s);
 // The rounds of Alg. 1 on every running job.  RD_BUILD: the job's clause tables
-// from j0 first; RD_SOLVE: one Solve first; RD_LOOP: rounds, at most limit of
+// from j0 first (jobs of at most PACKED_POINTS points with no records work out
+// j0 themselves; RD_FIRST: every job is one, and no first-partner launch has
+// come before); RD_SOLVE: one Solve first; RD_LOOP: rounds, at most limit of
 // them (0: until a verdict); RD_LEARN: Verify and GenerateClause under the
 // job's assignment only; RD_TIMED: the phases' clock ticks into the job state.
-constexpr int RD_BUILD = 1, RD_SOLVE = 2, RD_LOOP = 4, RD_LEARN = 8, RD_TIMED = 16;
-hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int flags, uint32_t limit,
+constexpr int RD_BUILD = 1, RD_SOLVE = 2, RD_LOOP = 4, RD_LEARN = 8, RD_TIMED = 16,
+              RD_FIRST = 32;
+// points of a job whose first partners the rounds kernel works out
+constexpr uint32_t PACKED_POINTS = 128;
+hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int form, int flags, uint32_t limit,
                          const CallBlock& call, hipStream_t s);
 
 }  // namespace rp

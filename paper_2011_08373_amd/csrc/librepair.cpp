@@ -270,13 +270,16 @@ void rotation_of(const ArrayScratch& a, uint64_t N, uint64_t& off, uint64_t& spa
   span = N - gap;
 }
 
-// Whether the closed form's bound takes the array (see above).
-bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B) {
+// Whether the closed form's bound takes the array (see above); form: raised to
+// the one it needs.
+bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B, uint32_t T,
+                  int& form) {
   if (a.n == 0 || a.span >= MAX_SPAN || a.bspan >= MAX_SPAN) return false;
   const double W = words, w = 2.0 * (double)a.span, wraps = 1 + std::floor(w / W);
   const double bw = 2.0 * (double)a.bspan;
   const bool cross = global && B > 1;
   double t0 = 1, t1 = cross ? 1 : 0;   // tests of a pair: same block, different blocks
+  bool plain = !a.many;
   if (a.many) {                        // whatever the steps are
     t0 = B;
     if (cross) t1 = std::min(bw + 1, (double)B * B);
@@ -284,6 +287,7 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   for (int u = 0; u < a.nc && !a.many; u++) {
     for (int v = 0; v <= u; v++) {
       const auto &p = a.c[u], &q = a.c[v];
+      plain = plain && p.bm == 1 && q.bm == 1;
       const double lcm = p.bm == q.bm ? p.bm : (double)p.bm * q.bm / gcd_of<uint32_t>(p.bm, q.bm);
       if (lcm < B) {
         const int64_t db = step_mod((int64_t)p.b - q.b, words);
@@ -297,13 +301,20 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
         if (n <= (double)p.Z * q.Z) t1 = std::max(t1, scan_trips(n, g, w, W));
         else t1 = std::max(t1, p.Z <= q.Z ? p.Z * scan_trips(q.Z, q.S, w, W)
                                           : q.Z * scan_trips(p.Z, p.S, w, W));
+        plain = plain && n <= (double)p.Z * q.Z;
       }
     }
   }
   const double n = (double)a.n, rec = (double)a.intra * B + (double)a.inter;
   const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
   const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
-  return work <= RECORDS_FREE + rec && serial <= SERIAL_FREE + rec / SERIAL_RECORDS;
+  if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) return false;
+  if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE || T > SMALL_SIZE ||
+      B > SMALL_SIZE)
+    form = FORM_WIDE;
+  else if (!plain)
+    form = std::max(form, FORM_SMALL);
+  return true;
 }
 
 bool divides(uint32_t words, int32_t a) {                // a = 0 mod words
@@ -442,7 +453,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
   uint64_t span_max = 1, intra = 0, inter = 0, log_intra = 0, log_inter = 0;
   pl.arrays.resize(k->n_arrays);
   pl.any_closed = false;
-  pl.closed_small = true;
+  pl.closed_form = FORM_PLAIN;
   for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
     const ArrayScratch& a = sc.arrays[arr];
     const uint32_t words = k->arrays[arr].words;
@@ -451,14 +462,12 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     rotation_of(a, words, off, span);
     span_max = std::max(span_max, span);
     o.off = (uint32_t)off;
-    o.closed = g_race_route == 0 && takes_closed(a, words, k->arrays[arr].space == RP_GLOBAL, pl.B);
+    o.closed = g_race_route == 0 && takes_closed(a, words, k->arrays[arr].space == RP_GLOBAL, pl.B,
+                                                 pl.T, pl.closed_form);
     intra += a.intra;
     inter += a.inter;
     if (o.closed) {
       pl.any_closed = true;
-      if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE ||
-          pl.T > SMALL_SIZE || pl.B > SMALL_SIZE)
-        pl.closed_small = false;
     } else {
       log_intra += a.intra;
       log_inter += a.inter;
@@ -504,7 +513,17 @@ void fill_points(const Plan& pl, DPoint* pts) {
       d.array = p.array;
       uint8_t f = (p.is_write ? PF_WRITE : 0) | (a.space == RP_GLOBAL ? PF_GLOBAL : 0);
       if (pa.closed) {
+        // the closed form's steps and first word, reduced (closed.h); a point
+        // that executes nowhere is none
         f |= PF_CLOSED;
+        if (g.cnt == 0 || g.nblk == 0) {
+          d.kind = RP_NOP;
+        } else {
+          const Access s = make_access(p.a, p.b, p.c, a.words, d.m, d.r, g.cnt, g.bm, g.br, pl.B);
+          d.a = s.A;
+          d.b = s.b;
+          d.c = (int32_t)s.base;
+        }
       } else {
         if ((a.words & (a.words - 1)) == 0) f |= PF_POW2;
         if (divides(a.words, p.a)) f |= PF_TCONST;

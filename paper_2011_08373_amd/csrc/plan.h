@@ -35,7 +35,7 @@ struct Plan {
   uint64_t log_intra = 0, log_inter = 0;
   uint64_t rblk = 0;                // same-block records per block
   bool any_closed = false;          // some array is decided in closed form
-  bool closed_small = true;         // every such array in 32-bit arithmetic
+  int closed_form = FORM_PLAIN;     // the narrowest form all of these fit
 };
 
 int validate_kernel(const rp_kernel* k);

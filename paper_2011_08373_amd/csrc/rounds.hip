@@ -27,6 +27,7 @@
 // sort and subsumption, Solve, count of running jobs) and a host wait, the
 // rounds of the small planted kernel took 84 us with their waits, of 512
 // instrumented programs 1.9 ms; in one launch 7 us and 0.47 ms.
+#include "closed_rows.h"
 #include "common.h"
 #include "launch.h"
 #include "solve.h"
@@ -47,13 +48,14 @@ struct BuildLds {
 };
 
 union RoundLds {
+  PackedLds<RD_WAVES> p;
   BuildLds b;
   SolveLds s;
 };
 
 // The job's tables behind the first phi_cap clauses of its scratch (which has
 // at least 2 P + 64 clauses of 16 bytes more): F, at most 2 P masks, and the
-// mask of each row.
+// masks of the racing rows.
 __device__ __forceinline__ uint64_t* full_of(const Job& J) { return (uint64_t*)(J.scratch + J.phi_cap); }
 __device__ __forceinline__ uint64_t* rows_of(const Job& J) { return full_of(J) + 2 * (uint64_t)J.P; }
 
@@ -76,7 +78,8 @@ __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t* sm, ui
   return pre + inc - v;
 }
 
-// Builds F (its size into st->n_full) and, if rows, the row masks.
+// Builds F and, if rows, the masks of the racing rows (their sizes into
+// st->n_full, low and high half).
 __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L, uint64_t* sm) {
   const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = tid >> 6, P = J.P;
   const uint32_t per = (P + RD_BLOCK - 1) / RD_BLOCK;
@@ -110,6 +113,7 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
   // with a later start ends no later
   uint32_t m = 0;                          // masks so far
   bool empty = false;
+  uint32_t n_rows = 0;
   uint64_t* const big = (uint64_t*)J.scratch;      // (free until the first Solve)
   for (uint32_t lv = 0; lv < 2; lv++) {
     const uint32_t n = lv ? (uint32_t)(nocc >> 32) : (uint32_t)nocc;
@@ -120,7 +124,15 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
       if (j >= P) continue;
       const uint32_t a = L.next[lv][i], b = L.next[lv][j];
       atomicMin(&L.end[a], b);
-      if (rows) rows_of(J)[(uint64_t)lv * P + i] = mask_of(lv, a, b);
+    }
+    // the racing rows' masks, in the order of their points
+    for (uint32_t b0 = 0; rows && b0 < P; b0 += RD_BLOCK) {
+      const uint32_t i = b0 + tid;
+      const uint32_t j = i < P ? J.j0[(uint64_t)lv * P + i] : NONE32;
+      uint64_t total;
+      const uint32_t at = (uint32_t)block_excl_scan(j < P, sm, &total);
+      if (j < P) rows_of(J)[n_rows + at] = mask_of(lv, L.next[lv][i], L.next[lv][j]);
+      n_rows += (uint32_t)total;
     }
     __syncthreads();
     const uint32_t pt = n / RD_BLOCK + 1;  // starts of this thread, [t0, t1)
@@ -173,7 +185,7 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
   if (any_empty) {
     if (tid == 0) {
       F[0] = 0;
-      st->n_full = 1;
+      st->n_full = 1 | n_rows << 16;
     }
     __syncthreads();
     return;
@@ -203,7 +215,7 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
   }
   uint64_t total;
   (void)block_excl_scan(alive, sm, &total);
-  if (tid == 0) st->n_full = (uint32_t)total;
+  if (tid == 0) st->n_full = (uint32_t)total | n_rows << 16;
   __syncthreads();
 }
 
@@ -262,16 +274,20 @@ __device__ uint32_t learn_one(const Job& J, rp_clause c, uint32_t n, uint32_t* s
   return *s_n;
 }
 
-// flags: RD_BUILD builds the tables; RD_SOLVE makes one Solve first (the option
+// flags: RD_BUILD builds the tables (from j0, which a job of few points works
+// out itself first; RD_FIRST: all jobs are such); RD_SOLVE makes one Solve first (the option
 // units); RD_LEARN generates the clauses under the job's assignment and stops.
 // limit: rounds to run (0: until a verdict).
+template <int FORM>
 __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict__ jobs, int flags,
                                                           uint32_t limit, CallBlock call) {
   __shared__ RoundLds L;
   __shared__ JobState s_st;
   __shared__ uint64_t sm[RD_WAVES];
   __shared__ uint32_t s_row, s_n, s_w[64];
-  stamp_if(call.stamps, flags & RD_BUILD ? STAMP_FIRST : STAMP_BEGIN);
+  // (a call's first kernel, unless first_kernel has come before)
+  const bool begins = !(flags & RD_BUILD) || (flags & RD_FIRST);
+  stamp_if(call.stamps, begins ? STAMP_BEGIN : STAMP_FIRST);
   const Job& J = jobs[blockIdx.x];
   const uint32_t tid = threadIdx.x, P = J.P;
   JobState* st = &s_st;
@@ -283,6 +299,10 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   // (a lone Solve reads its clauses where they are)
   if (flags & RD_BUILD)
     for (uint32_t q = tid; q < st->n_phi; q += RD_BLOCK) J.phi[q] = J.phi0[q];
+  if ((flags & RD_BUILD) && P <= PACKED_POINTS && J.nlog[0] == 0 && J.nlog[1] == 0) {
+    packed_first<FORM, RD_WAVES>(J, L.p, begins && blockIdx.x == 0 ? call.stamps : nullptr);
+    if (begins) stamp_if(call.stamps, STAMP_FIRST);
+  }
   if (flags & RD_BUILD) build_tables(J, st, J.policy == 1, L.b, sm);
   if (flags & RD_SOLVE) {
     solve_body(J, st, flags & RD_BUILD ? J.phi : J.phi0, st->n_phi, s_w, L.s);
@@ -301,7 +321,7 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   for (uint32_t r = 0; loop && st->state == ST_RUN; r++) {
     // ---- Verify
     const uint64_t x = st->x, div = x & J.div_if_enabled;
-    const uint32_t n_full = st->n_full;
+    const uint32_t n_full = st->n_full & 0xFFFFu, n_rows = st->n_full >> 16;
     uint32_t n = st->n_phi;
     if (tid == 0) s_row = NONE32;
     __syncthreads();                       // (everyone has read the state)
@@ -312,8 +332,8 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
     } else if (div == 0) {
       // the smallest racing row, same-block rows first
       const uint64_t* rows = rows_of(J);
-      for (uint32_t q = tid; q < 2 * P && mine == NONE32; q += RD_BLOCK)
-        if (J.j0[q] < P && (rows[q] & x) == 0) mine = q;
+      for (uint32_t q = tid; q < n_rows && mine == NONE32; q += RD_BLOCK)
+        if ((rows[q] & x) == 0) mine = q;
     }
     if (mine != NONE32) atomicMin(&s_row, mine);
     if (tid == 0) {
@@ -377,10 +397,11 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   finish_call(call, st);
 }
 
-hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int flags, uint32_t limit,
+hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int form, int flags, uint32_t limit,
                          const CallBlock& call, hipStream_t s) {
   if (njobs == 0) return hipSuccess;
-  rounds_kernel<<<njobs, RD_BLOCK, 0, s>>>(jobs, flags, limit, call);
+  if (form == FORM_WIDE) rounds_kernel<FORM_WIDE><<<njobs, RD_BLOCK, 0, s>>>(jobs, flags, limit, call);
+  else rounds_kernel<FORM_SMALL><<<njobs, RD_BLOCK, 0, s>>>(jobs, flags, limit, call);
   return hipGetLastError();
 }
 

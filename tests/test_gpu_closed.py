@@ -155,3 +155,46 @@ def test_check_both_ways(L):  # noqa: F811
 def test_check_no_points(L):  # noqa: F811
     km = synth.make_kernel(2, 4, [(8, 1)], [(1, 0)], [], [])
     assert L.check(km, 0)[:4] == O.check(km, 0) and L.check(km, 0)[1] == []
+
+
+@pytest.mark.parametrize("P", [1, 2, 63, 64, 65, 127, 128, 129, 200])
+def test_packed_rows(L, P):  # noqa: F811
+    # around the sizes where a job's rows are packed into the rounds kernel:
+    # repairs alone, in a batch with larger kernels, and through the server
+    kms = []
+    for seed, (B, T, words, sa, sb) in enumerate(SHAPES[:5]):
+        rng = np.random.default_rng(31 * P + seed)
+        km = _random_kernel(rng, B, T, words, (sa, sb), P=P, glob=seed % 2 == 0, conds=seed > 2)
+        n = min(4, P // 8)
+        km.slots = np.zeros(n, synth.SLOT_DT)
+        km.slots["level"], km.slots["weight"] = [q % 2 for q in range(n)], 1
+        for s in range(n):
+            km.points[(s + 1) * P // (n + 1)] = (1, 0, 0, 0, s, 0, 0, 0)
+        kms.append(km)
+        for kw in (dict(), dict(policy=1), dict(policy=1, solver=1)):
+            g, o = L.repair(km, **kw), O.repair(km, **kw)
+            assert same_repair(g, o), (seed, kw, g, o)
+        for x in (0, 1):
+            assert L.clauses(km, x) == O.clauses(km, x), (seed, x)
+    kms.append(synth.generate("plain-small", seed=P))
+    st, res = L.repair_batch(kms + [_random_kernel(np.random.default_rng(P), 2, 40, 64,
+                                                   ((1, 2), (0, 40)), P=300)])
+    assert st == 0
+    for km, r in zip(kms, res):
+        o = O.repair(km)
+        assert all(r[k] == o[k] for k in ("status", "assign", "weight", "rounds", "n_clauses"))
+
+
+def test_points_that_never_execute(L):  # noqa: F811
+    # an array whose accesses run on no thread has no records on either route
+    pts = [dict(kind=0, is_write=1, array=0, guard=1, a=1), dict(kind=1, slot=0),
+           dict(kind=0, is_write=1, array=0, guard=1, a=1)]
+    km = synth.make_kernel(2, 4, [(8, 1)], [(1, 0), (9, 8)], pts, [(0, 0, 1)])
+    for route in (0, 1):
+        old = L.set_tuning(L.TUNE_RACE_ROUTE, route)
+        try:
+            assert L.check(km, 0)[:4] == O.check(km, 0)
+            assert same_repair(L.repair(km), O.repair(km))
+            assert L.clauses(km, 0) == O.clauses(km, 0)
+        finally:
+            L.set_tuning(L.TUNE_RACE_ROUTE, old)
