@@ -40,14 +40,17 @@
 //      far (a shared word) as well as its own best key.  The optimum is
 //      unique, so the smallest of the waves' best keys is the answer whatever
 //      order the waves run in.
-// phi is staged in LDS (up to SV_CLAUSES clauses; more are read from memory
-// until few enough are open).  Bound: latency, a chain of workgroup-wide
-// reductions of one barrier each.  Measured: 300 runs over 56 slots of weights
-// 1 to 10, 87 us by reduction and path, 1 to 90 ms (two or three seconds at 64
-// slots) by the search alone; the 35 greedy rounds of plain-large one trace
-// at a time, 0.85 ms from 2.5 ms with LDS counters per slot and one thread
-// comparing them; the Solves of 512 instrumented programs 0.12 ms from 0.47
-// ms by enumeration alone.
+// Up to WV_CLAUSES clauses are held in the registers of a wave, one or two per
+// lane: every wave then runs the greedy strategy and the reduction alike, with
+// no barrier and no LDS.  More are staged in LDS (up to SV_CLAUSES; more again
+// are read from memory until few enough are open) and reduced by the whole
+// workgroup until they fit a wave.  Bound: latency, a chain of reductions.  Measured: 300 runs over 56 slots of weights
+// 1 to 10, 82 us by reduction and path, 1 to 90 ms (over a second at 64 slots)
+// by the search alone; the 35 greedy Solves of plain-large one trace at a time
+// 0.24 ms in a wave's registers, 0.73 ms with a barrier per pick, 2.4 ms with
+// LDS counters per slot and one thread comparing them; 512 instrumented
+// programs to their verdicts 0.10 ms, 0.14 ms reduced with barriers, 0.47 ms by
+// enumeration alone.
 #pragma once
 #include "common.h"
 
@@ -83,19 +86,38 @@ __device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
 __device__ __forceinline__ uint64_t wave_or(uint64_t v) {
   return ((uint64_t)wave_or32((uint32_t)(v >> 32)) << 32) | wave_or32((uint32_t)v);
 }
-__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
-  for (int off = 32; off > 0; off >>= 1) {
-    uint64_t o = __shfl_xor(v, off);
-    v = o < v ? o : v;
-  }
-  return v;
+// Sum over the wave (row prefixes by shifts, then the rows' totals).
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+  return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-  for (int off = 32; off > 0; off >>= 1) {
-    uint64_t o = __shfl_xor(v, off);
-    v = o > v ? o : v;
-  }
-  return v;
+// Minimum, maximum over the wave; a lane with no source keeps its own value.
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
+  const int lo = (int)(uint32_t)v, hi = (int)(uint32_t)(v >> 32);
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false) << 32) |
+         (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
+  auto mn = [](uint64_t a, uint64_t b) { return b < a ? b : a; };
+  v = mn(v, dpp64<0x111>(v));
+  v = mn(v, dpp64<0x112>(v));
+  v = mn(v, dpp64<0x114>(v));
+  v = mn(v, dpp64<0x118>(v));
+  v = mn(v, dpp64<0x142>(v));
+  v = mn(v, dpp64<0x143>(v));
+  return lane_value(v, 63);
+}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) { return ~wave_min_u64(~v); }
+// Total weight of the slots of x (the same in every lane).
+__device__ __forceinline__ uint64_t weight_of(uint64_t x, const uint32_t* s_w) {
+  const uint32_t w = (x >> __lane_id()) & 1 ? s_w[__lane_id()] : 0;
+  return ((uint64_t)wave_sum32(w >> 16) << 16) + wave_sum32(w & 0xFFFFu);
 }
 
 __device__ __forceinline__ Key block_min_key(Key k, uint64_t* smh, uint64_t* sml) {
@@ -176,6 +198,28 @@ __device__ __forceinline__ void block_or(uint64_t (&v)[K], SolveLds& L, uint32_t
   turn ^= 1;
 }
 
+// The lane (slot) with the largest c / w, the lowest one of equals; some c is
+// not 0.  From a first slot on, to the lowest slot that is better than it, as
+// long as there is one (every best slot is, so the last step meets the lowest).
+__device__ __forceinline__ uint32_t best_slot(uint32_t c, uint32_t w) {
+  auto of = [](uint32_t v, uint32_t l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+  uint32_t best = (uint32_t)__builtin_ctzll(__ballot(c != 0));
+  for (;;) {
+    const uint64_t m = __ballot((uint64_t)c * of(w, best) > (uint64_t)of(c, best) * w);
+    if (m == 0) return best;
+    best = (uint32_t)__builtin_ctzll(m);
+  }
+}
+
+// A greedy answer into the state (every thread of the workgroup calls it).
+__device__ __forceinline__ void greedy_answer(JobState* st, const uint32_t* s_w, uint64_t x) {
+  const uint64_t W = weight_of(x, s_w);
+  if (threadIdx.x != 0) return;
+  st->x = x;
+  st->weight = W;
+  if (st->max_rounds && st->rounds >= st->max_rounds) st->state = ST_ROUNDS;
+}
+
 // The mhs strategy's Solve (Section 2.4): the greedy minimal hitting set of
 // the positive clauses of phi -- repeatedly the slot hitting the most clauses
 // not yet hit per unit of weight (exact integer comparison, ties to the lower
@@ -184,8 +228,7 @@ __device__ __forceinline__ void block_or(uint64_t (&v)[K], SolveLds& L, uint32_t
 // phi has an empty clause, is too long, or the set breaks a clause of phi.
 // A lane is a slot: the waves share the clauses of a count (LDS: each clause
 // read once by all lanes; from memory a clause per lane, counted with LDS
-// adds), and every wave finds the best slot alike (a float quotient narrows
-// the lanes down, integer products decide), so a pick costs one barrier.
+// adds), and every wave finds the best slot alike, so a pick costs one barrier.
 template <bool LDS, class G>
 __device__ bool greedy_solve(const Job& J, const uint32_t* s_w, JobState* st, uint32_t n, G get,
                              SolveLds& L, uint32_t& turn) {
@@ -223,22 +266,7 @@ __device__ bool greedy_solve(const Job& J, const uint32_t* s_w, JobState* st, ui
     for (int q = 0; q < SV_WAVES; q++) c += L.c64[turn][q][lane];
     turn ^= 1;
     if (__ballot(c != 0) == 0) break;
-    const float f = (float)c / (float)w;
-    float top = f;
-    for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-    uint64_t cand = __ballot(c != 0 && f >= top * 0.9999f);
-    uint32_t best = (uint32_t)__builtin_ctzll(cand);
-    auto of = [](uint32_t v, uint32_t l) { return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)v, l); };
-    uint64_t bc = of(c, best), bw = of(w, best);
-    for (cand &= cand - 1; cand; cand &= cand - 1) {
-      const uint32_t b = (uint32_t)__builtin_ctzll(cand);
-      const uint64_t cb = of(c, b), wb = of(w, b);
-      if (cb * bw > bc * wb) {
-        best = b;
-        bc = cb;
-        bw = wb;
-      }
-    }
+    const uint32_t best = best_slot(c, w);
     x |= 1ull << best;
     if (lane == np) mine = best;
     np++;
@@ -259,14 +287,162 @@ __device__ bool greedy_solve(const Job& J, const uint32_t* s_w, JobState* st, ui
     viol = !((c.pos & x) || (c.neg & ~x));
   }
   if (__ballot(viol)) return false;
-  if (tid == 0) {
-    uint64_t W = 0;
-    for (uint64_t m = x; m; m &= m - 1) W += s_w[__builtin_ctzll(m)];
-    st->x = x;
-    st->weight = W;
-    if (st->max_rounds && st->rounds >= st->max_rounds) st->state = ST_ROUNDS;
-  }
+  greedy_answer(st, s_w, x);
   return true;
+}
+
+// Clauses held by a wave: clause 64 g + l in lane l.
+constexpr uint32_t WV_CLAUSES = 128;
+template <int G>
+struct WaveClauses {
+  uint64_t pos[G], neg[G];
+  bool on[G];                              // there is (still) such a clause
+};
+template <int G>
+__device__ __forceinline__ WaveClauses<G> wave_clauses(const rp_clause* C, uint32_t n) {
+  WaveClauses<G> c;
+#pragma unroll
+  for (int g = 0; g < G; g++) {
+    const uint32_t q = 64 * g + __lane_id();
+    c.on[g] = q < n;
+    const rp_clause v = c.on[g] ? C[q] : rp_clause{0, 0};
+    c.pos[g] = v.pos;
+    c.neg[g] = v.neg;
+  }
+  return c;
+}
+
+// greedy_solve on clauses held by every wave alike.  A lane is a slot too: it
+// keeps the set of clauses its slot hits, one bit each.
+template <int G>
+__device__ __forceinline__ bool greedy_wave(uint32_t S, const uint32_t* s_w, JobState* st,
+                                            const WaveClauses<G>& c) {
+  const uint32_t lane = __lane_id();
+  bool empty = false;
+  uint64_t hits[G], todo[G];
+#pragma unroll
+  for (int g = 0; g < G; g++) {
+    empty = empty || (c.on[g] && c.pos[g] == 0 && c.neg[g] == 0);
+    const uint64_t p = c.on[g] && c.neg[g] == 0 ? c.pos[g] : 0;     // a positive clause
+    todo[g] = __ballot(p != 0);
+    hits[g] = 0;
+    if (todo[g] == 0) continue;
+    for (uint32_t s = 0; s < S; s++) {
+      const uint64_t m = __ballot((p >> s) & 1);
+      hits[g] = lane == s ? m : hits[g];
+    }
+  }
+  if (__ballot(empty)) return false;
+  const uint32_t w = lane < S ? s_w[lane] : 1;
+  uint64_t x = 0;
+  uint32_t np = 0, mine = 0;               // picks; lane q keeps the q-th
+  for (;;) {
+    uint32_t k = 0;
+#pragma unroll
+    for (int g = 0; g < G; g++) k += (uint32_t)__popcll(hits[g] & todo[g]);
+    if (__ballot(k != 0) == 0) break;
+    const uint32_t best = best_slot(k, w);
+    x |= 1ull << best;
+    if (lane == np) mine = best;
+    np++;
+#pragma unroll
+    for (int g = 0; g < G; g++) todo[g] &= ~lane_value(hits[g], best);
+  }
+  for (uint32_t k = np; k-- > 0;) {
+    const uint64_t y = x & ~(1ull << __builtin_amdgcn_readlane(mine, k));
+    bool miss = false;
+#pragma unroll
+    for (int g = 0; g < G; g++)
+      miss = miss || (c.on[g] && c.pos[g] && !c.neg[g] && !(c.pos[g] & y));
+    if (__ballot(miss) == 0) x = y;
+  }
+  bool viol = false;
+#pragma unroll
+  for (int g = 0; g < G; g++)
+    viol = viol || (c.on[g] && !((c.pos[g] & x) || (c.neg[g] & ~x)));
+  if (__ballot(viol)) return false;
+  greedy_answer(st, s_w, x);
+  return true;
+}
+
+// The slots of core that another one makes needless: d has the slots in every
+// open clause of the lane's slot, negs those in a negative literal.
+__device__ __forceinline__ uint64_t needless(uint64_t d, uint64_t core, uint64_t negs,
+                                             const uint32_t* s_w) {
+  const uint32_t lane = __lane_id();
+  bool worse = false;
+  if ((core >> lane) & 1) {
+    const uint32_t w = s_w[lane];
+    for (uint64_t t = d & core & ~negs & ~(1ull << lane); t && !worse; t &= t - 1) {
+      const uint32_t b = (uint32_t)__builtin_ctzll(t);
+      worse = s_w[b] < w || (s_w[b] == w && b < lane);
+    }
+  }
+  return __ballot(worse);
+}
+
+// The reduction on clauses held by every wave alike, to its fixpoint: on and
+// off grow, satisfied and subsumed clauses go, the others are restricted to
+// the free slots.  Returns false when they cannot be satisfied.
+template <int G>
+__device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, const uint32_t* s_w,
+                                            uint64_t& on, uint64_t& off) {
+  const uint32_t lane = __lane_id();
+  for (;;) {
+    uint64_t vp = 0, vn = 0, up = 0, un = 0;
+    bool bad = false;
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+      if (!c.on[g] || (c.pos[g] & on) || (c.neg[g] & off)) {
+        c.on[g] = false;
+        continue;
+      }
+      const uint64_t p = c.pos[g] &= ~off, m = c.neg[g] &= ~on;
+      vp |= p;
+      vn |= m;
+      if (p == 0 && m == 0) bad = true;
+      else if (p == 0 && (m & (m - 1)) == 0) un |= m;
+      else if (m == 0 && (p & (p - 1)) == 0) up |= p;
+    }
+    if (__ballot(bad)) return false;
+    const uint64_t core = wave_or(vp), negs = __ballot(vn != 0) ? wave_or(vn) : 0;
+    uint64_t non = 0, noff = 0;
+    if (__ballot((up | un) != 0)) {
+      non = wave_or(up);
+      noff = wave_or(un);
+      if ((non & (off | noff)) || (noff & (on | non))) return false;
+    }
+    const uint64_t nz = all & ~on & ~off & ~non & ~noff & ~core;
+    on |= non;
+    off |= noff | nz;
+    if (non | noff | nz) continue;
+    if (core == 0) return true;
+    // every clause past every lane: as a slot, the lane keeps what is in all
+    // clauses of its slot; as a clause, it is dropped for a subset
+    uint64_t d = ~0ull;
+    bool dead[G] = {};
+#pragma unroll
+    for (int h = 0; h < G; h++) {
+      for (uint64_t m = __ballot(c.on[h]); m; m &= m - 1) {
+        const uint32_t r = (uint32_t)__builtin_ctzll(m);
+        const uint64_t p = lane_value(c.pos[h], r), q = lane_value(c.neg[h], r);
+        if ((p >> lane) & 1) d &= p;
+#pragma unroll
+        for (int g = 0; g < G; g++)
+          dead[g] = dead[g] || ((p & ~c.pos[g]) == 0 && (q & ~c.neg[g]) == 0 &&
+                                (p != c.pos[g] || q != c.neg[g] || 64 * h + r < 64 * g + lane));
+      }
+    }
+    bool died = false;
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+      died = died || (c.on[g] && dead[g]);
+      c.on[g] = c.on[g] && !dead[g];
+    }
+    const uint64_t drop = needless(d, core, negs, s_w);
+    off |= drop;
+    if (drop == 0 && __ballot(died) == 0) return true;
+  }
 }
 
 // Reduction of the n clauses get(q): on and off grow to the fixpoint, by units
@@ -308,34 +484,25 @@ __device__ bool propagate(G get, uint32_t n, uint64_t all, const uint32_t* s_w, 
     __syncthreads();
     for (int q = 0; q < SV_WAVES; q++) d &= L.dom[turn][q][lane];
     turn ^= 1;
-    bool worse = false;
-    if ((core >> lane) & 1) {
-      const uint32_t w = s_w[lane];
-      for (uint64_t t = d & core & ~v[3] & ~(1ull << lane); t && !worse; t &= t - 1) {
-        const uint32_t b = (uint32_t)__builtin_ctzll(t);
-        worse = s_w[b] < w || (s_w[b] == w && b < lane);
-      }
-    }
-    const uint64_t drop = __ballot(worse);
+    const uint64_t drop = needless(d, core, v[3], s_w);
     if (drop == 0) return true;
     off |= drop;
   }
 }
 
 // The optimum over the slots of M when every clause is positive and a
-// contiguous run of them; first[h]: the largest first slot of the clauses
-// whose last slot is h (-1: none), last[l]: the largest last slot of those
-// whose first is l.  Slots are taken in ascending order: a chosen slot s may
+// contiguous run of them; fl: the largest first slot of the clauses whose last
+// slot is this lane (-1: none), ll: the largest last slot of those whose first
+// is this lane.  Slots are taken in ascending order: a chosen slot s may
 // follow a chosen slot p exactly when no clause lies wholly between them,
 // that is when p >= the largest first slot of the clauses that end before s.
 // Every wave computes the same; lane p keeps the best key of a choice that
 // ends with p.  A run of linked slots longer than ENUM_MAX and than the node
 // budget counts as a search that spends it (returns false).
-__device__ bool interval_optimum(uint64_t M, const uint32_t* s_w, uint64_t budget,
-                                 const SolveLds& L, uint64_t& answer) {
+__device__ bool interval_optimum(uint64_t M, const uint32_t* s_w, uint64_t budget, int32_t fl,
+                                 int32_t ll, uint64_t& answer) {
   const uint32_t lane = __lane_id();
   const uint32_t w = (M >> lane) & 1 ? s_w[lane] : 0;
-  const int32_t fl = L.first[lane], ll = L.last[lane];
   uint64_t bh = ~0ull, bl = 0;             // this lane's best key
   int32_t need = -1, reach = -1;           // largest first slot that ended; last slot reached
   uint32_t run = 0;
@@ -399,6 +566,71 @@ __device__ bool intervals_of(const rp_clause* U, uint32_t n, uint64_t M, SolveLd
   return other[0] == 0;
 }
 
+// The same for clauses held by a wave: fl and ll by passing every clause by
+// every lane.  False when some clause is no run of M.
+template <int G>
+__device__ __forceinline__ bool wave_intervals(const WaveClauses<G>& c, uint64_t M, int32_t& fl,
+                                               int32_t& ll) {
+  const int32_t lane = (int32_t)__lane_id();
+  fl = ll = -1;
+#pragma unroll
+  for (int g = 0; g < G; g++) {
+    uint32_t lo = 0, hi = 0;
+    bool other = false;
+    if (c.on[g]) {
+      other = c.pos[g] == 0 || c.neg[g] != 0;
+      if (!other) {
+        lo = (uint32_t)__builtin_ctzll(c.pos[g]);
+        hi = 63u - (uint32_t)__builtin_clzll(c.pos[g]);
+        other = (M & (~0ull >> (63 - hi)) & (~0ull << lo)) != c.pos[g];
+      }
+    }
+    if (__ballot(other)) return false;
+    for (uint64_t m = __ballot(c.on[g]); m; m &= m - 1) {
+      const uint32_t r = (uint32_t)__builtin_ctzll(m);
+      const int32_t l = __builtin_amdgcn_readlane(lo, r), h = __builtin_amdgcn_readlane(hi, r);
+      if (h == lane) fl = l > fl ? l : fl;
+      if (l == lane) ll = h > ll ? h : ll;
+    }
+  }
+  return true;
+}
+
+// The reduction in the waves (of W[0..n), every wave alike) and, where that
+// leaves runs of slots, the path: result.  Else left has the slots left, and
+// L.cl[0..n) their clauses.  sat: they can be satisfied.  Returns false when
+// the job has failed.
+template <int G>
+__device__ bool solve_wave(const Job& J, JobState* st, const rp_clause* W, uint32_t& n, uint64_t all,
+                           const uint32_t* s_w, SolveLds& L, int wv, uint64_t& on, uint64_t& off,
+                           bool& sat, uint64_t& result, uint64_t& left) {
+  WaveClauses<G> c = wave_clauses<G>(W, n);
+  sat = reduce_wave(c, all, s_w, on, off);
+  left = sat ? all & ~on & ~off : 0;
+  if (left == 0) return true;
+  int32_t fl, ll;
+  if (wave_intervals(c, left, fl, ll)) {
+    if (!interval_optimum(left, s_w, J.node_limit, fl, ll, result)) {
+      if (threadIdx.x == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
+      return false;
+    }
+    left = 0;
+    return true;
+  }
+  // (the waves hold the same clauses: the first writes them out)
+  n = 0;
+  __syncthreads();                         // (everyone has read W)
+#pragma unroll
+  for (int g = 0; g < G; g++) {
+    const uint64_t m = __ballot(c.on[g]);
+    if (wv == 0 && c.on[g])
+      L.cl[n + (uint32_t)__popcll(m & lanemask_lt())] = rp_clause{c.pos[g], c.neg[g]};
+    n += (uint32_t)__popcll(m);
+  }
+  __syncthreads();
+  return true;
+}
+
 // Solve over phi = C[0..n) for the job state *st (in LDS; thread 0 writes it):
 // x and weight, or a final state.  s_w: the slots' weights (LDS).  Every
 // thread of the workgroup calls it.
@@ -410,50 +642,56 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
   const uint64_t all = S >= 64 ? ~0ull : ((1ull << S) - 1);
   const uint32_t phase = st->phase;
   uint32_t turn = 0;
-  const bool lds = n <= SV_CLAUSES;
-  if (lds)
-    for (uint32_t q = tid; q < n; q += SV_BLOCK) L.cl[q] = C[q];
-  __syncthreads();          // (and every thread has the phase before thread 0 may change it)
-  auto in_lds = [&](uint32_t q) { return L.cl[q]; };
-  auto in_memory = [&](uint32_t q) { return C[q]; };
-  if (phase == PH_GREEDY && (lds ? greedy_solve<true>(J, s_w, st, n, in_lds, L, turn)
-                                 : greedy_solve<false>(J, s_w, st, n, in_memory, L, turn)))
-    return;
-
-  // ---- 1. reduction
   uint64_t on = 0, off = 0;
-  bool sat = lds ? propagate<false>(in_lds, n, all, s_w, on, off, L, turn)
-                 : propagate<false>(in_memory, n, all, s_w, on, off, L, turn);
+  bool sat = true;
   rp_clause* U = L.cl;
   uint32_t nu = n;
-  if (sat && !lds) {
-    // the open clauses alone, restricted, into LDS if they fit, else into the
-    // first phi_cap clauses of scratch (which hold at least n)
-    uint64_t open = 0;
-    if (tid == 0) L.cnt = 0;
+  // ---- 1. reduction
+  const rp_clause* W = C;   // the clauses of the waves' reduction, where there are few enough
+  if (n <= WV_CLAUSES) {
+    __syncthreads();        // (every thread has the phase before thread 0 may change it)
+    if (phase == PH_GREEDY && (n <= 64 ? greedy_wave(S, s_w, st, wave_clauses<1>(C, n))
+                                       : greedy_wave(S, s_w, st, wave_clauses<2>(C, n))))
+      return;
+  } else {
+    const bool lds = n <= SV_CLAUSES;
+    if (lds)
+      for (uint32_t q = tid; q < n; q += SV_BLOCK) L.cl[q] = C[q];
     __syncthreads();
-    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-      const rp_clause c = C[q];
-      if (!(c.pos & on) && !(c.neg & off)) open++;
+    auto in_lds = [&](uint32_t q) { return L.cl[q]; };
+    auto in_memory = [&](uint32_t q) { return C[q]; };
+    if (phase == PH_GREEDY && (lds ? greedy_solve<true>(J, s_w, st, n, in_lds, L, turn)
+                                   : greedy_solve<false>(J, s_w, st, n, in_memory, L, turn)))
+      return;
+    sat = lds ? propagate<false>(in_lds, n, all, s_w, on, off, L, turn)
+              : propagate<false>(in_memory, n, all, s_w, on, off, L, turn);
+    if (sat && !lds) {
+      // the open clauses alone, restricted, into LDS if they fit, else into the
+      // first phi_cap clauses of scratch (which hold at least n)
+      uint64_t open = 0;
+      if (tid == 0) L.cnt = 0;
+      __syncthreads();
+      for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+        const rp_clause c = C[q];
+        if (!(c.pos & on) && !(c.neg & off)) open++;
+      }
+      if (open) atomicAdd(&L.cnt, (uint32_t)open);
+      __syncthreads();
+      if (L.cnt > SV_CLAUSES) U = J.scratch;
+      __syncthreads();
+      if (tid == 0) L.cnt = 0;
+      __syncthreads();
+      for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+        const rp_clause c = C[q];
+        if ((c.pos & on) || (c.neg & off)) continue;
+        U[atomicAdd(&L.cnt, 1u)] = rp_clause{c.pos & ~off, c.neg & ~on};
+      }
+      __syncthreads();
+      nu = L.cnt;
     }
-    if (open) atomicAdd(&L.cnt, (uint32_t)open);
-    __syncthreads();
-    if (L.cnt > SV_CLAUSES) U = J.scratch;
-    __syncthreads();
-    if (tid == 0) L.cnt = 0;
-    __syncthreads();
-    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-      const rp_clause c = C[q];
-      if ((c.pos & on) || (c.neg & off)) continue;
-      U[atomicAdd(&L.cnt, 1u)] = rp_clause{c.pos & ~off, c.neg & ~on};
-    }
-    __syncthreads();
-    nu = L.cnt;
-  }
-  if (U == L.cl) {
-    // restrict, drop the satisfied and the subsumed, reduce again until that
-    // changes nothing
-    while (sat && nu) {
+    // restrict, drop the satisfied and the subsumed; reduce again until that
+    // changes nothing, or until a wave can hold them
+    while (sat && nu && U == L.cl) {
       for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
         const rp_clause c = L.cl[q];
         L.cl[q] = (c.pos & on) || (c.neg & off) ? rp_clause{~0ull, ~0ull}     // (a tautology)
@@ -474,30 +712,41 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
       __syncthreads();
       nu = L.cnt;
       const uint64_t fixed = on | off;
-      sat = propagate<true>([&](uint32_t q) { return L.u[q]; }, nu, all, s_w, on, off, L, turn);
+      const bool few = nu <= WV_CLAUSES;
+      if (!few)
+        sat = propagate<true>([&](uint32_t q) { return L.u[q]; }, nu, all, s_w, on, off, L, turn);
       __syncthreads();
       for (uint32_t q = tid; q < nu; q += SV_BLOCK) L.cl[q] = L.u[q];
       __syncthreads();
-      if (fixed == (on | off)) break;
+      if (few || fixed == (on | off)) break;
+    }
+    W = U;
+  }
+  uint64_t result = 0, left = 0;
+  bool paths = U == L.cl;                  // (a component over more clauses is refused below)
+  if (sat && nu <= WV_CLAUSES) {
+    // ---- 2. in the waves; one path over all that is left
+    const bool done = nu <= 64 ? solve_wave<1>(J, st, W, nu, all, s_w, L, wv, on, off, sat, result, left)
+                               : solve_wave<2>(J, st, W, nu, all, s_w, L, wv, on, off, sat, result, left);
+    if (!done) return;
+    U = L.cl;
+  } else if (sat) {
+    left = all & ~on & ~off;
+    if (left && paths && intervals_of(U, nu, left, L, turn)) {
+      uint64_t x;
+      if (!interval_optimum(left, s_w, J.node_limit, L.first[lane], L.last[lane], x)) {
+        if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
+        return;
+      }
+      result = x;
+      left = 0;
     }
   }
   if (!sat) {
     if (tid == 0) st->state = ST_UNSAT;
     return;
   }
-  uint64_t result = on;
-  uint64_t left = all & ~on & ~off;
-  // ---- 2. one path over all that is left
-  const bool paths = U == L.cl;            // (a component over more clauses is refused below)
-  if (left && paths && intervals_of(U, nu, left, L, turn)) {
-    uint64_t x;
-    if (!interval_optimum(left, s_w, J.node_limit, L, x)) {
-      if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
-      return;
-    }
-    result |= x;
-    left = 0;
-  }
+  result |= on;
   while (left) {
     // ---- 3. component of the lowest free slot
     uint64_t comp = left & (~left + 1);
@@ -515,7 +764,7 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
     const int k = __popcll(comp);
     if (paths && intervals_of(U, nu, comp, L, turn)) {
       uint64_t x;
-      if (!interval_optimum(comp, s_w, J.node_limit, L, x)) {
+      if (!interval_optimum(comp, s_w, J.node_limit, L.first[lane], L.last[lane], x)) {
         if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
         return;
       }
@@ -733,20 +982,19 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
     result |= best.lo;   // lo is the global mask of the component's optimum
     __syncthreads();
   }
+  const uint64_t weight = weight_of(result, s_w);
   if (tid == 0) {
-    uint64_t W = 0;
-    for (uint64_t m = result; m; m &= m - 1) W += s_w[__builtin_ctzll(m)];
     if (phase == PH_FINAL) {
       // the exact query after the greedy answer was verified SAFE
       st->phase = PH_EXACT;
       if (result == st->x) {
-        st->weight = W;
+        st->weight = weight;
         st->state = ST_SAFE;
         return;
       }
     }
     st->x = result;
-    st->weight = W;
+    st->weight = weight;
     if (st->max_rounds && st->rounds >= st->max_rounds) st->state = ST_ROUNDS;
   }
 }
