@@ -26,7 +26,8 @@
 // of masks and clauses).  With four launches per round (interval scan, clause
 // sort and subsumption, Solve, count of running jobs) and a host wait, the
 // rounds of the small planted kernel took 84 us with their waits, of 512
-// instrumented programs 1.9 ms; in one launch 7 us and 0.47 ms.
+// instrumented programs 1.9 ms; in one launch, with the small kernel's first
+// partners, 12 us, and 0.09 ms.
 #include "closed_rows.h"
 #include "common.h"
 #include "launch.h"
@@ -76,6 +77,22 @@ __device__ __forceinline__ uint64_t block_excl_scan(uint64_t v, uint64_t* sm, ui
   __syncthreads();
   *total = tot;
   return pre + inc - v;
+}
+
+// Rank of this thread among those of the workgroup with hit, and their number.
+__device__ __forceinline__ uint32_t block_rank(bool hit, uint64_t* sm, uint32_t* total) {
+  const uint32_t w = threadIdx.x >> 6;
+  const uint64_t m = __ballot(hit);
+  if (__lane_id() == 0) sm[w] = (uint64_t)__popcll(m);
+  __syncthreads();
+  uint32_t pre = 0, tot = 0;
+  for (uint32_t q = 0; q < (uint32_t)RD_WAVES; q++) {
+    if (q < w) pre += (uint32_t)sm[q];
+    tot += (uint32_t)sm[q];
+  }
+  __syncthreads();
+  *total = tot;
+  return pre + (uint32_t)__popcll(m & lanemask_lt());
 }
 
 // Builds F and, if rows, the masks of the racing rows (their sizes into
@@ -129,10 +146,10 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
     for (uint32_t b0 = 0; rows && b0 < P; b0 += RD_BLOCK) {
       const uint32_t i = b0 + tid;
       const uint32_t j = i < P ? J.j0[(uint64_t)lv * P + i] : NONE32;
-      uint64_t total;
-      const uint32_t at = (uint32_t)block_excl_scan(j < P, sm, &total);
+      uint32_t total;
+      const uint32_t at = block_rank(j < P, sm, &total);
       if (j < P) rows_of(J)[n_rows + at] = mask_of(lv, L.next[lv][i], L.next[lv][j]);
-      n_rows += (uint32_t)total;
+      n_rows += total;
     }
     __syncthreads();
     const uint32_t pt = n / RD_BLOCK + 1;  // starts of this thread, [t0, t1)
@@ -179,8 +196,8 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
     __syncthreads();
   }
   // ---- F: duplicates and supersets dropped, ascending
-  uint64_t any_empty;
-  (void)block_excl_scan(empty, sm, &any_empty);
+  uint32_t any_empty;
+  (void)block_rank(empty, sm, &any_empty);
   uint64_t* const F = full_of(J);
   if (any_empty) {
     if (tid == 0) {
@@ -222,34 +239,33 @@ __device__ void build_tables(const Job& J, JobState* st, bool rows, BuildLds& L,
 // GenerateClause over every trace under x: the divergent slots' units and the
 // masks of F that x misses, behind the n clauses of phi.  Returns the number
 // of clauses of phi (the caller has checked that something is learned).
-__device__ uint32_t learn_all(const Job& J, uint64_t x, uint64_t div, uint32_t n, uint32_t n_full,
-                              uint64_t* sm) {
+__device__ __forceinline__ uint32_t learn_all(rp_clause* phi, uint32_t cap, uint64_t x, uint64_t div, uint32_t n,
+                              const uint64_t* F, uint32_t n_full, uint64_t* sm) {
   const uint32_t tid = threadIdx.x;
-  const uint64_t* F = full_of(J);
   if (n_full == 1 && F[0] == 0) {
     __syncthreads();
-    if (tid == 0) J.phi[0] = rp_clause{0, 0};
+    if (tid == 0) phi[0] = rp_clause{0, 0};
     return 1;
   }
   if (tid < 64 && ((div >> tid) & 1)) {
     const uint32_t at = n + (uint32_t)__popcll(div & ((1ull << tid) - 1));
-    if (at < J.phi_cap) J.phi[at] = rp_clause{0, 1ull << tid};
+    if (at < cap) phi[at] = rp_clause{0, 1ull << tid};
   }
   n += (uint32_t)__popcll(div);
   for (uint32_t b = 0; b < n_full; b += RD_BLOCK) {
     const uint32_t q = b + tid;
     const uint64_t mk = q < n_full ? F[q] : ~0ull;
     const bool hit = q < n_full && (mk & x) == 0;
-    uint64_t total;
-    const uint32_t at = n + (uint32_t)block_excl_scan(hit, sm, &total);
-    if (hit && at < J.phi_cap) J.phi[at] = rp_clause{mk, 0};
-    n += (uint32_t)total;
+    uint32_t total;
+    const uint32_t at = n + block_rank(hit, sm, &total);
+    if (hit && at < cap) phi[at] = rp_clause{mk, 0};
+    n += total;
   }
   return n;
 }
 
 // One trace: clause c joins phi, whose supersets of it leave.
-__device__ uint32_t learn_one(const Job& J, rp_clause c, uint32_t n, uint32_t* s_n) {
+__device__ __forceinline__ uint32_t learn_one(rp_clause* phi, uint32_t cap, rp_clause c, uint32_t n, uint32_t* s_n) {
   if (threadIdx.x < 64) {
     const uint32_t lane = threadIdx.x;
     uint32_t k = 0;
@@ -258,20 +274,38 @@ __device__ uint32_t learn_one(const Job& J, rp_clause c, uint32_t n, uint32_t* s
       rp_clause p{0, 0};
       bool keep = false;
       if (q < n) {
-        p = J.phi[q];
+        p = phi[q];
         keep = (c.pos & ~p.pos) != 0 || (c.neg & ~p.neg) != 0;
       }
       const uint64_t m = __ballot(keep);
-      if (keep) J.phi[k + (uint32_t)__popcll(m & lanemask_lt())] = p;   // (never past q)
+      if (keep) phi[k + (uint32_t)__popcll(m & lanemask_lt())] = p;   // (never past q)
       k += (uint32_t)__popcll(m);
     }
     if (lane == 0) {
-      if (k < J.phi_cap) J.phi[k] = c;
+      if (k < cap) phi[k] = c;
       *s_n = k + 1;
     }
   }
   __syncthreads();
   return *s_n;
+}
+
+// What one-trace rounds (many, of small steps) read and write, in the parts of
+// the solver's LDS that it leaves alone while phi has at most WV_CLAUSES
+// clauses: the racing rows' masks, phi and the trajectory since it was last
+// written out.  From memory each step waited for the one before it to reach L2
+// and come back.  Other jobs end after a few rounds, which do not pay for the
+// copy (1 us of a small kernel's 12).
+constexpr uint32_t NEAR = SV_CLAUSES - WV_CLAUSES;
+__device__ __forceinline__ rp_clause* near_phi(SolveLds& L) { return L.cl + WV_CLAUSES; }
+__device__ __forceinline__ uint64_t* near_masks(SolveLds& L) { return L.la + WV_CLAUSES; }
+__device__ __forceinline__ uint64_t* near_traj(SolveLds& L) { return L.ln + WV_CLAUSES; }
+
+// Writes out the rounds [from, to) of the trajectory.
+__device__ __forceinline__ void save_traj(const Job& J, SolveLds& L, uint32_t from, uint32_t to) {
+  if (!J.traj) return;
+  for (uint32_t q = from + threadIdx.x; q < to && q < J.traj_cap; q += RD_BLOCK)
+    J.traj[q] = near_traj(L)[q - from];
 }
 
 // flags: RD_BUILD builds the tables (from j0, which a job of few points works
@@ -284,19 +318,18 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   __shared__ RoundLds L;
   __shared__ JobState s_st;
   __shared__ uint64_t sm[RD_WAVES];
-  __shared__ uint32_t s_row, s_n, s_w[64];
+  __shared__ uint32_t s_hit[RD_WAVES], s_n;
+  __shared__ SlotKeys s_keys;
   // (a call's first kernel, unless first_kernel has come before)
   const bool begins = !(flags & RD_BUILD) || (flags & RD_FIRST);
   stamp_if(call.stamps, begins ? STAMP_BEGIN : STAMP_FIRST);
   const Job& J = jobs[blockIdx.x];
-  const uint32_t tid = threadIdx.x, P = J.P;
+  const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = sv_uni(tid >> 6), P = J.P;
   JobState* st = &s_st;
   if (J.st->state != ST_RUN) return;
   if (tid < sizeof(JobState) / 4) ((uint32_t*)st)[tid] = ((const uint32_t*)J.st)[tid];
-  if (tid < 64) s_w[tid] = tid < J.S ? J.weights[tid] : 0;
   __syncthreads();
   const bool one = J.policy == 1 && !(flags & RD_LEARN);
-  // (a lone Solve reads its clauses where they are)
   if (flags & RD_BUILD)
     for (uint32_t q = tid; q < st->n_phi; q += RD_BLOCK) J.phi[q] = J.phi0[q];
   if ((flags & RD_BUILD) && P <= PACKED_POINTS && J.nlog[0] == 0 && J.nlog[1] == 0) {
@@ -304,11 +337,6 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
     if (begins) stamp_if(call.stamps, STAMP_FIRST);
   }
   if (flags & RD_BUILD) build_tables(J, st, J.policy == 1, L.b, sm);
-  if (flags & RD_SOLVE) {
-    solve_body(J, st, flags & RD_BUILD ? J.phi : J.phi0, st->n_phi, s_w, L.s);
-    __syncthreads();
-  }
-  const uint64_t* F = full_of(J);
   const bool timed = flags & RD_TIMED;
   uint64_t t0 = timed ? wall_clock64() : 0;
   auto lap = [&](uint32_t& ticks) {        // (thread 0's clock)
@@ -318,72 +346,111 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
     t0 = t;
   };
   const bool loop = flags & (RD_LOOP | RD_LEARN);
-  for (uint32_t r = 0; loop && st->state == ST_RUN; r++) {
-    // ---- Verify
-    const uint64_t x = st->x, div = x & J.div_if_enabled;
-    const uint32_t n_full = st->n_full & 0xFFFFu, n_rows = st->n_full >> 16;
+  const uint32_t n_full = st->n_full & 0xFFFFu, n_rows = st->n_full >> 16;
+  const uint64_t* masks = one ? rows_of(J) : full_of(J);   // what Verify tests
+  rp_clause* phi = J.phi;
+  uint32_t saved = st->rounds;             // rounds of the trajectory that are written out
+  bool near = one && loop && st->state == ST_RUN && st->n_phi <= WV_CLAUSES && n_rows <= NEAR;
+  if (near) {
+    __syncthreads();                       // (the tables' LDS is free)
+    for (uint32_t q = tid; q < n_rows; q += RD_BLOCK) near_masks(L.s)[q] = masks[q];
+    for (uint32_t q = tid; q < st->n_phi; q += RD_BLOCK) near_phi(L.s)[q] = phi[q];
+    masks = near_masks(L.s);
+    phi = near_phi(L.s);
+    __syncthreads();
+  }
+  bool keyed = false;                      // s_keys is there (a job may end without a Solve)
+  bool first = flags & RD_SOLVE;           // the Solve before the rounds
+  for (uint32_t r = 0; first || (loop && st->state == ST_RUN); r++) {
     uint32_t n = st->n_phi;
-    if (tid == 0) s_row = NONE32;
-    __syncthreads();                       // (everyone has read the state)
-    uint32_t mine = NONE32;
-    if (!one) {
-      for (uint32_t q = tid; q < n_full && mine == NONE32; q += RD_BLOCK)
-        if ((F[q] & x) == 0) mine = q;
-    } else if (div == 0) {
-      // the smallest racing row, same-block rows first
-      const uint64_t* rows = rows_of(J);
-      for (uint32_t q = tid; q < n_rows && mine == NONE32; q += RD_BLOCK)
-        if ((rows[q] & x) == 0) mine = q;
-    }
-    if (mine != NONE32) atomicMin(&s_row, mine);
-    if (tid == 0) {
-      if (J.traj && st->rounds < J.traj_cap) J.traj[st->rounds] = x;
-      st->rounds += 1;
-      st->divergent = div;
-    }
-    __syncthreads();
-    const uint32_t row = s_row;
-    lap(st->t_check);
     bool solve = true;
-    if (row == NONE32 && div == 0) {
-      // SAFE; under the mhs strategy the exact query still decides
-      if (st->phase != PH_GREEDY || (flags & RD_LEARN)) solve = false;
-      __syncthreads();
-      if (tid == 0) {
-        if (st->phase == PH_GREEDY) st->phase = PH_FINAL;
-        else st->state = ST_SAFE;
+    if (!first) {
+      // ---- Verify
+      const uint64_t x = st->x, div = x & J.div_if_enabled;
+      // (one trace: the smallest racing row, same-block rows first)
+      const uint32_t nm = !one ? n_full : div == 0 ? n_rows : 0;
+      uint32_t mine = NONE32;
+      for (uint32_t b = wv * 64; b < nm && mine == NONE32; b += RD_BLOCK) {
+        const uint64_t m = __ballot(b + lane < nm && (masks[b + lane] & x) == 0);
+        if (m) mine = b + (uint32_t)__builtin_ctzll(m);
       }
-    } else {
-      // ---- GenerateClause
-      if (!one) {
-        n = learn_all(J, x, div, n, n_full, sm);
-      } else {
-        rp_clause c{0, div & (~div + 1)};
-        if (div == 0) c.pos = rows_of(J)[row];
-        n = learn_one(J, c, n, &s_n);
+      if (lane == 0) s_hit[wv] = mine;
+      if (tid == 0) {
+        if (near) near_traj(L.s)[st->rounds - saved] = x;
+        else if (J.traj && st->rounds < J.traj_cap) J.traj[st->rounds] = x;
+        st->rounds += 1;
+        st->divergent = div;
       }
       __syncthreads();
-      if (tid == 0) {
-        st->n_phi = n;
-        if (n > J.phi_cap) {
-          st->err = ERR_PHI_CAP;
-          st->state = ST_ERROR;
+      uint32_t row = NONE32;
+      for (int q = 0; q < RD_WAVES; q++) row = s_hit[q] < row ? s_hit[q] : row;
+      lap(st->t_check);
+      if (row == NONE32 && div == 0) {
+        // SAFE; under the mhs strategy the exact query still decides
+        if (st->phase != PH_GREEDY || (flags & RD_LEARN)) solve = false;
+        __syncthreads();
+        if (tid == 0) {
+          if (st->phase == PH_GREEDY) st->phase = PH_FINAL;
+          else st->state = ST_SAFE;
         }
+      } else {
+        // ---- GenerateClause
+        if (!one) {
+          n = learn_all(phi, J.phi_cap, x, div, n, masks, n_full, sm);
+        } else {
+          rp_clause c{0, div & (~div + 1)};
+          if (div == 0) c.pos = masks[row];
+          n = learn_one(phi, near ? NEAR : J.phi_cap, c, n, &s_n);
+        }
+        __syncthreads();
+        if (tid == 0) {
+          st->n_phi = n;
+          if (n > J.phi_cap) {
+            st->err = ERR_PHI_CAP;
+            st->state = ST_ERROR;
+          }
+        }
+        if (n > J.phi_cap) solve = false;
       }
-      if (n > J.phi_cap) solve = false;
-    }
-    __syncthreads();
-    lap(st->t_clause);
-    if (flags & RD_LEARN) break;
-    if (solve) {
-      solve_body(J, st, J.phi, n, s_w, L.s);
       __syncthreads();
+      lap(st->t_clause);
+      if (flags & RD_LEARN) break;
+      if (near && (n > WV_CLAUSES || st->rounds - saved == NEAR)) {
+        // written out; phi and the masks stay in memory once phi is long
+        save_traj(J, L.s, saved, st->rounds);
+        saved = st->rounds;
+        if (n > WV_CLAUSES) {
+          for (uint32_t q = tid; q < n && q < J.phi_cap; q += RD_BLOCK) J.phi[q] = phi[q];
+          near = false;
+          phi = J.phi;
+          masks = rows_of(J);
+        }
+        __syncthreads();
+      }
+    }
+    // (a lone Solve reads its clauses where they are)
+    if (solve && !keyed) {
+      slot_keys(J, s_keys);
+      keyed = true;
+      __syncthreads();
+    }
+    if (solve) solve_body(J, st, first && !(flags & RD_BUILD) ? J.phi0 : phi, n, s_keys, L.s);
+    __syncthreads();
+    if (first) {
+      first = false;
+      r--;
+      if (timed) t0 = wall_clock64();
+      continue;
     }
     lap(st->t_solve);
-    __syncthreads();
     if ((limit != 0 && r + 1 == limit) || r + 1 == ROUNDS_MAX) break;
   }
   __syncthreads();
+  if (near) {
+    save_traj(J, L.s, saved, st->rounds);
+    for (uint32_t q = tid; q < st->n_phi && q < J.phi_cap; q += RD_BLOCK) J.phi[q] = phi[q];
+    __syncthreads();
+  }
   if (tid < sizeof(JobState) / 4) ((uint32_t*)J.st)[tid] = ((const uint32_t*)st)[tid];
   if (call.page) {
     // (a call over one job)

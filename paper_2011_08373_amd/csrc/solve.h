@@ -44,12 +44,15 @@
 // lane: every wave then runs the greedy strategy and the reduction alike, with
 // no barrier and no LDS.  More are staged in LDS (up to SV_CLAUSES; more again
 // are read from memory until few enough are open) and reduced by the whole
-// workgroup until they fit a wave.  Bound: latency, a chain of reductions.  Measured: 300 runs over 56 slots of weights
-// 1 to 10, 82 us by reduction and path, 1 to 90 ms (over a second at 64 slots)
-// by the search alone; the 35 greedy Solves of plain-large one trace at a time
-// 0.24 ms in a wave's registers, 0.73 ms with a barrier per pick, 2.4 ms with
-// LDS counters per slot and one thread comparing them; 512 instrumented
-// programs to their verdicts 0.10 ms, 0.14 ms reduced with barriers, 0.47 ms by
+// workgroup until they fit a wave.  Bound: latency, a chain of reductions: keys
+// are compared in 32 bits where they fit, and what a wave does not need is out
+// of line.  Measured: 300 runs over 56 slots of weights 1 to 10, 69 us by
+// reduction and path (81 us with 64-bit keys and one clause read at a time), 1
+// to 90 ms (over a second at 64 slots) by the search alone; the 35 greedy rounds
+// of plain-large one trace at a time 0.25 ms, 0.36 ms with 64-bit keys, weights
+// compared slot by slot and phi in memory, 0.85 ms with a barrier per pick, 2.5
+// ms with LDS counters per slot and one thread comparing them; 512 instrumented
+// programs to their verdicts 0.09 ms, 0.14 ms reduced with barriers, 0.47 ms by
 // enumeration alone.
 #pragma once
 #include "common.h"
@@ -72,6 +75,9 @@ __device__ __forceinline__ uint64_t lane_value(uint64_t v, uint32_t l) {   // v 
   return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l) << 32) |
          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
 }
+
+// Whether lane l's bit of the uniform mask m is set.
+__device__ __forceinline__ bool lane_bit(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // OR over the wave (DPP row shifts and broadcasts; the result is uniform).
 __device__ __forceinline__ uint32_t wave_or32(uint32_t v) {
@@ -113,6 +119,18 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
   v = mn(v, dpp64<0x143>(v));
   return lane_value(v, 63);
 }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  auto mn = [](uint32_t a, int b) { return (uint32_t)b < a ? (uint32_t)b : a; };
+  v = mn(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xF, 0xF, false));
+  v = mn(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xF, 0xF, false));
+  v = mn(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xF, 0xF, false));
+  v = mn(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xF, 0xF, false));
+  v = mn(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xF, 0xF, false));
+  v = mn(v, __builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xF, 0xF, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) { return wave_min_u32(v); }
+__device__ __forceinline__ uint64_t wave_min(uint64_t v) { return wave_min_u64(v); }
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) { return ~wave_min_u64(~v); }
 // Total weight of the slots of x (the same in every lane).
 __device__ __forceinline__ uint64_t weight_of(uint64_t x, const uint32_t* s_w) {
@@ -150,6 +168,29 @@ struct DfsFrame { uint64_t ones, zeros, khi, klo, todo, tried; };
 constexpr int SPLIT_DEPTH = 3;           // depth whose nodes are dealt out to the waves
 
 constexpr uint32_t GREEDY_MAX = 16384;   // clauses the greedy step handles
+
+// A job's weights and, per slot, the slots with a smaller key (LDS).
+struct SlotKeys {
+  uint32_t w[64];
+  union {
+    uint64_t less[64];
+    uint16_t part[64][SV_WAVES];           // (a quarter by each wave)
+  };
+};
+__device__ __forceinline__ void slot_keys(const Job& J, SlotKeys& K) {
+  static_assert(64 / SV_WAVES == 16, "a wave's quarter");
+  const uint32_t l = __lane_id(), wv = sv_uni(threadIdx.x >> 6), t0 = wv * 16;
+  const uint32_t w = l < J.S ? J.weights[l] : 0;
+  uint32_t m = 0;
+  if (t0 < J.S)
+#pragma unroll
+    for (uint32_t k = 0; k < 16; k++) {    // (a slot past the last one is in no clause)
+      const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)w, t0 + k);
+      m |= (o < w || (o == w && t0 + k < l) ? 1u : 0u) << k;
+    }
+  K.part[l][wv] = (uint16_t)m;
+  if (wv == 0) K.w[l] = w;
+}
 
 // LDS of the solver.
 struct SolveLds {
@@ -201,11 +242,15 @@ __device__ __forceinline__ void block_or(uint64_t (&v)[K], SolveLds& L, uint32_t
 // The lane (slot) with the largest c / w, the lowest one of equals; some c is
 // not 0.  From a first slot on, to the lowest slot that is better than it, as
 // long as there is one (every best slot is, so the last step meets the lowest).
+// NARROW: counts below 2^8 and weights below 2^24, a product in 32 bits.
+template <bool NARROW>
 __device__ __forceinline__ uint32_t best_slot(uint32_t c, uint32_t w) {
   auto of = [](uint32_t v, uint32_t l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
   uint32_t best = (uint32_t)__builtin_ctzll(__ballot(c != 0));
   for (;;) {
-    const uint64_t m = __ballot((uint64_t)c * of(w, best) > (uint64_t)of(c, best) * w);
+    const uint32_t cb = of(c, best), wb = of(w, best);
+    const uint64_t m = NARROW ? __ballot(__umul24(c, wb) > __umul24(cb, w))
+                              : __ballot((uint64_t)c * wb > (uint64_t)cb * w);
     if (m == 0) return best;
     best = (uint32_t)__builtin_ctzll(m);
   }
@@ -266,7 +311,7 @@ __device__ bool greedy_solve(const Job& J, const uint32_t* s_w, JobState* st, ui
     for (int q = 0; q < SV_WAVES; q++) c += L.c64[turn][q][lane];
     turn ^= 1;
     if (__ballot(c != 0) == 0) break;
-    const uint32_t best = best_slot(c, w);
+    const uint32_t best = best_slot<false>(c, w);
     x |= 1ull << best;
     if (lane == np) mine = best;
     np++;
@@ -326,14 +371,20 @@ __device__ __forceinline__ bool greedy_wave(uint32_t S, const uint32_t* s_w, Job
     const uint64_t p = c.on[g] && c.neg[g] == 0 ? c.pos[g] : 0;     // a positive clause
     todo[g] = __ballot(p != 0);
     hits[g] = 0;
-    if (todo[g] == 0) continue;
-    for (uint32_t s = 0; s < S; s++) {
-      const uint64_t m = __ballot((p >> s) & 1);
-      hits[g] = lane == s ? m : hits[g];
+    uint32_t lo = 0, hi = 0;
+    for (uint32_t m = (uint32_t)todo[g]; m; m &= m - 1) {
+      const uint32_t r = (uint32_t)__builtin_ctz(m);
+      if (lane_bit(lane_value(p, r))) lo |= 1u << r;
     }
+    for (uint32_t m = (uint32_t)(todo[g] >> 32); m; m &= m - 1) {
+      const uint32_t r = (uint32_t)__builtin_ctz(m);
+      if (lane_bit(lane_value(p, 32 + r))) hi |= 1u << r;
+    }
+    hits[g] = (uint64_t)hi << 32 | lo;
   }
   if (__ballot(empty)) return false;
   const uint32_t w = lane < S ? s_w[lane] : 1;
+  const bool narrow = __ballot(w >= 1u << 24) == 0;
   uint64_t x = 0;
   uint32_t np = 0, mine = 0;               // picks; lane q keeps the q-th
   for (;;) {
@@ -341,7 +392,7 @@ __device__ __forceinline__ bool greedy_wave(uint32_t S, const uint32_t* s_w, Job
 #pragma unroll
     for (int g = 0; g < G; g++) k += (uint32_t)__popcll(hits[g] & todo[g]);
     if (__ballot(k != 0) == 0) break;
-    const uint32_t best = best_slot(k, w);
+    const uint32_t best = narrow ? best_slot<true>(k, w) : best_slot<false>(k, w);
     x |= 1ull << best;
     if (lane == np) mine = best;
     np++;
@@ -368,24 +419,15 @@ __device__ __forceinline__ bool greedy_wave(uint32_t S, const uint32_t* s_w, Job
 // The slots of core that another one makes needless: d has the slots in every
 // open clause of the lane's slot, negs those in a negative literal.
 __device__ __forceinline__ uint64_t needless(uint64_t d, uint64_t core, uint64_t negs,
-                                             const uint32_t* s_w) {
-  const uint32_t lane = __lane_id();
-  bool worse = false;
-  if ((core >> lane) & 1) {
-    const uint32_t w = s_w[lane];
-    for (uint64_t t = d & core & ~negs & ~(1ull << lane); t && !worse; t &= t - 1) {
-      const uint32_t b = (uint32_t)__builtin_ctzll(t);
-      worse = s_w[b] < w || (s_w[b] == w && b < lane);
-    }
-  }
-  return __ballot(worse);
+                                             const uint64_t* less) {
+  return core & __ballot((d & core & ~negs & less[__lane_id()]) != 0);
 }
 
 // The reduction on clauses held by every wave alike, to its fixpoint: on and
 // off grow, satisfied and subsumed clauses go, the others are restricted to
 // the free slots.  Returns false when they cannot be satisfied.
 template <int G>
-__device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, const uint32_t* s_w,
+__device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, const uint64_t* less,
                                             uint64_t& on, uint64_t& off) {
   const uint32_t lane = __lane_id();
   for (;;) {
@@ -415,7 +457,7 @@ __device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, con
     const uint64_t nz = all & ~on & ~off & ~non & ~noff & ~core;
     on |= non;
     off |= noff | nz;
-    if (non | noff | nz) continue;
+    if (non | noff | (nz & negs)) continue;
     if (core == 0) return true;
     // every clause past every lane: as a slot, the lane keeps what is in all
     // clauses of its slot; as a clause, it is dropped for a subset
@@ -423,14 +465,25 @@ __device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, con
     bool dead[G] = {};
 #pragma unroll
     for (int h = 0; h < G; h++) {
-      for (uint64_t m = __ballot(c.on[h]); m; m &= m - 1) {
-        const uint32_t r = (uint32_t)__builtin_ctzll(m);
-        const uint64_t p = lane_value(c.pos[h], r), q = lane_value(c.neg[h], r);
-        if ((p >> lane) & 1) d &= p;
+      if (negs == 0) {
+        for (uint64_t m = __ballot(c.on[h]); m; m &= m - 1) {
+          const uint32_t r = (uint32_t)__builtin_ctzll(m);
+          const uint64_t p = lane_value(c.pos[h], r);
+          if (lane_bit(p)) d &= p;
 #pragma unroll
-        for (int g = 0; g < G; g++)
-          dead[g] = dead[g] || ((p & ~c.pos[g]) == 0 && (q & ~c.neg[g]) == 0 &&
-                                (p != c.pos[g] || q != c.neg[g] || 64 * h + r < 64 * g + lane));
+          for (int g = 0; g < G; g++)
+            dead[g] = dead[g] || ((p & ~c.pos[g]) == 0 && (p != c.pos[g] || 64 * h + r < 64 * g + lane));
+        }
+      } else {
+        for (uint64_t m = __ballot(c.on[h]); m; m &= m - 1) {
+          const uint32_t r = (uint32_t)__builtin_ctzll(m);
+          const uint64_t p = lane_value(c.pos[h], r), q = lane_value(c.neg[h], r);
+          if (lane_bit(p)) d &= p;
+#pragma unroll
+          for (int g = 0; g < G; g++)
+            dead[g] = dead[g] || ((p & ~c.pos[g]) == 0 && (q & ~c.neg[g]) == 0 &&
+                                  (p != c.pos[g] || q != c.neg[g] || 64 * h + r < 64 * g + lane));
+        }
       }
     }
     bool died = false;
@@ -439,7 +492,7 @@ __device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, con
       died = died || (c.on[g] && dead[g]);
       c.on[g] = c.on[g] && !dead[g];
     }
-    const uint64_t drop = needless(d, core, negs, s_w);
+    const uint64_t drop = needless(d, core, negs, less);
     off |= drop;
     if (drop == 0 && __ballot(died) == 0) return true;
   }
@@ -449,7 +502,7 @@ __device__ __forceinline__ bool reduce_wave(WaveClauses<G>& c, uint64_t all, con
 // and, with DOM (clauses in LDS), by slots another one makes needless.
 // Returns false when the clauses cannot be satisfied.
 template <bool DOM, class G>
-__device__ bool propagate(G get, uint32_t n, uint64_t all, const uint32_t* s_w, uint64_t& on,
+__device__ bool propagate(G get, uint32_t n, uint64_t all, const uint64_t* less, uint64_t& on,
                           uint64_t& off, SolveLds& L, uint32_t& turn) {
   const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = sv_uni(tid >> 6);
   for (;;) {
@@ -484,7 +537,7 @@ __device__ bool propagate(G get, uint32_t n, uint64_t all, const uint32_t* s_w, 
     __syncthreads();
     for (int q = 0; q < SV_WAVES; q++) d &= L.dom[turn][q][lane];
     turn ^= 1;
-    const uint64_t drop = needless(d, core, v[3], s_w);
+    const uint64_t drop = needless(d, core, v[3], less);
     if (drop == 0) return true;
     off |= drop;
   }
@@ -497,48 +550,54 @@ __device__ bool propagate(G get, uint32_t n, uint64_t all, const uint32_t* s_w, 
 // follow a chosen slot p exactly when no clause lies wholly between them,
 // that is when p >= the largest first slot of the clauses that end before s.
 // Every wave computes the same; lane p keeps the best key of a choice that
-// ends with p.  A run of linked slots longer than ENUM_MAX and than the node
-// budget counts as a search that spends it (returns false).
-__device__ bool interval_optimum(uint64_t M, const uint32_t* s_w, uint64_t budget, int32_t fl,
-                                 int32_t ll, uint64_t& answer) {
+// ends with p, its first part in an H.  A run of linked slots longer than
+// ENUM_MAX and than the node budget counts as a search that spends it (returns
+// false).
+template <class H>
+__device__ __forceinline__ bool interval_path(uint64_t M, const uint32_t* s_w, uint64_t budget,
+                                              int32_t fl, int32_t ll, uint64_t& answer) {
   const uint32_t lane = __lane_id();
-  const uint32_t w = (M >> lane) & 1 ? s_w[lane] : 0;
-  uint64_t bh = ~0ull, bl = 0;             // this lane's best key
+  const bool slot = lane_bit(M);
+  const H w = slot ? (H)s_w[lane] * 128u + 1u : 0;
+  H bh = (H)~(H)0;                         // this lane's best key
+  uint64_t bl = 0;
   int32_t need = -1, reach = -1;           // largest first slot that ended; last slot reached
   uint32_t run = 0;
+  // the least key of the lanes in
+  auto least = [&](bool in, H& h) {
+    h = wave_min(in ? bh : (H)~(H)0);
+    uint64_t tie = __ballot(in && bh == h);
+    uint64_t l = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
+    for (tie &= tie - 1; tie; tie &= tie - 1) {
+      const uint64_t o = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
+      l = o < l ? o : l;
+    }
+    return l;
+  };
   for (uint64_t m = M; m; m &= m - 1) {
     const uint32_t s = (uint32_t)__builtin_ctzll(m);
     run = reach >= (int32_t)s ? run + 1 : 1;
     if (run > (uint32_t)ENUM_MAX && run > budget) return false;
-    Key k = {0, 0};                        // nothing before s has to be hit
-    if (need >= 0) {
-      const bool in = lane < s && (int32_t)lane >= need && ((M >> lane) & 1);
-      const uint64_t h = wave_min_u64(in ? bh : ~0ull);
-      uint64_t tie = __ballot(in && bh == h);
-      k.hi = h;
-      k.lo = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
-      for (tie &= tie - 1; tie; tie &= tie - 1) {
-        const uint64_t o = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
-        k.lo = o < k.lo ? o : k.lo;
-      }
-    }
+    H h = 0;                               // nothing before s has to be hit
+    uint64_t l = 0;
+    if (need >= 0) l = least(slot && lane < s && (int32_t)lane >= need, h);
     if (lane == s) {
-      bh = k.hi + (uint64_t)w * 128u + 1u;
-      bl = k.lo | 1ull << s;
+      bh = h + w;
+      bl = l | 1ull << s;
     }
-    const int32_t f = __builtin_amdgcn_readlane(fl, s), l = __builtin_amdgcn_readlane(ll, s);
+    const int32_t f = __builtin_amdgcn_readlane(fl, s), e = __builtin_amdgcn_readlane(ll, s);
     need = f > need ? f : need;
-    reach = l > reach ? l : reach;
+    reach = e > reach ? e : reach;
   }
-  const bool in = (int32_t)lane >= need && ((M >> lane) & 1);
-  const uint64_t h = wave_min_u64(in ? bh : ~0ull);
-  uint64_t tie = __ballot(in && bh == h);
-  answer = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
-  for (tie &= tie - 1; tie; tie &= tie - 1) {
-    const uint64_t o = lane_value(bl, (uint32_t)__builtin_ctzll(tie));
-    answer = o < answer ? o : answer;
-  }
+  H h;
+  answer = least(slot && (int32_t)lane >= need, h);
   return true;
+}
+__device__ __forceinline__ bool interval_optimum(uint64_t M, const uint32_t* s_w, uint64_t budget,
+                                                 int32_t fl, int32_t ll, uint64_t& answer) {
+  // (a key's first part is at most 128 times the total weight and 64)
+  return weight_of(M, s_w) < (1u << 25) - 1 ? interval_path<uint32_t>(M, s_w, budget, fl, ll, answer)
+                                            : interval_path<uint64_t>(M, s_w, budget, fl, ll, answer);
 }
 
 // Whether the clauses U[0..n) inside the slots M are all positive contiguous
@@ -602,15 +661,15 @@ __device__ __forceinline__ bool wave_intervals(const WaveClauses<G>& c, uint64_t
 // the job has failed.
 template <int G>
 __device__ bool solve_wave(const Job& J, JobState* st, const rp_clause* W, uint32_t& n, uint64_t all,
-                           const uint32_t* s_w, SolveLds& L, int wv, uint64_t& on, uint64_t& off,
+                           const SlotKeys& K, SolveLds& L, int wv, uint64_t& on, uint64_t& off,
                            bool& sat, uint64_t& result, uint64_t& left) {
   WaveClauses<G> c = wave_clauses<G>(W, n);
-  sat = reduce_wave(c, all, s_w, on, off);
+  sat = reduce_wave(c, all, K.less, on, off);
   left = sat ? all & ~on & ~off : 0;
   if (left == 0) return true;
   int32_t fl, ll;
   if (wave_intervals(c, left, fl, ll)) {
-    if (!interval_optimum(left, s_w, J.node_limit, fl, ll, result)) {
+    if (!interval_optimum(left, K.w, J.node_limit, fl, ll, result)) {
       if (threadIdx.x == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
       return false;
     }
@@ -631,122 +690,119 @@ __device__ bool solve_wave(const Job& J, JobState* st, const rp_clause* W, uint3
   return true;
 }
 
-// Solve over phi = C[0..n) for the job state *st (in LDS; thread 0 writes it):
-// x and weight, or a final state.  s_w: the slots' weights (LDS).  Every
-// thread of the workgroup calls it.
-__device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint32_t n,
-                           const uint32_t* s_w, SolveLds& L) {
+// The rest of Solve, by the whole workgroup and out of line: the rounds' code is
+// what is left of solve_body.
+//
+// Clauses too many for a wave: the greedy strategy (answered), the reduction
+// and, over all that is left, the path.
+struct Reduced {
+  uint64_t on, off, result, left;
+  rp_clause* U;                            // open clauses
+  uint32_t nu;
+  bool sat, answered;
+};
+__device__ __noinline__ Reduced reduce_many(const Job& J, JobState* st, const rp_clause* C, uint32_t n,
+                                            uint64_t all, uint32_t phase, const SlotKeys& K,
+                                            SolveLds& L) {
+  const uint32_t tid = threadIdx.x, lane = __lane_id();
+  uint32_t turn = 0;
+  Reduced R{0, 0, 0, 0, L.cl, n, true, true};
+  const bool lds = n <= SV_CLAUSES;
+  if (lds)
+    for (uint32_t q = tid; q < n; q += SV_BLOCK) L.cl[q] = C[q];
+  __syncthreads();
+  auto in_lds = [&](uint32_t q) { return L.cl[q]; };
+  auto in_memory = [&](uint32_t q) { return C[q]; };
+  if (phase == PH_GREEDY && (lds ? greedy_solve<true>(J, K.w, st, n, in_lds, L, turn)
+                                 : greedy_solve<false>(J, K.w, st, n, in_memory, L, turn)))
+    return R;
+  R.sat = lds ? propagate<false>(in_lds, n, all, K.less, R.on, R.off, L, turn)
+              : propagate<false>(in_memory, n, all, K.less, R.on, R.off, L, turn);
+  if (R.sat && !lds) {
+    // the open clauses alone, restricted, into LDS if they fit, else into the
+    // first phi_cap clauses of scratch (which hold at least n)
+    uint64_t open = 0;
+    if (tid == 0) L.cnt = 0;
+    __syncthreads();
+    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+      const rp_clause c = C[q];
+      if (!(c.pos & R.on) && !(c.neg & R.off)) open++;
+    }
+    if (open) atomicAdd(&L.cnt, (uint32_t)open);
+    __syncthreads();
+    if (L.cnt > SV_CLAUSES) R.U = J.scratch;
+    __syncthreads();
+    if (tid == 0) L.cnt = 0;
+    __syncthreads();
+    for (uint32_t q = tid; q < n; q += SV_BLOCK) {
+      const rp_clause c = C[q];
+      if ((c.pos & R.on) || (c.neg & R.off)) continue;
+      R.U[atomicAdd(&L.cnt, 1u)] = rp_clause{c.pos & ~R.off, c.neg & ~R.on};
+    }
+    __syncthreads();
+    R.nu = L.cnt;
+  }
+  // restrict, drop the satisfied and the subsumed; reduce again until that
+  // changes nothing, or until a wave can hold them
+  while (R.sat && R.nu && R.U == L.cl) {
+    for (uint32_t q = tid; q < R.nu; q += SV_BLOCK) {
+      const rp_clause c = L.cl[q];
+      L.cl[q] = (c.pos & R.on) || (c.neg & R.off) ? rp_clause{~0ull, ~0ull}     // (a tautology)
+                                                  : rp_clause{c.pos & ~R.off, c.neg & ~R.on};
+    }
+    if (tid == 0) L.cnt = 0;
+    __syncthreads();
+    for (uint32_t q = tid; q < R.nu; q += SV_BLOCK) {
+      const rp_clause c = L.cl[q];
+      bool dead = (c.pos & c.neg) != 0;
+      for (uint32_t r = 0; r < R.nu && !dead; r += 8) {      // (eight reads in flight)
+#pragma unroll
+        for (uint32_t k = 0; k < 8; k++) {
+          const rp_clause d = L.cl[r + k];
+          dead = dead || (r + k < R.nu && (d.pos & ~c.pos) == 0 && (d.neg & ~c.neg) == 0 &&
+                          (d.pos != c.pos || d.neg != c.neg || r + k < q));
+        }
+      }
+      if (!dead) L.u[atomicAdd(&L.cnt, 1u)] = c;
+    }
+    __syncthreads();
+    R.nu = L.cnt;
+    const uint64_t fixed = R.on | R.off;
+    const bool few = R.nu <= WV_CLAUSES;
+    if (!few)
+      R.sat = propagate<true>([&](uint32_t q) { return L.u[q]; }, R.nu, all, K.less, R.on, R.off, L, turn);
+    __syncthreads();
+    for (uint32_t q = tid; q < R.nu; q += SV_BLOCK) L.cl[q] = L.u[q];
+    __syncthreads();
+    if (few || fixed == (R.on | R.off)) break;
+  }
+  R.answered = false;
+  if (!R.sat || R.nu <= WV_CLAUSES) return R;
+  R.left = all & ~R.on & ~R.off;
+  if (R.left && R.U == L.cl && intervals_of(R.U, R.nu, R.left, L, turn)) {
+    if (!interval_optimum(R.left, K.w, J.node_limit, L.first[lane], L.last[lane], R.result)) {
+      if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
+      R.answered = true;
+    }
+    R.left = 0;
+  }
+  return R;
+}
+
+// The components of the slots left, with their nu open clauses U: the result,
+// or none (a final state).
+struct Found {
+  uint64_t result;
+  bool ok;
+};
+__device__ __noinline__ Found solve_components(const Job& J, JobState* st, const rp_clause* U,
+                                               uint32_t nu, uint64_t left, const SlotKeys& K,
+                                               SolveLds& L) {
   uint64_t *smA = L.smA, *smB = L.smB;
   const int tid = threadIdx.x, lane = __lane_id(), wv = tid >> 6;
-  const uint32_t S = J.S;
-  const uint64_t all = S >= 64 ? ~0ull : ((1ull << S) - 1);
-  const uint32_t phase = st->phase;
+  const bool paths = U == L.cl;            // (a component over more clauses is refused below)
   uint32_t turn = 0;
-  uint64_t on = 0, off = 0;
-  bool sat = true;
-  rp_clause* U = L.cl;
-  uint32_t nu = n;
-  // ---- 1. reduction
-  const rp_clause* W = C;   // the clauses of the waves' reduction, where there are few enough
-  if (n <= WV_CLAUSES) {
-    __syncthreads();        // (every thread has the phase before thread 0 may change it)
-    if (phase == PH_GREEDY && (n <= 64 ? greedy_wave(S, s_w, st, wave_clauses<1>(C, n))
-                                       : greedy_wave(S, s_w, st, wave_clauses<2>(C, n))))
-      return;
-  } else {
-    const bool lds = n <= SV_CLAUSES;
-    if (lds)
-      for (uint32_t q = tid; q < n; q += SV_BLOCK) L.cl[q] = C[q];
-    __syncthreads();
-    auto in_lds = [&](uint32_t q) { return L.cl[q]; };
-    auto in_memory = [&](uint32_t q) { return C[q]; };
-    if (phase == PH_GREEDY && (lds ? greedy_solve<true>(J, s_w, st, n, in_lds, L, turn)
-                                   : greedy_solve<false>(J, s_w, st, n, in_memory, L, turn)))
-      return;
-    sat = lds ? propagate<false>(in_lds, n, all, s_w, on, off, L, turn)
-              : propagate<false>(in_memory, n, all, s_w, on, off, L, turn);
-    if (sat && !lds) {
-      // the open clauses alone, restricted, into LDS if they fit, else into the
-      // first phi_cap clauses of scratch (which hold at least n)
-      uint64_t open = 0;
-      if (tid == 0) L.cnt = 0;
-      __syncthreads();
-      for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-        const rp_clause c = C[q];
-        if (!(c.pos & on) && !(c.neg & off)) open++;
-      }
-      if (open) atomicAdd(&L.cnt, (uint32_t)open);
-      __syncthreads();
-      if (L.cnt > SV_CLAUSES) U = J.scratch;
-      __syncthreads();
-      if (tid == 0) L.cnt = 0;
-      __syncthreads();
-      for (uint32_t q = tid; q < n; q += SV_BLOCK) {
-        const rp_clause c = C[q];
-        if ((c.pos & on) || (c.neg & off)) continue;
-        U[atomicAdd(&L.cnt, 1u)] = rp_clause{c.pos & ~off, c.neg & ~on};
-      }
-      __syncthreads();
-      nu = L.cnt;
-    }
-    // restrict, drop the satisfied and the subsumed; reduce again until that
-    // changes nothing, or until a wave can hold them
-    while (sat && nu && U == L.cl) {
-      for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
-        const rp_clause c = L.cl[q];
-        L.cl[q] = (c.pos & on) || (c.neg & off) ? rp_clause{~0ull, ~0ull}     // (a tautology)
-                                                : rp_clause{c.pos & ~off, c.neg & ~on};
-      }
-      if (tid == 0) L.cnt = 0;
-      __syncthreads();
-      for (uint32_t q = tid; q < nu; q += SV_BLOCK) {
-        const rp_clause c = L.cl[q];
-        bool dead = (c.pos & c.neg) != 0;
-        for (uint32_t r = 0; r < nu && !dead; r++) {
-          const rp_clause d = L.cl[r];
-          dead = (d.pos & ~c.pos) == 0 && (d.neg & ~c.neg) == 0 &&
-                 (d.pos != c.pos || d.neg != c.neg || r < q);
-        }
-        if (!dead) L.u[atomicAdd(&L.cnt, 1u)] = c;
-      }
-      __syncthreads();
-      nu = L.cnt;
-      const uint64_t fixed = on | off;
-      const bool few = nu <= WV_CLAUSES;
-      if (!few)
-        sat = propagate<true>([&](uint32_t q) { return L.u[q]; }, nu, all, s_w, on, off, L, turn);
-      __syncthreads();
-      for (uint32_t q = tid; q < nu; q += SV_BLOCK) L.cl[q] = L.u[q];
-      __syncthreads();
-      if (few || fixed == (on | off)) break;
-    }
-    W = U;
-  }
-  uint64_t result = 0, left = 0;
-  bool paths = U == L.cl;                  // (a component over more clauses is refused below)
-  if (sat && nu <= WV_CLAUSES) {
-    // ---- 2. in the waves; one path over all that is left
-    const bool done = nu <= 64 ? solve_wave<1>(J, st, W, nu, all, s_w, L, wv, on, off, sat, result, left)
-                               : solve_wave<2>(J, st, W, nu, all, s_w, L, wv, on, off, sat, result, left);
-    if (!done) return;
-    U = L.cl;
-  } else if (sat) {
-    left = all & ~on & ~off;
-    if (left && paths && intervals_of(U, nu, left, L, turn)) {
-      uint64_t x;
-      if (!interval_optimum(left, s_w, J.node_limit, L.first[lane], L.last[lane], x)) {
-        if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
-        return;
-      }
-      result = x;
-      left = 0;
-    }
-  }
-  if (!sat) {
-    if (tid == 0) st->state = ST_UNSAT;
-    return;
-  }
-  result |= on;
+  uint64_t result = 0;
   while (left) {
     // ---- 3. component of the lowest free slot
     uint64_t comp = left & (~left + 1);
@@ -764,9 +820,9 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
     const int k = __popcll(comp);
     if (paths && intervals_of(U, nu, comp, L, turn)) {
       uint64_t x;
-      if (!interval_optimum(comp, s_w, J.node_limit, L.first[lane], L.last[lane], x)) {
+      if (!interval_optimum(comp, K.w, J.node_limit, L.first[lane], L.last[lane], x)) {
         if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
-        return;
+        return Found{0, false};
       }
       result |= x;
       continue;
@@ -775,7 +831,7 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
     if (tid < 64 && ((comp >> lane) & 1)) {
       const uint32_t b = (uint32_t)__popcll(comp & lanemask_lt());
       L.gslot[b] = lane;
-      L.kh[b] = (uint64_t)s_w[lane] * 128u + 1u;
+      L.kh[b] = (uint64_t)K.w[lane] * 128u + 1u;
       L.kl[b] = 1ull << lane;
     }
     if (tid == 0) L.cnt = 0;
@@ -807,7 +863,7 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
     const uint32_t nc = L.cnt;
     if (nc > SV_CLAUSES) {
       if (tid == 0) { st->err = ERR_SCRATCH; st->state = ST_ERROR; }
-      return;
+      return Found{0, false};
     }
     Key best = {~0ull, ~0ull};
     if (enumerate) {
@@ -965,7 +1021,7 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
       __syncthreads();
       if (L.overflow) {
         if (tid == 0) { st->err = ERR_NODES; st->state = ST_ERROR; }
-        return;
+        return Found{0, false};
       }
       best.hi = L.inch[0];
       best.lo = L.incl[0];
@@ -977,12 +1033,62 @@ __device__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint3
     }
     if (best.hi == ~0ull && best.lo == ~0ull) {
       if (tid == 0) st->state = ST_UNSAT;
-      return;
+      return Found{0, false};
     }
     result |= best.lo;   // lo is the global mask of the component's optimum
     __syncthreads();
   }
-  const uint64_t weight = weight_of(result, s_w);
+  return Found{result, true};
+}
+
+// Solve over phi = C[0..n) for the job state *st (in LDS; thread 0 writes it):
+// x and weight, or a final state.  K: the job's keys (LDS).  Every
+// thread of the workgroup calls it.
+__device__ __forceinline__ void solve_body(const Job& J, JobState* st, const rp_clause* C, uint32_t n,
+                                           const SlotKeys& K, SolveLds& L) {
+  const int tid = threadIdx.x, wv = tid >> 6;
+  const uint32_t S = J.S;
+  const uint64_t all = S >= 64 ? ~0ull : ((1ull << S) - 1);
+  const uint32_t phase = st->phase;
+  uint64_t on = 0, off = 0, result = 0, left = 0;
+  bool sat = true;
+  const rp_clause* U = C;                  // the clauses to reduce further
+  uint32_t nu = n;
+  __syncthreads();          // (every thread has the phase before thread 0 may change it)
+  // ---- 1. reduction
+  if (n <= WV_CLAUSES) {
+    if (phase == PH_GREEDY && (n <= 64 ? greedy_wave(S, K.w, st, wave_clauses<1>(C, n))
+                                       : greedy_wave(S, K.w, st, wave_clauses<2>(C, n))))
+      return;
+  } else {
+    const Reduced R = reduce_many(J, st, C, n, all, phase, K, L);
+    if (R.answered) return;
+    on = R.on;
+    off = R.off;
+    result = R.result;
+    left = R.left;
+    sat = R.sat;
+    U = R.U;
+    nu = R.nu;
+  }
+  if (sat && nu <= WV_CLAUSES) {
+    // ---- 2. in the waves; one path over all that is left
+    const bool done = nu <= 64 ? solve_wave<1>(J, st, U, nu, all, K, L, wv, on, off, sat, result, left)
+                               : solve_wave<2>(J, st, U, nu, all, K, L, wv, on, off, sat, result, left);
+    if (!done) return;
+    U = L.cl;
+  }
+  if (!sat) {
+    if (tid == 0) st->state = ST_UNSAT;
+    return;
+  }
+  result |= on;
+  if (left) {
+    const Found f = solve_components(J, st, U, nu, left, K, L);
+    if (!f.ok) return;
+    result |= f.result;
+  }
+  const uint64_t weight = weight_of(result, K.w);
   if (tid == 0) {
     if (phase == PH_FINAL) {
       // the exact query after the greedy answer was verified SAFE

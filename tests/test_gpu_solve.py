@@ -90,3 +90,44 @@ def test_greedy_and_exact_on_ragged_kernels(L):  # noqa: F811
             assert same_repair(L.repair(km, policy=policy), o), (seed, policy)
             g = L.repair(km, policy=policy, solver=1)
             assert (g["status"], g["assign"], g["weight"]) == (o["status"], o["assign"], o["weight"])
+
+
+def _races(S, groups, between, wmax, seed):
+    """groups of races with between random slots each, on words of their own;
+    below three, one word written twice by either thread in turn instead."""
+    rng = np.random.default_rng(seed)
+    pts = [dict(kind=1, slot=s) for s in range(S)]
+
+    def write(thread, word):
+        return dict(kind=0, is_write=1, array=0, guard=1 + thread, a=0, b=0, c=word)
+
+    for g in range(groups):
+        gap = [dict(kind=1, slot=int(s)) for s in rng.choice(S, between, replace=False)]
+        if between < 3:
+            pts += [write(g % 2, 0), write(g % 2, 0)] + gap
+        else:
+            pts += [write(0, g)] + gap + [write(1, g)]
+    slots = [(0, 0, int(w)) for w in rng.integers(max(1, wmax // 2), wmax + 1, size=S)]
+    return synth.make_kernel(1, 2, [(groups, 0)], [(1, 0), (2, 0), (2, 1)], pts, slots)
+
+
+# phi past the 128 clauses of a wave in the middle of the rounds, more racing
+# rows than the rounds keep near (1,408), and weights around what is compared
+# in 32 bits (2^24 for the greedy picks, a total of 2^25 for the path)
+@pytest.mark.parametrize("S,groups,between,wmax", [
+    (14, 300, 3, 3), (15, 400, 3, 3), (20, 1000, 2, 1), (30, 60, 3, 2**24 - 1), (30, 60, 3, 2**24),
+    (30, 60, 3, 2**32 - 1)])
+def test_long_one_trace_rounds(L, S, groups, between, wmax):  # noqa: F811
+    km = _races(S, groups, between, wmax, S + groups)
+    o = O.repair(km, policy=1, solver=1)
+    g = L.repair(km, policy=1, solver=1)
+    assert same_repair(g, o), (g, o)
+
+
+@pytest.mark.parametrize("total", [2**25 - 2, 2**25 - 1, 2**25])
+def test_path_weights(L, total):  # noqa: F811
+    for S in (21, 64):
+        rng = np.random.default_rng(S)
+        cl = _runs(rng, S, 2 * S, 6)
+        w = [total // S] * (S - 1) + [total - total // S * (S - 1)]
+        assert L.min_barriers(cl, w, S) == _best_runs(cl, w, S)
