@@ -93,6 +93,33 @@ struct Unsigned<int32_t> { using type = uint32_t; };
 template <>
 struct Unsigned<int64_t> { using type = uint64_t; };
 
+// Division by a fixed d > 0, rounded down.  In 32 bits by a reciprocal in
+// double precision: for a numerator |x| < 2^31, x + 1/2 is at least 1/2 from
+// every multiple of d, 2^-32 of x, and the reciprocal is right to 40 bits.
+// (An integer division is 25 instructions, five of them quarter rate; this is
+// four, and four for the reciprocal.)
+template <class I>
+struct Divisor;
+template <>
+struct Divisor<int32_t> {
+  double inv;
+  RP_HD explicit Divisor(int32_t d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double r = __builtin_amdgcn_rcp((double)d);
+    inv = r + r * (1.0 - (double)d * r);
+#else
+    inv = 1.0 / (double)d;
+#endif
+  }
+  RP_HD int32_t floor(int32_t x) const { return (int32_t)__builtin_floor(((double)x + 0.5) * inv); }
+};
+template <>
+struct Divisor<int64_t> {
+  int64_t d;
+  RP_HD explicit Divisor(int64_t by) : d(by) {}
+  RP_HD int64_t floor(int64_t x) const { return x >= 0 ? x / d : -((d - 1 - x) / d); }
+};
+
 template <class I>
 RP_HD I gcd_of(I x, I y) {     // x, y >= 0
   while (y != 0) {
@@ -102,15 +129,23 @@ RP_HD I gcd_of(I x, I y) {     // x, y >= 0
   }
   return x;
 }
+template <>
+RP_HD int32_t gcd_of<int32_t>(int32_t x, int32_t y) {
+  while (y != 0) {
+    const int32_t t = x - Divisor<int32_t>(y).floor(x) * y;
+    x = y;
+    y = t;
+  }
+  return x;
+}
 
 // Inverse of p mod n (n >= 2, gcd(p, n) = 1), in [1, n).
 template <class I>
 RP_HD I inverse_of(I p, I n) {
-  I r0 = n, r1 = p % n;
-  if (r1 < 0) r1 += n;
+  I r0 = n, r1 = p - Divisor<I>(n).floor(p) * n;
   I t0 = 0, t1 = 1;
   while (r1 > 1) {
-    const I q = r0 / r1;
+    const I q = Divisor<I>(r1).floor(r0);
     const I r2 = r0 - q * r1, t2 = t0 - q * t1;
     r0 = r1;
     r1 = r2;
@@ -121,11 +156,11 @@ RP_HD I inverse_of(I p, I n) {
 }
 
 // a * b mod n for a, b in [0, n)
-RP_HD int32_t mul_mod(int32_t a, int32_t b, int32_t n) {
-  if (n <= 46340) return a * b % n;
+RP_HD int32_t mul_mod(int32_t a, int32_t b, int32_t n, const Divisor<int32_t>& by) {
+  if (n <= 46340) return a * b - by.floor(a * b) * n;
   return (int32_t)((uint64_t)a * (uint64_t)b % (uint64_t)n);
 }
-RP_HD int64_t mul_mod(int64_t a, int64_t b, int64_t n) {      // n < 2^32
+RP_HD int64_t mul_mod(int64_t a, int64_t b, int64_t n, const Divisor<int64_t>&) {   // n < 2^32
   return (int64_t)((uint64_t)a * (uint64_t)b % (uint64_t)n);
 }
 
@@ -176,8 +211,9 @@ struct PairEq {
       g = 1;
       if (abs_of(B) > 1) {
         g = gcd_of(abs_of(A), abs_of(B));
-        p = A / g;
-        q = B / g;
+        const Divisor<I> by(g);
+        p = by.floor(A);
+        q = by.floor(B);
       }
       const I n = abs_of(q);
       inv = n == 1 ? 0 : n == 2 ? 1 : inverse_of(p, n);
@@ -191,37 +227,46 @@ struct PairEq {
     if (neg) e = -e;
     if (B == 0) {
       if (A == 0) return e == 0 && (!off || X > 1 || Y > 1 || differ(0, 0));
-      if (e % A != 0) return false;
-      const I x = e / A;
+      I x = Divisor<I>(abs_of(A)).floor(e);
+      if (x * abs_of(A) != e) return false;
+      if (A < 0) x = -x;
       return x >= 0 && x < X && (!off || Y > 1 || differ(x, 0));
     }
     I f = e;
     if (g > 1) {
-      if (e % g != 0) return false;
-      f = e / g;
+      f = Divisor<I>(g).floor(e);
+      if (f * g != e) return false;
     }
     // x = x0 + n*t, y = y0 + s*t
     const I n = abs_of(q), s = q < 0 ? -p : p;
-    I x0 = 0;
+    I x0 = 0, y0 = -f, t0 = 0, t1 = X - 1;
     if (n > 1) {
-      I fm = f % n;
-      if (fm < 0) fm += n;
-      x0 = n == 2 ? fm : mul_mod(fm, inv, n);
+      const Divisor<I> by(n);
+      const I fm = f - by.floor(f) * n;
+      x0 = n == 2 ? fm : mul_mod(fm, inv, n, by);
       if (x0 >= X) return false;
+      y0 = by.floor(p * x0 - f);
+      t1 = by.floor(X - 1 - x0);
     }
-    I y0 = p * x0 - f;
-    y0 = n == 1 ? (q < 0 ? -y0 : y0) : y0 / q;
-    I t0 = 0, t1 = n == 1 ? X - 1 : (X - 1 - x0) / n;
+    if (q < 0) y0 = -y0;
+    const I d = abs_of(s);
+    I lo_y, hi_y;                          // steps to the ends of [0, Y) in s's direction
     if (s > 0) {
       if (y0 >= Y) return false;
-      if (y0 < 0) t0 = s == 1 ? -y0 : (-y0 + s - 1) / s;
-      const I u = Y - 1 - y0, ty = s == 1 ? u : u / s;
-      if (ty < t1) t1 = ty;
+      lo_y = -y0;
+      hi_y = Y - 1 - y0;
     } else {
-      const I d = -s;
       if (y0 < 0) return false;
-      if (y0 >= Y) t0 = d == 1 ? y0 - Y + 1 : (y0 - Y + d) / d;
-      const I ty = d == 1 ? y0 : y0 / d;
+      lo_y = y0 - Y + 1;
+      hi_y = y0;
+    }
+    if (d == 1) {
+      if (lo_y > 0) t0 = lo_y;
+      if (hi_y < t1) t1 = hi_y;
+    } else {
+      const Divisor<I> by(d);
+      if (lo_y > 0) t0 = by.floor(lo_y - 1) + 1;
+      const I ty = by.floor(hi_y);
       if (ty < t1) t1 = ty;
     }
     if (t0 > t1) return false;
@@ -229,6 +274,9 @@ struct PairEq {
     return differ(x0 + n * t0, y0 + s * t0) || differ(x0 + n * t1, y0 + s * t1);
   }
 };
+
+RP_HD uint32_t quotient(int32_t x, int32_t d) { return (uint32_t)Divisor<int32_t>(d).floor(x); }
+RP_HD uint32_t quotient(int64_t x, int64_t d) { return (uint32_t)x / (uint32_t)d; }   // (below 2^32)
 
 // Some z in [0, n) with ok(z) and a solution for D = D0 + beta*z mod W, where
 // v0 = (D0 - lo) mod W.  Values of D outside the interval are stepped over.
@@ -252,12 +300,12 @@ RP_HD bool closed_scan(const PairEq<I>& q, uint32_t W, uint32_t v0, int32_t beta
       if (v < 0) v += Wl;
     } else if (beta > 0) {
       // to the first value past the top of the range
-      const uint32_t s = (uint32_t)(Wl - v - 1) / (uint32_t)beta + 1;
+      const uint32_t s = quotient((I)(Wl - v - 1), (I)beta) + 1;
       z += s;
       v = (I)((U)v + (U)s * (U)beta - (U)Wl);       // in [0, beta)
     } else {
       const uint32_t d = (uint32_t)(-(int64_t)beta);
-      const uint32_t s = (uint32_t)(v - w - 1) / d + 1;
+      const uint32_t s = quotient((I)(v - w - 1), (I)d) + 1;
       z += s;
       v = (I)((U)v - (U)s * (U)d);                  // in (w - d, w]
       if (v < 0) v += Wl;
@@ -271,6 +319,7 @@ RP_HD bool self_same_block(const Access& p) {
   if (p.X < 2) return false;
   if (p.A == 0) return true;
   const uint32_t a = (uint32_t)(p.A < 0 ? -(int64_t)p.A : (int64_t)p.A);
+  if ((uint64_t)a * (p.X - 1) < p.W) return false;     // (nothing wraps)
   return p.W / gcd_of<uint32_t>(p.W, a) < p.X;
 }
 
@@ -292,7 +341,7 @@ RP_HD uint64_t common_blocks(const Access& p, const Access& q, uint32_t B, uint3
     if (n > 1) {
       u = (d / (int64_t)g) % n;
       if (u < 0) u += n;
-      u = mul_mod(u, inverse_of<int64_t>((int64_t)(p.bm / g), n), n);
+      u = mul_mod(u, inverse_of<int64_t>((int64_t)(p.bm / g), n), n, Divisor<int64_t>(n));
     }
     step = (uint64_t)p.bm * (uint64_t)n;
     k = (uint64_t)p.br + (uint64_t)p.bm * (uint64_t)u;
