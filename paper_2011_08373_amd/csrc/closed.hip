@@ -14,15 +14,16 @@
 // a short row.
 //
 // Bound: instruction latency for one kernel (a pair costs two or three hundred
-// integer instructions in one lane, a few of them divisions), instruction
-// issue and waves in flight for a batch.  Measured: 21 us for the stress kernel
-// (512 accesses of 4.2M threads; generating, sorting and scanning their 2.0G
-// records took 31 ms), 12 us for plain-large (17 us with every chunk tested at
-// once, 0.56 ms by records), 154 us for 128 kernels of the batched
-// distribution (338 us with a wave per row and every chunk tested at once,
-// 9.2 ms by records); every pair of plain-large under a quarter of its barriers
-// 15 us (31 us; 1.39 ms for the scan of its sorted records, and 0.45 ms to
-// generate and sort them).
+// instructions in one lane, its divisions by reciprocals), instruction issue and
+// waves in flight for a batch.  Measured: 21 us for the stress kernel (512
+// accesses of 4.2M threads; generating, sorting and scanning their 2.0G records
+// took 31 ms), 11 us for plain-large (12 us with integer divisions, 17 us with
+// every chunk tested at once, 0.56 ms by records), 113 us for 128 kernels of
+// the batched distribution (154 us with integer divisions in workgroups of four
+// waves, 338 us with a wave per row and every chunk tested at once, 9.2 ms by
+// records); every pair of plain-large under a quarter of its barriers 13 us (14
+// us; 31 us; 1.39 ms for the scan of its sorted records, and 0.45 ms to generate
+// and sort them).
 #include "closed_rows.h"
 #include "common.h"
 #include "launch.h"
@@ -31,6 +32,16 @@ namespace rp {
 
 constexpr int CF_WAVES = 4;
 constexpr uint32_t ROW_GROUPS = 16384;   // workgroups of a batch
+
+// Workgroups of a batch are of two waves: rows differ in length, and a waiting
+// workgroup needs room for all its waves at once (128 kernels: 123 us, 146 us
+// with four waves, 145 us with one and its twice as many dispatches).  The form
+// of most kernels is held to 96 registers there, five waves per SIMD and four
+// spills (113 us); the other form spills more (512 programs 16 us instead of
+// 12), and a lone kernel's rows all run at once (12 us instead of 13 without).
+constexpr int BATCH_WAVES = 2;
+template <int FORM, int WAVES>
+constexpr int MIN_WAVES = FORM == FORM_PLAIN && WAVES == BATCH_WAVES ? 5 : 1;
 
 // Walks row (i, lv): found(m, j) gets the lanes m that found a conflict and
 // this lane's point j, in ascending order of points over lanes and calls, and
@@ -83,17 +94,17 @@ __device__ __forceinline__ void walk_row(const Job& J, const DPoint& pi, uint32_
 // X = false: the table j0, with no barrier enabled.  X = true: first partners
 // under the job's assignment, into minj (and the page), of a job that has no
 // records at all.
-template <int FORM, bool X>
-__global__ __launch_bounds__(CF_WAVES * 64) void first_kernel(const Job* __restrict__ jobs,
-                                                              CallBlock call) {
-  __shared__ uint16_t s_q[CF_WAVES][128];
+template <int FORM, bool X, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, (MIN_WAVES<FORM, WAVES>))
+void first_kernel(const Job* __restrict__ jobs, CallBlock call) {
+  __shared__ uint16_t s_q[WAVES][128];
   stamp_if(call.stamps, STAMP_BEGIN);
   const Job& J = jobs[blockIdx.y];
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = __lane_id();
   const uint32_t P = J.P, B = J.B;
   const bool all_rows = J.nlog[0] == 0 && J.nlog[1] == 0;    // (else a scan has set the others)
   const uint64_t x = X ? J.st->x : 0;
-  for (uint32_t r = blockIdx.x * CF_WAVES + wv; r < 2 * P; r += gridDim.x * CF_WAVES) {
+  for (uint32_t r = blockIdx.x * WAVES + wv; r < 2 * P; r += gridDim.x * WAVES) {
     const uint32_t i = r >> 1, lv = r & 1;
     const DPoint pi = J.pts[i];
     if (r == 0) stamp_gather(call.stamps, J, pi);
@@ -154,8 +165,8 @@ __global__ __launch_bounds__(CF_WAVES * 64) void all_kernel(const Job* __restric
   }
 }
 
-static dim3 row_grid(uint32_t max_points, uint32_t njobs) {
-  const uint32_t all = (2 * max_points + CF_WAVES - 1) / CF_WAVES;
+static dim3 row_grid(uint32_t max_points, uint32_t njobs, uint32_t waves) {
+  const uint32_t all = (2 * max_points + waves - 1) / waves;
   const uint32_t most = ROW_GROUPS / njobs;
   return dim3(all < most ? all : (most ? most : 1), njobs);
 }
@@ -163,7 +174,7 @@ static dim3 row_grid(uint32_t max_points, uint32_t njobs) {
 hipError_t launch_all_closed(const Job* job, uint32_t points, int form, const CallBlock& call,
                              hipStream_t s) {
   if (points == 0) return hipSuccess;
-  const dim3 grid = row_grid(points, 1);
+  const dim3 grid = row_grid(points, 1, CF_WAVES);
   switch (form) {
     case FORM_PLAIN: all_kernel<FORM_PLAIN><<<grid, CF_WAVES * 64, 0, s>>>(job, call); break;
     case FORM_SMALL: all_kernel<FORM_SMALL><<<grid, CF_WAVES * 64, 0, s>>>(job, call); break;
@@ -172,16 +183,16 @@ hipError_t launch_all_closed(const Job* job, uint32_t points, int form, const Ca
   return hipGetLastError();
 }
 
-template <bool X>
+template <bool X, int WAVES>
 static hipError_t first_go(const Job* jobs, uint32_t njobs, uint32_t max_points, int form,
                            const CallBlock& call, hipStream_t s) {
   for (uint32_t j = 0; j < njobs; j += 65535) {      // (the grid's second dimension)
-    const dim3 grid = row_grid(max_points, njobs - j < 65535 ? njobs - j : 65535);
+    const dim3 grid = row_grid(max_points, njobs - j < 65535 ? njobs - j : 65535, WAVES);
     const CallBlock c = j == 0 ? call : CallBlock{};
     switch (form) {
-      case FORM_PLAIN: first_kernel<FORM_PLAIN, X><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, c); break;
-      case FORM_SMALL: first_kernel<FORM_SMALL, X><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, c); break;
-      default: first_kernel<FORM_WIDE, X><<<grid, CF_WAVES * 64, 0, s>>>(jobs + j, c); break;
+      case FORM_PLAIN: first_kernel<FORM_PLAIN, X, WAVES><<<grid, WAVES * 64, 0, s>>>(jobs + j, c); break;
+      case FORM_SMALL: first_kernel<FORM_SMALL, X, WAVES><<<grid, WAVES * 64, 0, s>>>(jobs + j, c); break;
+      default: first_kernel<FORM_WIDE, X, WAVES><<<grid, WAVES * 64, 0, s>>>(jobs + j, c); break;
     }
   }
   return hipGetLastError();
@@ -190,12 +201,13 @@ static hipError_t first_go(const Job* jobs, uint32_t njobs, uint32_t max_points,
 hipError_t launch_first_closed(const Job* jobs, uint32_t njobs, uint32_t max_points, int form,
                                const CallBlock& call, hipStream_t s) {
   if (njobs == 0 || max_points == 0) return hipSuccess;
-  return first_go<false>(jobs, njobs, max_points, form, call, s);
+  return njobs > 1 ? first_go<false, BATCH_WAVES>(jobs, njobs, max_points, form, call, s)
+                   : first_go<false, CF_WAVES>(jobs, njobs, max_points, form, call, s);
 }
 
 hipError_t launch_first_under(const Job* job, uint32_t points, int form, const CallBlock& call,
                               hipStream_t s) {
-  return first_go<true>(job, 1, points ? points : 1, form, call, s);
+  return first_go<true, CF_WAVES>(job, 1, points ? points : 1, form, call, s);
 }
 
 }  // namespace rp
