@@ -86,8 +86,17 @@ def _time(L, kms, batch, ws, reps):
 
 
 def tune(kms, reps: int = 3, ws=None, candidates=None, passes_only: bool = False) -> dict:
-    """Time every candidate on a batch (or one kernel) and cache the best."""
+    """Time every candidate on a batch (or one kernel) and cache the best.
+    Every array is put on the records, whose sort is what is tuned."""
     from . import librepair as L
+    route = L.set_tuning(L.TUNE_RACE_ROUTE, 1)
+    try:
+        return _tune(L, kms, reps, ws, candidates, passes_only)
+    finally:
+        L.set_tuning(L.TUNE_RACE_ROUTE, route)
+
+
+def _tune(L, kms, reps, ws, candidates, passes_only) -> dict:
     batch = isinstance(kms, (list, tuple)) or isinstance(kms, L.BatchArg)
     if batch and not isinstance(kms, L.BatchArg):
         kms = L.BatchArg(kms)

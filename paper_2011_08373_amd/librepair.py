@@ -387,8 +387,7 @@ def batch_workspace_bytes(kms) -> int:
 def repair_batch(kms, policy: int = 0, grid: int = 1, inspect: int = 1, max_rounds: int = 0,
                  ws=None, stream=None, solver: int = 0):
     """Alg. 1 over many kernels in one batched run; (status, [result dict per kernel]).
-    Runs on a dedicated non-default stream unless one is given, so that each
-    round can be replayed as a captured graph."""
+    Runs on a dedicated non-default stream unless one is given."""
     import torch
     b = kms if isinstance(kms, BatchArg) else BatchArg(kms)
     ptr, size = (ws or _ws).get(b.need())
