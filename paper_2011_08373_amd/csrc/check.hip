@@ -875,10 +875,12 @@ __global__ __launch_bounds__(CONF_BLOCK) void j0_kernel(const Job* __restrict__ 
 
 // Bitmap rows (level, i) in order -> pair list.  Each row's pairs are counted
 // into minj (by the closed form, or by count_rows_kernel), then PR_ROWS rows
-// go to a workgroup: it sums the counts of all rows before its own, one wave
-// takes a row at a time, a lane one of its words, and lanes write their pairs
-// behind those of the lanes below.  For a 512-point kernel's list 7.2 us, from
-// 13.6 us by one workgroup of 1024 threads.
+// go to a workgroup: it sums the counts of all rows before its own, and its
+// waves take a quarter of the rows each, a word at a time, a lane one of its
+// bits, so that neighbouring lanes write neighbouring pairs.  Bound: latency;
+// everything it reads is asked for at the start.  Plain-large's list 8.4 us (14.4
+// us with a row's words one per lane, each lane writing its own pairs one after
+// the other), of a 16-point kernel 5.5 us (8.6).
 constexpr int PR_BLOCK = 256, PR_WAVES = PR_BLOCK / 64;
 constexpr uint32_t PR_ROWS = 16;
 
@@ -900,38 +902,50 @@ __global__ __launch_bounds__(PR_BLOCK) void pairs_kernel(const Job* __restrict__
   const uint32_t P = J.P, rows = 2 * P, wpr = J.wpr;
   const uint32_t r0 = blockIdx.x * PR_ROWS;
   const uint32_t tid = threadIdx.x, lane = __lane_id(), wv = tid >> 6;
+  constexpr uint32_t PER = PR_ROWS / PR_WAVES;       // rows of a wave
+  // the workgroup's counts and the wave's words, before they are needed
+  const uint32_t n = lane < PR_ROWS && r0 + lane < rows ? J.minj[r0 + lane] : 0;
+  uint64_t m[PER];
+#pragma unroll
+  for (uint32_t k = 0; k < PER; k++) {
+    const uint32_t r = r0 + wv * PER + k;
+    m[k] = r < rows && lane < wpr ? J.bitmap[(uint64_t)r * wpr + lane] : 0;
+  }
   uint64_t sum = 0;
+#pragma unroll 4
   for (uint32_t r = tid; r < r0; r += PR_BLOCK) sum += J.minj[r];
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
   if (lane == 0) s_sum[wv] = sum;
   __syncthreads();
   uint64_t pos = 0;
   for (int w = 0; w < PR_WAVES; w++) pos += s_sum[w];
-  for (uint32_t r = r0; r < r0 + PR_ROWS && r < rows; r++) {
-    const uint32_t n = J.minj[r];
-    if ((r - r0) % PR_WAVES == wv && n != 0) {
-      uint64_t m = lane < wpr ? J.bitmap[(uint64_t)r * wpr + lane] : 0;
-      const uint32_t c = (uint32_t)__popcll(m);
-      uint32_t inc = c;
-      for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o);
-        if (lane >= (uint32_t)o) inc += y;
+  uint32_t before = lane < wv * PER ? n : 0;         // (of the other waves' rows)
+  uint32_t own = n;
+  for (int o = 32; o > 0; o >>= 1) {
+    before += __shfl_xor(before, o);
+    own += __shfl_xor(own, o);
+  }
+  uint64_t at = pos + before;
+  pos += own;
+  rp_pair* const head = call.page ? (rp_pair*)call.page->tail() : nullptr;
+#pragma unroll
+  for (uint32_t k = 0; k < PER; k++) {
+    const uint32_t r = r0 + wv * PER + k;
+    rp_pair pr;
+    pr.i = (uint16_t)(r >= P ? r - P : r);
+    pr.level = r >= P;
+    pr.pad = 0;
+    for (uint64_t some = __ballot(m[k] != 0); some; some &= some - 1) {
+      const uint32_t w = (uint32_t)__builtin_ctzll(some);
+      const uint64_t word = __shfl(m[k], w);
+      if ((word >> lane) & 1) {
+        const uint64_t to = at + (uint32_t)__popcll(word & lanemask_lt());
+        pr.j = (uint16_t)(w * 64 + lane);
+        out[to] = pr;
+        if (head && to < PAGE_PAIRS) head[to] = pr;
       }
-      uint64_t at = pos + (inc - c);
-      rp_pair* const head = call.page ? (rp_pair*)call.page->tail() : nullptr;
-      rp_pair pr;
-      pr.i = (uint16_t)(r >= P ? r - P : r);
-      pr.level = r >= P;
-      pr.pad = 0;
-      while (m) {
-        pr.j = (uint16_t)(lane * 64 + __builtin_ctzll(m));
-        m &= m - 1;
-        out[at] = pr;
-        if (head && at < PAGE_PAIRS) head[at] = pr;
-        at++;
-      }
+      at += (uint32_t)__popcll(word);
     }
-    pos += n;
   }
   if (r0 + PR_ROWS >= rows && tid == 0) {
     *total = pos;
