@@ -198,3 +198,14 @@ def test_points_that_never_execute(L):  # noqa: F811
             assert L.clauses(km, 0) == O.clauses(km, 0)
         finally:
             L.set_tuning(L.TUNE_RACE_ROUTE, old)
+
+
+@pytest.mark.parametrize("P", [1, 7, 8, 9, 63, 64, 65, 129, 1030])
+def test_pair_list_sizes(L, P):  # noqa: F811
+    # full words, empty words and rows, a last group of rows that is not full
+    for writes in (1.0, 0.02):
+        rng = np.random.default_rng(P)
+        pts = [dict(kind=0, is_write=int(rng.random() < writes), array=int(rng.random() < 0.1), a=0,
+                    b=int(rng.integers(0, 2)), c=0) for _ in range(P)]
+        km = synth.make_kernel(2, 3, [(4, 1), (4, 0)], [(1, 0)], pts, [])
+        assert L.check(km, 0)[:4] == O.check(km, 0), writes
