@@ -18,9 +18,9 @@ __device__ __forceinline__ bool closed_point(const DPoint& d) {
 // The kernels' forms.  FORM_WIDE: any closed array; FORM_SMALL: 32-bit
 // arithmetic; FORM_PLAIN: that, no block conditions, and the block strides of
 // an array share a divisor that keeps their terms below the pairs of blocks
-// (all but odd kernels): without the other cases' code the kernel keeps 121
-// registers instead of 142, four waves per SIMD instead of three (128 batched
-// kernels 167 us from 231 us).
+// (all but odd kernels): without the other cases' code the kernel keeps 105
+// registers instead of 126.  (With integer divisions, 121 instead of 142 and so
+// four waves per SIMD instead of three: 128 batched kernels 167 us from 231 us.)
 template <int FORM>
 using FormInt = std::conditional_t<FORM == FORM_WIDE, int64_t, int32_t>;
 
@@ -85,8 +85,9 @@ __device__ __forceinline__ void stamp_gather(uint64_t* stamps, const Job& J, con
 // PACKED_POINTS points and no records, by one workgroup of WAVES waves.  Such
 // a job has many short rows, a handful of candidates each, so the pairs of
 // several rows are gathered until 64 are together and tested one per lane;
-// each row's least partner is kept in LDS.  (A wave per row took 71 us for
-// 512 programs of 41 points on average, most of its lanes idle.)
+// each row's least partner is kept in LDS.  A wave per row, most of its lanes
+// idle, took 71 us for 512 programs of 41 points on average, before their
+// rounds; now 12 us for the few larger programs, the rest inside the rounds.
 template <int WAVES>
 struct PackedLds {
   uint32_t q[WAVES][128];                  // gathered pairs: view << 16 | i << 8 | j
