@@ -313,10 +313,12 @@ rp_status rp_repair_batch(const rp_kernel* const* ks, uint32_t n, const rp_repai
     outs[j].status = ok[j] ? RP_ERR_DEVICE : RP_ERR_INVALID;   // invalid: this job only
     if (ok[j]) idx.push_back(j);
   }
-  // kernels with more points first: the device starts the long ones at once,
-  // and the pair tests are launched over those that need them
-  std::stable_sort(idx.begin(), idx.end(),
-                   [&](uint32_t a, uint32_t b) { return plans[a].P > plans[b].P; });
+  // kernels with more points first: the device starts the long ones at once;
+  // packed ones last, so that the pair tests are launched over those that need
+  // them
+  std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) {
+    return plans[a].packed != plans[b].packed ? plans[b].packed : plans[a].P > plans[b].P;
+  });
   std::vector<JobInput> v(idx.size());
   for (size_t q = 0; q < idx.size(); q++) {
     const Plan& pl = plans[idx[q]];

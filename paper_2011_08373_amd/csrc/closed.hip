@@ -108,7 +108,7 @@ void first_kernel(const Job* __restrict__ jobs, CallBlock call) {
     const uint32_t i = r >> 1, lv = r & 1;
     const DPoint pi = J.pts[i];
     if (r == 0) stamp_gather(call.stamps, J, pi);
-    if (!X && all_rows && P <= PACKED_POINTS) return;    // (the rounds kernel's own)
+    if (!X && J.packed) return;                          // (the rounds kernel's own)
     uint32_t best = NONE32;
     if (row_runs(pi, B, lv))
       walk_row<FORM, X>(J, pi, i, lv, x, s_q[wv], [&](uint64_t m, uint32_t j) {

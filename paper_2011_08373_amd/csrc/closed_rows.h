@@ -81,13 +81,13 @@ __device__ __forceinline__ void stamp_gather(uint64_t* stamps, const Job& J, con
   stamp_if(stamps, STAMP_SORT);
 }
 
-// First partners, with no barrier enabled, of a whole job of at most
-// PACKED_POINTS points and no records, by one workgroup of WAVES waves.  Such
+// First partners, with no barrier enabled, of a whole job of few points and few
+// pair tests (Job::packed), by one workgroup of WAVES waves.  Such
 // a job has many short rows, a handful of candidates each, so the pairs of
 // several rows are gathered until 64 are together and tested one per lane;
 // each row's least partner is kept in LDS.  A wave per row, most of its lanes
 // idle, took 71 us for 512 programs of 41 points on average, before their
-// rounds; now 12 us for the few larger programs, the rest inside the rounds.
+// rounds.
 template <int WAVES>
 struct PackedLds {
   uint32_t q[WAVES][128];                  // gathered pairs: view << 16 | i << 8 | j

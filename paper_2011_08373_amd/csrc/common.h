@@ -140,7 +140,8 @@ struct Job {
   uint32_t phi_cap, scratch_cap;
   JobState* st;
   uint64_t* traj;             // [traj_cap] assignment verified per round
-  uint32_t traj_cap, pad2;
+  uint32_t traj_cap;
+  uint32_t packed;            // no records, and few pair tests: packed_first
   uint64_t node_limit;        // nodes the exact solver's branch and bound may visit
 };
 

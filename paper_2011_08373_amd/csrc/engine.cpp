@@ -354,6 +354,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
       J.st = (JobState*)(d + L.o_states) + j;
       J.traj = o.traj_cap ? (uint64_t*)(d + L.o_traj[j]) : nullptr;
       J.traj_cap = o.traj_cap;
+      J.packed = p.packed;
       J.node_limit = 1ull << solver_nodes_log2(0, false);
       JobState& S = hs[j];
       S.x = jobs[j].x;
@@ -454,10 +455,10 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
       tm.mark(T_SUMMARY);
       HIPCHK(launch_save_j0(djobs, (uint32_t)N, s));
     }
-    // (the rounds kernel does the jobs of few points itself)
+    // (the rounds kernel does the packed jobs itself)
     uint32_t large = 0;                // jobs up to the last one it is for
     for (size_t j = 0; j < N; j++)
-      if (jobs[j].plan->P > PACKED_POINTS || !L.ssegs.empty()) large = (uint32_t)j + 1;
+      if (!jobs[j].plan->packed) large = (uint32_t)j + 1;
     if (large && (L.ssegs.empty() || any_closed)) {
       HIPCHK(launch_first_closed(djobs, large, maxP, form, call, s));
       if (L.ssegs.empty()) tm.mark(T_SUMPRE);
@@ -588,11 +589,13 @@ int engine_run(const std::vector<JobInput>& jobs, const EngineOpts& o, void* ws,
   uint32_t* dtiles = derr + 9;     // conf tiles of the all-pairs scan
   uint32_t maxP = 1;
   int form = FORM_PLAIN;
+  bool packed = true;              // all of them
   for (const JobInput& j : jobs) {
     maxP = std::max(maxP, j.plan->P);
     form = std::max(form, j.plan->closed_form);
+    packed = packed && j.plan->packed;
   }
-  const int build = RD_BUILD | (nseg == 0 && maxP <= PACKED_POINTS ? RD_FIRST : 0);
+  const int build = RD_BUILD | (packed ? RD_FIRST : 0);
   const JobState* hst = page ? &page->st : (const JobState*)rb;
   const uint32_t* herr = page ? page->words : (const uint32_t*)(rb + words_at);
   uint64_t* ptraj = page ? page->traj : (uint64_t*)(rb + words_at + 64);

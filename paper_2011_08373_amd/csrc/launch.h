@@ -73,15 +73,25 @@ hipError_t launch_all_closed(const Job* job, uint32_t points, int form, const Ca
 hipError_t launch_pairs(const Job* job, uint32_t points, bool counted, rp_pair* out,
                         uint64_t* total, const CallBlock& call, hipStream_t s);
 // The rounds of Alg. 1 on every running job.  RD_BUILD: the job's clause tables
-// from j0 first (jobs of at most PACKED_POINTS points with no records work out
-// j0 themselves; RD_FIRST: every job is one, and no first-partner launch has
+// from j0 first (a packed job, see PACKED_TESTS, works out
+// j0 itself; RD_FIRST: every job is one, and no first-partner launch has
 // come before); RD_SOLVE: one Solve first; RD_LOOP: rounds, at most limit of
 // them (0: until a verdict); RD_LEARN: Verify and GenerateClause under the
 // job's assignment only; RD_TIMED: the phases' clock ticks into the job state.
 constexpr int RD_BUILD = 1, RD_SOLVE = 2, RD_LOOP = 4, RD_LEARN = 8, RD_TIMED = 16,
               RD_FIRST = 32;
-// points of a job whose first partners the rounds kernel works out
+// Most points, and most pair tests by the plan's bound, of a job whose first
+// partners the rounds kernel works out (Job::packed).  Its one workgroup tests
+// 256 pairs at a time, a test 1.6 to 2.8 us there (nothing else hides its
+// latency), where the launch of first_kernel costs a lone job 5 to 8 us and
+// spreads the rows over the chip: 128 points of one array that never conflict
+// 64 and 12 + 5 us over one view, 189 and 12 + 8 us over two, and 15 ms and 0.3
+// ms where a pair's walk meets 256 values; 32 points over one view 40 and 37 us
+// a call.  512 programs together took 78 us with none packed, 68 to 69 us with
+// the line at 512 or 1,024 and 70 us with all up to 128 points; 128 batched
+// kernels 161 us, 180 us from 4,096 on.
 constexpr uint32_t PACKED_POINTS = 128;
+constexpr double PACKED_TESTS = 512;
 hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int form, int flags, uint32_t limit,
                          const CallBlock& call, hipStream_t s);
 

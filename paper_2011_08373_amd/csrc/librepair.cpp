@@ -271,9 +271,9 @@ void rotation_of(const ArrayScratch& a, uint64_t N, uint64_t& off, uint64_t& spa
 }
 
 // Whether the closed form's bound takes the array (see above); form: raised to
-// the one it needs.
+// the one it needs; tests: the bound is added.
 bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B, uint32_t T,
-                  int& form) {
+                  int& form, double& tests) {
   if (a.n == 0 || a.span >= MAX_SPAN || a.bspan >= MAX_SPAN) return false;
   const double W = words, w = 2.0 * (double)a.span, wraps = 1 + std::floor(w / W);
   const double bw = 2.0 * (double)a.bspan;
@@ -314,6 +314,7 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
     form = FORM_WIDE;
   else if (!plain)
     form = std::max(form, FORM_SMALL);
+  tests += work;
   return true;
 }
 
@@ -454,6 +455,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
   pl.arrays.resize(k->n_arrays);
   pl.any_closed = false;
   pl.closed_form = FORM_PLAIN;
+  double tests = 0;
   for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
     const ArrayScratch& a = sc.arrays[arr];
     const uint32_t words = k->arrays[arr].words;
@@ -463,7 +465,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     span_max = std::max(span_max, span);
     o.off = (uint32_t)off;
     o.closed = g_race_route == 0 && takes_closed(a, words, k->arrays[arr].space == RP_GLOBAL, pl.B,
-                                                 pl.T, pl.closed_form);
+                                                 pl.T, pl.closed_form, tests);
     intra += a.intra;
     inter += a.inter;
     if (o.closed) {
@@ -480,6 +482,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
   pl.n_inter = inter;
   pl.log_intra = log_intra * pl.B;
   pl.log_inter = log_inter;
+  pl.packed = pl.P <= PACKED_POINTS && tests <= PACKED_TESTS && log_intra + log_inter == 0;
   pl.grid_slots = pl.pre_slots = 0;
   for (uint32_t s = 0; s < pl.S; s++) {
     if (k->slots[s].level == RP_GRID) pl.grid_slots |= 1ull << s;

@@ -36,6 +36,7 @@ struct Plan {
   uint64_t rblk = 0;                // same-block records per block
   bool any_closed = false;          // some array is decided in closed form
   int closed_form = FORM_PLAIN;     // the narrowest form all of these fit
+  bool packed = false;              // its first partners are the rounds kernel's
 };
 
 int validate_kernel(const rp_kernel* k);

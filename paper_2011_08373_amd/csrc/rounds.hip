@@ -308,8 +308,8 @@ __device__ __forceinline__ void save_traj(const Job& J, SolveLds& L, uint32_t fr
     J.traj[q] = near_traj(L)[q - from];
 }
 
-// flags: RD_BUILD builds the tables (from j0, which a job of few points works
-// out itself first; RD_FIRST: all jobs are such); RD_SOLVE makes one Solve first (the option
+// flags: RD_BUILD builds the tables (from j0, which a packed job works out
+// itself first; RD_FIRST: all jobs are such); RD_SOLVE makes one Solve first (the option
 // units); RD_LEARN generates the clauses under the job's assignment and stops.
 // limit: rounds to run (0: until a verdict).
 template <int FORM>
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(RD_BLOCK) void rounds_kernel(const Job* __restrict_
   const bool one = J.policy == 1 && !(flags & RD_LEARN);
   if (flags & RD_BUILD)
     for (uint32_t q = tid; q < st->n_phi; q += RD_BLOCK) J.phi[q] = J.phi0[q];
-  if ((flags & RD_BUILD) && P <= PACKED_POINTS && J.nlog[0] == 0 && J.nlog[1] == 0) {
+  if ((flags & RD_BUILD) && J.packed) {
     packed_first<FORM, RD_WAVES>(J, L.p, begins && blockIdx.x == 0 ? call.stamps : nullptr);
     if (begins) stamp_if(call.stamps, STAMP_FIRST);
   }

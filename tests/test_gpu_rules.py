@@ -1,0 +1,75 @@
+"""Kernels on both sides of the plan's lines (how conflicts are decided and by
+which kernel) against the oracle: alone, together in a batch, and served."""
+import pytest
+
+from oracle import oracle as O
+from paper_2011_08373_amd import synth
+from test_gpu_parity import L, same_repair  # noqa: F401  (L is a fixture)
+from test_plan_rules import _one_array
+
+pytestmark = pytest.mark.gpu
+
+
+def _with_barriers(km, every):
+    """km with a slot's barrier after every so many points, and some of its
+    accesses moved onto the others' words."""
+    pts, slots = [], []
+    for i, p in enumerate(km.points):
+        d = {k: int(p[k]) for k in ("kind", "is_write", "array", "guard", "slot", "a", "b", "c")}
+        if i % 5 == 3:
+            d["c"] += 1
+        pts.append(d)
+        if i % every == every - 1 and len(slots) < 6:
+            pts.append(dict(kind=1, slot=len(slots)))
+            slots.append((len(slots) % 2, 0, 1 + len(slots)))
+    return synth.make_kernel(km.blocks, km.threads, [(1 << 20, 1)], [(1, 0)], pts, slots)
+
+
+def _edge_kernels():
+    kms = []
+    for P, T, B, step, apart in ((16, 64, 1, 2, 0), (31, 64, 1, 2, 0), (32, 64, 1, 2, 0),
+                                 (22, 33, 4, 2, 0), (23, 33, 4, 2, 0), (16, 64, 64, 2, 2),
+                                 (100, 33, 40, 128, 2), (128, 64, 3, 2, 64), (130, 64, 3, 2, 64)):
+        km = _one_array(P, T, B, step, apart)
+        kms += [km, _with_barriers(km, max(3, P // 6))]
+    return kms
+
+
+def test_packed_and_not(L):  # noqa: F811
+    kms = _edge_kernels()
+    for q, km in enumerate(kms):
+        for kw in (dict(), dict(policy=1), dict(policy=1, solver=1)):
+            g, o = L.repair(km, **kw), O.repair(km, **kw)
+            assert same_repair(g, o), (q, kw, g, o)
+        assert L.clauses(km, 0) == O.clauses(km, 0), q
+    for order in (kms, kms[::-1], kms[1::2] + [synth.generate("plain-small", seed=4)] + kms[::2]):
+        st, res = L.repair_batch(order)
+        assert st == 0
+        for km, r in zip(order, res):
+            o = O.repair(km)
+            assert all(r[k] == o[k] for k in ("status", "assign", "weight", "rounds", "n_clauses"))
+    srv = L.Server(arena_bytes=4 << 30, max_resident=8)
+    for q, km in enumerate(kms):
+        assert srv.submit(km, q) == 0
+    got = {}
+    while len(got) < len(kms):
+        srv.step()
+        got.update((job, r) for job, r, _ in srv.poll())
+    for q, km in enumerate(kms):
+        o = O.repair(km)
+        assert all(got[q][k] == o[k] for k in ("status", "assign", "weight", "rounds")), q
+
+
+def test_long_walks_are_spread(L):  # noqa: F811
+    # 8,256 pairs, each meeting 256 values: by the rows of the chip in both
+    # calls, not by one workgroup in one of them (50 times the other's time)
+    km = _one_array(128, 256, 256, 2, 2)
+    times = []
+    for call in (L.first_partners, L.repair):
+        ms = []
+        for _ in range(4):
+            call(km)
+            assert L.last_stats()["records"] == 0
+            ms.append(L.last_stats()["ms_total"])
+        times.append(min(ms))
+    assert times[1] < 8 * times[0], times

@@ -1,0 +1,57 @@
+"""The plan's rules for how conflicts are decided, on the CPU: the lines are
+drawn by the work that a kernel's pair tests are bounded by."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2011_08373_amd import build, synth
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "plan_facts.so")
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip",
+                           "--cuda-host-only", "-std=c++17", "-O1", "-shared", "-fPIC",
+                           "-o", so, os.path.join(HERE, "plan_facts.cpp"),
+                           os.path.join(build.CSRC, "librepair.cpp")])
+    return C.CDLL(so)
+
+
+@pytest.fixture(scope="module")
+def arg():
+    import torch  # noqa: F401  (its HIP runtime is the one the library is to use)
+    from paper_2011_08373_amd import librepair
+    return librepair.KernelArg
+
+
+def _one_array(P, T, B, step, apart):
+    """P accesses of one array that never conflict: reads of even words and
+    writes of odd ones, step apart per thread, their block strides differing
+    by apart."""
+    pts = [dict(kind=0, is_write=i & 1, a=step, b=apart * (i & 1), c=i & 1) for i in range(P)]
+    return synth.make_kernel(B, T, [(1 << 20, 1)], [(1, 0)], pts, [])
+
+
+@pytest.mark.parametrize("km,packed", [
+    (_one_array(16, 64, 1, 2, 0), 1),
+    (_one_array(31, 64, 1, 2, 0), 1),          # 496 pairs, one test each
+    (_one_array(32, 64, 1, 2, 0), 0),          # 528
+    (_one_array(22, 64, 4, 2, 0), 1),          # two views of 253 pairs
+    (_one_array(23, 64, 4, 2, 0), 0),
+    (_one_array(16, 64, 64, 2, 2), 0),         # few pairs, each meeting up to 127 values
+    (_one_array(128, 256, 256, 128, 2), 0),
+    (_one_array(0, 1, 1, 2, 0), 1),
+], ids=lambda v: "%dx%dx%d" % (v.n_points, v.threads, v.blocks) if hasattr(v, "blocks") else str(v))
+def test_packed_by_tests(plan, arg, km, packed):
+    # one workgroup tests a packed kernel's pairs: few points are not enough
+    # where each pair's test walks many values
+    assert plan.plan_packed(arg(km).ref) == packed
+
+
+def test_small_kernels_are_packed(plan, arg):
+    for seed in range(20):
+        assert plan.plan_packed(arg(synth.generate("plain-small", seed=seed)).ref) == 1
