@@ -319,8 +319,7 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
 }
 
 bool divides(uint32_t words, int32_t a) {                // a = 0 mod words
-  return (words & (words - 1)) == 0 ? ((int64_t)a & ((int64_t)words - 1)) == 0
-                                    : (int64_t)a % (int64_t)words == 0;
+  return word_mod(a, words) == 0;
 }
 
 // Records of an access point (the reductions are listed in common.h): per
@@ -531,8 +530,10 @@ void fill_points(const Plan& pl, DPoint* pts) {
         if ((a.words & (a.words - 1)) == 0) f |= PF_POW2;
         if (divides(a.words, p.a)) f |= PF_TCONST;
         if (divides(a.words, p.b)) f |= PF_BCONST;
-        if (pa.off != 0)
-          d.c = (int32_t)(((uint64_t)word_mod(p.c, a.words) + pa.off) % a.words);
+        if (pa.off != 0) {
+          const uint64_t c = (uint64_t)word_mod(p.c, a.words) + pa.off;      // (off < words)
+          d.c = (int32_t)(uint32_t)(c >= a.words ? c - a.words : c);
+        }
       }
       d.flags = f;
     }
