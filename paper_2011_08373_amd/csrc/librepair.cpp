@@ -142,17 +142,25 @@ int validate_kernel(const rp_kernel* k) {
 // array with n points, pairs <= n(n+1)/2, and the tests of a pair are bounded
 // by how often the progression can enter the interval and how long it can
 // stay there: trips = (terms * |step| / W + 1) * (width / |step| + 2), at most
-// one per term.  Measured on pairs that never conflict: a test 14 ps with the
-// chip full (512 kernels of 64 points, 64 blocks) and 0.2 to 0.4 us one after
-// another in one lane (64 points, 4,096 blocks); a record of the log costs 16
-// ps (31.9 ms for the 2.0G records of the stress kernel) and the log's
-// launches alone about 0.1 ms.  So the closed form is taken where its bound
-// is no larger than the log's own work (RECORDS_FREE tests cost no more than
-// the launches), and where the tests of one lane in sequence end before the
-// log would.
+// one per term.  Measured on pairs that never conflict: a test 5 to 11 ps with
+// the chip full (2,800 points of 32 threads, one block; 64 such kernels and one)
+// and 0.26 to 0.54 us one after another in one lane (0.85 us in 64 bits); a
+// record of the log costs 16 ps (31.9 ms for the 2.0G records of the stress
+// kernel) and the log's launches alone 0.1 ms, 0.3 ms where one block holds
+// all records.  So the closed form is taken where its bound is no larger than
+// the log's own work (RECORDS_FREE tests cost no more than the launches), and
+// where the tests of one lane in sequence end before the log would (at the
+// line, 250 points of 352 threads and 2,048 blocks: 3.2 ms, 3.9 by records).
+// A pair's gcd and inverse come on top: 6 ps per step of Euclid's algorithm in
+// 32 bits and 8.5 ps in 64 (2,000 and 2,800 points of unrelated steps: 85 and
+// 134 ps a pair), EUCLID tests.  With them the bound has to end before such a
+// log, too (COST_FREE): 2,800 points of steps up to 2^25 in 64 bits take 0.52 ms
+// in closed form and 0.34 ms by records, 2,000 points of steps up to 2^22 0.17
+// and 0.3 ms.
 namespace {
 constexpr uint32_t CW_BINS = 256;
 constexpr double RECORDS_FREE = 4.0e6, SERIAL_FREE = 512, SERIAL_RECORDS = 16384;
+constexpr double COST_FREE = 2.0e7, EUCLID = 0.5;
 
 // [min, max] of x * (r + m*u) over u in [0, n) (n >= 1); false on overflow
 bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64_t& hi) {
@@ -167,6 +175,18 @@ bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64
   hi = h;
   return true;
 }
+
+// Steps of the Euclidean algorithm on x and y, on average where they are not known.
+double euclid_steps(uint32_t x, uint32_t y) {
+  int n = 0;
+  for (; y != 0; n++) {
+    const uint32_t t = x % y;
+    x = y;
+    y = t;
+  }
+  return n;
+}
+double euclid_mean(int64_t largest) { return 0.584 * std::log2((double)largest + 1); }
 
 double scan_trips(double n, double step, double w, double W) {
   step = step < 0 ? -step : step;
@@ -190,10 +210,17 @@ struct ArrayScratch {
   bool used = false, full = false;       // some access; an arc round the circle
   uint64_t bins[CW_BINS / 64] = {};
   // the closed form's bound
-  static constexpr int MAXC = 8;         // distinct (b, block condition) of its points
+  // distinct (b, block condition) of its points that are told apart, and distinct
+  // |A|: their pairs are gone through one by one (planning 64 points of one
+  // array takes 0.65 us with one stride, 2.0 us with eight)
+  static constexpr int MAXC = 8;
   struct Blocks { int32_t b, S; uint32_t bm, br, Z; } c[MAXC];
   int nc = 0;
   bool many = false;                     // more than MAXC of them
+  uint32_t step[MAXC];
+  int ns = 0;
+  bool steps = false;                    // more than MAXC of them
+  uint32_t step_max = 0;                 // the largest of all
   uint64_t n = 0, intra = 0, inter = 0;  // points, records per block, cross-block records
   int64_t span = 0, bspan = 0;           // largest |A| * (X - 1) and |S| * (Z - 1)
 };
@@ -279,11 +306,16 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   const double bw = 2.0 * (double)a.bspan;
   const bool cross = global && B > 1;
   double t0 = 1, t1 = cross ? 1 : 0;   // tests of a pair: same block, different blocks
+  double e0 = 0, e1 = 0;               // Euclid's steps on two threads' steps, on two blocks'
   bool plain = !a.many;
   if (a.many) {                        // whatever the steps are
     t0 = B;
     if (cross) t1 = std::min(bw + 1, (double)B * B);
+    if (cross) e1 = euclid_mean(words);
   }
+  if (a.steps) e0 = euclid_mean(a.step_max);
+  for (int u = 0; u < a.ns && !a.steps; u++)
+    for (int v = 0; v < u; v++) e0 = std::max(e0, euclid_steps(a.step[u], a.step[v]));
   for (int u = 0; u < a.nc && !a.many; u++) {
     for (int v = 0; v <= u; v++) {
       const auto &p = a.c[u], &q = a.c[v];
@@ -297,6 +329,7 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
       if (cross) {
         const double sp = std::abs((double)p.S), sq = std::abs((double)q.S);
         const double g = gcd_of<int64_t>((int64_t)sp, (int64_t)sq);
+        e1 = std::max(e1, euclid_steps((uint32_t)sp, (uint32_t)sq));
         const double n = g > 0 ? (sp * (p.Z - 1.0) + sq * (q.Z - 1.0)) / g + 1 : 1;
         if (n <= (double)p.Z * q.Z) t1 = std::max(t1, scan_trips(n, g, w, W));
         else t1 = std::max(t1, p.Z <= q.Z ? p.Z * scan_trips(q.Z, q.S, w, W)
@@ -308,7 +341,10 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   const double n = (double)a.n, rec = (double)a.intra * B + (double)a.inter;
   const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
   const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
-  if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) return false;
+  const double cost = work + n * (n + 1) / 2 * EUCLID * (e0 * (cross ? 2 : 1) + e1);
+  if (work > RECORDS_FREE + rec || cost > COST_FREE + rec ||
+      serial > SERIAL_FREE + rec / SERIAL_RECORDS)
+    return false;
   if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE || T > SMALL_SIZE ||
       B > SMALL_SIZE)
     form = FORM_WIDE;
@@ -420,11 +456,18 @@ void make_plan(const rp_kernel* k, Plan& pl) {
         const Access s = make_access(p.a, p.b, 0, ar.words, t.m, t.r, g.cnt, g.bm, g.br, pl.B);
         a.span = std::max<int64_t>(a.span, abs_of<int64_t>(s.A) * (int64_t)(s.X - 1));
         a.bspan = std::max<int64_t>(a.bspan, abs_of<int64_t>(s.S) * (int64_t)(s.Z - 1));
+        const uint32_t as = (uint32_t)abs_of<int64_t>(s.A);
+        a.step_max = std::max(a.step_max, as);
         int q = 0;
-        while (q < a.nc && !(a.c[q].b == s.b && a.c[q].bm == s.bm && a.c[q].br == s.br)) q++;
-        if (q == a.nc) {
-          if (a.nc == ArrayScratch::MAXC) a.many = true;
-          else a.c[a.nc++] = {s.b, s.S, s.bm, s.br, s.Z};
+        if (!a.many) {
+          while (q < a.nc && !(a.c[q].b == s.b && a.c[q].bm == s.bm && a.c[q].br == s.br)) q++;
+          if (q == ArrayScratch::MAXC) a.many = true;
+          else if (q == a.nc) a.c[a.nc++] = {s.b, s.S, s.bm, s.br, s.Z};
+        }
+        if (!a.steps) {
+          for (q = 0; q < a.ns && a.step[q] != as;) q++;
+          if (q == ArrayScratch::MAXC) a.steps = true;
+          else if (q == a.ns) a.step[a.ns++] = as;
         }
       }
     }

@@ -4,8 +4,8 @@ import pytest
 
 from oracle import oracle as O
 from paper_2011_08373_amd import synth
-from test_gpu_parity import L, same_repair  # noqa: F401  (L is a fixture)
-from test_plan_rules import _one_array
+from test_gpu_parity import L, _first_from_pairs, same_repair  # noqa: F401  (L is a fixture)
+from test_plan_rules import _one_array, _steps
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,16 @@ def test_long_walks_are_spread(L):  # noqa: F811
             ms.append(L.last_stats()["ms_total"])
         times.append(min(ms))
     assert times[1] < 8 * times[0], times
+
+
+@pytest.mark.parametrize("P,words,records", [
+    (500, 0xFFFFFFF1, False), (2800, 0xFFFFFFF1, True), (700, (1 << 27) - 39, False),
+    (700, (1 << 20) - 3, True),          # (a pair's range is 16 times the array)
+    (3000, (1 << 20) - 3, True)])
+def test_steps_that_share_no_divisor(L, P, words, records):  # noqa: F811
+    km = _steps(P, 32, words, lambda i: 1 + 7919 * i, 2654435761)
+    st, first, div = L.first_partners(km, 0)
+    assert (L.last_stats()["records"] > 0) == records
+    o = O.check(km, 0)
+    assert st == 0 and div == o[2]
+    assert (first.astype("uint64") == _first_from_pairs(o[1], km.n_points)).all()

@@ -18,7 +18,9 @@ def plan(tmp_path_factory):
                            "--cuda-host-only", "-std=c++17", "-O1", "-shared", "-fPIC",
                            "-o", so, os.path.join(HERE, "plan_facts.cpp"),
                            os.path.join(build.CSRC, "librepair.cpp")])
-    return C.CDLL(so)
+    lib = C.CDLL(so)
+    lib.plan_records.restype = C.c_longlong
+    return lib
 
 
 @pytest.fixture(scope="module")
@@ -55,3 +57,23 @@ def test_packed_by_tests(plan, arg, km, packed):
 def test_small_kernels_are_packed(plan, arg):
     for seed in range(20):
         assert plan.plan_packed(arg(synth.generate("plain-small", seed=seed)).ref) == 1
+
+
+def _steps(P, T, words, steps, gap):
+    """P writes of T threads of one block, gap words apart, thread steps in turn."""
+    pts = [dict(kind=0, is_write=1, a=steps(i), b=0, c=gap * i % (1 << 31)) for i in range(P)]
+    return synth.make_kernel(1, T, [(words, 0)], [(1, 0)], pts, [])
+
+
+@pytest.mark.parametrize("km,records", [
+    (_steps(2800, 32, 1 << 17, lambda i: 1, 32), False),
+    (_steps(2800, 32, 0xFFFFFFF0, lambda i: 1, 32), False),
+    (_steps(2800, 32, 0xFFFFFFF0, lambda i: (1, 2, 4, -1)[i % 4], 128), False),
+    # unrelated steps: twenty-odd steps of Euclid's algorithm a pair
+    (_steps(2800, 32, 0xFFFFFFF1, lambda i: 1 + 7919 * i, 2654435761), True),
+    (_steps(3900, 1024, 0xFFFFFFF1, lambda i: 1 + 397 * i, 2654435761), True),
+    (_steps(500, 32, 0xFFFFFFF1, lambda i: 1 + 7919 * i, 2654435761), False),
+    (_steps(3000, 32, (1 << 27) - 39, lambda i: 1 + 1399 * i, 2654435761), True),
+], ids=["one", "one-64-bit", "related", "unrelated", "unrelated-wide", "few", "unrelated-32-bit"])
+def test_steps_that_share_no_divisor(plan, arg, km, records):
+    assert (plan.plan_records(arg(km).ref) > 0) == records
