@@ -58,6 +58,11 @@ static void make_plans(const rp_kernel* const* ks, uint32_t n, std::vector<Plan>
   over_jobs(n, points, [&](uint32_t first, uint32_t last) {
     for (uint32_t j = first; j < last; j++) one(j);
   });
+  std::vector<Plan*> call;
+  call.reserve(n);
+  for (uint32_t j = 0; j < n; j++)
+    if (ok[j]) call.push_back(&plans[j]);
+  choose_routes(call.data(), call.size());
 }
 
 // The result of one repair job from its final device state.

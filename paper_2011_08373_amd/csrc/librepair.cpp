@@ -153,14 +153,18 @@ int validate_kernel(const rp_kernel* k) {
 // line, 250 points of 352 threads and 2,048 blocks: 3.2 ms, 3.9 by records).
 // A pair's gcd and inverse come on top: 6 ps per step of Euclid's algorithm in
 // 32 bits and 8.5 ps in 64 (2,000 and 2,800 points of unrelated steps: 85 and
-// 134 ps a pair), EUCLID tests.  With them the bound has to end before such a
-// log, too (COST_FREE): 2,800 points of steps up to 2^25 in 64 bits take 0.52 ms
-// in closed form and 0.34 ms by records, 2,000 points of steps up to 2^22 0.17
-// and 0.3 ms.
+// 134 ps a pair), EUCLID tests each.  What the bounds of all arrays of a call
+// cost with them beyond the arrays' own records has to end before a log's
+// launches, which the call would make once (COST_FREE, 0.2 ms); the arrays of
+// most cost are left to the records where it does not (choose_routes).  2,800
+// points of steps up to 2^25 in 64 bits take 0.52 ms in closed form and 0.34 ms
+// by records, 2,000 points of steps up to 2^22 0.17 and 0.3 ms; the 64 kernels
+// above 1.28 and 0.33 ms (0.04 and 0.25 alone), 64 of 1,000 points 0.16 and
+// 0.26 ms.  128 batched kernels come to 2 to 3M tests, 1,024 to 17M.
 namespace {
 constexpr uint32_t CW_BINS = 256;
 constexpr double RECORDS_FREE = 4.0e6, SERIAL_FREE = 512, SERIAL_RECORDS = 16384;
-constexpr double COST_FREE = 2.0e7, EUCLID = 0.5;
+constexpr double COST_FREE = 4.0e7, EUCLID = 1;
 
 // [min, max] of x * (r + m*u) over u in [0, n) (n >= 1); false on overflow
 bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64_t& hi) {
@@ -297,10 +301,10 @@ void rotation_of(const ArrayScratch& a, uint64_t N, uint64_t& off, uint64_t& spa
   span = N - gap;
 }
 
-// Whether the closed form's bound takes the array (see above); form: raised to
-// the one it needs; tests: the bound is added.
-bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B, uint32_t T,
-                  int& form, double& tests) {
+// Whether the closed form's bound can take the array (see above): then the form
+// it needs, the bound on its tests, and what that costs beyond its own records.
+bool bound_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B, uint32_t T,
+                  PlanArray& o) {
   if (a.n == 0 || a.span >= MAX_SPAN || a.bspan >= MAX_SPAN) return false;
   const double W = words, w = 2.0 * (double)a.span, wraps = 1 + std::floor(w / W);
   const double bw = 2.0 * (double)a.bspan;
@@ -342,15 +346,15 @@ bool takes_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
   const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
   const double cost = work + n * (n + 1) / 2 * EUCLID * (e0 * (cross ? 2 : 1) + e1);
-  if (work > RECORDS_FREE + rec || cost > COST_FREE + rec ||
-      serial > SERIAL_FREE + rec / SERIAL_RECORDS)
-    return false;
+  if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) return false;
+  o.form = FORM_PLAIN;
   if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE || T > SMALL_SIZE ||
       B > SMALL_SIZE)
-    form = FORM_WIDE;
+    o.form = FORM_WIDE;
   else if (!plain)
-    form = std::max(form, FORM_SMALL);
-  tests += work;
+    o.form = FORM_SMALL;
+  o.tests = work;
+  o.over = std::max(0.0, cost - rec);
   return true;
 }
 
@@ -493,11 +497,8 @@ void make_plan(const rp_kernel* k, Plan& pl) {
       mark_bins(a, 0, e0 - N);
     }
   }
-  uint64_t span_max = 1, intra = 0, inter = 0, log_intra = 0, log_inter = 0;
-  pl.arrays.resize(k->n_arrays);
-  pl.any_closed = false;
-  pl.closed_form = FORM_PLAIN;
-  double tests = 0;
+  uint64_t span_max = 1, intra = 0, inter = 0;
+  pl.arrays.assign(k->n_arrays, PlanArray{});
   for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
     const ArrayScratch& a = sc.arrays[arr];
     const uint32_t words = k->arrays[arr].words;
@@ -506,29 +507,66 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     rotation_of(a, words, off, span);
     span_max = std::max(span_max, span);
     o.off = (uint32_t)off;
-    o.closed = g_race_route == 0 && takes_closed(a, words, k->arrays[arr].space == RP_GLOBAL, pl.B,
-                                                 pl.T, pl.closed_form, tests);
+    o.bounded = g_race_route == 0 && bound_closed(a, words, k->arrays[arr].space == RP_GLOBAL,
+                                                  pl.B, pl.T, o);
+    o.intra = a.intra;
+    o.inter = a.inter;
     intra += a.intra;
     inter += a.inter;
-    if (o.closed) {
-      pl.any_closed = true;
-    } else {
-      log_intra += a.intra;
-      log_inter += a.inter;
-    }
   }
   pl.nbits = bits_for(span_max - 1);
   pl.key_bits = pl.abits + pl.nbits;
-  pl.rblk = log_intra;
   pl.n_intra = intra * pl.B;
   pl.n_inter = inter;
-  pl.log_intra = log_intra * pl.B;
-  pl.log_inter = log_inter;
-  pl.packed = pl.P <= PACKED_POINTS && tests <= PACKED_TESTS && log_intra + log_inter == 0;
   pl.grid_slots = pl.pre_slots = 0;
   for (uint32_t s = 0; s < pl.S; s++) {
     if (k->slots[s].level == RP_GRID) pl.grid_slots |= 1ull << s;
     if (k->slots[s].preexisting) pl.pre_slots |= 1ull << s;
+  }
+  Plan* const self = &pl;
+  choose_routes(&self, 1);
+}
+
+void choose_routes(Plan* const* plans, size_t n) {
+  // the least cost over an array's own records that no longer fits
+  std::vector<double> over;
+  double sum = 0, line = INFINITY;
+  for (size_t j = 0; j < n; j++)
+    for (const PlanArray& a : plans[j]->arrays)
+      if (a.bounded && a.over > 0) {
+        over.push_back(a.over);
+        sum += a.over;
+      }
+  if (sum > COST_FREE) {
+    std::sort(over.begin(), over.end());
+    sum = 0;
+    for (double v : over)
+      if ((sum += v) > COST_FREE) {
+        line = v;
+        break;
+      }
+  }
+  for (size_t j = 0; j < n; j++) {
+    Plan& pl = *plans[j];
+    uint64_t intra = 0, inter = 0;
+    double tests = 0;
+    pl.any_closed = false;
+    pl.closed_form = FORM_PLAIN;
+    for (PlanArray& a : pl.arrays) {
+      a.closed = a.bounded && a.over < line;
+      if (a.closed) {
+        pl.any_closed = true;
+        pl.closed_form = std::max(pl.closed_form, a.form);
+        tests += a.tests;
+      } else {
+        intra += a.intra;
+        inter += a.inter;
+      }
+    }
+    pl.rblk = intra;
+    pl.log_intra = intra * pl.B;
+    pl.log_inter = inter;
+    pl.packed = pl.P <= PACKED_POINTS && tests <= PACKED_TESTS && intra + inter == 0;
   }
 }
 

@@ -14,8 +14,12 @@ struct PlanGuard {                  // a guard over the kernel's threads and blo
   uint32_t bm, br, nblk;            // block condition, executing blocks
 };
 struct PlanArray {
-  uint32_t off;                     // rotation of its words in the log
-  bool closed;                      // decided in closed form: no records
+  uint32_t off = 0;                 // rotation of its words in the log
+  bool bounded = false;             // the closed form's bound can take it
+  bool closed = false;              // decided in closed form: no records
+  int form = FORM_PLAIN;            // the narrowest form it fits
+  double tests = 0, over = 0;       // the bound; its cost beyond the records' own
+  uint64_t intra = 0, inter = 0;    // records per block, cross-block records
 };
 
 // What the host works out of a kernel model.  The kernel's descriptors have
@@ -41,6 +45,10 @@ struct Plan {
 
 int validate_kernel(const rp_kernel* k);
 void make_plan(const rp_kernel* k, Plan& pl);
+// Which arrays of a call's kernels are decided in closed form.  make_plan has
+// done it for its kernel alone; a call over several decides them together (its
+// launches, which make room for work beyond the records' own, are shared).
+void choose_routes(Plan* const* plans, size_t n);
 // The device's point table, and the prefix tables of its records ([P + 1]).
 void fill_points(const Plan& pl, DPoint* pts);
 void fill_prefixes(const Plan& pl, const DPoint* pts, uint64_t* cnt_pre, uint64_t* gcnt_pre);

@@ -239,6 +239,10 @@ rp_status rp_server_step(void* srv, uint32_t* n_resident, uint32_t* n_pending) {
       n_take++;
     }
     if (n_take) {
+      // (no size depends on the routes)
+      std::vector<Plan*> plans(n_take);
+      for (size_t q = 0; q < n_take; q++) plans[q] = &sv->pending[q]->plan;
+      choose_routes(plans.data(), n_take);
       std::vector<PreparedJob> prep;
       const int rc = engine_prepare_group(group, sv->arena + off, gbytes, s, prep, sv->staging);
       if (rc != RP_OK) {

@@ -86,3 +86,24 @@ def test_steps_that_share_no_divisor(L, P, words, records):  # noqa: F811
     o = O.check(km, 0)
     assert st == 0 and div == o[2]
     assert (first.astype("uint64") == _first_from_pairs(o[1], km.n_points)).all()
+
+
+def test_one_allowance_per_call(L):  # noqa: F811
+    # each of the large ones in closed form alone, all of them by records
+    # together, the small ones in closed form beside them
+    kms = [_steps(2800, 32, (1 << 17) - q, lambda i: 1, 32 + (q == 3)) for q in range(11)]
+    kms[2:2] = [synth.generate("plain-small", mode="planted", seed=s) for s in range(10)]
+    assert L.repair(kms[0])["status"] == 0 and L.last_stats()["records"] == 0
+    want = [O.repair(km) for km in kms]
+    st, res = L.repair_batch(kms)
+    assert st == 0 and L.last_stats()["records"] == 11 * 2800 * 32
+    srv = L.Server(arena_bytes=4 << 30, max_resident=32)
+    for q, km in enumerate(kms):
+        assert srv.submit(km, q) == 0
+    got = {}
+    while len(got) < len(kms):
+        srv.step()
+        got.update((job, r) for job, r, _ in srv.poll())
+    for q, o in enumerate(want):
+        for r in (res[q], got[q]):
+            assert all(r[k] == o[k] for k in ("status", "assign", "weight", "rounds", "n_clauses")), q

@@ -19,7 +19,7 @@ def plan(tmp_path_factory):
                            "-o", so, os.path.join(HERE, "plan_facts.cpp"),
                            os.path.join(build.CSRC, "librepair.cpp")])
     lib = C.CDLL(so)
-    lib.plan_records.restype = C.c_longlong
+    lib.plan_records.restype = lib.call_records.restype = C.c_longlong
     return lib
 
 
@@ -77,3 +77,27 @@ def _steps(P, T, words, steps, gap):
 ], ids=["one", "one-64-bit", "related", "unrelated", "unrelated-wide", "few", "unrelated-32-bit"])
 def test_steps_that_share_no_divisor(plan, arg, km, records):
     assert (plan.plan_records(arg(km).ref) > 0) == records
+
+
+def test_one_allowance_per_call(plan, arg):
+    # what the closed form may cost beyond the records stands for the launches
+    # of a log, which a batch makes once
+    from paper_2011_08373_amd import librepair as L
+    one = _steps(2800, 32, 1 << 17, lambda i: 1, 32)          # 3.9M pairs
+    small = synth.generate("plain-small", seed=1)
+
+    def records(kms):
+        b = L.BatchArg(kms)
+        over = C.c_double(0)
+        n = plan.call_records(b.ptrs, b.n, C.byref(over))
+        return n, over.value
+
+    n, over = records([one])
+    assert n == 0 and 3.5e6 < over < 4e6
+    assert records([one] * 10 + [small] * 50)[0] == 0
+    assert records([one] * 11 + [small] * 50) == (11 * 2800 * 32, 11 * over)
+    # arrays of less cost first
+    half = _steps(1400, 32, 1 << 17, lambda i: 1, 32)
+    assert records([one] * 10 + [half] * 8)[0] == 10 * 2800 * 32
+    big = [synth.generate_batch(n=128, mode="planted", seed=s) for s in (3, 4)]
+    assert [records(kms)[0] for kms in big] == [0, 0]         # ordinary batches
