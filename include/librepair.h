@@ -82,8 +82,8 @@ typedef enum {
   RP_ERR_DEVICE = -4,       /* a HIP call or a device-side check failed */
   RP_ERR_ROUNDS = -5,       /* max_rounds Verify calls made without a verdict */
   RP_ERR_BUDGET = -6,       /* server: the job can never fit the memory budget */
-  RP_ERR_SEARCH = -7        /* the exact solver's branch and bound spent its node
-                               budget (RP_TUNE_SOLVER_NODES) on one component */
+  RP_ERR_SEARCH = -7        /* the exact solver spent its node budget
+                               (RP_TUNE_SOLVER_NODES) on one component */
 } rp_status;
 
 enum { RP_ACCESS = 0, RP_BARRIER = 1, RP_NOP = 2 };
@@ -367,7 +367,12 @@ uint32_t rp_sort_key_bits(const rp_kernel* const* ks, uint32_t n);
  *                            branch and bound on one component of the
  *                            constraint set, per wave of the workgroup that
  *                            searches it (4..40, default 28).  A job whose
- *                            search spends it ends with RP_ERR_SEARCH;
+ *                            search spends it ends with RP_ERR_SEARCH.  A
+ *                            component of more than 20 slots whose clauses
+ *                            are runs of neighbouring slots is decided
+ *                            without a search, and counts one node a slot
+ *                            (so budgets of 16 and 32 refuse what a search
+ *                            would not have ended on);
  *   RP_TUNE_SCAN_PIPELINE    first-partner scan: 0 = each wave loads a range
  *                            of records after scanning the one before it,
  *                            1 = the next range's loads are in flight while

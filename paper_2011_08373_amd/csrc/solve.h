@@ -550,9 +550,10 @@ __device__ bool propagate(G get, uint32_t n, uint64_t all, const uint64_t* less,
 // follow a chosen slot p exactly when no clause lies wholly between them,
 // that is when p >= the largest first slot of the clauses that end before s.
 // Every wave computes the same; lane p keeps the best key of a choice that
-// ends with p, its first part in an H.  A run of linked slots longer than
-// ENUM_MAX and than the node budget counts as a search that spends it (returns
-// false).
+// ends with p, its first part in an H.  The budget counts one node per slot of
+// a run of linked slots longer than ENUM_MAX (returns false when it is spent):
+// a caller that sets a budget of fewer nodes than there are slots gets the
+// status that the search gave it, which takes more nodes than slots there.
 template <class H>
 __device__ __forceinline__ bool interval_path(uint64_t M, const uint32_t* s_w, uint64_t budget,
                                               int32_t fl, int32_t ll, uint64_t& answer) {
