@@ -331,8 +331,10 @@ def batched_leg(L, torch, kms):
             "repaired": rep, "unsat": uns, "other": len(kms) - rep - uns,
             "batched_equals_plain": same, "records": bstats["records"],
             "accesses": bstats["accesses"], "rounds": bstats["rounds"],
+            # (with no records ms_gen and ms_sort are no generation and no sort)
             "phases_ms": {k: bstats[k] for k in ("ms_gen", "ms_sort", "ms_j0", "ms_check",
-                                                 "ms_clause", "ms_solve", "ms_total")},
+                                                 "ms_clause", "ms_solve", "ms_total")
+                          if bstats["records"] or k not in ("ms_gen", "ms_sort")},
             # the race-check phase of the batched call, as for the main leg
             "race_check_phase": phase_roofline([bstats]),
             "autotuned": tuned}

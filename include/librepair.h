@@ -149,7 +149,8 @@ typedef struct {
  * are then the time in which its first wave has its own access and has picked
  * the accesses of that array out of the first 64 points, ms_j0 (ms_check of
  * rp_check) the rest of the pair tests, ms_total the time from the first
- * kernel's start to the last one's end, and ms_upload 0. */
+ * kernel's start to the last one's end, and ms_upload 0.  At RP_TUNE_TIMING 2
+ * such a call is timed by hipEvents too, and ms_gen and ms_sort are 0. */
 typedef struct {
   double ms_gen, ms_sort, ms_check, ms_clause, ms_solve, ms_total;
   double ms_sort_pass_max;       /* longest single sort pass */
@@ -160,7 +161,10 @@ typedef struct {
                                     where closed forms decide every conflict */
   uint64_t accesses;             /* (point, block, thread) accesses */
   uint64_t records_scanned;      /* records read by conflict scans */
-  uint32_t sort_passes, sort_launches, rounds, conf_launches;
+  uint32_t sort_passes;          /* radix passes that a log of these kernels is
+                                    sorted in (RP_TUNE_SORT_DIGIT_BITS, ...) */
+  uint32_t sort_launches;        /* passes made; 0 with no records */
+  uint32_t rounds, conf_launches;
   double ms_upload;              /* descriptor upload before record generation */
   double ms_conf_kernels;        /* duration of the scan kernel over the
                                     sorted logs (first partners or all pairs) */

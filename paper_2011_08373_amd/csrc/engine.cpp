@@ -391,14 +391,15 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   }
   tm.mark(T_START);
   HIPCHK(hipMemcpyAsync(d, hbuf, L.upload, hipMemcpyHostToDevice, s));
-  HIPCHK(launch_items((const Job*)(d + L.o_jobs), (const SortSeg*)(d + L.o_ssegs),
-                      (uint32_t)L.ssegs.size(), L.n_chunks, L.chunk_len, (GenItem*)(d + L.o_items),
-                      (SortChunk*)(d + L.o_chunks), s));
+  if (log)
+    HIPCHK(launch_items((const Job*)(d + L.o_jobs), (const SortSeg*)(d + L.o_ssegs),
+                        (uint32_t)L.ssegs.size(), L.n_chunks, L.chunk_len,
+                        (GenItem*)(d + L.o_items), (SortChunk*)(d + L.o_chunks), s));
   tm.mark(T_UPLOAD);
   const Job* djobs = (const Job*)(d + L.o_jobs);
   uint32_t* derr = (uint32_t*)(d + L.o_err);
   // ---- records and sort
-  const int passes = (int)L.passes;
+  const int passes = log ? (int)L.passes : 0;
   const SortSeg* dss = (const SortSeg*)(d + L.o_ssegs);
   const SortChunk* dch = (const SortChunk*)(d + L.o_chunks);
   const uint32_t nch = L.n_chunks;
@@ -409,10 +410,12 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   // every location's records together and in generation order, and the
   // scans need nothing more); generation counts the first pass's digit
   const std::vector<DigitPass>& dg = L.digits;
-  HIPCHK(launch_gen(passes > 0 ? (int)dg[0].bits : 8, (const GenItem*)(d + L.o_items), nch,
-                    djobs, dss, (uint64_t*)(d + L.o_recA), dcnt,
-                    passes > 0 ? (int)dg[0].lo : -1, s));
-  tm.mark(T_GEN);
+  if (log) {
+    HIPCHK(launch_gen(passes > 0 ? (int)dg[0].bits : 8, (const GenItem*)(d + L.o_items), nch,
+                      djobs, dss, (uint64_t*)(d + L.o_recA), dcnt,
+                      passes > 0 ? (int)dg[0].lo : -1, s));
+    tm.mark(T_GEN);
+  }
   for (int p = 0; p < passes; p++) {
     const uint64_t* in = (const uint64_t*)(d + ((p % 2 == 0) ? L.o_recA : L.o_recB));
     uint64_t* out = (uint64_t*)(d + ((p % 2 == 0) ? L.o_recB : L.o_recA));
@@ -427,7 +430,7 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
                                doff, derr + 10, derr, last ? nullptr : dig, s));
     tm.mark(T_SORT);
   }
-  tm.mark(T_SORT, 2);
+  if (log) tm.mark(T_SORT, 2);
   ConfSeg* dcs = (ConfSeg*)(d + L.o_csegs);
   // ---- first partners with no barrier enabled (once per job): every
   // later Verify call resolves its first partners from them

@@ -107,3 +107,25 @@ def test_one_allowance_per_call(L):  # noqa: F811
     for q, o in enumerate(want):
         for r in (res[q], got[q]):
             assert all(r[k] == o[k] for k in ("status", "assign", "weight", "rounds", "n_clauses")), q
+
+
+def test_no_sort_where_there_is_no_log(L):  # noqa: F811
+    # what the statistics say of a call whose conflicts are all in closed form,
+    # and of the same one by records, with every phase timed
+    km = synth.generate("plain-large", mode="planted")
+    old = L.set_tuning(L.TUNE_TIMING, 2), L.set_tuning(L.TUNE_RACE_ROUTE, 0)
+    try:
+        r0 = L.repair(km)
+        s = L.last_stats()
+        assert s["records"] == s["sort_launches"] == s["conf_launches"] == 0
+        assert s["ms_gen"] == s["ms_sort"] == s["ms_sort_kernels"] == s["ms_sort_pass_max"] == 0
+        assert s["ms_upload"] > 0 and s["ms_j0"] > 0 and s["ms_total"] > 0
+        L.set_tuning(L.TUNE_RACE_ROUTE, 1)
+        r1 = L.repair(km)
+        s = L.last_stats()
+        assert s["records"] > 0 and s["sort_launches"] == s["sort_passes"] > 0
+        assert s["ms_gen"] > 0 and s["ms_sort"] > 0 and s["ms_sort_kernels"] > 0
+        assert same_repair(r0, r1)
+    finally:
+        L.set_tuning(L.TUNE_TIMING, old[0])
+        L.set_tuning(L.TUNE_RACE_ROUTE, old[1])
