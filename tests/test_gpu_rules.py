@@ -1,5 +1,6 @@
 """Kernels on both sides of the plan's lines (how conflicts are decided and by
 which kernel) against the oracle: alone, together in a batch, and served."""
+import numpy as np
 import pytest
 
 from oracle import oracle as O
@@ -129,3 +130,41 @@ def test_no_sort_where_there_is_no_log(L):  # noqa: F811
     finally:
         L.set_tuning(L.TUNE_TIMING, old[0])
         L.set_tuning(L.TUNE_RACE_ROUTE, old[1])
+
+
+def _large_words(seed):
+    """Points whose steps come up to the largest spans of 32-bit arithmetic, on
+    arrays of up to 2^30 words; a third of them on words that others touch."""
+    rng = np.random.default_rng(seed)
+    T = int(round(2 ** rng.uniform(3, 10)))
+    B = int(rng.integers(1, 9))
+    W = int(round(2 ** rng.uniform(16, 30)))
+    most = min((2**28 - 1) // (T - 1), W // 2)
+    steps = [1, most, most - 1] + [max(1, int(most ** u)) for u in rng.random(3)]
+    strides = [0, min(T, W // 2)] + [int(min(W // 2, 2**27 // max(1, B - 1)) ** u) for u in rng.random(2)]
+    pts = []
+    for i in range(60):
+        if i % 12 == 11:
+            pts.append(dict(kind=1, slot=i // 12))
+            continue
+        a, b = int(rng.choice(steps)) * int(rng.choice([1, -1])), int(rng.choice(strides))
+        c = int(rng.integers(0, min(W, 2**31)))
+        if i % 3 == 0:
+            c = (int(rng.choice(steps)) * int(rng.integers(0, T))) % W
+        pts.append(dict(kind=0, is_write=int(rng.random() < 0.6), a=a, b=b, c=c))
+    slots = [(s % 2, 0, 1) for s in range(5)]
+    return synth.make_kernel(B, T, [(W, 1)], [(1, 0)], pts, slots)
+
+
+def test_large_words(L):  # noqa: F811
+    closed = 0
+    for seed in range(100):
+        km = _large_words(seed)
+        for x in (0, 5):
+            g = L.check(km, x)[:4]
+            closed += L.last_stats()["records"] == 0
+            assert g == O.check(km, x), (seed, x)
+        st, first, _ = L.first_partners(km, 0)
+        assert (first.astype("uint64") == _first_from_pairs(O.check(km, 0)[1], km.n_points)).all()
+        assert same_repair(L.repair(km), O.repair(km)), seed
+    assert closed >= 80
