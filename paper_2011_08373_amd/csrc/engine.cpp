@@ -11,6 +11,7 @@
 #include "common.h"
 #include "launch.h"
 #include "plan.h"
+#include "stage.h"
 
 namespace rp {
 
@@ -254,59 +255,6 @@ size_t engine_workspace(const std::vector<JobInput>& jobs, const EngineOpts& o) 
     if ((x) != hipSuccess) return RP_ERR_DEVICE; \
   } while (0)
 
-// Page-locked host staging for the descriptor upload, one per host thread,
-// grown on demand and kept for the life of the thread (never freed: a
-// thread-exit free could run after the runtime is gone).  A call waits for
-// its stream before it returns; one that fails before that leaves an event
-// behind its upload, which the next call waits for before writing.
-struct PinnedStage {
-  uint8_t* p = nullptr;
-  size_t cap = 0;
-  hipEvent_t done = nullptr;
-  bool pending = false;
-  uint8_t* get(size_t n) {
-    if (pending) {
-      if (!done || hipEventSynchronize(done) != hipSuccess) return nullptr;
-      pending = false;
-    }
-    if (n > cap) {
-      if (p) (void)hipHostFree(p);
-      p = nullptr;
-      cap = 0;
-      if (hipHostMalloc((void**)&p, n < 4096 ? 4096 : n, hipHostMallocDefault) != hipSuccess) {
-        p = nullptr;
-        return nullptr;
-      }
-      cap = n < 4096 ? 4096 : n;
-    }
-    return p;
-  }
-  // page-locked space for results read back by this thread's calls (each
-  // call waits for its copies before it returns)
-  uint8_t* rb = nullptr;
-  size_t rb_cap = 0;
-  template <class T = uint32_t>
-  T* readback(size_t n) {
-    if (n > rb_cap) {
-      if (rb) (void)hipHostFree(rb);
-      rb = nullptr;
-      rb_cap = 0;
-      const size_t want = n < 4096 ? 4096 : n;
-      if (hipHostMalloc((void**)&rb, want, hipHostMallocDefault) != hipSuccess) {
-        rb = nullptr;
-        return nullptr;
-      }
-      rb_cap = want;
-    }
-    return reinterpret_cast<T*>(rb);
-  }
-  // the uploads out of the buffer were enqueued on s
-  void in_flight(hipStream_t s) {
-    if (!done && hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) done = nullptr;
-    if (done && hipEventRecord(done, s) == hipSuccess) pending = true;
-    else (void)hipStreamSynchronize(s);
-  }
-};
 thread_local PinnedStage t_stage;
 
 namespace {
