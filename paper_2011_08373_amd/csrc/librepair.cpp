@@ -180,17 +180,19 @@ bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64
   return true;
 }
 
-// Steps of the Euclidean algorithm on x and y, on average where they are not known.
-double euclid_steps(uint32_t x, uint32_t y) {
-  int n = 0;
-  for (; y != 0; n++) {
+// The gcd of x and y, and the steps of Euclid's algorithm to it (n: the most so
+// far); their mean where the two are not known.
+uint32_t gcd_steps(uint32_t x, uint32_t y, double& n) {
+  int k = 0;
+  for (; y > 1; k++) {
     const uint32_t t = x % y;
     x = y;
     y = t;
   }
-  return n;
+  if (k > n) n = k;
+  return y ? 1 : x;
 }
-double euclid_mean(int64_t largest) { return 0.584 * std::log2((double)largest + 1); }
+double mean_steps(int64_t largest) { return 0.584 * std::log2((double)largest + 1); }
 
 double scan_trips(double n, double step, double w, double W) {
   step = step < 0 ? -step : step;
@@ -207,6 +209,13 @@ struct Combo {
   uint64_t intra = 0, inter = 0;         // records per block, cross-block records
   int64_t lo = 0, hi = 0;                // range of a*t + b*k
 };
+
+// Its place in the table: the top bits of a product, so that strides that are
+// multiples of the table's size (block strides commonly are) differ in it.
+uint32_t combo_index(const rp_point& p) {
+  return (((uint32_t)p.array * 31u + (uint32_t)p.guard * 7u + (uint32_t)p.a * 5u + (uint32_t)p.b) *
+          0x9E3779B1u) >> 24;
+}
 
 struct ArrayScratch {
   uint64_t bw = 1;                       // words per bin; its shift where a power of two
@@ -315,11 +324,11 @@ bool bound_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   if (a.many) {                        // whatever the steps are
     t0 = B;
     if (cross) t1 = std::min(bw + 1, (double)B * B);
-    if (cross) e1 = euclid_mean(words);
+    if (cross) e1 = mean_steps(words);
   }
-  if (a.steps) e0 = euclid_mean(a.step_max);
+  if (a.steps) e0 = mean_steps(a.step_max);
   for (int u = 0; u < a.ns && !a.steps; u++)
-    for (int v = 0; v < u; v++) e0 = std::max(e0, euclid_steps(a.step[u], a.step[v]));
+    for (int v = 0; v < u; v++) (void)gcd_steps(a.step[u], a.step[v], e0);
   for (int u = 0; u < a.nc && !a.many; u++) {
     for (int v = 0; v <= u; v++) {
       const auto &p = a.c[u], &q = a.c[v];
@@ -332,8 +341,7 @@ bool bound_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
       }
       if (cross) {
         const double sp = std::abs((double)p.S), sq = std::abs((double)q.S);
-        const double g = gcd_of<int64_t>((int64_t)sp, (int64_t)sq);
-        e1 = std::max(e1, euclid_steps((uint32_t)sp, (uint32_t)sq));
+        const double g = gcd_steps((uint32_t)sp, (uint32_t)sq, e1);
         const double n = g > 0 ? (sp * (p.Z - 1.0) + sq * (q.Z - 1.0)) / g + 1 : 1;
         if (n <= (double)p.Z * q.Z) t1 = std::max(t1, scan_trips(n, g, w, W));
         else t1 = std::max(t1, p.Z <= q.Z ? p.Z * scan_trips(q.Z, q.S, w, W)
@@ -374,6 +382,43 @@ void records_of(uint32_t cnt, uint64_t nblk, bool tconst, bool bconst, bool cros
 }
 
 }  // namespace
+
+// The least cost beyond an array's own records that no longer fits into the
+// plans' allowance, least cost first.
+static double cost_line(Plan* const* plans, size_t n) {
+  std::vector<double> over;
+  for (size_t j = 0; j < n; j++)
+    for (const PlanArray& a : plans[j]->arrays)
+      if (a.over > 0) over.push_back(a.over);
+  std::sort(over.begin(), over.end());
+  double sum = 0;
+  for (double v : over)
+    if ((sum += v) > COST_FREE) return v;
+  return INFINITY;
+}
+
+// The arrays below the line in closed form, and what follows from it.
+static void set_routes(Plan& pl, double line) {
+  uint64_t intra = 0, inter = 0;
+  double tests = 0;
+  pl.any_closed = false;
+  pl.closed_form = FORM_PLAIN;
+  for (PlanArray& a : pl.arrays) {
+    a.closed = a.bounded && a.over < line;
+    if (a.closed) {
+      pl.any_closed = true;
+      pl.closed_form = std::max(pl.closed_form, a.form);
+      tests += a.tests;
+    } else {
+      intra += a.intra;
+      inter += a.inter;
+    }
+  }
+  pl.rblk = intra;
+  pl.log_intra = intra * pl.B;
+  pl.log_inter = inter;
+  pl.packed = pl.P <= PACKED_POINTS && tests <= PACKED_TESTS && intra + inter == 0;
+}
 
 void make_plan(const rp_kernel* k, Plan& pl) {
   pl.k = k;
@@ -438,8 +483,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     }
     const rp_array& ar = k->arrays[p.array];
     ArrayScratch& a = sc.arrays[p.array];
-    Combo& c = sc.combos[((uint32_t)p.array * 31u + (uint32_t)p.guard * 7u + (uint32_t)p.a * 5u +
-                          (uint32_t)p.b) & 255u];
+    Combo& c = sc.combos[combo_index(p)];
     if (!(c.epoch == sc.epoch && c.array == p.array && c.guard == p.guard && c.a == p.a &&
           c.b == p.b)) {
       c.epoch = sc.epoch;
@@ -499,6 +543,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
   }
   uint64_t span_max = 1, intra = 0, inter = 0;
   pl.arrays.assign(k->n_arrays, PlanArray{});
+  pl.over = 0;
   for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
     const ArrayScratch& a = sc.arrays[arr];
     const uint32_t words = k->arrays[arr].words;
@@ -509,6 +554,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     o.off = (uint32_t)off;
     o.bounded = g_race_route == 0 && bound_closed(a, words, k->arrays[arr].space == RP_GLOBAL,
                                                   pl.B, pl.T, o);
+    pl.over += o.over;
     o.intra = a.intra;
     o.inter = a.inter;
     intra += a.intra;
@@ -524,50 +570,15 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     if (k->slots[s].preexisting) pl.pre_slots |= 1ull << s;
   }
   Plan* const self = &pl;
-  choose_routes(&self, 1);
+  set_routes(pl, pl.over <= COST_FREE ? INFINITY : cost_line(&self, 1));
 }
 
 void choose_routes(Plan* const* plans, size_t n) {
-  // the least cost over an array's own records that no longer fits
-  std::vector<double> over;
-  double sum = 0, line = INFINITY;
-  for (size_t j = 0; j < n; j++)
-    for (const PlanArray& a : plans[j]->arrays)
-      if (a.bounded && a.over > 0) {
-        over.push_back(a.over);
-        sum += a.over;
-      }
-  if (sum > COST_FREE) {
-    std::sort(over.begin(), over.end());
-    sum = 0;
-    for (double v : over)
-      if ((sum += v) > COST_FREE) {
-        line = v;
-        break;
-      }
-  }
-  for (size_t j = 0; j < n; j++) {
-    Plan& pl = *plans[j];
-    uint64_t intra = 0, inter = 0;
-    double tests = 0;
-    pl.any_closed = false;
-    pl.closed_form = FORM_PLAIN;
-    for (PlanArray& a : pl.arrays) {
-      a.closed = a.bounded && a.over < line;
-      if (a.closed) {
-        pl.any_closed = true;
-        pl.closed_form = std::max(pl.closed_form, a.form);
-        tests += a.tests;
-      } else {
-        intra += a.intra;
-        inter += a.inter;
-      }
-    }
-    pl.rblk = intra;
-    pl.log_intra = intra * pl.B;
-    pl.log_inter = inter;
-    pl.packed = pl.P <= PACKED_POINTS && tests <= PACKED_TESTS && intra + inter == 0;
-  }
+  double over = 0;
+  for (size_t j = 0; j < n; j++) over += plans[j]->over;
+  if (over <= COST_FREE) return;             // (nor is any of them over it alone)
+  const double line = cost_line(plans, n);
+  for (size_t j = 0; j < n; j++) set_routes(*plans[j], line);
 }
 
 void fill_points(const Plan& pl, DPoint* pts) {
