@@ -15,13 +15,13 @@
 //
 // Bound: instruction latency for one kernel (a pair costs two or three hundred
 // instructions in one lane, its divisions by reciprocals), instruction issue and
-// waves in flight for a batch.  Measured: 21 us for the stress kernel (512
+// waves in flight for a batch.  Measured: 22 us for the stress kernel (512
 // accesses of 4.2M threads; generating, sorting and scanning their 2.0G records
-// took 31 ms), 11 us for plain-large (12 us with integer divisions, 17 us with
-// every chunk tested at once, 0.56 ms by records), 113 us for 128 kernels of
-// the batched distribution (154 us with integer divisions in workgroups of four
-// waves, 338 us with a wave per row and every chunk tested at once, 9.2 ms by
-// records); every pair of plain-large under a quarter of its barriers 13 us (14
+// took 31 ms), 12 to 15 us for plain-large (a microsecond more with integer
+// divisions, 17 us with every chunk tested at once, 0.56 ms by records), 113 to
+// 116 us for 128 kernels of the batched distribution (154 us with integer
+// divisions in workgroups of four waves, 338 us with a wave per row and every
+// chunk tested at once, 9.2 ms by records); every pair of plain-large under a quarter of its barriers 13 us (14
 // us; 31 us; 1.39 ms for the scan of its sorted records, and 0.45 ms to generate
 // and sort them).
 #include "closed_rows.h"

@@ -121,7 +121,7 @@ struct Job {
   uint32_t nbits, policy;     // word-field width; learning policy
   const DPoint* pts;          // [P]
   const rp_clause* phi0;      // [n_phi at the start] option units, or a lone Solve's clauses
-  const void* unused[2];
+  const void* room[2];        // (workspace sizes follow the size of this table)
   const uint32_t* weights;    // [S]
   const uint64_t* cnt_pre;    // [P+1] prefix of same-block records per block
   const uint64_t* gcnt_pre;   // [P+1] prefix of cross-block records

@@ -380,8 +380,8 @@ int prepare_jobs(const std::vector<JobInput>& jobs, const EngineOpts& o, const L
   }
   if (log) tm.mark(T_SORT, 2);
   ConfSeg* dcs = (ConfSeg*)(d + L.o_csegs);
-  // ---- first partners with no barrier enabled (once per job): every
-  // later Verify call resolves its first partners from them
+  // ---- first partners with no barrier enabled (once per job): the rounds'
+  // clause tables, and the first partners under an assignment, follow from them
   // (a job without access records keeps the cleared table: no partner)
   // (with no log at all a check or a first-partner call goes to its pairs
   // directly, under its assignment)

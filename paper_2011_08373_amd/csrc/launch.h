@@ -87,9 +87,10 @@ constexpr int RD_BUILD = 1, RD_SOLVE = 2, RD_LOOP = 4, RD_LEARN = 8, RD_TIMED = 
 // spreads the rows over the chip: 128 points of one array that never conflict
 // 64 and 12 + 5 us over one view, 189 and 12 + 8 us over two, and 15 ms and 0.3
 // ms where a pair's walk meets 256 values; 32 points over one view 40 and 37 us
-// a call.  512 programs together took 78 us with none packed, 68 to 69 us with
-// the line at 512 or 1,024 and 70 us with all up to 128 points; 128 batched
-// kernels 161 us, 180 us from 4,096 on.
+// a call.  In batches the launch is shared and the line matters less: 512
+// programs together 104 us with the line at 128, 512 or 1,024 and 101 us with all
+// up to 128 points packed, 128 batched kernels 154 us up to 2,048 and 162 us
+// with all (means over eight seeds).
 constexpr uint32_t PACKED_POINTS = 128;
 constexpr double PACKED_TESTS = 512;
 hipError_t launch_rounds(const Job* jobs, uint32_t njobs, int form, int flags, uint32_t limit,
