@@ -151,6 +151,10 @@ int validate_kernel(const rp_kernel* k) {
 // the log's own work (RECORDS_FREE tests cost no more than the launches), and
 // where the tests of one lane in sequence end before the log would (at the
 // line, 250 points of 352 threads and 2,048 blocks: 3.2 ms, 3.9 by records).
+// Where 64-bit steps share no divisor a test in one lane takes 2 us (SLOW_STEP:
+// six 64-bit divisions that others are spared): 120 points in 22 rows of 289
+// such tests 0.63 ms, by records 0.31.
+//
 // A pair's gcd and inverse come on top: 6 ps per step of Euclid's algorithm in
 // 32 bits and 8.5 ps in 64 (2,000 and 2,800 points of unrelated steps: 85 and
 // 134 ps a pair), EUCLID tests each.  What the bounds of all arrays of a call
@@ -165,6 +169,7 @@ namespace {
 constexpr uint32_t CW_BINS = 256;
 constexpr double RECORDS_FREE = 4.0e6, SERIAL_FREE = 512, SERIAL_RECORDS = 16384;
 constexpr double COST_FREE = 4.0e7, EUCLID = 1;
+constexpr double SLOW_STEP = 5;
 
 // [min, max] of x * (r + m*u) over u in [0, n) (n >= 1); false on overflow
 bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64_t& hi) {
@@ -352,15 +357,17 @@ bool bound_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   }
   const double n = (double)a.n, rec = (double)a.intra * B + (double)a.inter;
   const double work = n * (n + 1) / 2 * (t0 + t1) * wraps;
-  const double serial = std::ceil(n / 64) * std::max(t0, t1) * wraps;
+  const bool wide = a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE ||
+                    T > SMALL_SIZE || B > SMALL_SIZE;
+  // one lane's chain of tests
+  const bool slow = wide && e0 + e1 > 2;
+  const double serial = std::ceil(n / 64) * (std::max(t0, t1) * wraps * (slow ? SLOW_STEP : 1) +
+                                             (slow ? e0 + e1 : 0));
   const double cost = work + n * (n + 1) / 2 * EUCLID * (e0 * (cross ? 2 : 1) + e1);
   if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) return false;
   o.form = FORM_PLAIN;
-  if (a.span >= SMALL_SPAN || a.bspan >= SMALL_SPAN || words > SMALL_SIZE || T > SMALL_SIZE ||
-      B > SMALL_SIZE)
-    o.form = FORM_WIDE;
-  else if (!plain)
-    o.form = FORM_SMALL;
+  if (wide) o.form = FORM_WIDE;
+  else if (!plain) o.form = FORM_SMALL;
   o.tests = work;
   o.over = std::max(0.0, cost - rec);
   return true;

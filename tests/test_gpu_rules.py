@@ -6,7 +6,7 @@ import pytest
 from oracle import oracle as O
 from paper_2011_08373_amd import synth
 from test_gpu_parity import L, _first_from_pairs, same_repair  # noqa: F401  (L is a fixture)
-from test_plan_rules import _one_array, _steps
+from test_plan_rules import UNRELATED, _one_array, _steps, _walks
 
 pytestmark = pytest.mark.gpu
 
@@ -168,3 +168,15 @@ def test_large_words(L):  # noqa: F811
         assert (first.astype("uint64") == _first_from_pairs(O.check(km, 0)[1], km.n_points)).all()
         assert same_repair(L.repair(km), O.repair(km)), seed
     assert closed >= 80
+
+
+@pytest.mark.parametrize("words", [(1 << 30) - 35, 0xFFFFFFF1])
+def test_chains_of_64_bit_divisions(L, words):  # noqa: F811
+    # in closed form in 32 bits, by records in 64
+    km = _walks(words, (1007, 2003, 3001), UNRELATED)
+    for q in range(1, 28, 2):
+        km.points["c"][q] = km.points["c"][q - 1] + (q % 3)
+    o = O.check(km, 0)
+    assert L.check(km, 0)[:4] == o
+    assert (L.last_stats()["records"] == 0) == (words < 2**30)
+    assert same_repair(L.repair(km), O.repair(km))

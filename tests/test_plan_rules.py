@@ -51,12 +51,14 @@ def _one_array(P, T, B, step, apart):
 def test_packed_by_tests(plan, arg, km, packed):
     # one workgroup tests a packed kernel's pairs: few points are not enough
     # where each pair's test walks many values
-    assert plan.plan_packed(arg(km).ref) == packed
+    ka = arg(km)
+    assert plan.plan_packed(ka.ref) == packed
 
 
 def test_small_kernels_are_packed(plan, arg):
     for seed in range(20):
-        assert plan.plan_packed(arg(synth.generate("plain-small", seed=seed)).ref) == 1
+        ka = arg(synth.generate("plain-small", seed=seed))
+        assert plan.plan_packed(ka.ref) == 1
 
 
 def _steps(P, T, words, steps, gap):
@@ -76,7 +78,31 @@ def _steps(P, T, words, steps, gap):
     (_steps(3000, 32, (1 << 27) - 39, lambda i: 1 + 1399 * i, 2654435761), True),
 ], ids=["one", "one-64-bit", "related", "unrelated", "unrelated-wide", "few", "unrelated-32-bit"])
 def test_steps_that_share_no_divisor(plan, arg, km, records):
-    assert (plan.plan_records(arg(km).ref) > 0) == records
+    ka = arg(km)
+    assert (plan.plan_records(ka.ref) > 0) == records
+
+
+def _walks(words, steps, strides):
+    """28 accesses of 100 threads and 20 blocks: pairs of different block strides
+    are gone through block by block."""
+    pts = [dict(kind=0, is_write=i & 1, a=steps[i % len(steps)], b=strides[i % len(strides)],
+                c=1000 * i) for i in range(28)]
+    return synth.make_kernel(20, 100, [(words, 1)], [(1, 0)], pts, [])
+
+
+UNRELATED = (171417, -254275, 309673)
+
+
+@pytest.mark.parametrize("km,records", [
+    (_walks((1 << 30) - 35, (1007, 2003, 3001), UNRELATED), False),
+    (_walks(0xFFFFFFF1, (1007, 2003, 3001), UNRELATED), True),
+    (_walks(0xFFFFFFF1, (1,), (0, 100)), False),
+], ids=["32-bit", "unrelated-64-bit", "related-64-bit"])
+def test_chains_of_64_bit_divisions(plan, arg, km, records):
+    # one lane's chain of tests, each several 64-bit divisions where the steps
+    # share no divisor
+    ka = arg(km)
+    assert (plan.plan_records(ka.ref) > 0) == records
 
 
 def test_one_allowance_per_call(plan, arg):
