@@ -374,7 +374,7 @@ bool bound_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
 }
 
 bool divides(uint32_t words, int32_t a) {                // a = 0 mod words
-  return word_mod(a, words) == 0;
+  return (a < 0 ? 0u - (uint32_t)a : (uint32_t)a) % words == 0;
 }
 
 // Records of an access point (the reductions are listed in common.h): per

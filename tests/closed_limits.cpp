@@ -33,6 +33,16 @@ int main(int argc, char** argv) {
     const double u = (double)(g() >> 11) / 9007199254740992.0;
     return (int64_t)std::llround(lo * std::pow(hi / lo, u));
   };
+  // the device's reduction: values of every size, near multiples and at the ends
+  for (long it = 0; it < 4 * rounds; it++) {
+    const uint32_t W = (uint32_t)log_pick(3, 4294967295.0);
+    int64_t v = (int64_t)g() >> pick(0, 62);
+    if (pick(0, 1)) v -= v % (int64_t)W + pick(-2, 2);
+    if (pick(0, 999) == 0) v = pick(0, 1) ? INT64_MAX - pick(0, 9) : INT64_MIN + pick(0, 9);
+    const int64_t r = v % (int64_t)W, want = r < 0 ? r + (int64_t)W : r;
+    if ((int64_t)mod_by_doubles(v, W) != want && wrong++ < 10)
+      std::printf("mod_by_doubles(%lld, %u) = %u\n", (long long)v, W, mod_by_doubles(v, W));
+  }
   for (long it = 0; it < rounds; it++) {
     uint32_t W = (uint32_t)log_pick(2, (double)SMALL_SIZE);
     if (pick(0, 3) == 0) W = 1u << pick(1, 30);
