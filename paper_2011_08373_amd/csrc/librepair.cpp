@@ -151,9 +151,10 @@ int validate_kernel(const rp_kernel* k) {
 // the log's own work (RECORDS_FREE tests cost no more than the launches), and
 // where the tests of one lane in sequence end before the log would (at the
 // line, 250 points of 352 threads and 2,048 blocks: 3.2 ms, 3.9 by records).
-// Where 64-bit steps share no divisor a test in one lane takes 2 us (SLOW_STEP:
-// six 64-bit divisions that others are spared): 120 points in 22 rows of 289
-// such tests 0.63 ms, by records 0.31.
+// Where 64-bit steps share no divisor a test in one lane takes 2 us and a step of
+// Euclid's algorithm 0.6 (SLOW_STEP, SLOW_EUCLID; six 64-bit divisions that
+// others are spared): 120 points in rows of 289 such tests 0.63 ms, by records
+// 0.31; 2,800 points of three related steps, 44 chunks a row, 0.18 ms and 0.34.
 //
 // A pair's gcd and inverse come on top: 6 ps per step of Euclid's algorithm in
 // 32 bits and 8.5 ps in 64 (2,000 and 2,800 points of unrelated steps: 85 and
@@ -169,7 +170,9 @@ namespace {
 constexpr uint32_t CW_BINS = 256;
 constexpr double RECORDS_FREE = 4.0e6, SERIAL_FREE = 512, SERIAL_RECORDS = 16384;
 constexpr double COST_FREE = 4.0e7, EUCLID = 1;
-constexpr double SLOW_STEP = 5;
+constexpr double SLOW_STEP = 4, SLOW_EUCLID = 1.5;
+// for calls with a log, in ps
+constexpr double RECORD_PS = 16, TEST_PS = 6, CHAIN_PS = 0.4e6, FIRST_LAUNCH = 10e6, CHAIN_GAIN = 10e6;
 
 // [min, max] of x * (r + m*u) over u in [0, n) (n >= 1); false on overflow
 bool lin_range(int64_t x, uint64_t r, uint64_t m, uint64_t n, int64_t& lo, int64_t& hi) {
@@ -362,13 +365,15 @@ bool bound_closed(const ArrayScratch& a, uint32_t words, bool global, uint32_t B
   // one lane's chain of tests
   const bool slow = wide && e0 + e1 > 2;
   const double serial = std::ceil(n / 64) * (std::max(t0, t1) * wraps * (slow ? SLOW_STEP : 1) +
-                                             (slow ? e0 + e1 : 0));
+                                             (slow ? SLOW_EUCLID * (e0 + e1) : 0));
   const double cost = work + n * (n + 1) / 2 * EUCLID * (e0 * (cross ? 2 : 1) + e1);
   if (work > RECORDS_FREE + rec || serial > SERIAL_FREE + rec / SERIAL_RECORDS) return false;
   o.form = FORM_PLAIN;
   if (wide) o.form = FORM_WIDE;
   else if (!plain) o.form = FORM_SMALL;
   o.tests = work;
+  o.cost = cost;
+  o.serial = serial;
   o.over = std::max(0.0, cost - rec);
   return true;
 }
@@ -404,14 +409,46 @@ static double cost_line(Plan* const* plans, size_t n) {
   return INFINITY;
 }
 
-// The arrays below the line in closed form, and what follows from it.
-static void set_routes(Plan& pl, double line) {
+// Where a call makes a log anyway, for arrays that no bound can take, the closed
+// form of the others saves no launches: the longest chain of tests that is worth
+// it.  The arrays up to a chain cost a launch, the chain (rows run beside each
+// other) and their tests, and save their records.  All that can are kept unless
+// a shorter chain, or none, is better by CHAIN_GAIN, less than a tenth of any call
+// with a log.  51 points of 71 threads and 5 blocks, two of their four arrays on
+// the log: 396 us with the others' chains of 350 tests, 249 by records alone.
+static double longest_chain(Plan* const* plans, size_t n) {
+  std::vector<const PlanArray*> v;
+  double time = FIRST_LAUNCH, best = 0, at = -1;
+  for (size_t j = 0; j < n; j++)
+    for (const PlanArray& a : plans[j]->arrays)
+      if (a.bounded) {
+        v.push_back(&a);
+        best += a.rec * RECORD_PS;
+      }
+  std::sort(v.begin(), v.end(),
+            [](const PlanArray* a, const PlanArray* b) { return a->serial < b->serial; });
+  time += best;
+  double all = best;
+  for (size_t q = 0; q < v.size(); q++) {
+    time += v[q]->cost * TEST_PS - v[q]->rec * RECORD_PS;
+    if (q + 1 < v.size() && v[q + 1]->serial == v[q]->serial) continue;
+    all = time + v[q]->serial * CHAIN_PS;
+    if (all < best) {
+      best = all;
+      at = v[q]->serial;
+    }
+  }
+  return all - best > CHAIN_GAIN ? at : INFINITY;
+}
+
+// The arrays below the lines in closed form, and what follows from it.
+static void set_routes(Plan& pl, double line, double chain) {
   uint64_t intra = 0, inter = 0;
   double tests = 0;
   pl.any_closed = false;
   pl.closed_form = FORM_PLAIN;
   for (PlanArray& a : pl.arrays) {
-    a.closed = a.bounded && a.over < line;
+    a.closed = a.bounded && a.over < line && a.serial <= chain;
     if (a.closed) {
       pl.any_closed = true;
       pl.closed_form = std::max(pl.closed_form, a.form);
@@ -551,6 +588,7 @@ void make_plan(const rp_kernel* k, Plan& pl) {
   uint64_t span_max = 1, intra = 0, inter = 0;
   pl.arrays.assign(k->n_arrays, PlanArray{});
   pl.over = 0;
+  pl.log = false;
   for (uint32_t arr = 0; arr < k->n_arrays; arr++) {
     const ArrayScratch& a = sc.arrays[arr];
     const uint32_t words = k->arrays[arr].words;
@@ -561,7 +599,9 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     o.off = (uint32_t)off;
     o.bounded = g_race_route == 0 && bound_closed(a, words, k->arrays[arr].space == RP_GLOBAL,
                                                   pl.B, pl.T, o);
+    o.rec = (double)a.intra * pl.B + (double)a.inter;
     pl.over += o.over;
+    pl.log = pl.log || (!o.bounded && o.rec > 0);
     o.intra = a.intra;
     o.inter = a.inter;
     intra += a.intra;
@@ -577,15 +617,21 @@ void make_plan(const rp_kernel* k, Plan& pl) {
     if (k->slots[s].preexisting) pl.pre_slots |= 1ull << s;
   }
   Plan* const self = &pl;
-  set_routes(pl, pl.over <= COST_FREE ? INFINITY : cost_line(&self, 1));
+  set_routes(pl, pl.over <= COST_FREE ? INFINITY : cost_line(&self, 1),
+             pl.log ? longest_chain(&self, 1) : INFINITY);
 }
 
 void choose_routes(Plan* const* plans, size_t n) {
   double over = 0;
-  for (size_t j = 0; j < n; j++) over += plans[j]->over;
-  if (over <= COST_FREE) return;             // (nor is any of them over it alone)
-  const double line = cost_line(plans, n);
-  for (size_t j = 0; j < n; j++) set_routes(*plans[j], line);
+  bool log = false;
+  for (size_t j = 0; j < n; j++) {
+    over += plans[j]->over;
+    log = log || plans[j]->log;
+  }
+  if (over <= COST_FREE && !log) return;     // (nor has any of them a line of its own)
+  const double line = over <= COST_FREE ? INFINITY : cost_line(plans, n);
+  const double chain = log ? longest_chain(plans, n) : INFINITY;
+  for (size_t j = 0; j < n; j++) set_routes(*plans[j], line, chain);
 }
 
 void fill_points(const Plan& pl, DPoint* pts) {

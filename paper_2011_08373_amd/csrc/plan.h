@@ -18,8 +18,10 @@ struct PlanArray {
   bool bounded = false;             // the closed form's bound can take it
   bool closed = false;              // decided in closed form: no records
   int form = FORM_PLAIN;            // the narrowest form it fits
-  double tests = 0, over = 0;       // the bound; its cost beyond the records' own (0 if
-                                    // it cannot)
+  // the bound: tests, their cost with the gcds, the longest chain of tests in one
+  // lane; the cost beyond the records' own (0 if it cannot)
+  double tests = 0, cost = 0, serial = 0, over = 0;
+  double rec = 0;                   // records of all its accesses
   uint64_t intra = 0, inter = 0;    // records per block, cross-block records
 };
 
@@ -40,6 +42,7 @@ struct Plan {
   uint64_t log_intra = 0, log_inter = 0;
   uint64_t rblk = 0;                // same-block records per block
   double over = 0;                  // of its arrays together
+  bool log = false;                 // some array's accesses have to be records
   bool any_closed = false;          // some array is decided in closed form
   int closed_form = FORM_PLAIN;     // the narrowest form all of these fit
   bool packed = false;              // its first partners are the rounds kernel's

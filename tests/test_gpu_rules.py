@@ -6,7 +6,7 @@ import pytest
 from oracle import oracle as O
 from paper_2011_08373_amd import synth
 from test_gpu_parity import L, _first_from_pairs, same_repair  # noqa: F401  (L is a fixture)
-from test_plan_rules import UNRELATED, _one_array, _steps, _walks
+from test_plan_rules import UNRELATED, _one_array, _steps, _two_arrays, _walks
 
 pytestmark = pytest.mark.gpu
 
@@ -180,3 +180,21 @@ def test_chains_of_64_bit_divisions(L, words):  # noqa: F811
     assert L.check(km, 0)[:4] == o
     assert (L.last_stats()["records"] == 0) == (words < 2**30)
     assert same_repair(L.repair(km), O.repair(km))
+
+
+@pytest.mark.parametrize("steps,arrays", [((1, 2), 1), ([104729 * (2 * q + 1) for q in range(8)], 2)],
+                         ids=["short", "long"])
+def test_beside_a_log(L, steps, arrays):  # noqa: F811
+    # one array on the records, the other in closed form or beside it; alone and
+    # in a batch, where one such kernel decides for all
+    km = _two_arrays(steps)
+    o = O.check(km, 0)
+    assert L.check(km, 0)[:4] == o
+    assert L.last_stats()["records"] == 24 * 71 * 100 * (1 + arrays)
+    assert same_repair(L.repair(km), O.repair(km))
+    kms = [synth.generate("plain-small", mode="planted", seed=s) for s in range(4)] + [km]
+    st, res = L.repair_batch(kms + kms[::-1])
+    assert st == 0
+    for k, r in zip(kms + kms[::-1], res):
+        want = O.repair(k)
+        assert all(r[q] == want[q] for q in ("status", "assign", "weight", "rounds", "n_clauses"))

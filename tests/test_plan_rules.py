@@ -83,11 +83,11 @@ def test_steps_that_share_no_divisor(plan, arg, km, records):
 
 
 def _walks(words, steps, strides):
-    """28 accesses of 100 threads and 20 blocks: pairs of different block strides
+    """28 accesses of 100 threads and 40 blocks: pairs of different block strides
     are gone through block by block."""
     pts = [dict(kind=0, is_write=i & 1, a=steps[i % len(steps)], b=strides[i % len(strides)],
                 c=1000 * i) for i in range(28)]
-    return synth.make_kernel(20, 100, [(words, 1)], [(1, 0)], pts, [])
+    return synth.make_kernel(40, 100, [(words, 1)], [(1, 0)], pts, [])
 
 
 UNRELATED = (171417, -254275, 309673)
@@ -103,6 +103,27 @@ def test_chains_of_64_bit_divisions(plan, arg, km, records):
     # share no divisor
     ka = arg(km)
     assert (plan.plan_records(ka.ref) > 0) == records
+
+
+def _two_arrays(steps):
+    """24 accesses each of a global array whose pairs meet too many values for any
+    bound, and of a shared one of the given thread steps; 71 threads, 100 blocks."""
+    far = [104729 * (2 * q + 1) for q in range(8)]
+    pts = []
+    for i in range(24):
+        pts.append(dict(kind=0, is_write=i & 1, array=0, a=far[i % 8],
+                        b=(188366, -458584, 157627)[i % 3], c=37 * i))
+        pts.append(dict(kind=0, is_write=i & 1, array=1, a=steps[i % len(steps)], b=71, c=41 * i))
+    return synth.make_kernel(100, 71, [(1 << 20, 1), (1 << 20, 0)], [(1, 0)], pts, [])
+
+
+@pytest.mark.parametrize("steps,arrays", [((1, 2), 1), ([104729 * (2 * q + 1) for q in range(8)], 2)],
+                         ids=["short", "long"])
+def test_beside_a_log(plan, arg, steps, arrays):
+    # where the launches of a log are made anyway, chains of tests beside it are
+    # worth no more than the records they save
+    ka = arg(_two_arrays(steps))
+    assert plan.plan_records(ka.ref) == 24 * 71 * 100 * (1 + arrays)
 
 
 def test_one_allowance_per_call(plan, arg):
